@@ -1,0 +1,345 @@
+"""Timed workloads of the embedding-lookup path and of the model around it.
+
+Every case is one pass a serving program makes through the public entry points of
+``paper_2512_19342_amd``: a whole lookup iteration (staged, fused, weighted with mean pooling or in
+one launch), a window of batches through the bounded-lag inference loop, or one iteration of the
+per-rank loop.  Shapes are those of the repository's benchmark workloads and tests; indices are
+uniform or Zipf-distributed, table values N(0, 0.01^2), dense features uniform in [0, 1).
+"""
+from __future__ import annotations
+
+import math
+from types import SimpleNamespace
+
+import numpy as np
+import torch
+
+import paper_2512_19342_amd as bls
+from paper_2512_19342_amd.runner import BlsDlrm, BlsDlrmRanks, DenseModel, Pipeline
+
+N_DENSE = 13                 # dense features per sample of the click-log datasets
+WINDOW = 4                   # batches a pass of the inference loop takes before it drains the ring
+ELEM_BYTES = {"fp32": 4, "fp16": 2}
+
+
+def _case(name, path, *, P, T, D, B, k, rows, bag, part="table", owner="round_robin", dtype="fp32", zipf=0.0,
+          rows_law="equal", rows_min=1000, perm=False, mlp="", fold=False):
+    return dict(name=name, path=path, P=P, T=T, D=D, B=B, k=k, rows=rows, rows_min=rows_min, rows_law=rows_law,
+                bag_lo=bag[0], bag_hi=bag[1], part=part, owner=owner, dtype=dtype, zipf=zipf, perm=perm, mlp=mlp, fold=fold)
+
+
+def listed():
+    return [
+        # the smallest calls: eight little tables, one index each, a batch of 128 (latency and launches)
+        _case("small one launch", "one_launch", P=2, T=8, D=16, B=128, k=1, rows=10_000, bag=(1, 1)),
+        # click-log shape, 26 features with one index each, through the staged calls, with the index exchange's order
+        _case("click log staged", "staged", P=4, T=26, D=64, B=2048, k=1, rows=100_000, rows_law="loguniform", bag=(1, 1),
+              owner="balanced", perm=True),
+        # the paper's heterogeneous setting: 1 to 100 indices per table, batch 512, in one launch
+        _case("heterogeneous one launch", "one_launch", P=8, T=26, D=64, B=512, k=2, rows=1_000_000, rows_law="loguniform",
+              bag=(1, 100), owner="balanced"),
+        # multi-hot bags over tables sharded by rows, staged
+        _case("row-wise staged", "staged", P=8, T=26, D=128, B=8192, k=2, rows=1_000_000, bag=(1, 40), part="row", zipf=1.05),
+        # the imbalanced benchmark workload (40 GB, popular rows, largest tables on one rank), staged
+        _case("imbalanced staged", "staged", P=8, T=64, D=128, B=16384, k=4, rows=40_000_000, rows_law="powerlaw", bag=(1, 64),
+              owner="hot0", zipf=1.2),
+        # half-precision tables sharded by rows, a large batch, pooled straight into the ring slot
+        _case("fp16 row-wise fused", "fused", P=8, T=8, D=128, B=65536, k=4, rows=20_000_000, bag=(32, 32), part="row",
+              dtype="fp16", zipf=1.05),
+        # indices without popular rows: nothing for a cache to keep
+        _case("uniform fused", "fused", P=8, T=16, D=128, B=16384, k=2, rows=4_000_000, bag=(1, 64)),
+        # per-sample weights and mean pooling, sizes that nothing divides, empty bags among them
+        _case("weighted mean ragged", "weighted_mean", P=7, T=13, D=100, B=5003, k=2, rows=300_007, bag=(0, 30), part="row",
+              zipf=1.05, perm=True),
+        # 8-bit row-quantised tables
+        _case("quantised fused", "fused", P=8, T=32, D=128, B=8192, k=2, rows=1_000_000, bag=(1, 64), dtype="u8rq", zipf=1.05),
+        # the whole model through the bounded-lag loop: a throughput-sized batch, completion folded into the interaction
+        _case("model large", "model", P=8, T=64, D=128, B=16384, k=4, rows=4_000_000, rows_law="powerlaw", bag=(1, 64),
+              owner="hot0", zipf=1.2, mlp="full", fold=True),
+        # the model at the click-log shape: a latency-sized batch, copy-out before the interaction
+        _case("model click log", "model", P=4, T=26, D=64, B=2048, k=2, rows=100_000, rows_law="loguniform", bag=(1, 1),
+              owner="balanced", mlp="full"),
+        # the same model run by every simulated rank on a stream of its own
+        _case("model rank streams", "ranks", P=4, T=26, D=64, B=2048, k=2, rows=100_000, rows_law="loguniform", bag=(1, 1),
+              owner="balanced", mlp="full"),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return min(hi, max(lo, int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))))
+
+
+def draw(rng):
+    """A case of the listed ranges: one of the paths with its sizes spread over their logarithm."""
+    cap = max(work(c)["bytes"] for c in listed() if c["path"] == "staged")
+    flop_cap = max(work(c)["flops"] for c in listed() if c["path"] == "model")
+    while True:
+        path = rng.choice(["one_launch", "staged", "staged", "fused", "fused", "weighted_mean", "model", "ranks"])
+        part = "table" if path in ("one_launch", "ranks") else rng.choice(["table", "row"])
+        dtype = "fp32" if path in ("model", "ranks") else rng.choice(["fp32", "fp32", "fp16", "u8rq", "f8rq"])
+        P = rng.choice([2, 4]) if path == "ranks" else rng.choice([1, 2, 3, 4, 7, 8])
+        T = _log_int(rng, 2, 64)
+        D = rng.choice([16, 32, 48, 64, 64, 96, 112, 128, 128, 256])
+        B = _log_int(rng, 64, 4096 if path in ("one_launch", "ranks") else 40_000)
+        hi = _log_int(rng, 1, 100)
+        lo = rng.choice([0, 1, hi])
+        rows = _log_int(rng, 1000, 8_000_000)
+        c = _case("", path, P=P, T=T, D=D, B=B, k=rng.choice([1, 2, 4]), rows=rows, rows_min=min(rows, 1000),
+                  rows_law=rng.choice(["equal", "loguniform", "powerlaw"]), bag=(min(lo, hi), hi), part=part, dtype=dtype,
+                  owner=rng.choice(["round_robin", "balanced", "hot0"]), zipf=rng.choice([0.0, 1.05, 1.2]),
+                  perm=path in ("staged", "weighted_mean") and rng.random() < 0.5,
+                  mlp=rng.choice(["full", "medium"]) if path in ("model", "ranks") else "", fold=rng.random() < 0.5)
+        del c["name"]
+        F = P if part == "row" else 1
+        if path == "one_launch" and T * P > 2048:
+            continue
+        if path in ("model", "ranks") and (T + 31) // 32 * 32 * (D + 1) + D > 16_000:    # vectors of one sample in LDS
+            continue
+        if sum(_rows(c)) * _row_bytes(c) > 16e9 or 4 * F * T * B * D > 2.2e9:
+            continue
+        if T * B * (c["bag_lo"] + hi) / 2 * (WINDOW if path == "model" else 1) > 3e7:
+            continue
+        w = work(c)
+        if w["bytes"] > cap or w["flops"] > flop_cap:
+            continue
+        return c
+
+
+# ---- shapes ------------------------------------------------------------------------------------------
+
+def _rows(c):
+    T, top, low = c["T"], c["rows"], c["rows_min"]
+    if c["rows_law"] == "powerlaw":
+        return [max(low, int(top / (t + 1) ** 1.7)) for t in range(T)]
+    if c["rows_law"] == "loguniform":     # evenly spread over the logarithm, in an order that mixes large and small
+        at = [((t * 0.6180339887498949) % 1.0) for t in range(T)]
+        return [int(low * (top / low) ** u) for u in at]
+    return [top] * T
+
+
+def _owners(c, rows):
+    T, P = c["T"], c["P"]
+    order = sorted(range(T), key=lambda t: (-rows[t], t))
+    if c["part"] == "row":
+        return [0] * T
+    if c["owner"] == "balanced":
+        load, own = [0] * P, [0] * T
+        for t in order:
+            d = min(range(P), key=lambda r: (load[r], r))
+            own[t] = d
+            load[d] += rows[t]
+        return own
+    if c["owner"] == "hot0" and P > 1:    # the eight largest tables on rank 0
+        own, nxt, hot = [0] * T, 0, set(order[:8])
+        for t in range(T):
+            if t not in hot:
+                own[t] = 1 + nxt % (P - 1)
+                nxt += 1
+        return own
+    return [t % P for t in range(T)]
+
+
+def _row_bytes(c):
+    D = c["D"]
+    return (D + 8 + 15) // 16 * 16 if c["dtype"] in ("u8rq", "f8rq") else D * ELEM_BYTES[c["dtype"]]
+
+
+def _mlp_widths(c):
+    z = c["D"] + c["T"] * (c["T"] + 1) // 2
+    if c["mlp"] == "full":
+        return [N_DENSE, 512, 256, c["D"]], [z, 1024, 1024, 512, 256, 1]
+    return [N_DENSE, 128, c["D"]], [z, 256, 128, 1]
+
+
+# ---- inputs ------------------------------------------------------------------------------------------
+
+def _table(c, rows, gen, dev):
+    D = c["D"]
+    if c["dtype"] in ("u8rq", "f8rq"):
+        tab = torch.randint(0, 256, (rows, _row_bytes(c)), dtype=torch.uint8, device=dev, generator=gen)
+        if c["dtype"] == "f8rq":
+            tab.bitwise_and_(0xBF)                                    # magnitudes below 2, no NaN codes
+        scale = torch.rand(rows, 1, device=dev, generator=gen) * 9.9e-3 + 1e-4
+        bias = torch.rand(rows, 1, device=dev, generator=gen) - 0.5
+        tab[:, D:D + 4] = scale.view(torch.uint8)
+        tab[:, D + 4:D + 8] = bias.view(torch.uint8)
+        return tab
+    dt = torch.float16 if c["dtype"] == "fp16" else torch.float32
+    return torch.empty((rows, D), dtype=dt, device=dev).normal_(0.0, 0.01, generator=gen)
+
+
+def _coprime(rows):
+    a = max(1, int(0.618 * rows))
+    while math.gcd(a, rows) != 1:
+        a += 1
+    return a
+
+
+def _batch(c, rows, gen, dev, cdfs):
+    """(indices, offsets, nnz): table-major bags, int64; Zipf ranks are scattered over the table."""
+    T, B = c["T"], c["B"]
+    lens = torch.randint(c["bag_lo"], c["bag_hi"] + 1, (T * B,), device=dev, generator=gen)
+    offsets = torch.zeros(T * B + 1, dtype=torch.int64, device=dev)
+    torch.cumsum(lens, 0, out=offsets[1:])
+    edges = offsets[::B].tolist()
+    indices = torch.empty(edges[-1], dtype=torch.int64, device=dev)
+    for t in range(T):
+        n = edges[t + 1] - edges[t]
+        if c["zipf"]:
+            if rows[t] not in cdfs:
+                z = torch.arange(1, rows[t] + 1, dtype=torch.float64, device=dev).pow_(-c["zipf"])
+                cdfs[rows[t]] = torch.cumsum(z, 0)
+            cdf = cdfs[rows[t]]
+            u = torch.rand(n, dtype=torch.float64, device=dev, generator=gen) * cdf[-1]
+            rank = torch.searchsorted(cdf, u, right=True).clamp_(max=rows[t] - 1)
+            indices[edges[t]:edges[t + 1]] = (rank * _coprime(rows[t])) % rows[t]
+        else:
+            indices[edges[t]:edges[t + 1]] = torch.randint(0, rows[t], (n,), device=dev, generator=gen)
+    return indices, offsets, edges[-1]
+
+
+def _layers(widths, gen, dev):
+    """The reference recommendation model's initialisation: W ~ N(0, 2/(K+N)), bias ~ N(0, 1/N)."""
+    return [(torch.randn(n, k, device=dev, generator=gen) * math.sqrt(2.0 / (k + n)),
+             torch.randn(n, device=dev, generator=gen) * math.sqrt(1.0 / n)) for k, n in zip(widths[:-1], widths[1:])]
+
+
+def prepare(case, seed):
+    c = case
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev).manual_seed(seed)
+    rows = _rows(c)
+    w = SimpleNamespace(P=c["P"], T=c["T"], D=c["D"], k=c["k"], B=c["B"], rows=rows, table_owner=_owners(c, rows),
+                        table_dtype=c["dtype"], part_kind=bls.BLS_ROW_WISE if c["part"] == "row" else bls.BLS_TABLE_WISE)
+    tables = [_table(c, r, gen, dev) for r in rows]
+    cdfs = {}
+    batches = [_batch(c, rows, gen, dev, cdfs) for _ in range(WINDOW if c["path"] == "model" else 1)]
+    pipe = Pipeline(w, tables, c["T"] * c["B"] * c["bag_hi"], want_perm=c["perm"])    # room for the longest batch
+    st = dict(case=c, pipe=pipe, batches=batches, out=pipe.new_out())
+    if c["path"] == "weighted_mean":
+        st["weights"] = torch.rand(batches[0][2], device=dev, generator=gen) * 2.0 - 0.5
+    if c["mlp"]:
+        bottom, top = _mlp_widths(c)
+        model = DenseModel(pipe.ctx, _layers(bottom, gen, dev), _layers(top, gen, dev), c["B"])
+        st["model"] = model
+        st["dense"] = [torch.rand(c["B"], N_DENSE, device=dev, generator=gen) for _ in batches]
+        if c["path"] == "ranks":
+            st["streams"] = [torch.cuda.Stream() for _ in range(c["P"])]
+            st["loop"] = BlsDlrmRanks(pipe, model, st["streams"])
+            st["next"] = 0
+        else:
+            st["loop"] = BlsDlrm(pipe, model, fused_completion=c["fold"])
+    return st
+
+
+# ---- passes ------------------------------------------------------------------------------------------
+
+def _plan_outputs(pipe):
+    r = dict(sendcounts=pipe.sendcounts, sdispls=pipe.sdispls, recvcounts=pipe.recvcounts, rdispls=pipe.rdispls,
+             ridx=pipe.ridx, segoff=pipe.segoff)                      # as large as the longest batch needs them
+    if pipe.perm is not None:
+        r["perm"] = pipe.perm
+    return r
+
+
+def run(state):
+    c, pipe, out = state["case"], state["pipe"], state["out"]
+    path = c["path"]
+    if path == "model":
+        return _run_model(state)
+    if path == "ranks":
+        return _run_ranks(state)
+    indices, offsets, nnz = state["batches"][0]
+    if path == "one_launch":
+        it = pipe.step_one_launch(indices, offsets, nnz, out)
+        return dict(_plan_outputs(pipe), pooled=pipe.pooled, send=pipe.send, slot=pipe.slot_view(it % pipe.ctx.K), out=out)
+    if path == "staged":
+        it, slot = pipe.issue(indices, offsets, nnz)
+        pipe.complete(it, out)
+        return dict(_plan_outputs(pipe), pooled=pipe.pooled, send=pipe.send, slot=pipe.slot_view(slot), out=out)
+    if path == "fused":
+        it, slot = pipe.issue_fused(indices, offsets, nnz)
+        pipe.complete(it, out)
+        return dict(_plan_outputs(pipe), slot=pipe.slot_view(slot), out=out)
+    it, slot = pipe.issue_weighted(indices, offsets, state["weights"], nnz, fused=True)
+    pipe.complete(it, out, mean_offsets=offsets)
+    return dict(_plan_outputs(pipe), rweights=pipe.rweights, slot=pipe.slot_view(slot), out=out)
+
+
+def _run_model(state):
+    """A window of batches through the loop of the paper's Listing 2, drained at its end."""
+    loop, model = state["loop"], state["model"]
+    done = []
+    for i, ((indices, offsets, nnz), dense) in enumerate(zip(state["batches"], state["dense"])):
+        done += loop.forward(dense, indices, offsets, nnz, last_batch=i == len(state["batches"]) - 1)
+    return dict(predictions=[p for _, p in done], x=loop.x_list[done[-1][0] % len(loop.x_list)], z=model.z,
+                bottom=model.bot_act[:-1], top=model.top_act[:-1])
+
+
+def _run_ranks(state):
+    """One iteration of every rank, each on its own stream, behind one shared plan."""
+    pipe, loop = state["pipe"], state["loop"]
+    (indices, offsets, nnz), dense, it = state["batches"][0], state["dense"][0], state["next"]
+    state["next"] = it + 1
+    here = torch.cuda.current_stream()
+    pipe.ctx.bls_plan(indices, offsets, nnz, pipe.sendcounts, pipe.sdispls, pipe.recvcounts, pipe.rdispls, pipe.ridx,
+                      pipe.segoff, pipe.perm, pipe.ws)
+    for d, s in enumerate(state["streams"]):
+        s.wait_stream(here)
+        loop.issue(d, it, pipe.ridx, pipe.segoff, nnz, dense)
+    for d, s in enumerate(state["streams"]):
+        prediction = loop.finish(d, it)
+        here.wait_stream(s)
+    return dict(_plan_outputs(pipe), prediction=prediction, x=loop.x_list[it % len(loop.x_list)],
+                emb=loop.emb[it % pipe.ctx.K], z=state["model"].z)
+
+
+# ---- what a pass cannot do without -----------------------------------------------------------------------
+
+def _distinct_rows(rows, n, alpha):
+    """Expected number of different rows among n lookups of one table."""
+    if not alpha:
+        return rows * -math.expm1(-n / rows)
+    edges = np.unique(np.concatenate([np.arange(1, min(rows, 64) + 1), np.geomspace(1, rows + 1, 400).astype(np.int64), [rows + 1]]))
+    lo, hi = edges[:-1].astype(np.float64), edges[1:].astype(np.float64)
+    count = hi - lo
+    p = (0.5 * (lo + hi - 1)) ** -alpha
+    p /= float((p * count).sum())
+    return float((count * -np.expm1(-n * p)).sum())
+
+
+def work(case):
+    c = case
+    T, B, D = c["T"], c["B"], c["D"]
+    F = c["P"] if c["part"] == "row" else 1
+    bags = T * B
+    nnz = bags * (c["bag_lo"] + c["bag_hi"]) / 2
+    rows = _rows(c)
+    seen = sum(_distinct_rows(r, nnz / T, c["zipf"]) for r in rows)
+    # indices and offsets in, ridx and segoff out (perm where it is asked for), the rows
+    bytes_ = 8 * nnz + 8 * bags + 8 * nnz + 8 * F * bags + seen * _row_bytes(c) + (8 * nnz if c["perm"] else 0)
+    pooled, out = 4 * F * bags * D, 4 * bags * D
+    flops = nnz * D
+    if c["path"] in ("one_launch", "staged"):
+        bytes_ += 3 * pooled + out
+    elif c["path"] in ("fused", "weighted_mean"):
+        bytes_ += pooled + out + (8 * nnz if c["path"] == "weighted_mean" else 0)
+    else:
+        bottom, top = _mlp_widths(c)
+        pairs = [*zip(bottom[:-1], bottom[1:]), *zip(top[:-1], top[1:])]
+        weights = 4 * sum(k * n + n for k, n in pairs)
+        bytes_ += pooled + 4 * B * (N_DENSE + sum(bottom[1:]) + sum(top)) + (0 if c["fold"] and c["path"] == "model" else out)
+        flops += 2 * B * sum(k * n for k, n in pairs) + B * T * (T + 1) * D
+        if c["path"] == "model":
+            bytes_, flops = WINDOW * bytes_, WINDOW * flops
+        bytes_ += weights
+    return {"bytes": bytes_, "flops": flops}
+
+
+def tolerance(case):
+    """The lookup path adds a bag's rows in bag order and is exact.  The dense layers and the dot
+    interaction are 32-bit sums in any order: against 64 bits the worst activation of the listed and of
+    drawn models showed 8.8e-7 in the 2-norm and 9.1e-6 at one element; four times that."""
+    if case["mlp"]:
+        return {"rel": 3.5e-6, "max": 3.7e-5}
+    return "exact"
