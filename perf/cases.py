@@ -187,10 +187,11 @@ def _batch(c, rows, gen, dev, cdfs):
         n = edges[t + 1] - edges[t]
         if c["zipf"]:
             if rows[t] not in cdfs:
-                z = torch.arange(1, rows[t] + 1, dtype=torch.float64, device=dev).pow_(-c["zipf"])
+                # whole weights: a sum of floating-point ones differs from run to run
+                z = torch.arange(1, rows[t] + 1, dtype=torch.float64, device=dev).pow_(-c["zipf"]).mul_(2.0 ** 48).to(torch.int64)
                 cdfs[rows[t]] = torch.cumsum(z, 0)
             cdf = cdfs[rows[t]]
-            u = torch.rand(n, dtype=torch.float64, device=dev, generator=gen) * cdf[-1]
+            u = (torch.rand(n, dtype=torch.float64, device=dev, generator=gen) * cdf[-1]).to(torch.int64)
             rank = torch.searchsorted(cdf, u, right=True).clamp_(max=rows[t] - 1)
             indices[edges[t]:edges[t + 1]] = (rank * _coprime(rows[t])) % rows[t]
         else:
