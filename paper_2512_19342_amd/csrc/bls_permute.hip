@@ -9,8 +9,15 @@
 // stream (measured: 5.7-6.1 TB/s of read + write traffic, against 4.6-5.0 when both sides are
 // eight interleaved streams): pack reads Y in order, the exchange writes the slot in order,
 // unpack reads the slot in order.
-#include <stdlib.h>
-
+//
+// An iteration's vectors that are more than the caches keep are moved with the streaming hint:
+// nothing of them would be found there by the next call.  Which side carries it was measured on the
+// whole iteration, because what one kernel leaves behind in the memory-side cache the next one pays
+// for (hinting only the loads makes unpack 7 % shorter and the plan that follows 25 % longer): all
+// combinations, workload 4 (512 MB of vectors) 1593 us without, 1554 with pack and unpack hinted on
+// both sides and the exchange on its loads; row-wise workload 3 (832 MB) 1133 and 1064, that being
+// the best of 64; fused workload 5 (2 GB, unpack only) 1498 and 1422.  unpack_rowwise 195 -> 163 us
+// and the exchange 287 -> 258 us on workload 3.
 #include <algorithm>
 
 #include "bls_internal.h"
@@ -27,12 +34,20 @@ inline int lanes_log2(int64_t cols)
     return lg;
 }
 
-__device__ __forceinline__ void vdiv(float4 &a, float x) { a.x /= x; a.y /= x; a.z /= x; a.w /= x; }
-__device__ __forceinline__ void vdiv(float &a, float x) { a /= x; }
-__device__ __forceinline__ void vadd(float4 &a, const float4 &x) { a.x += x.x; a.y += x.y; a.z += x.z; a.w += x.w; }
-__device__ __forceinline__ void vadd(float &a, const float &x) { a += x; }
-__device__ __forceinline__ void vzero(float4 &a) { a = make_float4(0.f, 0.f, 0.f, 0.f); }
-__device__ __forceinline__ void vzero(float &a) { a = 0.f; }
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// HINT of a kernel: which side of the move carries the streaming hint
+constexpr int kPlain = 0, kLoads = 1, kBoth = 3;
+template <int HINT, class V> __device__ __forceinline__ V vload(const V *p)
+{
+    if constexpr ((HINT & 1) != 0) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+template <int HINT, class V> __device__ __forceinline__ void vstore(V *p, V v)
+{
+    if constexpr ((HINT & 2) != 0) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
 
 // Length of bag (t, b) as a float divisor for mean pooling; 1 for an empty or malformed bag.
 __device__ __forceinline__ float bag_divisor(const DevDesc &dd, const int64_t *off, int t, uint32_t b)
@@ -43,7 +58,7 @@ __device__ __forceinline__ float bag_divisor(const DevDesc &dd, const int64_t *o
 }
 
 // Pack: Y (read front to back) -> send regions.  Grid: x over groups of samples, y = q.
-template <class V>
+template <class V, int HINT>
 __global__ __launch_bounds__(kThreads) void pack_vectors(DevDesc dd, const float *__restrict__ Y, float *__restrict__ S, int lg)
 {
     constexpr int VEC = sizeof(V) / sizeof(float);
@@ -57,7 +72,7 @@ __global__ __launch_bounds__(kThreads) void pack_vectors(DevDesc dd, const float
     const V *__restrict__ ps = reinterpret_cast<const V *>(Y + ((int64_t)q * dd.B + b) * dd.D);
     V *__restrict__ pd = reinterpret_cast<V *>(S + bls_sigma(dd, q, s, b_loc, n) * dd.D);
     const int cols = dd.D / VEC;
-    for (int c = li; c < cols; c += G) pd[c] = ps[c];
+    for (int c = li; c < cols; c += G) vstore<HINT>(pd + c, vload<HINT>(ps + c));
 }
 
 // Position of a workgroup in receive order: requester s = s0 + ..., then `rows` rows (the Q
@@ -80,7 +95,7 @@ __device__ __forceinline__ RecvPos recv_position(const DevDesc &dd, int lg, uint
 }
 
 // Exchange: send regions -> the slot, written front to back.  Grid: x over (s, q, chunk).
-template <class V>
+template <class V, int HINT>
 __global__ __launch_bounds__(kThreads) void exchange_vectors(DevDesc dd, const float *__restrict__ S, float *__restrict__ R,
                                                              int lg, uint32_t chunks)
 {
@@ -92,11 +107,11 @@ __global__ __launch_bounds__(kThreads) void exchange_vectors(DevDesc dd, const f
     const V *__restrict__ ps = reinterpret_cast<const V *>(S + bls_sigma(dd, p.row, p.s, p.b_loc, p.n) * dd.D);
     V *__restrict__ pd = reinterpret_cast<V *>(R + bls_rho(dd, p.row, p.s, p.b_loc, p.n) * dd.D);
     const int cols = dd.D / VEC;
-    for (int c = li; c < cols; c += G) pd[c] = ps[c];
+    for (int c = li; c < cols; c += G) vstore<HINT>(pd + c, vload<HINT>(ps + c));
 }
 
 // Table-wise completion: the slot, read front to back -> Out[b][t].  Grid: x over (s, q, chunk).
-template <class V>
+template <class V, int HINT>
 __global__ __launch_bounds__(kThreads) void unpack_tablewise(DevDesc dd, const float *__restrict__ R, float *__restrict__ out,
                                                              int lg, uint32_t chunks, int s0,
                                                              const int64_t *__restrict__ mean_off, uint32_t b0, uint32_t bn)
@@ -113,16 +128,16 @@ __global__ __launch_bounds__(kThreads) void unpack_tablewise(DevDesc dd, const f
     const int cols = dd.D / VEC;
     if (mean_off) {
         const float div = bag_divisor(dd, mean_off, t, (uint32_t)b);
-        for (int c = li; c < cols; c += G) { V x = ps[c]; vdiv(x, div); pd[c] = x; }
+        for (int c = li; c < cols; c += G) vstore<HINT>(pd + c, vload<HINT>(ps + c) / div);
     } else {
-        for (int c = li; c < cols; c += G) pd[c] = ps[c];
+        for (int c = li; c < cols; c += G) vstore<HINT>(pd + c, vload<HINT>(ps + c));
     }
 }
 
 // Row-wise completion: Out[b][t] = sum over owners d = 0..P-1 (in that order, from +0) of the
 // partial vector rank d sent for (t, b).  Grid: x over (s, t, chunk): every owner's region of the
 // slot is read front to back.
-template <class V>
+template <class V, int HINT>
 __global__ __launch_bounds__(kThreads) void unpack_rowwise(DevDesc dd, const float *__restrict__ R, float *__restrict__ out,
                                                            int lg, uint32_t chunks, int s0,
                                                            const int64_t *__restrict__ mean_off, uint32_t b0, uint32_t bn)
@@ -138,14 +153,13 @@ __global__ __launch_bounds__(kThreads) void unpack_rowwise(DevDesc dd, const flo
     const int cols = dd.D / VEC;
     const float div = mean_off ? bag_divisor(dd, mean_off, t, (uint32_t)b) : 1.f;
     for (int c = li; c < cols; c += G) {
-        V acc;
-        vzero(acc);
+        V acc = 0.f;
         for (int d = 0; d < dd.P; ++d) {
             const V *__restrict__ ps = reinterpret_cast<const V *>(R + bls_rho(dd, d * dd.T + t, p.s, p.b_loc, p.n) * dd.D);
-            vadd(acc, ps[c]);
+            acc += vload<HINT>(ps + c);
         }
-        if (mean_off) vdiv(acc, div);
-        pd[c] = acc;
+        if (mean_off) acc /= div;
+        vstore<HINT>(pd + c, acc);
     }
 }
 
@@ -172,14 +186,29 @@ int bls_launch_delay(bls_ctx *ctx, uint32_t microseconds, hipStream_t st)
     return BLS_OK;
 }
 
+// Bytes of one iteration's pooled vectors from which on they are moved with the streaming hint.  Three
+// copies in a row, each reading what the one before wrote, take 58.8 us at 64 MB without and 63.0 with
+// hinted loads, 133.8 and 117.3 at 128 MB: source and destination together outgrow the 256 MB
+// memory-side cache there.
+constexpr size_t kStreamBytes = size_t(96) << 20;
+
+// kernel<vector type, hint>: rows of whole 16-byte pieces (vec) or not, large problems with the kernel's hint
+#define BLS_PERMUTE(kernel, hint, vec, grid, st, ...)                                          \
+    do {                                                                                       \
+        const bool large = ctx->slot_bytes >= kStreamBytes;                                    \
+        if (vec && large) kernel<f32x4, hint><<<grid, kThreads, 0, st>>>(__VA_ARGS__);         \
+        else if (vec) kernel<f32x4, kPlain><<<grid, kThreads, 0, st>>>(__VA_ARGS__);           \
+        else if (large) kernel<float, hint><<<grid, kThreads, 0, st>>>(__VA_ARGS__);           \
+        else kernel<float, kPlain><<<grid, kThreads, 0, st>>>(__VA_ARGS__);                    \
+    } while (0)
+
 int bls_launch_pack(bls_ctx *ctx, const float *Y, float *S, hipStream_t st)
 {
     const bool vec = ctx->D % 4 == 0;
     const int lg = lanes_log2(vec ? ctx->D / 4 : ctx->D);
     const uint32_t per_block = kThreads >> lg;
     const dim3 grid((unsigned)((ctx->B + per_block - 1) / per_block), (unsigned)ctx->Q);
-    if (vec) pack_vectors<float4><<<grid, kThreads, 0, st>>>(ctx->desc, Y, S, lg);
-    else pack_vectors<float><<<grid, kThreads, 0, st>>>(ctx->desc, Y, S, lg);
+    BLS_PERMUTE(pack_vectors, kBoth, vec, grid, st, ctx->desc, Y, S, lg);
     BLS_HIP(ctx, hipGetLastError());
     return BLS_OK;
 }
@@ -204,8 +233,7 @@ int bls_launch_exchange(bls_ctx *ctx, const float *S, float *R, hipStream_t st)
     dim3 grid;
     const int rc = recv_grid(ctx, lg, (uint32_t)ctx->Q, 0, ctx->P - 1, &chunks, &grid);
     if (rc) return rc;
-    if (vec) exchange_vectors<float4><<<grid, kThreads, 0, st>>>(ctx->desc, S, R, lg, chunks);
-    else exchange_vectors<float><<<grid, kThreads, 0, st>>>(ctx->desc, S, R, lg, chunks);
+    BLS_PERMUTE(exchange_vectors, kLoads, vec, grid, st, ctx->desc, S, R, lg, chunks);
     BLS_HIP(ctx, hipGetLastError());
     return BLS_OK;
 }
@@ -225,13 +253,8 @@ int bls_launch_unpack(bls_ctx *ctx, const float *R, float *out, const int64_t *m
     dim3 grid;
     const int rc = recv_grid(ctx, lg, (uint32_t)(rowwise ? ctx->T : ctx->Q), s0, s1, &chunks, &grid);
     if (rc) return rc;
-    if (rowwise) {
-        if (vec) unpack_rowwise<float4><<<grid, kThreads, 0, st>>>(ctx->desc, R, out, lg, chunks, s0, mean_off, b0, bn);
-        else unpack_rowwise<float><<<grid, kThreads, 0, st>>>(ctx->desc, R, out, lg, chunks, s0, mean_off, b0, bn);
-    } else {
-        if (vec) unpack_tablewise<float4><<<grid, kThreads, 0, st>>>(ctx->desc, R, out, lg, chunks, s0, mean_off, b0, bn);
-        else unpack_tablewise<float><<<grid, kThreads, 0, st>>>(ctx->desc, R, out, lg, chunks, s0, mean_off, b0, bn);
-    }
+    if (rowwise) BLS_PERMUTE(unpack_rowwise, kBoth, vec, grid, st, ctx->desc, R, out, lg, chunks, s0, mean_off, b0, bn);
+    else BLS_PERMUTE(unpack_tablewise, kBoth, vec, grid, st, ctx->desc, R, out, lg, chunks, s0, mean_off, b0, bn);
     BLS_HIP(ctx, hipGetLastError());
     return BLS_OK;
 }
