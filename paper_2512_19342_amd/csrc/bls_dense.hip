@@ -1,10 +1,9 @@
 // bls_mlp_layer and bls_interact: the dense part of the model around the lookup (apply_mlp and
-// interact_features of Listings 1 and 2), in fp32 on the matrix cores.
+// interact_features of Listings 1 and 2), fp32 in and out, on the matrix cores.
 //
-// Both are dense contractions, so both run on v_mfma_f32_32x32x2_f32: one instruction multiplies
-// a 32x2 by a 2x32 fp32 block into a 32x32 fp32 accumulator held in 16 registers per lane.
-// Operand layout: lane l supplies A[l % 32][l / 32] and B[l / 32][l % 32]; accumulator register
-// v of lane l is element (8 * (v / 4) + 4 * (l / 32) + v % 4, l % 32).
+// Operand layouts.  v_mfma_f32_32x32x2_f32: lane l supplies A[l % 32][l / 32] and B[l / 32][l % 32].
+// v_mfma_f32_32x32x16_bf16: lane l supplies the eight k from 8 * (l / 32) of row (column) l % 32.  Both:
+// accumulator register v of lane l is element (8 * (v / 4) + 4 * (l / 32) + v % 4, l % 32).
 #include <stdint.h>
 
 #include "bls_internal.h"
@@ -12,6 +11,12 @@
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
 
@@ -25,24 +30,79 @@ __device__ __forceinline__ float activate(float v)
 
 // ---- one layer: Y[M][N] = act(X[M][K] * W[N][K]^T + bias[N]) ---------------------------------
 //
-// A workgroup of four wavefronts owns a 128 x 128 tile of Y; each wavefront a 64 x 64 quarter
-// (2 x 2 accumulators).  X and W tiles of 16 columns of K are staged through LDS, transposed
-// to k-major so that the 32 lanes of a half-wavefront read 32 consecutive floats for one k, and
-// double-buffered: the loads of the next tile are in flight while the current one is multiplied.
-// Workgroups are numbered so that the eight that share rows of X follow each other on one XCD
+// fp32 operands on the bf16 matrix instructions.  A float is the sum of three bf16 numbers, exactly
+// (24 significant bits, eight in each, the second and third being what rounding to nearest left), and
+// of the nine products of two such sums the six largest are added up in fp32; what is left out is
+// below 2^-24 of the product, less than the rounding of one fp32 multiply-add.
+// v_mfma_f32_32x32x16_bf16 takes 32 cycles for 16 k, v_mfma_f32_32x32x2_f32 64 for 2: six of the
+// former against eight of the latter are 192 cycles against 512.  The products of the first parts and
+// the five small ones have an accumulator each: one rounding of the large sum per 16 k.  Against 64
+// bits the error is a third of the fp32 instruction's (2-norm, K = 1024: 1.5e-7 and 4.1e-7; K = 2208:
+// 2.2e-7 and 5.9e-7; K = 13: 3.9e-8 and 6.7e-8); with one accumulator for all six it is larger
+// (K = 1024: 4.7e-7).
+//
+// A result that is not finite says nothing (an infinity has no three parts, and a float that rounds
+// up to the bf16 infinity neither): it is taken again on the fp32 matrix instructions.  A finite one
+// had finite operands: no product of an infinity or a NaN is finite.
+//
+// A workgroup of four wavefronts, two by two, owns a tile of 64 TI x 64 TJ; each wavefront multiplies
+// 32 TI x 32 TJ.  Every element is summed over k in the same order whatever the tile, so that a
+// sample's result does not depend on how many others are in the call.
+// Tiles are staged already split, in planes of eight k: what a lane needs of a row is one 16-byte
+// read, rows consecutive; two buffers, and the loads of the step after the next in flight while one is
+// multiplied.  Workgroups are numbered so that those that share rows of X follow each other on one XCD
 // (one L2), N-tile fastest.
-#ifndef BLS_GEMM_BK
-#define BLS_GEMM_BK 16
-#endif
-constexpr int BM = 128, BN = 128, BK = BLS_GEMM_BK, LDT = BM + 4;
+//
+// M = 16384, us, fp32 instructions / this: 2208 -> 1024 593 / 387 (192 TFLOP/s), 1024 -> 1024 284 / 189,
+// 1024 -> 512 152 / 98, 512 -> 256 55 / 33, 256 -> 128 32 / 12.  M = 2048: 415 -> 1024 54 / 19,
+// 1024 -> 1024 94 / 35, 512 -> 256 52 / 14.  The matrix pipe is busy for 46 % of the first of these; the
+// splitting and the LDS reads, which every wavefront does between its multiplies, are the rest.
+__device__ __forceinline__ bool finite(float v) { return __builtin_fabsf(v) <= 3.402823466e38f; }
 
-template <bool VEC, int ACT>
-__global__ __launch_bounds__(kThreads) void mlp_gemm(const float *__restrict__ X, const float *__restrict__ W,
-                                                     const float *__restrict__ bias, float *__restrict__ Y,
-                                                     int64_t M, int N, int K, uint32_t n_tiles, uint32_t tiles)
+struct Chunk { float v[8]; };                                 // eight consecutive k of one row
+
+// Eight floats from k of a row of K (zeros from K on); rows need no alignment beyond the float's.
+__device__ __forceinline__ Chunk load_chunk(const float *__restrict__ row, bool in, int k, int K)
 {
-    __shared__ float As[2][BK][LDT];
-    __shared__ float Bs[2][BK][LDT];
+    Chunk c;
+    f32x4 lo = 0.f, hi = 0.f;
+    if (in) {
+        if (k + 8 <= K) {
+            lo = *reinterpret_cast<const f32x4_a4 *>(row + k);
+            hi = *reinterpret_cast<const f32x4_a4 *>(row + k + 4);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (k + j < K) lo[j] = row[k + j];
+                if (k + 4 + j < K) hi[j] = row[k + 4 + j];
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { c.v[j] = lo[j]; c.v[4 + j] = hi[j]; }
+    return c;
+}
+
+// Two floats as bf16 (to nearest), the first in the low half; what they leave is returned in place.
+__device__ __forceinline__ uint32_t take_bf16(float &a, float &b)
+{
+    const f32x2 v = {a, b};
+    const uint32_t p = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+    a -= __uint_as_float(p << 16);                            // exact
+    b -= __uint_as_float(p & 0xffff0000u);
+    return p;
+}
+
+template <int TI, int TJ, int CH, int ACT>
+__global__ __launch_bounds__(kThreads, TI * TJ == 4 ? 2 : 3) void mlp_gemm(const float *__restrict__ X, const float *__restrict__ W,
+                                                        const float *__restrict__ bias, float *__restrict__ Y,
+                                                        int64_t M, int N, int K, uint32_t n_tiles, uint32_t tiles)
+{
+    constexpr int BM = 64 * TI, BN = 64 * TJ, BK = 8 * CH;    // CH planes of eight k per step
+    // rows per plane plus padding that spreads the planes one thread row writes over the banks
+    constexpr int LA = BM + 8 / CH, LB = BN + 8 / CH;
+    constexpr int SIDE_A = 3 * CH * LA, BUF = 3 * CH * (LA + LB);
+    __shared__ u32x4 lds[2 * BUF];
 
     // XCD x gets the tiles [x * per, (x + 1) * per) in launch order
     const uint32_t per = (tiles + 7u) / 8u;
@@ -52,112 +112,146 @@ __global__ __launch_bounds__(kThreads) void mlp_gemm(const float *__restrict__ X
     const int n0 = (int)(tile % n_tiles) * BN;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
+    const int wm = (wave >> 1) * 32 * TI, wn = (wave & 1) * 32 * TJ;
     const int half = lane >> 5, l32 = lane & 31;
 
-    // staging registers for one tile of X and one of W
-    constexpr int NLD = VEC ? BM * BK / 4 / kThreads : BM * BK / kThreads;
-    float4 xa[VEC ? NLD : 1], wa[VEC ? NLD : 1];
-    float xs[VEC ? 1 : NLD], ws[VEC ? 1 : NLD];
-
+    // thread tid stages planes c of rows r, r + 256 / CH, ...: CH threads read a row's step together
+    constexpr int NA = BM * CH / kThreads, NB = BN * CH / kThreads, RSTEP = kThreads / CH;
+    const int sr = tid / CH, sc = tid % CH;
+    Chunk xa[NA], xb[NB];
     auto fetch = [&](int k0) {
 #pragma unroll
-        for (int i = 0; i < NLD; ++i) {
-            const int idx = tid + i * kThreads;
-            if constexpr (VEC) {
-                const int row = idx / (BK / 4), kq = (idx % (BK / 4)) * 4;
-                const bool kin = k0 + kq < K;                 // K % 4 == 0: a whole float4 is in or out
-                xa[i] = (kin && m0 + row < M) ? *reinterpret_cast<const float4 *>(X + (m0 + row) * K + k0 + kq)
-                                              : make_float4(0.f, 0.f, 0.f, 0.f);
-                wa[i] = (kin && n0 + row < N) ? *reinterpret_cast<const float4 *>(W + (int64_t)(n0 + row) * K + k0 + kq)
-                                              : make_float4(0.f, 0.f, 0.f, 0.f);
-            } else {
-                const int row = idx / BK, k = idx % BK;
-                const bool kin = k0 + k < K;
-                xs[i] = (kin && m0 + row < M) ? X[(m0 + row) * K + k0 + k] : 0.f;
-                ws[i] = (kin && n0 + row < N) ? W[(int64_t)(n0 + row) * K + k0 + k] : 0.f;
-            }
+        for (int i = 0; i < NA; ++i) {
+            const int64_t row = m0 + sr + i * RSTEP;
+            xa[i] = load_chunk(X + row * K, row < M, k0 + 8 * sc, K);
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int row = n0 + sr + i * RSTEP;
+            xb[i] = load_chunk(W + (int64_t)row * K, row < N, k0 + 8 * sc, K);
+        }
+    };
+    auto put = [&](Chunk c, u32x4 *at, int plane) {           // the three parts lie CH planes apart
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            u32x4 w;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) w[j] = take_bf16(c.v[2 * j], c.v[2 * j + 1]);
+            at[p * CH * plane] = w;
         }
     };
     auto stage = [&](int buf) {
 #pragma unroll
-        for (int i = 0; i < NLD; ++i) {
-            const int idx = tid + i * kThreads;
-            if constexpr (VEC) {
-                const int row = idx / (BK / 4), kq = (idx % (BK / 4)) * 4;
-                As[buf][kq + 0][row] = xa[i].x; As[buf][kq + 1][row] = xa[i].y;
-                As[buf][kq + 2][row] = xa[i].z; As[buf][kq + 3][row] = xa[i].w;
-                Bs[buf][kq + 0][row] = wa[i].x; Bs[buf][kq + 1][row] = wa[i].y;
-                Bs[buf][kq + 2][row] = wa[i].z; Bs[buf][kq + 3][row] = wa[i].w;
-            } else {
-                const int row = idx / BK, k = idx % BK;
-                As[buf][k][row] = xs[i];
-                Bs[buf][k][row] = ws[i];
-            }
-        }
+        for (int i = 0; i < NA; ++i) put(xa[i], lds + buf * BUF + sc * LA + sr + i * RSTEP, LA);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) put(xb[i], lds + buf * BUF + SIDE_A + sc * LB + sr + i * RSTEP, LB);
     };
 
-    f32x16 acc[2][2];
+    f32x16 acc[TI][TJ], low[TI][TJ];                          // sums of the first parts' products, of the rest
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-    // operands of the next pair of k are read from LDS before the four multiplies of the current
-    // pair are issued, so their latency passes while the matrix pipe is busy
+        for (int j = 0; j < TJ; ++j) acc[i][j] = low[i][j] = 0.f;
     auto multiply = [&](int buf) {
-        const float *pa = &As[buf][half][wm + l32], *pb = &Bs[buf][half][wn + l32];
-        float a0 = pa[0], a1 = pa[32], b0 = pb[0], b1 = pb[32];
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
 #pragma unroll
-        for (int kk = 0; kk < BK; kk += 2) {
-            float na0 = 0.f, na1 = 0.f, nb0 = 0.f, nb1 = 0.f;
-            if (kk + 2 < BK) {
-                na0 = pa[(kk + 2) * LDT]; na1 = pa[(kk + 2) * LDT + 32];
-                nb0 = pb[(kk + 2) * LDT]; nb1 = pb[(kk + 2) * LDT + 32];
+        for (int kc = 0; kc < CH; kc += 2) {
+            const u32x4 *pa = lds + buf * BUF + (kc + half) * LA + wm + l32;
+            const u32x4 *pb = lds + buf * BUF + SIDE_A + (kc + half) * LB + wn + l32;
+            bf16x8 a[3][TI], b[3][TJ];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+#pragma unroll
+                for (int i = 0; i < TI; ++i) a[p][i] = __builtin_bit_cast(bf16x8, pa[p * CH * LA + 32 * i]);
+#pragma unroll
+                for (int j = 0; j < TJ; ++j) b[p][j] = __builtin_bit_cast(bf16x8, pb[p * CH * LB + 32 * j]);
             }
-            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
-            a0 = na0; a1 = na1; b0 = nb0; b1 = nb1;
-            // keep that order in the schedule: the LDS reads of the pair, then its four multiplies
-            if (kk + 2 < BK) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+#pragma unroll
+            for (int o = 2; o >= 0; --o)                      // parts p and o - p
+#pragma unroll
+                for (int p = 0; p <= o; ++p)
+#pragma unroll
+                    for (int i = 0; i < TI; ++i)
+#pragma unroll
+                        for (int j = 0; j < TJ; ++j) {
+                            f32x16 &sum = o ? low[i][j] : acc[i][j];
+                            sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[p][i], b[o - p][j], sum, 0, 0, 0);
+                        }
         }
     };
 
+    const int steps = (K + BK - 1) / BK;
     fetch(0);
     stage(0);
+    fetch(BK);
     __syncthreads();
-    const int steps = (K + BK - 1) / BK;
-    int buf = 0;
     for (int t = 1; t < steps; ++t) {
-        fetch(t * BK);                                        // in flight during the multiplies below
-        multiply(buf);
-        stage(buf ^ 1);                                       // the other buffer: nobody reads it now
+        multiply((t - 1) & 1);
+        stage(t & 1);                                         // the other buffer: nobody reads it now
+        fetch((t + 1) * BK);                                  // in flight during the next multiplies
         __syncthreads();
-        buf ^= 1;
     }
-    multiply(buf);
+    multiply((steps - 1) & 1);
 
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < TJ; ++j) {
+            f32x16 r = acc[i][j] + low[i][j];
+            bool odd = false;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) odd = odd || !finite(r[v]);
             const int col = n0 + wn + j * 32 + l32;
+            if (__any(odd)) {                                 // the results that are not finite once more, in fp32
+                const int64_t arow = m0 + wm + i * 32 + l32;
+                f32x16 s = 0.f;
+                for (int k = 0; k < K; k += 2) {
+                    const int kk = k + half;
+                    const float a = arow < M && kk < K ? X[arow * K + kk] : 0.f;
+                    const float b = col < N && kk < K ? W[(int64_t)col * K + kk] : 0.f;
+                    s = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, s, 0, 0, 0);
+                }
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    if (!finite(r[v])) r[v] = s[v];
+            }
             if (col >= N) continue;
             const float bv = bias ? bias[col] : 0.f;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int64_t row = m0 + wm + i * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-                if (row < M) Y[row * N + col] = activate<ACT>(acc[i][j][v] + bv);
+                if (row < M) Y[row * N + col] = activate<ACT>(r[v] + bv);
             }
         }
 }
 
+// One to four outputs per sample: a wavefront per row, the row's products summed lane by lane (k, k + 64,
+// ...) and then across the lanes.  A matrix tile would spend 128 columns on them.
+constexpr int kNarrow = 4;
+constexpr int64_t kNarrowRows = (int64_t)1 << 30;              // a grid of 2^28 workgroups
+template <int ACT>
+__global__ __launch_bounds__(kThreads) void mlp_narrow(const float *__restrict__ X, const float *__restrict__ W,
+                                                       const float *__restrict__ bias, float *__restrict__ Y,
+                                                       int64_t M, int N, int K)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t row = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+    if (row >= M) return;
+    float sum[kNarrow] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int k = lane; k < K; k += 64) {
+        const float x = X[row * K + k];
+#pragma unroll
+        for (int n = 0; n < kNarrow; ++n)
+            if (n < N) sum[n] = fmaf(x, W[(int64_t)n * K + k], sum[n]);
+    }
+#pragma unroll
+    for (int n = 0; n < kNarrow; ++n) {
+        if (n >= N) break;
+#pragma unroll
+        for (int sh = 32; sh >= 1; sh >>= 1) sum[n] += __shfl_xor(sum[n], sh, 64);
+        if (lane == n) Y[row * N + n] = activate<ACT>(sum[n] + (bias ? bias[n] : 0.f));
+    }
+}
 // ---- dot interaction ---------------------------------------------------------------------------
 //
 // One workgroup per sample.  The sample's T pooled vectors are copied to LDS (rows padded to a
@@ -292,28 +386,45 @@ __global__ __launch_bounds__(kThreads) void interact_gram(DevDesc dd, const floa
     }
 }
 
+// The largest tile that still gives every compute unit two workgroups: a large tile splits and reads a
+// value of X or W for more multiplies, but one workgroup alone does not fill a compute unit.  us with
+// tiles of 128 x 128 / 128 x 64 / 64 x 64, M K N: 16384 1024 512 (512 large tiles) 98 / 106 / 116,
+// 16384 512 256 (256) 39 / 33 / 37, 4096 1024 1024 (256) 64 / 55 / 64, 2048 1024 1024 (128) 64 / 42 / 35,
+// 2048 512 256 (32) 33 / 20 / 14.
+template <int TI, int TJ, int CH, int ACT>
+bool launch_tiles(const bls_ctx *ctx, const float *x, int64_t M, int K, const float *W, const float *bias, int N, float *y,
+                  bool any, hipStream_t st)
+{
+    constexpr int BM = 64 * TI, BN = 64 * TJ;
+    const uint64_t n_tiles = (uint64_t)((N + BN - 1) / BN), tiles = (uint64_t)((M + BM - 1) / BM) * n_tiles;
+    if (!any && tiles < 2 * (uint64_t)(ctx->compute_units > 0 ? ctx->compute_units : 256)) return false;
+    const dim3 grid((unsigned)((tiles + 7u) / 8u * 8u));
+    mlp_gemm<TI, TJ, CH, ACT><<<grid, kThreads, 0, st>>>(x, W, bias, y, M, N, K, (uint32_t)n_tiles, (uint32_t)tiles);
+    return true;
+}
+
+template <int ACT>
+void launch_layer(const bls_ctx *ctx, const float *x, int64_t M, int K, const float *W, const float *bias, int N, float *y,
+                  hipStream_t st)
+{
+    // M = 16384, K = 256, N = 1: 27 us as a column of tiles of 128, 9.2 of 64, 8.4 a wavefront per row
+    if (N <= kNarrow && M <= kNarrowRows) mlp_narrow<ACT><<<dim3((unsigned)((M + 3) / 4)), kThreads, 0, st>>>(x, W, bias, y, M, N, K);
+    else if (launch_tiles<2, 2, 2, ACT>(ctx, x, M, K, W, bias, N, y, false, st)) return;
+    else if (launch_tiles<2, 1, 4, ACT>(ctx, x, M, K, W, bias, N, y, false, st)) return;
+    else (void)launch_tiles<1, 1, 4, ACT>(ctx, x, M, K, W, bias, N, y, true, st);
+}
+
 }  // namespace
 
 int bls_launch_mlp_layer(bls_ctx *ctx, const float *x, int64_t M, int K, const float *W, const float *bias, int N,
                          int act, float *y, hipStream_t st)
 {
     if (M == 0) return BLS_OK;
-    const uint64_t m_tiles = (uint64_t)((M + BM - 1) / BM), n_tiles = (uint64_t)((N + BN - 1) / BN);
-    if (m_tiles * n_tiles > 0x7fffffffull - 8) return bls_fail(ctx, BLS_EINVAL, "bls_mlp_layer: too many tiles");
-    const uint32_t tiles = (uint32_t)(m_tiles * n_tiles);
-    const dim3 grid((tiles + 7u) / 8u * 8u);
-    const bool vec = K % 4 == 0 && (((uintptr_t)x | (uintptr_t)W) & 15u) == 0;
-#define BLS_GEMM(V, A) mlp_gemm<V, A><<<grid, kThreads, 0, st>>>(x, W, bias, y, M, N, K, (uint32_t)n_tiles, tiles)
-    if (vec) {
-        if (act == BLS_ACT_RELU) BLS_GEMM(true, BLS_ACT_RELU);
-        else if (act == BLS_ACT_SIGMOID) BLS_GEMM(true, BLS_ACT_SIGMOID);
-        else BLS_GEMM(true, BLS_ACT_NONE);
-    } else {
-        if (act == BLS_ACT_RELU) BLS_GEMM(false, BLS_ACT_RELU);
-        else if (act == BLS_ACT_SIGMOID) BLS_GEMM(false, BLS_ACT_SIGMOID);
-        else BLS_GEMM(false, BLS_ACT_NONE);
-    }
-#undef BLS_GEMM
+    const uint64_t tiles = (uint64_t)((M + 127) / 128) * (uint64_t)((N + 127) / 128);
+    if (tiles > 0x7fffffffull - 8) return bls_fail(ctx, BLS_EINVAL, "bls_mlp_layer: too many tiles");
+    if (act == BLS_ACT_RELU) launch_layer<BLS_ACT_RELU>(ctx, x, M, K, W, bias, N, y, st);
+    else if (act == BLS_ACT_SIGMOID) launch_layer<BLS_ACT_SIGMOID>(ctx, x, M, K, W, bias, N, y, st);
+    else launch_layer<BLS_ACT_NONE>(ctx, x, M, K, W, bias, N, y, st);
     BLS_HIP(ctx, hipGetLastError());
     return BLS_OK;
 }

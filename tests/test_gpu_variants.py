@@ -55,3 +55,61 @@ def test_permutes_on_both_sides_of_the_streaming_size(part, P, T, D, B, mean):
     assert np.array_equal(R.cpu().numpy().view(np.uint32), r.view(np.uint32))
     ref = oracle.unpack(case, r, offsets if mean else None)
     assert np.array_equal(out.cpu().numpy().view(np.uint32), ref.view(np.uint32))
+
+
+def layer(c, x, W, b, act=0):
+    y = torch.full((x.shape[0], W.shape[0]), float("nan"), device=DEV)
+    c.bls_mlp_layer(x, W, b, act, y)
+    return y
+
+
+def dense_ctx():
+    import paper_2512_19342_amd as A
+    return A.Context(1, 2, 4, 1, 4, [8] * 2, [0] * 2, A.BLS_FP32, 0)
+
+
+# both sides of each line between the tiles (512 workgroups of 128 x 128, of 128 x 64) and a row per wavefront; sizes
+# that no tile divides, steps of 16 and 32 k with and without a remainder
+@pytest.mark.parametrize("M,K,N", [(65409, 33, 33), (65409, 415, 128), (32768, 64, 256), (65408, 16, 70), (32513, 45, 65),
+                                   (16384, 31, 200), (16300, 8, 256), (4000, 129, 31), (257, 1, 5), (1029, 67, 4), (300, 130, 1)])
+def test_layer_tiles(M, K, N):
+    c = dense_ctx()
+    g = torch.Generator(device=DEV).manual_seed(M + K)
+    x, W, b = (torch.randn(s, device=DEV, generator=g) for s in ((M, K), (N, K), (N,)))
+    y = layer(c, x, W, b)
+    at = torch.unique(torch.cat([torch.arange(0, M, 61, device=DEV), torch.arange(max(0, M - 200), M, device=DEV)]))
+    some = x[at].contiguous()
+    assert torch.equal(layer(c, some, W, b), y[at])      # a sample's result does not depend on the others
+    ref = some.double() @ W.double().t() + b.double()
+    err = (K + 3) * 2.0 ** -24 * (some.abs().double() @ W.abs().double().t() + b.abs().double())
+    assert bool(((y[at].double() - ref).abs() <= err).all())
+    c.bls_check()
+
+
+# what has no three bf16 parts, or parts outside the normal range
+@pytest.mark.parametrize("M", [3, 70000])
+def test_layer_infinities_and_the_ends_of_the_range(M):
+    c = dense_ctx()
+    K, N, inf, big = 40, 130, float("inf"), 3.4028234663852886e38
+    x, W = torch.ones((M, K), device=DEV), torch.ones((N, K), device=DEV)
+    x[0, 5], x[1, 7] = inf, float("nan")
+    x[2] = 0.0
+    x[2, 3] = big                                       # rounds up to the bf16 infinity
+    x[M - 1, 9] = -inf
+    W[:, 30] = torch.where(torch.arange(N, device=DEV) % 2 == 0, 1.0, 0.0)
+    W[4, 5], W[6, 3] = 0.0, 0.5                         # inf * 0, big * 0.5
+    W[7, 9] = inf                                       # a column that is infinite everywhere but where x is 0
+    y = layer(c, x, W, None).cpu().double()
+    ref = x.cpu().double() @ W.cpu().double().t()
+    assert torch.equal(torch.isnan(y), torch.isnan(ref)) and torch.equal(torch.isinf(y), torch.isinf(ref))
+    fin = torch.isfinite(ref)
+    assert torch.equal(y[fin], ref[fin])                # small whole numbers and single products
+    assert torch.equal(torch.sign(y[torch.isinf(y)]), torch.sign(ref[torch.isinf(ref)]))
+    for ex, ew in ((-100, 90), (-116, 110), (110, -120), (60, 50)):
+        g = torch.Generator(device=DEV).manual_seed(ex + 200)
+        x = torch.randn((min(M, 300), K), device=DEV, generator=g)
+        W = torch.randn((N, K), device=DEV, generator=g)
+        one, scaled = layer(c, x, W, None), layer(c, x * 2.0 ** ex, W * 2.0 ** ew, None)
+        # a part below 2^-126 may count as nothing: 2^-126 per value, against values of 2^ex and 2^ew
+        loss = K * 4 * 4 * (2.0 ** (-126 - ex) + 2.0 ** (-126 - ew))
+        assert bool(((scaled.double() * 2.0 ** -(ex + ew) - one.double()).abs() <= loss).all())
