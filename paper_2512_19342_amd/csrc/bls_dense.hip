@@ -6,6 +6,8 @@
 // accumulator register v of lane l is element (8 * (v / 4) + 4 * (l / 32) + v % 4, l % 32).
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "bls_internal.h"
 
 namespace {
@@ -49,33 +51,36 @@ __device__ __forceinline__ float activate(float v)
 // 32 TI x 32 TJ.  Every element is summed over k in the same order whatever the tile, so that a
 // sample's result does not depend on how many others are in the call.
 // Tiles are staged already split, in planes of eight k: what a lane needs of a row is one 16-byte
-// read, rows consecutive; two buffers, and the loads of the step after the next in flight while one is
-// multiplied.  Workgroups are numbered so that those that share rows of X follow each other on one XCD
+// read, rows consecutive; two buffers, and the loads of two further steps in flight while one is
+// multiplied.  Whole steps are loaded without a branch and the splitting is spread behind the multiplies
+// (a branch per chunk made the compiler wait for the loads before the first multiply: 394 us for
+// 16384 x 2208 -> 1024 instead of 375, 28 for 512 x 1024 -> 1024 instead of 21).  Workgroups are numbered so that those that share rows of X follow each other on one XCD
 // (one L2), N-tile fastest.
 //
-// M = 16384, us, fp32 instructions / this: 2208 -> 1024 593 / 387 (192 TFLOP/s), 1024 -> 1024 284 / 189,
-// 1024 -> 512 152 / 98, 512 -> 256 55 / 33, 256 -> 128 32 / 12.  M = 2048: 415 -> 1024 54 / 19,
-// 1024 -> 1024 94 / 35, 512 -> 256 52 / 14.  The matrix pipe is busy for 46 % of the first of these; the
-// splitting and the LDS reads, which every wavefront does between its multiplies, are the rest.
+// M = 16384, us, fp32 instructions / this: 2208 -> 1024 593 / 375 (198 TFLOP/s), 1024 -> 1024 284 / 184,
+// 1024 -> 512 152 / 95, 512 -> 256 55 / 32, 256 -> 128 32 / 13.  M = 2048: 415 -> 1024 54 / 19,
+// 1024 -> 1024 94 / 33, 512 -> 256 52 / 12.  The first of these is 1.19 PFLOP/s of bf16 products, 48 % of
+// the matrix pipe's peak; a step's 12 reads and 6 writes of 16 bytes a lane keep the LDS busy for about as
+// many cycles as its 24 multiplies take.
 __device__ __forceinline__ bool finite(float v) { return __builtin_fabsf(v) <= 3.402823466e38f; }
 
 struct Chunk { float v[8]; };                                 // eight consecutive k of one row
 
 // Eight floats from k of a row of K (zeros from K on); rows need no alignment beyond the float's.
-__device__ __forceinline__ Chunk load_chunk(const float *__restrict__ row, bool in, int k, int K)
+// WHOLE: all eight are there.
+template <bool WHOLE>
+__device__ __forceinline__ Chunk load_chunk(const float *__restrict__ row, int k, int K)
 {
     Chunk c;
     f32x4 lo = 0.f, hi = 0.f;
-    if (in) {
-        if (k + 8 <= K) {
-            lo = *reinterpret_cast<const f32x4_a4 *>(row + k);
-            hi = *reinterpret_cast<const f32x4_a4 *>(row + k + 4);
-        } else {
+    if (WHOLE || k + 8 <= K) {
+        lo = *reinterpret_cast<const f32x4_a4 *>(row + k);
+        hi = *reinterpret_cast<const f32x4_a4 *>(row + k + 4);
+    } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (k + j < K) lo[j] = row[k + j];
-                if (k + 4 + j < K) hi[j] = row[k + 4 + j];
-            }
+        for (int j = 0; j < 4; ++j) {
+            if (k + j < K) lo[j] = row[k + j];
+            if (k + 4 + j < K) hi[j] = row[k + 4 + j];
         }
     }
 #pragma unroll
@@ -94,7 +99,7 @@ __device__ __forceinline__ uint32_t take_bf16(float &a, float &b)
 }
 
 template <int TI, int TJ, int CH, int ACT>
-__global__ __launch_bounds__(kThreads, TI * TJ == 4 ? 2 : 3) void mlp_gemm(const float *__restrict__ X, const float *__restrict__ W,
+__global__ __launch_bounds__(kThreads, TI * TJ > 1 ? 2 : 3) void mlp_gemm(const float *__restrict__ X, const float *__restrict__ W,
                                                         const float *__restrict__ bias, float *__restrict__ Y,
                                                         int64_t M, int N, int K, uint32_t n_tiles, uint32_t tiles)
 {
@@ -118,18 +123,29 @@ __global__ __launch_bounds__(kThreads, TI * TJ == 4 ? 2 : 3) void mlp_gemm(const
     // thread tid stages planes c of rows r, r + 256 / CH, ...: CH threads read a row's step together
     constexpr int NA = BM * CH / kThreads, NB = BN * CH / kThreads, RSTEP = kThreads / CH;
     const int sr = tid / CH, sc = tid % CH;
-    Chunk xa[NA], xb[NB];
-    auto fetch = [&](int k0) {
+    // rows past the last repeat it: what they give is not stored
+    const float *xrow[NA], *wrow[NB];
 #pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            const int64_t row = m0 + sr + i * RSTEP;
-            xa[i] = load_chunk(X + row * K, row < M, k0 + 8 * sc, K);
-        }
+    for (int i = 0; i < NA; ++i) {
+        const int64_t row = m0 + sr + i * RSTEP;
+        xrow[i] = X + (row < M ? row : M - 1) * K;
+    }
 #pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            const int row = n0 + sr + i * RSTEP;
-            xb[i] = load_chunk(W + (int64_t)row * K, row < N, k0 + 8 * sc, K);
-        }
+    for (int i = 0; i < NB; ++i) {
+        const int row = n0 + sr + i * RSTEP;
+        wrow[i] = W + (int64_t)(row < N ? row : N - 1) * K;
+    }
+    struct Held { Chunk x[NA], w[NB]; } even, odd;            // of an even and of an odd step, on their way
+    auto load = [&](Held &h, int k0, auto whole) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) h.x[i] = load_chunk<decltype(whole)::value>(xrow[i], k0 + 8 * sc, K);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) h.w[i] = load_chunk<decltype(whole)::value>(wrow[i], k0 + 8 * sc, K);
+    };
+    const int steps = (K + BK - 1) / BK, full = K / BK;
+    auto fetch = [&](Held &h, int step, auto whole) {         // nothing past the last step
+        if (decltype(whole)::value || step < full) load(h, step * BK, std::true_type());
+        else if (step < steps) load(h, step * BK, std::false_type());
     };
     auto put = [&](Chunk c, u32x4 *at, int plane) {           // the three parts lie CH planes apart
 #pragma unroll
@@ -140,11 +156,11 @@ __global__ __launch_bounds__(kThreads, TI * TJ == 4 ? 2 : 3) void mlp_gemm(const
             at[p * CH * plane] = w;
         }
     };
-    auto stage = [&](int buf) {
+    auto stage = [&](const Held &h, int buf) {
 #pragma unroll
-        for (int i = 0; i < NA; ++i) put(xa[i], lds + buf * BUF + sc * LA + sr + i * RSTEP, LA);
+        for (int i = 0; i < NA; ++i) put(h.x[i], lds + buf * BUF + sc * LA + sr + i * RSTEP, LA);
 #pragma unroll
-        for (int i = 0; i < NB; ++i) put(xb[i], lds + buf * BUF + SIDE_A + sc * LB + sr + i * RSTEP, LB);
+        for (int i = 0; i < NB; ++i) put(h.w[i], lds + buf * BUF + SIDE_A + sc * LB + sr + i * RSTEP, LB);
     };
 
     f32x16 acc[TI][TJ], low[TI][TJ];                          // sums of the first parts' products, of the rest
@@ -179,16 +195,43 @@ __global__ __launch_bounds__(kThreads, TI * TJ == 4 ? 2 : 3) void mlp_gemm(const
         }
     };
 
-    const int steps = (K + BK - 1) / BK;
-    fetch(0);
-    stage(0);
-    fetch(BK);
-    __syncthreads();
-    for (int t = 1; t < steps; ++t) {
+    // step t - 1 multiplied, step t put into the other buffer (nobody reads it now), step t + 2 asked for
+    auto advance = [&](Held &h, int t, auto whole) {
         multiply((t - 1) & 1);
-        stage(t & 1);                                         // the other buffer: nobody reads it now
-        fetch((t + 1) * BK);                                  // in flight during the next multiplies
+        stage(h, t & 1);
+        fetch(h, t + 2, whole);
+        // the reads first, then the splitting spread evenly behind the multiplies
+        constexpr int kMfma = 3 * TI * TJ * CH, kValu = (44 * (NA + NB) + kMfma - 1) / kMfma, kWrites = 3 * (NA + NB);
+        __builtin_amdgcn_sched_group_barrier(0x100, 3 * (TI + TJ) * CH / 2, 0);
+#pragma unroll
+        for (int i = 0; i < kMfma; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);
+            if ((i + 1) * kWrites / kMfma > i * kWrites / kMfma) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x020, 2 * (NA + NB), 0);
         __syncthreads();
+    };
+    if (full >= 3) {
+        load(even, 0, std::true_type());
+        load(odd, BK, std::true_type());
+        stage(even, 0);
+        load(even, 2 * BK, std::true_type());
+    } else {
+        fetch(even, 0, std::false_type());
+        fetch(odd, 1, std::false_type());
+        stage(even, 0);
+        fetch(even, 2, std::false_type());
+    }
+    __syncthreads();
+    int t = 1;
+    for (; t + 3 < full; t += 2) {                            // steps t + 2 and t + 3 are whole
+        advance(odd, t, std::true_type());
+        advance(even, t + 1, std::true_type());
+    }
+    for (; t < steps; t += 2) {
+        advance(odd, t, std::false_type());
+        if (t + 1 < steps) advance(even, t + 1, std::false_type());
     }
     multiply((steps - 1) & 1);
 
@@ -197,11 +240,11 @@ __global__ __launch_bounds__(kThreads, TI * TJ == 4 ? 2 : 3) void mlp_gemm(const
 #pragma unroll
         for (int j = 0; j < TJ; ++j) {
             f32x16 r = acc[i][j] + low[i][j];
-            bool odd = false;
+            bool redo = false;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) odd = odd || !finite(r[v]);
+            for (int v = 0; v < 16; ++v) redo = redo || !finite(r[v]);
             const int col = n0 + wn + j * 32 + l32;
-            if (__any(odd)) {                                 // the results that are not finite once more, in fp32
+            if (__any(redo)) {                                 // the results that are not finite once more, in fp32
                 const int64_t arow = m0 + wm + i * 32 + l32;
                 f32x16 s = 0.f;
                 for (int k = 0; k < K; k += 2) {
@@ -390,7 +433,7 @@ __global__ __launch_bounds__(kThreads) void interact_gram(DevDesc dd, const floa
 // value of X or W for more multiplies, but one workgroup alone does not fill a compute unit.  us with
 // tiles of 128 x 128 / 128 x 64 / 64 x 64, M K N: 16384 1024 512 (512 large tiles) 98 / 106 / 116,
 // 16384 512 256 (256) 39 / 33 / 37, 4096 1024 1024 (256) 64 / 55 / 64, 2048 1024 1024 (128) 64 / 42 / 35,
-// 2048 512 256 (32) 33 / 20 / 14.
+// 2048 512 256 (32) 33 / 20 / 14 (taken with one step of loads in flight).
 template <int TI, int TJ, int CH, int ACT>
 bool launch_tiles(const bls_ctx *ctx, const float *x, int64_t M, int K, const float *W, const float *bias, int N, float *y,
                   bool any, hipStream_t st)

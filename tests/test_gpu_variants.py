@@ -113,3 +113,19 @@ def test_layer_infinities_and_the_ends_of_the_range(M):
         # a part below 2^-126 may count as nothing: 2^-126 per value, against values of 2^ex and 2^ew
         loss = K * 4 * 4 * (2.0 ** (-126 - ex) + 2.0 ** (-126 - ew))
         assert bool(((scaled.double() * 2.0 ** -(ex + ew) - one.double()).abs() <= loss).all())
+
+
+# layers of no, one, ... six whole steps of k, with and without a remainder, in each of the tiles
+@pytest.mark.parametrize("M,N,step", [(65536, 65, 16), (32768, 127, 32), (190, 70, 32)])
+def test_layer_steps(M, N, step):
+    c = dense_ctx()
+    for K in [1, *(n * step + d for n in range(1, 7) for d in (-1, 0, 1))]:
+        g = torch.Generator(device=DEV).manual_seed(K)
+        x, W, b = (torch.randn(s, device=DEV, generator=g) for s in ((M, K), (N, K), (N,)))
+        y = layer(c, x, W, b)
+        some, last = x[-150:].contiguous(), y[-150:]
+        assert torch.equal(layer(c, some, W, b), last), K
+        ref = some.double() @ W.double().t() + b.double()
+        err = (K + 3) * 2.0 ** -24 * (some.abs().double() @ W.abs().double().t() + b.abs().double())
+        assert bool(((last.double() - ref).abs() <= err).all()), K
+    c.bls_check()
