@@ -303,11 +303,83 @@ __global__ __launch_bounds__(kThreads) void mlp_narrow(const float *__restrict__
 // tile one accumulator over D / 2 matrix instructions; the last wavefront also takes the T
 // products with the dense vector x.  Output row: x, then for i = 1..T the products of pooled
 // vector i-1 with x and with pooled vectors 0..i-2.
-// SLOT = false: emb is the completed lookup [B][T][D].  SLOT = true: emb is a ring slot in receive
-// order and the copy to LDS is the completion itself - vector (b, t) is read where its owner put
+// FROM_OUT: emb is the completed lookup [B][T][D].  FROM_SLOT, FROM_PARTIALS: emb is a ring slot in
+// receive order and the copy to LDS is the completion itself - vector (b, t) is read where its owner put
 // it, and for a row-wise partition the P partial vectors are added in increasing owner rank from
 // +0, exactly as the copy-out kernel does.
-template <bool SLOT>
+// Memory bounds the kernel (16384 samples of 64 vectors of 128: 0.68 GB, 130 us at the rate of a copy).  A
+// thread's eight loads of a round are all issued before the first is used: added up one by one as they
+// come, a slot's took 290 us at that size, now 206.
+enum Source { FROM_OUT, FROM_SLOT, FROM_PARTIALS };
+
+// The sample's vectors in pieces of V (one float, or four), thread by thread, to rows of LD floats at Es.
+// The d-th partial of vector t starts at vec0 + t_q[t] * vec_step + d * part_step (FROM_OUT: t for t_q[t]).
+template <Source SRC, typename V>
+__device__ __forceinline__ void fill_vectors(float *Es, uint32_t T, uint32_t D, uint32_t LD, int F, const float *vec0,
+                                             const int32_t *__restrict__ t_q, int64_t vec_step, int64_t part_step)
+{
+    constexpr uint32_t W = sizeof(V) / sizeof(float);
+    constexpr int kFill = 8;
+    const uint32_t per = D / W, n = T * per, dr = kThreads / per, dc = kThreads % per;
+    uint32_t r = threadIdx.x / per, c = threadIdx.x % per;
+    for (uint32_t base = 0; base < n; base += kThreads * kFill) {
+        const float *src[kFill];
+        uint32_t at[kFill], col[kFill];
+        int32_t q[kFill];
+        bool live[kFill];
+#pragma unroll
+        for (int u = 0; u < kFill; ++u) {
+            live[u] = r < T;
+            at[u] = r * LD + c * W;
+            col[u] = c * W;
+            const uint32_t t = live[u] ? r : T - 1;           // no branch between the eight reads of t_q
+            q[u] = SRC == FROM_OUT ? (int32_t)t : t_q[t];
+            r += dr;
+            c += dc;
+            if (c >= per) { c -= per; ++r; }
+        }
+        // all of them waited for here, once: otherwise waits for t_q come between the vectors' loads
+        if constexpr (SRC != FROM_OUT) {
+#pragma unroll
+            for (int u = 0; u < kFill; ++u) asm volatile("" : "+v"(q[u]));
+        }
+#pragma unroll
+        for (int u = 0; u < kFill; ++u) src[u] = vec0 + q[u] * vec_step + col[u];
+        V v[kFill];
+#pragma unroll
+        for (int u = 0; u < kFill; ++u) {
+            v[u] = 0.f;
+            if (SRC != FROM_PARTIALS && live[u]) v[u] = *reinterpret_cast<const V *>(src[u]);
+        }
+        if constexpr (SRC == FROM_SLOT) {
+#pragma unroll
+            for (int u = 0; u < kFill; ++u) v[u] = (V)(0.f) + v[u];   // a sum from +0: no negative zero
+        }
+        if constexpr (SRC == FROM_PARTIALS) {
+            for (int d = 0; d < F; ++d) {
+                V part[kFill];
+#pragma unroll
+                for (int u = 0; u < kFill; ++u) {
+                    part[u] = 0.f;
+                    if (live[u]) part[u] = *reinterpret_cast<const V *>(src[u] + d * part_step);
+                }
+#pragma unroll
+                for (int u = 0; u < kFill; ++u) v[u] += part[u];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kFill; ++u)
+            if (live[u]) {
+                if constexpr (W == 1) Es[at[u]] = v[u];
+                else {
+#pragma unroll
+                    for (uint32_t j = 0; j < W; ++j) Es[at[u] + j] = v[u][j];
+                }
+            }
+    }
+}
+
+template <Source SRC>
 __global__ __launch_bounds__(kThreads) void interact_gram(DevDesc dd, const float *__restrict__ x, const float *__restrict__ emb,
                                                           float *__restrict__ z, int T, int D, int TP, int LD,
                                                           uint32_t b0, int vec4)
@@ -318,81 +390,23 @@ __global__ __launch_bounds__(kThreads) void interact_gram(DevDesc dd, const floa
     const int64_t b = (int64_t)b0 + blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t Wz = (int64_t)D + (int64_t)T * (T + 1) / 2;
-    const float *__restrict__ e = emb + b * T * D;               // SLOT = false only
     float *__restrict__ zb = z + b * Wz;
     int64_t slot_base = 0, slot_step = 0;                        // vector (q, b) of the slot: slot_base + q * slot_step
-    if constexpr (SLOT) {
+    if constexpr (SRC != FROM_OUT) {
         int s; uint32_t b_loc, n;
         bls_split_sample(dd, (uint32_t)b, s, b_loc, n);
         slot_base = (int64_t)dd.Q * dd.first[s] + b_loc;
         slot_step = n;
     }
-    // start of the d-th partial (d < F; F = 1 table-wise) of pooled vector t of this sample
-    auto partial = [&](uint32_t t, int d) -> const float * {
-        return emb + (slot_base + (int64_t)(dd.t_q[t] + d * dd.T) * slot_step) * D;
-    };
+    const float *vec0 = emb + (SRC == FROM_OUT ? b * T : slot_base) * D;
+    const int64_t vec_step = SRC == FROM_OUT ? D : slot_step * D, part_step = dd.T * slot_step * D;
 
     // zeros: the padding columns behind every vector and the padding rows behind the last one
     const int padc = LD - D;
     for (int i = tid; i < T * padc; i += kThreads) Es[(i / padc) * LD + D + i % padc] = 0.f;
     for (int i = T * LD + tid; i < TP * LD; i += kThreads) Es[i] = 0.f;
-    // the vectors themselves: eight independent loads per lane in flight, then the LDS writes
-    constexpr int kFill = 8;
-    if (vec4) {
-        const float4 *__restrict__ e4 = reinterpret_cast<const float4 *>(e);
-        const uint32_t n4 = (uint32_t)T * (uint32_t)D / 4u, c4n = (uint32_t)D / 4u;
-        for (uint32_t base = 0; base < n4; base += kThreads * kFill) {
-            float4 v[kFill];
-#pragma unroll
-            for (int u = 0; u < kFill; ++u) {
-                const uint32_t i = base + u * kThreads + tid;
-                v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if constexpr (SLOT) {
-                    if (i < n4) {
-                        const uint32_t r = i / c4n, c = (i - r * c4n) * 4u;
-                        for (int d = 0; d < dd.F; ++d) {
-                            const float4 part = *reinterpret_cast<const float4 *>(partial(r, d) + c);
-                            v[u].x += part.x; v[u].y += part.y; v[u].z += part.z; v[u].w += part.w;
-                        }
-                    }
-                } else if (i < n4) {
-                    v[u] = e4[i];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kFill; ++u) {
-                const uint32_t i = base + u * kThreads + tid;
-                if (i < n4) {
-                    const uint32_t r = i / c4n, c = (i - r * c4n) * 4u;
-                    float *d = Es + r * LD + c;
-                    d[0] = v[u].x; d[1] = v[u].y; d[2] = v[u].z; d[3] = v[u].w;
-                }
-            }
-        }
-    } else {
-        const uint32_t n1 = (uint32_t)T * (uint32_t)D;
-        for (uint32_t base = 0; base < n1; base += kThreads * kFill) {
-            float v[kFill];
-#pragma unroll
-            for (int u = 0; u < kFill; ++u) {
-                const uint32_t i = base + u * kThreads + tid;
-                v[u] = 0.f;
-                if constexpr (SLOT) {
-                    if (i < n1) {
-                        const uint32_t r = i / (uint32_t)D, c = i - r * (uint32_t)D;
-                        for (int d = 0; d < dd.F; ++d) v[u] += partial(r, d)[c];
-                    }
-                } else if (i < n1) {
-                    v[u] = e[i];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kFill; ++u) {
-                const uint32_t i = base + u * kThreads + tid;
-                if (i < n1) { const uint32_t r = i / (uint32_t)D; Es[r * LD + (i - r * (uint32_t)D)] = v[u]; }
-            }
-        }
-    }
+    if (vec4) fill_vectors<SRC, f32x4>(Es, T, D, LD, dd.F, vec0, dd.t_q, vec_step, part_step);
+    else fill_vectors<SRC, float>(Es, T, D, LD, dd.F, vec0, dd.t_q, vec_step, part_step);
     for (int c = tid; c < D; c += kThreads) {
         const float v = x[b * D + c];
         xsh[c] = v;
@@ -486,8 +500,9 @@ int bls_launch_interact(bls_ctx *ctx, const float *x, const float *emb, int from
     const int TP = (T + 31) / 32 * 32, LD = ((D + 1) & ~1) + 1;
     const int vec4 = D % 4 == 0 && ((uintptr_t)emb & 15u) == 0;   // every vector then starts 16-byte aligned
     const size_t lds = bls_interact_lds_bytes(T, D);
-    if (from_slot) interact_gram<true><<<dim3(bn), kThreads, lds, st>>>(ctx->desc, x, emb, z, T, D, TP, LD, b0, vec4);
-    else interact_gram<false><<<dim3(bn), kThreads, lds, st>>>(ctx->desc, x, emb, z, T, D, TP, LD, b0, vec4);
+    if (!from_slot) interact_gram<FROM_OUT><<<dim3(bn), kThreads, lds, st>>>(ctx->desc, x, emb, z, T, D, TP, LD, b0, vec4);
+    else if (ctx->desc.F == 1) interact_gram<FROM_SLOT><<<dim3(bn), kThreads, lds, st>>>(ctx->desc, x, emb, z, T, D, TP, LD, b0, vec4);
+    else interact_gram<FROM_PARTIALS><<<dim3(bn), kThreads, lds, st>>>(ctx->desc, x, emb, z, T, D, TP, LD, b0, vec4);
     BLS_HIP(ctx, hipGetLastError());
     return BLS_OK;
 }

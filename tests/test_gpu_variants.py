@@ -129,3 +129,27 @@ def test_layer_steps(M, N, step):
         err = (K + 3) * 2.0 ** -24 * (some.abs().double() @ W.abs().double().t() + b.abs().double())
         assert bool(((last.double() - ref).abs() <= err).all()), K
     c.bls_check()
+
+
+# the interaction's copy to LDS: more columns than threads, more pieces than a round of loads, one vector,
+# odd lengths, whole tables and partial vectors; negative zeros among the values
+@pytest.mark.parametrize("part,P,T,D,B", [(0, 3, 3, 479, 7), (1, 3, 3, 479, 7), (0, 2, 64, 200, 5), (1, 3, 64, 200, 5),
+                                          (0, 1, 1, 4, 3), (1, 5, 1, 1, 9), (0, 4, 33, 100, 11), (1, 4, 26, 64, 33)])
+def test_interaction_copies(part, P, T, D, B):
+    c = permute_ctx(P, T, D, B, part)
+    case = oracle.Case(P, T, D, B, part, [P * P] * T, [t % P for t in range(T)] if part == 0 else [0] * T, 0)
+    rng = np.random.default_rng(T * D)
+    S = rng.normal(size=c.n_vec * D).astype(np.float32)
+    S[rng.random(S.size) < 0.1] = -0.0
+    emb = oracle.unpack(case, oracle.exchange(case, S), None)
+    x = rng.normal(size=(B, D)).astype(np.float32)
+    dx, z, zs = (torch.from_numpy(x).to(DEV), *(torch.full((B, D + T * (T + 1) // 2), float("nan"), device=DEV) for _ in range(2)))
+    c.bls_set_ring(torch.empty(c.n_vec * D, device=DEV))
+    it, slot = c.bls_ring_advance()
+    c.bls_alltoallv_local(torch.from_numpy(S).to(DEV), slot)
+    c.bls_unpack_interact(it, dx, zs)
+    c.bls_interact(dx, torch.from_numpy(emb).to(DEV), z)
+    c.bls_check()
+    ref, err = oracle.interact(x, emb)
+    assert np.array_equal(zs.cpu().numpy().view(np.uint32), z.cpu().numpy().view(np.uint32))
+    assert np.all(np.abs(z.cpu().numpy().astype(np.float64) - ref) <= err)
