@@ -193,7 +193,8 @@ def dense_section(args, w, pipe, batches, nnzs, note) -> dict:
             "library_gemm_tflops_same_shape": lib_tflops,
             "mlp_tflops": sum(flops[k] for k in mm) / (sum(ms[k] for k in mm) * 1e-3) / 1e12,
             "mfma_roofline": {"bound": "mfma", "kernel": f"mlp_gemm ({names[big]})", "achieved": kernels[names[big]]["tflops"],
-                              "peak": 157.3, "unit": "TFLOP/s", "frac": kernels[names[big]]["tflops"] / 157.3},
+                              # six bf16 products per fp32 one, at 2.5 PFLOP/s
+                              "peak": 2500 / 6, "unit": "TFLOP/s", "frac": kernels[names[big]]["tflops"] / (2500 / 6)},
             "loop": {"entry_points": "bls_plan + bls_embbag_pool_put + bls_mlp_layer x3 | bls_unpack + bls_interact "
                                      "(or bls_unpack_interact) + bls_mlp_layer x5", "bound": w.k, **loops}}
 
