@@ -223,6 +223,15 @@ int bls_ring_advance(bls_ctx *ctx, int64_t *iter_out, int32_t *slot_out, void *h
  * `slot` must be the slot of the youngest iteration started and not yet exchanged. */
 int bls_alltoallv_local(bls_ctx *ctx, const float *d_send, int32_t slot, void *hip_stream);
 
+/* bls_embbag_pool, bls_pack, bls_ring_advance and bls_alltoallv_local in that order, in one launch
+ * where that is possible: a pooled vector is stored to Y, S and R out of the pooling kernel's
+ * registers, so that pack and exchange need not read it again.  Every output, the ring and the errors
+ * are as the four calls leave them; the stream waits for the slot's earlier copy-out before it pools.
+ * The calls are made one by one for rows that are not four or more lanes' whole pieces and with
+ * hot-row lists. */
+int bls_embbag_pool_exchange(bls_ctx *ctx, const int64_t *d_ridx, const int64_t *d_segoff, int64_t nnz, float *d_pooled,
+                             float *d_send, int64_t *iter_out, int32_t *slot_out, void *hip_stream);
+
 /* The owner side in one pass: EmbeddingBag sum whose results are put straight into the
  * receive regions of ring slot `slot` (Alltoallv initiation is a sequence of one-sided puts
  * into R(dst, slot); here the source of each put is the pooling kernel's accumulator rather

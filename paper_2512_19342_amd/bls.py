@@ -21,7 +21,7 @@ BLS_TABLE_WISE, BLS_ROW_WISE = 0, 1
 
 EXPORTS = [
     "bls_create", "bls_destroy", "bls_set_shard", "bls_shard_range", "bls_desc_bytes", "bls_commit", "bls_set_hot_rows", "bls_set_pool_tuning", "bls_set_plan_tuning", "bls_sizes", "bls_pooled_counts", "bls_plan", "bls_plan_noalloc", "bls_plan_weighted", "bls_step_tablewise",
-    "bls_embbag_pool", "bls_embbag_pool_weighted", "bls_embbag_pool_put", "bls_embbag_pool_put_weighted", "bls_pack",
+    "bls_embbag_pool", "bls_embbag_pool_weighted", "bls_embbag_pool_put", "bls_embbag_pool_put_weighted", "bls_embbag_pool_exchange", "bls_pack",
     "bls_set_ring", "bls_ring_advance", "bls_alltoallv_local", "bls_unpack", "bls_unpack_mean", "bls_ring_state",
     "bls_rank_put", "bls_rank_complete", "bls_rank_delay", "bls_mlp_layer", "bls_interact", "bls_unpack_interact", "bls_check", "bls_last_error",
 ]
@@ -75,6 +75,7 @@ def lib() -> C.CDLL:
         L.bls_rank_complete.argtypes = [vp, C.c_int32, C.c_int64, i64p, vp, vp]
         L.bls_rank_delay.argtypes = [vp, C.c_uint32, vp]
         L.bls_embbag_pool_put.argtypes = [vp, i64p, i64p, C.c_int64, C.c_int32, vp]
+        L.bls_embbag_pool_exchange.argtypes = [vp, i64p, i64p, C.c_int64, vp, vp, C.POINTER(C.c_int64), C.POINTER(C.c_int32), vp]
         L.bls_pack.argtypes = [vp, vp, vp, vp]
         L.bls_set_ring.argtypes = [vp, vp, C.c_size_t]
         L.bls_ring_advance.argtypes = [vp, C.POINTER(C.c_int64), C.POINTER(C.c_int32), vp]
@@ -238,6 +239,12 @@ class Context:
 
     def bls_embbag_pool_put(self, ridx, segoff, nnz, slot, stream=None):
         self._call("bls_embbag_pool_put", _ptr(ridx), _ptr(segoff), int(nnz), int(slot), _stream(stream))
+
+    def bls_embbag_pool_exchange(self, ridx, segoff, nnz, pooled, send, stream=None):
+        it, slot = C.c_int64(), C.c_int32()
+        self._call("bls_embbag_pool_exchange", _ptr(ridx), _ptr(segoff), int(nnz), _ptr(pooled), _ptr(send), C.byref(it),
+                   C.byref(slot), _stream(stream))
+        return it.value, slot.value
 
     def bls_pack(self, pooled, send, stream=None):
         self._call("bls_pack", _ptr(pooled), _ptr(send), _stream(stream))

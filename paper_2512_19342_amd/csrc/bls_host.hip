@@ -601,6 +601,42 @@ extern "C" int bls_embbag_pool_put_weighted(bls_ctx *ctx, const int64_t *d_ridx,
     return put_common(ctx, d_ridx, nnz > 0 ? d_rweights : nullptr, d_segoff, nnz, slot, hip_stream);
 }
 
+extern "C" int bls_embbag_pool_exchange(bls_ctx *ctx, const int64_t *d_ridx, const int64_t *d_segoff, int64_t nnz, float *d_pooled,
+                                        float *d_send, int64_t *iter_out, int32_t *slot_out, void *hip_stream)
+{
+    if (!ctx) return BLS_EINVAL;
+    // One launch waits for the slot before it pools, the calls only before they exchange.  It is the shorter one
+    // also where another stream copies the slot out: us an iteration, the calls / one launch, rings of 1 and 2 slots,
+    // 16384 samples of 64 vectors of 128 1503 / 1392 and 1498 / 1381, row-wise 8192 of 26 1085 / 935 and 1088 / 906,
+    // 2048 of 26 of 64 50 / 43 and 39 / 34.  Where no slot can be taken the calls run, and end as they always did.
+    bool apart = !bls_pool_all_fits(ctx) || !ctx->slots || ctx->head - ctx->tail >= ctx->K;
+    for (size_t r = 0; r < ctx->rr.put_next.size(); ++r)
+        apart = apart || ctx->rr.put_next[r] != ctx->rr.done_next[r] || ctx->rr.put_next[r] != ctx->rr.put_next[0];
+    if (apart) {
+        int rc = bls_embbag_pool(ctx, d_ridx, d_segoff, nnz, d_pooled, hip_stream);
+        if (rc == BLS_OK) rc = bls_pack(ctx, d_pooled, d_send, hip_stream);
+        if (rc == BLS_OK) rc = bls_ring_advance(ctx, iter_out, slot_out, hip_stream);
+        return rc == BLS_OK ? bls_alltoallv_local(ctx, d_send, *slot_out, hip_stream) : rc;
+    }
+    if (nnz < 0 || !d_segoff || !d_pooled || !d_send || d_pooled == d_send || (nnz > 0 && !d_ridx))
+        return bls_fail(ctx, BLS_EINVAL, "bls_embbag_pool_exchange: NULL or aliased argument");
+    if ((((uintptr_t)d_pooled | (uintptr_t)d_send) & 15u) != 0)
+        return bls_fail(ctx, BLS_EINVAL, "bls_embbag_pool_exchange: buffers must be 16-byte aligned");
+    int rc = bls_ready(ctx);
+    if (rc == BLS_OK) rc = bls_ring_advance(ctx, iter_out, slot_out, hip_stream);
+    RingSlot *r = nullptr;
+    if (rc == BLS_OK) rc = slot_to_fill(ctx, *slot_out, "bls_embbag_pool_exchange", &r);
+    if (rc) return rc;
+    hipStream_t st = (hipStream_t)hip_stream;
+    rc = bls_launch_pool_all(ctx, d_ridx, d_segoff, nnz, d_pooled, d_send,
+                             (float *)(ctx->slots + (size_t)*slot_out * ctx->slot_bytes), st);
+    if (rc) return rc;
+    BLS_HIP(ctx, hipEventRecord(r->filled, st));
+    r->filled_on = st;
+    r->state = 2;
+    return BLS_OK;
+}
+
 static int unpack_common(bls_ctx *ctx, int64_t iter, const int64_t *mean_off, float *d_out, void *hip_stream)
 {
     if (ctx->head == ctx->tail) return bls_fail(ctx, BLS_ERING_EMPTY, "bls_unpack: nothing in flight");

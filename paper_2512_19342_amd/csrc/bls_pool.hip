@@ -38,6 +38,13 @@ constexpr int kRowsInFlightQuantised = BLS_POOL_UQ;
 
 __device__ __forceinline__ void flag_error(const DevDesc &dd) { atomicOr(dd.err, 1); }
 
+// Where a pooling launch leaves its vectors: Y alone (slot: Y is a ring slot, vectors in receive order), or
+// pooled order, send order and receive order at once.
+struct PoolDst {
+    float *Y, *S, *R;
+    int slot;
+};
+
 // 64-bit value of lane (gbase + k), k uniform.  A whole-wavefront group reads it into scalar
 // registers; narrower groups use the lane permute network (two ds_bpermute, no vector ALU
 // work beyond the address), which pipelines when several are issued back to back.
@@ -148,11 +155,11 @@ __device__ __forceinline__ uint32_t hot_hash(uint32_t row) { return (row * 26544
 // One lane group's work: G >= 4 lanes stream up to nb_max (< G) consecutive segments of (q, s)
 // block number gx / chunks_per_s, chunk gx % chunks_per_s.  HOT: rows found in `hot` are read from
 // LDS instead of global memory.
-template <int G, int DT, int VB, int U, bool WIDE, bool WGT, bool HOT>
+template <int G, int DT, int VB, int U, bool WIDE, bool WGT, bool HOT, bool ALL>
 __device__ __forceinline__ void stream_group(const DevDesc &dd, int q, uint32_t gx, const int64_t *__restrict__ ridx,
                                              const float *__restrict__ rw, const int64_t *__restrict__ segoff, int64_t nnz,
-                                             float *__restrict__ Y, int to_slot, int nb_max, uint32_t chunks_per_s,
-                                             const HotRows &hot)
+                                             float *__restrict__ Y, float *__restrict__ S, float *__restrict__ R, int to_slot,
+                                             int nb_max, uint32_t chunks_per_s, const HotRows &hot)
 {
     using A = Acc<DT, VB>;
     const int lane = threadIdx.x & 63;
@@ -170,6 +177,7 @@ __device__ __forceinline__ void stream_group(const DevDesc &dd, int q, uint32_t 
     // this group's segments: samples [b0, b0 + nb) of mini-batch s
     int nb = 0;
     int64_t sg0 = 0, out0 = 0;                                // first segment, its vector in the output
+    uint32_t y_at = 0, s_at = 0, r_at = 0;                    // ALL: the first vector in Y, S and R
     if (s < (uint32_t)dd.P) {
         const int64_t f = dd.first[s], n = dd.first[s + 1] - f;
         const int64_t bl0 = (int64_t)chunk * nb_max;
@@ -178,6 +186,9 @@ __device__ __forceinline__ void stream_group(const DevDesc &dd, int q, uint32_t 
             const int d = dd.q_d[q];
             sg0 = (int64_t)dd.nsum[d] * dd.B + (int64_t)dd.n_loc[d] * f + (int64_t)(q - dd.nsum[d]) * n + bl0;
             out0 = to_slot ? (int64_t)dd.Q * f + (int64_t)q * n + bl0 : (int64_t)q * dd.B + f + bl0;
+            y_at = (uint32_t)out0;
+            s_at = (uint32_t)sg0;
+            r_at = (uint32_t)((int64_t)dd.Q * f + (int64_t)q * n + bl0);
         }
     }
     // lane i of the group holds the start of segment i (i <= nb); all must be in order
@@ -206,7 +217,16 @@ __device__ __forceinline__ void stream_group(const DevDesc &dd, int q, uint32_t 
         do {
             const int nxt = __shfl(rel, gbase + (cur + 2 < G ? cur + 2 : G - 1), 64);
             if (cur_end == pos) {
-                if (col_ok) acc.store(Y + (out0 + cur) * dd.D + li * A::NV);
+                if (col_ok) {
+                    if constexpr (ALL) {
+                        // nobody on the path reads Y and S again, R is read by the completion
+                        acc.template store<true>(Y + (int64_t)(y_at + cur) * dd.D + li * A::NV);
+                        acc.template store<true>(S + (int64_t)(s_at + cur) * dd.D + li * A::NV);
+                        acc.store(R + (int64_t)(r_at + cur) * dd.D + li * A::NV);
+                    } else {
+                        acc.store(Y + (out0 + cur) * dd.D + li * A::NV);
+                    }
+                }
                 acc.zero();
                 ++cur;
                 cur_end = cur < nb ? nxt : -1;
@@ -300,12 +320,20 @@ __device__ __forceinline__ void stream_group(const DevDesc &dd, int q, uint32_t 
 // WIDE: row positions as 64-bit byte offsets; otherwise 32-bit, in units of VB bytes (shards
 // below 2^32 * VB bytes), which halves the lane exchanges and the registers they occupy.
 // WGT: per-sample weights rw[] (in ridx order) multiply every row before it is added.
-template <int G, int DT, int VB, int U, bool WIDE, bool WGT>
-__global__ __launch_bounds__(kThreads) void pool_stream(DevDesc dd, const int64_t *__restrict__ ridx,
+// ALL: every vector goes to Y (pooled order), S (send order) and R (a ring slot) from the registers it was summed in,
+// in place of pack and exchange, which read it again: five passes over the vectors up to the slot become three.  Vector
+// numbers of 32 bits and the launch bound keep the six wavefronts per SIMD of the plain kernel (81 registers without).
+// Y and S carry the streaming hint, the slot does not (the completion reads it).  A staged iteration, us, the separate
+// kernels / plain stores / this / the slot hinted as well: 16384 samples of 64 vectors of 128, Zipf 1568 / 1549 / 1495 /
+// 1488, bags of 1 to 4 743 / 656 / 640 / 522; row-wise 8192 of 26 over eight owners 1079 / 955 / 944 / 950, bags of one
+// 924 / 720 / 676 / 695; table-wise 168 MB of short bags 203 / - / 153 / 183; 2048 of 26 of 64 46.5 / 35.7 / 34.8 / 35.5.
+// Hinting the slot gains only for table-wise ones of 500 MB and loses up to a fifth elsewhere.
+template <int G, int DT, int VB, int U, bool WIDE, bool WGT, bool ALL>
+__global__ __launch_bounds__(kThreads, ALL && !WIDE ? 6 : 1) void pool_stream(DevDesc dd, const int64_t *__restrict__ ridx,
                                                         const float *__restrict__ rw,
                                                         const int64_t *__restrict__ segoff, int64_t nnz,
-                                                        float *__restrict__ Y, int to_slot, int nb_max, uint32_t chunks_per_s, uint32_t wgx,
-                                                        int q0, int qn)
+                                                        float *__restrict__ Y, float *__restrict__ S, float *__restrict__ R,
+                                                        int to_slot, int nb_max, uint32_t chunks_per_s, uint32_t wgx, int q0, int qn)
 {
     // wgx = 0: grid y = q.  Otherwise a flat grid dealt out so that the workgroups an XCD receives
     // (every eighth one) all belong to the same few tables: q = 8 * (round of tables) + XCD.
@@ -321,8 +349,8 @@ __global__ __launch_bounds__(kThreads) void pool_stream(DevDesc dd, const int64_
         q = qn == dd.Q ? dd.q_deal[pos] : q0 + pos;           // all shards: in the balanced order
     }
     const HotRows none{nullptr, nullptr, nullptr, 0};
-    stream_group<G, DT, VB, U, WIDE, WGT, false>(dd, q, bx * (kThreads / G) + threadIdx.x / G, ridx, rw, segoff, nnz, Y, to_slot,
-                                                 nb_max, chunks_per_s, none);
+    stream_group<G, DT, VB, U, WIDE, WGT, false, ALL>(dd, q, bx * (kThreads / G) + threadIdx.x / G, ridx, rw, segoff, nnz, Y, S, R,
+                                                      to_slot, nb_max, chunks_per_s, none);
 }
 
 // The same work by workgroups that stay: one workgroup of 1024 threads per compute unit, XCD x
@@ -374,8 +402,8 @@ __global__ __launch_bounds__(kHotThreads) void pool_stream_hot(DevDesc dd, const
         __syncthreads();
         const HotRows hot{data, keys, vals, n_hot};
         for (uint32_t blk = j; blk < blocks; blk += per_xcd)
-            stream_group<G, DT, VB, U, false, WGT, true>(dd, q, blk * per_wg + threadIdx.x / G, ridx, rw, segoff, nnz, Y, to_slot,
-                                                         nb_max, chunks_per_s, hot);
+            stream_group<G, DT, VB, U, false, WGT, true, false>(dd, q, blk * per_wg + threadIdx.x / G, ridx, rw, segoff, nnz, Y,
+                                                                nullptr, nullptr, to_slot, nb_max, chunks_per_s, hot);
     }
 }
 
@@ -425,7 +453,7 @@ __global__ __launch_bounds__(kThreads) void pool_rows_generic(DevDesc dd, const 
 }
 
 template <int G, int DT, int VB, int U>
-void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const int64_t *segoff, int64_t nnz, float *Y, int to_slot, int q0, int qn, hipStream_t st)
+void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const int64_t *segoff, int64_t nnz, const PoolDst &to, int q0, int qn, hipStream_t st)
 {
     constexpr int UU = U < G ? U : G;
     const uint32_t per_block = kThreads / G;
@@ -469,50 +497,56 @@ void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const
                 auto launch = [&](auto kernel) -> hipError_t {
                     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
                     if (e != hipSuccess) return e;
-                    kernel<<<hgrid, kHotThreads, lds, st>>>(ctx->desc, ridx, rw, segoff, nnz, Y, to_slot, nb, chunks, q0, qn, cap);
+                    kernel<<<hgrid, kHotThreads, lds, st>>>(ctx->desc, ridx, rw, segoff, nnz, to.Y, to.slot, nb, chunks, q0, qn, cap);
                     return hipSuccess;
                 };
                 if (cap > 0 && (rw ? launch(pool_stream_hot<G, DT, VB, UU, true>) : launch(pool_stream_hot<G, DT, VB, UU, false>)) == hipSuccess)
                     return;
             }
         }
+        auto launch = [&](auto kernel) {
+            kernel<<<grid, kThreads, 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, to.Y, to.S, to.R, to.slot, nb, chunks, deal, q0, qn);
+        };
         if (rw) {
-            if (wide) pool_stream<G, DT, VB, UU, true, true><<<grid, kThreads, 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, Y, to_slot, nb, chunks, deal, q0, qn);
-            else pool_stream<G, DT, VB, UU, false, true><<<grid, kThreads, 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, Y, to_slot, nb, chunks, deal, q0, qn);
+            if (wide) launch(pool_stream<G, DT, VB, UU, true, true, false>);
+            else launch(pool_stream<G, DT, VB, UU, false, true, false>);
+        } else if (to.S) {
+            if (wide) launch(pool_stream<G, DT, VB, UU, true, false, true>);
+            else launch(pool_stream<G, DT, VB, UU, false, false, true>);
         } else {
-            if (wide) pool_stream<G, DT, VB, UU, true, false><<<grid, kThreads, 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, Y, to_slot, nb, chunks, deal, q0, qn);
-            else pool_stream<G, DT, VB, UU, false, false><<<grid, kThreads, 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, Y, to_slot, nb, chunks, deal, q0, qn);
+            if (wide) launch(pool_stream<G, DT, VB, UU, true, false, false>);
+            else launch(pool_stream<G, DT, VB, UU, false, false, false>);
         }
     } else {
         dim3 grid((unsigned)((ctx->B + per_block - 1) / per_block), qn);
-        pool_rows<G, DT, VB, UU><<<grid, kThreads, 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, Y, to_slot, q0);
+        pool_rows<G, DT, VB, UU><<<grid, kThreads, 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, to.Y, to.slot, q0);
     }
 }
 
 template <int DT, int VB, int U>
 bool dispatch_lanes(const bls_ctx *ctx, int lanes, const int64_t *ridx, const float *rw, const int64_t *segoff, int64_t nnz,
-                    float *Y, int to_slot, int q0, int qn, hipStream_t st)
+                    const PoolDst &to, int q0, int qn, hipStream_t st)
 {
     switch (lanes) {
-    case 1: if constexpr (VB == 16) { launch_rows<1, DT, VB, U>(ctx, ridx, rw, segoff, nnz, Y, to_slot, q0, qn, st); return true; } break;
-    case 2: if constexpr (VB == 16) { launch_rows<2, DT, VB, U>(ctx, ridx, rw, segoff, nnz, Y, to_slot, q0, qn, st); return true; } break;
-    case 4: if constexpr (VB == 16) { launch_rows<4, DT, VB, U>(ctx, ridx, rw, segoff, nnz, Y, to_slot, q0, qn, st); return true; } break;
-    case 8: if constexpr (VB == 16) { launch_rows<8, DT, VB, U>(ctx, ridx, rw, segoff, nnz, Y, to_slot, q0, qn, st); return true; } break;
-    case 16: if constexpr (VB >= 8) { launch_rows<16, DT, VB, U>(ctx, ridx, rw, segoff, nnz, Y, to_slot, q0, qn, st); return true; } break;
-    case 32: launch_rows<32, DT, VB, U>(ctx, ridx, rw, segoff, nnz, Y, to_slot, q0, qn, st); return true;
-    case 64: launch_rows<64, DT, VB, U>(ctx, ridx, rw, segoff, nnz, Y, to_slot, q0, qn, st); return true;
+    case 1: if constexpr (VB == 16) { launch_rows<1, DT, VB, U>(ctx, ridx, rw, segoff, nnz, to, q0, qn, st); return true; } break;
+    case 2: if constexpr (VB == 16) { launch_rows<2, DT, VB, U>(ctx, ridx, rw, segoff, nnz, to, q0, qn, st); return true; } break;
+    case 4: if constexpr (VB == 16) { launch_rows<4, DT, VB, U>(ctx, ridx, rw, segoff, nnz, to, q0, qn, st); return true; } break;
+    case 8: if constexpr (VB == 16) { launch_rows<8, DT, VB, U>(ctx, ridx, rw, segoff, nnz, to, q0, qn, st); return true; } break;
+    case 16: if constexpr (VB >= 8) { launch_rows<16, DT, VB, U>(ctx, ridx, rw, segoff, nnz, to, q0, qn, st); return true; } break;
+    case 32: launch_rows<32, DT, VB, U>(ctx, ridx, rw, segoff, nnz, to, q0, qn, st); return true;
+    case 64: launch_rows<64, DT, VB, U>(ctx, ridx, rw, segoff, nnz, to, q0, qn, st); return true;
     }
     return false;
 }
 
 template <int DT>
 bool dispatch_rows(const bls_ctx *ctx, int vb, int lanes, const int64_t *ridx, const float *rw,
-                   const int64_t *segoff, int64_t nnz, float *Y, int to_slot, int q0, int qn, hipStream_t st)
+                   const int64_t *segoff, int64_t nnz, const PoolDst &to, int q0, int qn, hipStream_t st)
 {
     switch (vb) {
-    case 16: return dispatch_lanes<DT, 16, (is_rowq(DT) ? kRowsInFlightQuantised : kRowsInFlight)>(ctx, lanes, ridx, rw, segoff, nnz, Y, to_slot, q0, qn, st);
-    case 8: return dispatch_lanes<DT, 8, kRowsInFlight>(ctx, lanes, ridx, rw, segoff, nnz, Y, to_slot, q0, qn, st);
-    case 4: return dispatch_lanes<DT, 4, kRowsInFlight>(ctx, lanes, ridx, rw, segoff, nnz, Y, to_slot, q0, qn, st);
+    case 16: return dispatch_lanes<DT, 16, (is_rowq(DT) ? kRowsInFlightQuantised : kRowsInFlight)>(ctx, lanes, ridx, rw, segoff, nnz, to, q0, qn, st);
+    case 8: return dispatch_lanes<DT, 8, kRowsInFlight>(ctx, lanes, ridx, rw, segoff, nnz, to, q0, qn, st);
+    case 4: return dispatch_lanes<DT, 4, kRowsInFlight>(ctx, lanes, ridx, rw, segoff, nnz, to, q0, qn, st);
     }
     return false;
 }
@@ -520,29 +554,58 @@ bool dispatch_rows(const bls_ctx *ctx, int vb, int lanes, const int64_t *ridx, c
 
 }  // namespace
 
-int bls_launch_pool(bls_ctx *ctx, const int64_t *ridx, const float *rw, const int64_t *segoff, int64_t nnz, float *Y, int to_slot, int q0, int qn, hipStream_t st)
+// Bytes per lane and lanes per row of the kernels that read whole pieces of rows; false: pool_rows_generic.
+static bool pool_shape(const bls_ctx *ctx, int *lane_bytes, int *row_lanes)
 {
     const int64_t row_bytes = payload_bytes(ctx->dtype, ctx->D);
     // bytes per lane and row: 16 when the row length allows, unless bls_set_pool_tuning says otherwise
     int vb = ctx->tune_lane_bytes ? ctx->tune_lane_bytes : 16;
     while (vb > 4 && row_bytes % vb != 0) vb >>= 1;          // lanes must split the row evenly
     while (vb < 16 && row_bytes > 64 * (int64_t)vb) vb <<= 1; // and 64 of them must cover it
+    if (row_bytes % vb != 0 || row_bytes > 64 * (int64_t)vb) return false;
+    int lanes = 1;
+    while ((int64_t)lanes * vb < row_bytes) lanes <<= 1;
+    *lane_bytes = vb;
+    *row_lanes = lanes;
+    return true;
+}
+
+static int launch_pool(bls_ctx *ctx, const int64_t *ridx, const float *rw, const int64_t *segoff, int64_t nnz, const PoolDst &to, int q0, int qn, hipStream_t st)
+{
+    int vb = 0, lanes = 0;
     bool done = false;
-    if (row_bytes % vb == 0 && row_bytes <= 64 * (int64_t)vb) {
-        int lanes = 1;
-        while ((int64_t)lanes * vb < row_bytes) lanes <<= 1;
-        done = ctx->dtype == BLS_U8_ROWQ ? dispatch_rows<BLS_U8_ROWQ>(ctx, vb, lanes, ridx, rw, segoff, nnz, Y, to_slot, q0, qn, st)
-             : ctx->dtype == BLS_F8_ROWQ ? dispatch_rows<BLS_F8_ROWQ>(ctx, vb, lanes, ridx, rw, segoff, nnz, Y, to_slot, q0, qn, st)
-             : ctx->dtype == BLS_FP16  ? dispatch_rows<BLS_FP16>(ctx, vb, lanes, ridx, rw, segoff, nnz, Y, to_slot, q0, qn, st)
-                                       : dispatch_rows<BLS_FP32>(ctx, vb, lanes, ridx, rw, segoff, nnz, Y, to_slot, q0, qn, st);
-    }
+    if (pool_shape(ctx, &vb, &lanes))
+        done = ctx->dtype == BLS_U8_ROWQ ? dispatch_rows<BLS_U8_ROWQ>(ctx, vb, lanes, ridx, rw, segoff, nnz, to, q0, qn, st)
+             : ctx->dtype == BLS_F8_ROWQ ? dispatch_rows<BLS_F8_ROWQ>(ctx, vb, lanes, ridx, rw, segoff, nnz, to, q0, qn, st)
+             : ctx->dtype == BLS_FP16  ? dispatch_rows<BLS_FP16>(ctx, vb, lanes, ridx, rw, segoff, nnz, to, q0, qn, st)
+                                       : dispatch_rows<BLS_FP32>(ctx, vb, lanes, ridx, rw, segoff, nnz, to, q0, qn, st);
     if (!done) {
         dim3 grid((unsigned)((ctx->B + kThreads / 64 - 1) / (kThreads / 64)), qn);
-        if (ctx->dtype == BLS_U8_ROWQ) pool_rows_generic<BLS_U8_ROWQ><<<grid, kThreads, 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, Y, to_slot, q0);
-        else if (ctx->dtype == BLS_F8_ROWQ) pool_rows_generic<BLS_F8_ROWQ><<<grid, kThreads, 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, Y, to_slot, q0);
-        else if (ctx->dtype == BLS_FP16) pool_rows_generic<BLS_FP16><<<grid, kThreads, 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, Y, to_slot, q0);
-        else pool_rows_generic<BLS_FP32><<<grid, kThreads, 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, Y, to_slot, q0);
+        if (ctx->dtype == BLS_U8_ROWQ) pool_rows_generic<BLS_U8_ROWQ><<<grid, kThreads, 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, to.Y, to.slot, q0);
+        else if (ctx->dtype == BLS_F8_ROWQ) pool_rows_generic<BLS_F8_ROWQ><<<grid, kThreads, 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, to.Y, to.slot, q0);
+        else if (ctx->dtype == BLS_FP16) pool_rows_generic<BLS_FP16><<<grid, kThreads, 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, to.Y, to.slot, q0);
+        else pool_rows_generic<BLS_FP32><<<grid, kThreads, 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, to.Y, to.slot, q0);
     }
     BLS_HIP(ctx, hipGetLastError());
     return BLS_OK;
+}
+
+int bls_launch_pool(bls_ctx *ctx, const int64_t *ridx, const float *rw, const int64_t *segoff, int64_t nnz, float *Y, int to_slot, int q0, int qn, hipStream_t st)
+{
+    return launch_pool(ctx, ridx, rw, segoff, nnz, PoolDst{Y, nullptr, nullptr, to_slot}, q0, qn, st);
+}
+
+bool bls_pool_all_fits(const bls_ctx *ctx)
+{
+    int vb = 0, lanes = 0;
+    if (!pool_shape(ctx, &vb, &lanes) || ctx->nvec >= (int64_t)1 << 31) return false;   // 32-bit vector numbers
+    if (lanes < (vb == 16 ? 4 : 128 / vb)) return false;      // pool_rows, or no kernel of dispatch_lanes
+    for (const auto &h : ctx->q_hot)
+        if (!h.empty()) return false;
+    return true;
+}
+
+int bls_launch_pool_all(bls_ctx *ctx, const int64_t *ridx, const int64_t *segoff, int64_t nnz, float *Y, float *S, float *R, hipStream_t st)
+{
+    return launch_pool(ctx, ridx, nullptr, segoff, nnz, PoolDst{Y, S, R, 0}, 0, ctx->Q, st);
 }

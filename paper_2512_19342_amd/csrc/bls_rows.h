@@ -132,12 +132,17 @@ template <int DT, int VB> struct Acc {
             }
         }
     }
-    __device__ __forceinline__ void store(float *p) const
+    // HINT: past the caches, where nobody on the path reads the vector again soon
+    template <bool HINT = false> __device__ __forceinline__ void store(float *p) const
     {
         if constexpr (NV % 4 == 0) {
+            typedef float f32x4 __attribute__((ext_vector_type(4)));
 #pragma unroll
-            for (int i = 0; i < NV / 4; ++i)
-                reinterpret_cast<float4 *>(p)[i] = make_float4(a[4 * i], a[4 * i + 1], a[4 * i + 2], a[4 * i + 3]);
+            for (int i = 0; i < NV / 4; ++i) {
+                const f32x4 v = {a[4 * i], a[4 * i + 1], a[4 * i + 2], a[4 * i + 3]};
+                if constexpr (HINT) __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(p) + i);
+                else reinterpret_cast<f32x4 *>(p)[i] = v;
+            }
         } else if constexpr (NV == 2) {
             *reinterpret_cast<float2 *>(p) = make_float2(a[0], a[1]);
         } else {

@@ -93,16 +93,12 @@ class Pipeline:
 
     # one iteration, split where the ring allows other iterations in between
     def issue(self, indices: torch.Tensor, offsets: torch.Tensor, nnz: int, stream=None):
-        """plan, pool, pack, take a ring slot, exchange.  Returns (iteration, slot)."""
+        """plan, then pool, pack, take a ring slot and exchange.  Returns (iteration, slot)."""
         c = self.ctx
         assert nnz <= self.max_nnz
         c.bls_plan(indices, offsets, nnz, self.sendcounts, self.sdispls, self.recvcounts, self.rdispls,
                    self.ridx, self.segoff, self.perm, self.ws, stream)
-        c.bls_embbag_pool(self.ridx, self.segoff, nnz, self.pooled, stream)
-        c.bls_pack(self.pooled, self.send, stream)
-        it, slot = c.bls_ring_advance(stream)
-        c.bls_alltoallv_local(self.send, slot, stream)
-        return it, slot
+        return c.bls_embbag_pool_exchange(self.ridx, self.segoff, nnz, self.pooled, self.send, stream)
 
     def issue_fused(self, indices: torch.Tensor, offsets: torch.Tensor, nnz: int, stream=None):
         """plan, take a ring slot, pool straight into it (no pooled or send buffer)."""
