@@ -444,7 +444,7 @@ __global__ __launch_bounds__(kThreads) void mlp_narrow(const float *__restrict__
 }
 // ---- dot interaction ---------------------------------------------------------------------------
 //
-// One workgroup per sample.  The sample's T pooled vectors are copied to LDS (rows padded to a
+// One workgroup per sample.  interact_gram (any D): the sample's T pooled vectors are copied to LDS (rows padded to a
 // multiple of 32 with zeros, row stride odd so that 32 rows at one column fall in 32 banks); the
 // 32 x 32 tiles on and below the diagonal of their Gram matrix are dealt to the wavefronts, each
 // tile one accumulator over D / 2 matrix instructions; the last wavefront also takes the T
@@ -524,6 +524,7 @@ __device__ __forceinline__ void fill_vectors(float *Es, uint32_t T, uint32_t D, 
         for (int u = 0; u < kFill; ++u)
             if (live[u]) {
                 if constexpr (W == 1) Es[at[u]] = v[u];
+                else if (LD % 4 == 0) *reinterpret_cast<V *>(Es + at[u]) = v[u];
                 else {
 #pragma unroll
                     for (uint32_t j = 0; j < W; ++j) Es[at[u] + j] = v[u][j];
@@ -551,10 +552,99 @@ __device__ __forceinline__ void copy_vectors(float *Es, uint32_t T, uint32_t D, 
         for (int u = 0; u < kFill; ++u) {
             const uint32_t i = base + u * kThreads, r = i / per, c = (i - r * per) * 4;
             if (i < n) {
+                if (LD % 4 == 0) *reinterpret_cast<f32x4 *>(Es + r * LD + c) = v[u];
+                else {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) Es[r * LD + c + j] = v[u][j];
+                    for (int j = 0; j < 4; ++j) Es[r * LD + c + j] = v[u][j];
+                }
             }
         }
+    }
+}
+
+// Sample b's vectors to rows of LD floats at Es, from the completed lookup or out of a slot.
+template <Source SRC, int kFill, int kParts>
+__device__ __forceinline__ void fetch_sample(const DevDesc &dd, float *Es, const float *emb, int64_t b, int T, int D, int LD, int vec4)
+{
+    int64_t slot_base = 0, slot_step = 0;                        // vector (q, b) of the slot: slot_base + q * slot_step
+    if constexpr (SRC != FROM_OUT) {
+        int s; uint32_t b_loc, n;
+        bls_split_sample(dd, (uint32_t)b, s, b_loc, n);
+        slot_base = (int64_t)dd.Q * dd.first[s] + b_loc;
+        slot_step = n;
+    }
+    const float *vec0 = emb + (SRC == FROM_OUT ? b * T : slot_base) * D;
+    const int64_t vec_step = SRC == FROM_OUT ? D : slot_step * D, part_step = dd.T * slot_step * D;
+    if (SRC == FROM_OUT && vec4) copy_vectors<kFill>(Es, T, D, LD, vec0);
+    else if (vec4) fill_vectors<SRC, f32x4, kFill, kParts>(Es, T, D, LD, dd.F, vec0, dd.t_q, vec_step, part_step);
+    else fill_vectors<SRC, float, kFill, kParts>(Es, T, D, LD, dd.F, vec0, dd.t_q, vec_step, part_step);
+}
+
+// D a multiple of 16: tiles of 16 x 16 on v_mfma_f32_16x16x4_f32 (lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16];
+// register v of lane l is element (4 * (l / 16) + v, l % 16)).  Lane group l / 16 takes the four k from 16 s + 4 (l / 16)
+// of step s, so that four instructions are fed by one 16-byte read of a row; rows of D + 4 floats put the 16 rows of such
+// a read on different banks.  Smaller tiles leave less above the diagonal and deal out evenly (64 vectors: 10 tiles of
+// 1024 matrix cycles, three for the busiest wavefront, against three of 4096 and none for the fourth), the wavefronts
+// change parts from sample to sample, so that no SIMD always has the longest, and the products with x are shared by all
+// four.  Padding rows stay as they are: a product of theirs is stored nowhere.
+// us, tiles of 32 x 32 / this: 16384 samples of 64 vectors of 128 185-199 / 178-190 (147 without the products: they
+// still cost what the next samples' loads do not hide), 8192 of 26 of 128 50.2 / 38.8, of 64 of 112 94 / 89, 16384 of 2
+// 78 / 42, 4096 of 30 of 256 51 / 39, 8192 of 100 of 64 139 / 117, 2048 of 26 of 64 10.2 / 9.0.  Half or a quarter of the
+// columns at a time, for more workgroups per compute unit: 187, 227 at the first.
+template <Source SRC, int kFill, int kParts>
+__global__ __launch_bounds__(kThreads, SRC == FROM_PARTIALS ? 6 : 1) void interact_tiles(DevDesc dd, const float *__restrict__ x,
+                                                           const float *__restrict__ emb, float *__restrict__ z, int T, int D,
+                                                           int TP, uint32_t b0, int vec4)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    const int LD = D + 4;
+    float *Es = lds;                                          // [TP][LD]
+    float *xsh = lds + (size_t)TP * LD;                       // [D]
+    const int64_t b = (int64_t)b0 + blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = ((tid >> 6) + (blockIdx.x >> 3) + (blockIdx.x >> 8)) & 3;
+    float *__restrict__ zb = z + b * ((int64_t)D + (int64_t)T * (T + 1) / 2);
+    fetch_sample<SRC, kFill, kParts>(dd, Es, emb, b, T, D, LD, vec4);
+    for (int c = tid; c < D; c += kThreads) {
+        const float v = x[b * D + c];
+        xsh[c] = v;
+        zb[c] = v;
+    }
+    __syncthreads();
+
+    const int g = lane >> 4, l16 = lane & 15;
+    const int nt = TP / 16;
+    int tile = 0;
+    for (int ti = 0; ti < nt; ++ti)
+        for (int tj = 0; tj <= ti; ++tj, ++tile) {
+            if ((tile & 3) != wave) continue;
+            f32x4 acc = 0.f;
+            const float *pa = Es + (ti * 16 + l16) * LD + 4 * g;
+            const float *pb = Es + (tj * 16 + l16) * LD + 4 * g;
+            for (int k = 0; k < D; k += 16) {
+                const f32x4 a = *reinterpret_cast<const f32x4 *>(pa + k), c = *reinterpret_cast<const f32x4 *>(pb + k);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], c[j], acc, 0, 0, 0);
+            }
+            const int col = tj * 16 + l16;                    // the lower-numbered vector of the pair
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = ti * 16 + 4 * g + v;
+                if (row < T && col < row) zb[D + (int64_t)(row + 1) * row / 2 + col + 1] = acc[v];
+            }
+        }
+    for (int t0 = 16 * wave; t0 < T; t0 += 64) {
+        const float *e = Es + (t0 + l16) * LD + 4 * g;
+        float dot = 0.f;
+        for (int k = 0; k < D; k += 16) {
+            const f32x4 a = *reinterpret_cast<const f32x4 *>(e + k), c = *reinterpret_cast<const f32x4 *>(xsh + 4 * g + k);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) dot = fmaf(a[j], c[j], dot);
+        }
+        dot += __shfl_xor(dot, 16, 64);
+        dot += __shfl_xor(dot, 32, 64);
+        const int t = t0 + l16;
+        if (g == 0 && t < T) zb[D + (int64_t)(t + 1) * t / 2] = dot;
     }
 }
 
@@ -570,23 +660,11 @@ __global__ __launch_bounds__(kThreads, SRC == FROM_PARTIALS ? 6 : 1) void intera
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t Wz = (int64_t)D + (int64_t)T * (T + 1) / 2;
     float *__restrict__ zb = z + b * Wz;
-    int64_t slot_base = 0, slot_step = 0;                        // vector (q, b) of the slot: slot_base + q * slot_step
-    if constexpr (SRC != FROM_OUT) {
-        int s; uint32_t b_loc, n;
-        bls_split_sample(dd, (uint32_t)b, s, b_loc, n);
-        slot_base = (int64_t)dd.Q * dd.first[s] + b_loc;
-        slot_step = n;
-    }
-    const float *vec0 = emb + (SRC == FROM_OUT ? b * T : slot_base) * D;
-    const int64_t vec_step = SRC == FROM_OUT ? D : slot_step * D, part_step = dd.T * slot_step * D;
-
     // zeros: the padding columns behind every vector and the padding rows behind the last one
     const int padc = LD - D;
     for (int i = tid; i < T * padc; i += kThreads) Es[(i / padc) * LD + D + i % padc] = 0.f;
     for (int i = T * LD + tid; i < TP * LD; i += kThreads) Es[i] = 0.f;
-    if (SRC == FROM_OUT && vec4) copy_vectors<kFill>(Es, T, D, LD, vec0);
-    else if (vec4) fill_vectors<SRC, f32x4, kFill, kParts>(Es, T, D, LD, dd.F, vec0, dd.t_q, vec_step, part_step);
-    else fill_vectors<SRC, float, kFill, kParts>(Es, T, D, LD, dd.F, vec0, dd.t_q, vec_step, part_step);
+    fetch_sample<SRC, kFill, kParts>(dd, Es, emb, b, T, D, LD, vec4);
     for (int c = tid; c < D; c += kThreads) {
         const float v = x[b * D + c];
         xsh[c] = v;
@@ -714,9 +792,14 @@ int bls_launch_interact(bls_ctx *ctx, const float *x, const float *emb, int from
     const int T = ctx->T, D = ctx->D;
     const int TP = (T + 31) / 32 * 32, LD = ((D + 1) & ~1) + 1;
     const int vec4 = D % 4 == 0 && ((uintptr_t)emb & 15u) == 0;   // every vector then starts 16-byte aligned
-    const size_t lds = bls_interact_lds_bytes(T, D);
-#define BLS_INTERACT(src, fill, parts) \
-    interact_gram<src, fill, parts><<<dim3(bn), kThreads, lds, st>>>(ctx->desc, x, emb, z, T, D, TP, LD, b0, vec4)
+    const int tp16 = (T + 15) / 16 * 16;
+    const size_t lds = bls_interact_lds_bytes(T, D), lds16 = ((size_t)tp16 * (D + 4) + (size_t)D) * sizeof(float);
+    const bool tiles = D % 16 == 0 && lds16 <= 64 * 1024;     // else interact_gram: whole steps of k, and its LDS where that is less
+#define BLS_INTERACT(src, fill, parts)                                                                                              \
+    do {                                                                                                                           \
+        if (tiles) interact_tiles<src, fill, parts><<<dim3(bn), kThreads, lds16, st>>>(ctx->desc, x, emb, z, T, D, tp16, b0, vec4);  \
+        else interact_gram<src, fill, parts><<<dim3(bn), kThreads, lds, st>>>(ctx->desc, x, emb, z, T, D, TP, LD, b0, vec4);         \
+    } while (0)
     // eight loads in flight: pieces of one partial, or fewer pieces and more owners' partials of each.  us, two
     // pieces of four partials / four of two: 8 owners, 2 vectors of 128 (16384 samples) 105 / 114, 26 (8192) 225 /
     // 234, 64 (2048) 160 / 155; 2 owners, 26 vectors (8192) 68 / 60
