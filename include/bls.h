@@ -342,6 +342,14 @@ int bls_rank_delay(bls_ctx *ctx, uint32_t microseconds, void *hip_stream);
 enum { BLS_ACT_NONE = 0, BLS_ACT_RELU = 1, BLS_ACT_SIGMOID = 2 };
 int bls_mlp_layer(bls_ctx *ctx, const float *d_x, int64_t M, int32_t K, const float *d_W, const float *d_bias,
                   int32_t N, int32_t act, float *d_y, void *hip_stream);
+/* n layers, each on the one before: bls_mlp_layer with d_x, K for the first and layer[i-1].y, layer[i-1].N for layer i.
+ * `layer` is host memory, read during the call; nothing is launched if one of the layers is refused. */
+typedef struct {
+    const float *W, *bias;
+    float *y;
+    int32_t N, act;
+} bls_layer;
+int bls_mlp(bls_ctx *ctx, const float *d_x, int64_t M, int32_t K, const bls_layer *layer, int32_t n, void *hip_stream);
 int bls_interact(bls_ctx *ctx, const float *d_x, const float *d_emb, float *d_z, int64_t b0, int64_t bn,
                  void *hip_stream);
 int bls_unpack_interact(bls_ctx *ctx, int64_t iter, const float *d_x, float *d_z, void *hip_stream);

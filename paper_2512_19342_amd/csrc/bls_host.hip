@@ -807,16 +807,39 @@ extern "C" int bls_rank_delay(bls_ctx *ctx, uint32_t microseconds, void *hip_str
     return bls_launch_delay(ctx, microseconds, (hipStream_t)hip_stream);
 }
 
-extern "C" int bls_mlp_layer(bls_ctx *ctx, const float *d_x, int64_t M, int32_t K, const float *d_W, const float *d_bias,
-                             int32_t N, int32_t act, float *d_y, void *hip_stream)
+static int check_layer(bls_ctx *ctx, const float *d_x, int64_t M, int32_t K, const float *d_W, int32_t N, int32_t act, const float *d_y)
 {
-    if (!ctx) return BLS_EINVAL;
     if (M < 0 || K < 1 || N < 1 || K > 0x7fffffff / 128 || N > 0x7fffffff / 128)
         return bls_fail(ctx, BLS_EINVAL, "bls_mlp_layer: bad shape");
     if (act != BLS_ACT_NONE && act != BLS_ACT_RELU && act != BLS_ACT_SIGMOID)
         return bls_fail(ctx, BLS_EINVAL, "bls_mlp_layer: unknown activation");
     if (M > 0 && (!d_x || !d_W || !d_y)) return bls_fail(ctx, BLS_EINVAL, "bls_mlp_layer: NULL array");
+    return BLS_OK;
+}
+
+extern "C" int bls_mlp_layer(bls_ctx *ctx, const float *d_x, int64_t M, int32_t K, const float *d_W, const float *d_bias,
+                             int32_t N, int32_t act, float *d_y, void *hip_stream)
+{
+    if (!ctx) return BLS_EINVAL;
+    const int rc = check_layer(ctx, d_x, M, K, d_W, N, act, d_y);
+    if (rc) return rc;
     return bls_launch_mlp_layer(ctx, d_x, M, K, d_W, d_bias, N, act, d_y, (hipStream_t)hip_stream);
+}
+
+extern "C" int bls_mlp(bls_ctx *ctx, const float *d_x, int64_t M, int32_t K, const bls_layer *layer, int32_t n, void *hip_stream)
+{
+    if (!ctx) return BLS_EINVAL;
+    if (n < 0 || (n > 0 && !layer)) return bls_fail(ctx, BLS_EINVAL, "bls_mlp: bad list of layers");
+    for (int i = 0; i < n; ++i) {
+        const int rc = check_layer(ctx, i ? layer[i - 1].y : d_x, M, i ? layer[i - 1].N : K, layer[i].W, layer[i].N, layer[i].act, layer[i].y);
+        if (rc) return rc;
+    }
+    for (int i = 0; i < n; ++i) {
+        const int rc = bls_launch_mlp_layer(ctx, i ? layer[i - 1].y : d_x, M, i ? layer[i - 1].N : K, layer[i].W, layer[i].bias,
+                                            layer[i].N, layer[i].act, layer[i].y, (hipStream_t)hip_stream);
+        if (rc) return rc;
+    }
+    return BLS_OK;
 }
 
 extern "C" int bls_interact(bls_ctx *ctx, const float *d_x, const float *d_emb, float *d_z, int64_t b0, int64_t bn,

@@ -173,34 +173,27 @@ class DenseModel:
         """x = bottom MLP of the dense features ``[B, n_dense]``, written to ``x_out`` [B, D]
         (default: the model's own buffer, overwritten by the next call).  ``rows = (b0, bn)``
         restricts the work to those samples (one rank's mini-batch); every tensor is the full one."""
-        lo, hi = (0, self.B) if rows is None else (rows[0], rows[0] + rows[1])
-        a = dense[lo:hi]
-        for i, ((W, b), y) in enumerate(zip(self.bottom, self.bot_act)):
-            if x_out is not None and i == len(self.bottom) - 1:
-                y = x_out
-            self.ctx.bls_mlp_layer(a, W, b, bls.BLS_ACT_RELU, y[lo:hi], stream)
-            a = y[lo:hi]
-        return y
+        ys = self.bot_act if x_out is None else self.bot_act[:-1] + [x_out]
+        self.ctx.bls_mlp(dense, [(W, b, bls.BLS_ACT_RELU, y) for (W, b), y in zip(self.bottom, ys)],
+                         (0, self.B) if rows is None else rows, stream)
+        return ys[-1]
 
     def compute_ctr(self, x: torch.Tensor, emb, p_out: Optional[torch.Tensor] = None, stream=None,
                     rows: Optional[tuple] = None) -> torch.Tensor:
         """The prediction [B, 1] from the bottom MLP's output and the completed lookup [B, T, D].
         ``emb`` may instead be the number of the oldest iteration in flight: its completion is then
         folded into the interaction (bls_unpack_interact; whole batch only)."""
-        lo, hi = (0, self.B) if rows is None else (rows[0], rows[0] + rows[1])
         if isinstance(emb, int):
             assert rows is None
             self.ctx.bls_unpack_interact(emb, x, self.z, stream)
+            rows = (0, self.B)
         else:
-            self.ctx.bls_interact(x, emb, self.z, lo, hi - lo, stream)
-        a = self.z[lo:hi]
-        for i, ((W, b), y) in enumerate(zip(self.top, self.top_act)):
-            last = i == len(self.top) - 1
-            if last and p_out is not None:
-                y = p_out
-            self.ctx.bls_mlp_layer(a, W, b, bls.BLS_ACT_SIGMOID if last else bls.BLS_ACT_RELU, y[lo:hi], stream)
-            a = y[lo:hi]
-        return y
+            rows = (0, self.B) if rows is None else rows
+            self.ctx.bls_interact(x, emb, self.z, *rows, stream)
+        ys = self.top_act if p_out is None else self.top_act[:-1] + [p_out]
+        acts = [bls.BLS_ACT_RELU] * (len(ys) - 1) + [bls.BLS_ACT_SIGMOID]
+        self.ctx.bls_mlp(self.z, [(W, b, act, y) for (W, b), act, y in zip(self.top, acts, ys)], rows, stream)
+        return ys[-1]
 
 
 class BlsDlrm:
