@@ -67,25 +67,36 @@ __device__ __forceinline__ float activate(float v)
 // that those that share rows of X follow each other on one XCD (one L2), N-tile fastest.
 //
 // M = 16384, us, fp32 instructions / this: 2208 -> 1024 594 / 398 (186 TFLOP/s; 377 to 425 from card to card),
-// 1024 -> 1024 284 / 186, 1024 -> 512 155 / 96, 512 -> 256 55 / 33, 256 -> 128 33 / 13.5.  M = 2048: 415 -> 1024
-// 52 / 18.6, 1024 -> 1024 96 / 34, 512 -> 256 52 / 12.5.  Counted for the first (413 us under the profiler, 672000
+// 1024 -> 1024 284 / 186, 1024 -> 512 155 / 96, 512 -> 256 55 / 33, 256 -> 128 33 / 13.3.  M = 2048 (mlp_split): 415 -> 1024
+// 52 / 17, 1024 -> 1024 96 / 33, 512 -> 256 52 / 11.  Counted for the first (413 us under the profiler, 672000
 // cycles, i.e. 1.63 GHz: the card lowers its clock under these products): matrix pipe busy 63 % of the cycles,
 // vector operations issued 45 %, LDS 32 %, no bank conflicts; a wavefront waits 43 % of its time for its turn to
-// issue and 19 % for data or a barrier.  2048 x 1024 -> 1024: matrix pipe busy 27 %, 33 % and 27 %.
+// issue and 19 % for data or a barrier.
 __device__ __forceinline__ bool finite(float v) { return __builtin_fabsf(v) <= 3.402823466e38f; }
 
 struct Chunk { float v[8]; };                                 // eight consecutive k of one row
 
-// Eight floats from k of a row of K (zeros from K on); rows need no alignment beyond the float's.
-// WHOLE: all eight are there.
+// A chunk asked for at k that was loaded as the last eight of a row of K: zeros for what comes before k.
+__device__ __forceinline__ void clear_before(Chunk &c, int k, int K)
+{
+    const int gone = K < 8 ? 0 : k - std::min(k, K - 8);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) c.v[j] = j < gone ? 0.f : c.v[j];
+}
+
+// Eight floats from k of a row of K; rows need no alignment beyond the float's.  WHOLE: all eight are there.
+// Otherwise zeros stand for what is not: a row's last eight are loaded, without a branch, and those before k cleared
+// (rows of fewer than eight: from K on).  us, a branch per chunk and float / this: 10^6 x 13 -> 16 49 / 39, 10^5 x 5 -> 50
+// 14.5 / 12.3, 300000 x 64 -> 64 62 / 61.
 template <bool WHOLE>
 __device__ __forceinline__ Chunk load_chunk(const float *__restrict__ row, int k, int K)
 {
     Chunk c;
     f32x4 lo = 0.f, hi = 0.f;
-    if (WHOLE || k + 8 <= K) {
-        lo = *reinterpret_cast<const f32x4_a4 *>(row + k);
-        hi = *reinterpret_cast<const f32x4_a4 *>(row + k + 4);
+    if (WHOLE || K >= 8) {
+        const int at = WHOLE ? k : std::min(k, K - 8);
+        lo = *reinterpret_cast<const f32x4_a4 *>(row + at);
+        hi = *reinterpret_cast<const f32x4_a4 *>(row + at + 4);
     } else {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -95,6 +106,7 @@ __device__ __forceinline__ Chunk load_chunk(const float *__restrict__ row, int k
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) { c.v[j] = lo[j]; c.v[4 + j] = hi[j]; }
+    if (!WHOLE && K >= 8) clear_before(c, k, K);
     return c;
 }
 
@@ -215,7 +227,7 @@ __device__ __forceinline__ void finish(f32x16 (&r)[TJ], const float *__restrict_
 }
 
 template <int TI, int TJ, int CH, int ACT>
-__global__ __launch_bounds__(kThreads, TI * TJ > 1 ? 2 : 3) void mlp_gemm(const float *__restrict__ X, const float *__restrict__ W,
+__global__ __launch_bounds__(kThreads, 2) void mlp_gemm(const float *__restrict__ X, const float *__restrict__ W,
                                                         const float *__restrict__ bias, float *__restrict__ Y,
                                                         int64_t M, int N, int K, uint32_t n_tiles, uint32_t tiles)
 {
@@ -373,6 +385,115 @@ __global__ __launch_bounds__(kThreads, TI * TJ > 1 ? 2 : 3) void mlp_gemm(const 
     }
 }
 
+// Tiles of 64 x 64 for the layers that do not fill the card with larger ones: few wavefronts per SIMD, so that
+// splitting, LDS and multiplies of one wavefront follow each other more than they overlap (512 x 1024 -> 1024: 1300
+// cycles a step of 32 k, of them 384 of multiplies).  Here they have wavefronts of their own: four multiply (32 x 32
+// each), eight load, split and write, one chunk a step and thread, three per SIMD in all.  Per step one SIMD issues
+// 106 vector operations for 12 multiplies, 5 to 8 cycles each: that bounds it now (without the splitting 12.7 us of
+// 18.2, without the loads nothing less).
+// us, four wavefronts for everything / this, M K N: 512 1024 1024 20.8 / 18.2, 512 415 1024 13.9 / 11.0, 512 512 256
+// 12.2 / 10.5, 2048 1024 1024 34.1 / 32.7, 2048 1024 512 22.1 / 19.5, 2048 512 256 13.1 / 11.4, 16384 256 128
+// 15.1 / 13.7.  Four wavefronts that split: 20.9 at the first; steps of 64 k: 18.2 there and 37.3 for 2048 1024 1024;
+// tiles of 128 x 64 this way: 18.9 for 2048 415 1024 (17.3), 31.8 for 2048 1024 1024; three steps ahead: no change;
+// no LDS, every wavefront splitting its own operands: 33.7 at the first, bound by the 32 lines a load touches.
+// Every element is summed in mlp_gemm's order.
+constexpr int kSplitThreads = 768;
+template <int ACT>
+__global__ __launch_bounds__(kSplitThreads, 6) void mlp_split(const float *__restrict__ X, const float *__restrict__ W,
+                                                              const float *__restrict__ bias, float *__restrict__ Y,
+                                                              int64_t M, int N, int K, uint32_t n_tiles, uint32_t tiles)
+{
+    constexpr int BM = 64, CH = 4, BK = 8 * CH;               // CH planes of eight k per step
+    // rows of X, rows of W, and padding that spreads the planes one thread row writes over the banks
+    constexpr int L = 2 * BM + 8 / CH, BUF = 3 * CH * L;
+    __shared__ u32x4 lds[2 * BUF];
+
+    // XCD x gets the tiles [x * per, (x + 1) * per) in launch order
+    const uint32_t per = (tiles + 7u) / 8u;
+    const uint32_t tile = (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
+    if ((blockIdx.x >> 3) >= per || tile >= tiles) return;
+    const int64_t m0 = (int64_t)(tile / n_tiles) * BM;
+    const int n0 = (int)(tile % n_tiles) * BM;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar: the roles are a branch, not a mask
+    const int steps = (K + BK - 1) / BK, full = K / BK;
+
+    // Both roles pass `steps` barriers: step 0 is there, then one per further step.
+    if (wave >= 4) {
+        static_assert((kSplitThreads - 256) == 2 * BM * CH, "a chunk per thread");
+        const int tid = threadIdx.x - 256, r = tid / CH, sc = tid % CH;
+        // rows past the last repeat it: what they give is not stored
+        const float *row = r < BM ? X + std::min<int64_t>(m0 + r, M - 1) * K : W + (int64_t)std::min(n0 + r - BM, N - 1) * K;
+        auto load = [&](int step) {                           // past the last step its last eight again
+            return load_chunk<true>(row, std::min(step * BK + 8 * sc, K - 8), K);
+        };
+        auto stage = [&](Chunk c, int step) {
+            if (step == full) clear_before(c, step * BK + 8 * sc, K);
+            u32x4 part[3];
+            split(c, part);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) lds[(step & 1) * BUF + (p * CH + sc) * L + r] = part[p];
+        };
+        Chunk even, odd;                                      // two steps on their way
+        if (K >= 8) {
+            even = load(0);
+            odd = load(1);
+            stage(even, 0);
+            even = load(2);
+        } else stage(load_chunk<false>(row, 8 * sc, K), 0);   // the only step
+        __syncthreads();
+        for (int t = 1; t < steps; t += 2) {
+            stage(odd, t);
+            odd = load(t + 2);
+            __syncthreads();
+            if (t + 1 < steps) {
+                stage(even, t + 1);
+                even = load(t + 3);
+                __syncthreads();
+            }
+        }
+        return;
+    }
+
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+    f32x16 acc[1], low = 0.f;                                 // sums of the first parts' products, of the rest
+    acc[0] = 0.f;
+    auto part = [&](int buf, int p, int c, int at) { return __builtin_bit_cast(bf16x8, lds[buf * BUF + (p * CH + c) * L + at]); };
+    auto multiply = [&](int buf) {
+#pragma unroll
+        for (int kc = 0; kc < CH; kc += 2) {
+            bf16x8 a[3], b[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                a[p] = part(buf, p, kc + half, wm + l32);
+                b[p] = part(buf, p, kc + half, BM + wn + l32);
+            }
+#pragma unroll
+            for (int o = 2; o >= 0; --o)                      // parts p and o - p
+#pragma unroll
+                for (int p = 0; p <= o; ++p) {
+                    f32x16 &sum = o ? low : acc[0];
+                    sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[p], b[o - p], sum, 0, 0, 0);
+                }
+        }
+    };
+    __syncthreads();
+    for (int t = 1; t < steps; ++t) {
+        multiply((t - 1) & 1);
+        __syncthreads();
+    }
+    multiply((steps - 1) & 1);
+    if (K <= kAllK) {                                         // the three smallest products, of the only step
+#pragma unroll
+        for (int o = 4; o >= 2; --o) {
+            const int p = o == 2 ? 1 : 2, q = o == 3 ? 1 : 2; // parts 2 2, 2 1, 1 2
+            low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(part(0, p, half, wm + l32), part(0, q, half, BM + wn + l32), low, 0, 0, 0);
+        }
+    }
+    acc[0] += low;
+    finish<ACT>(acc, X, W, bias, Y, M, N, K, m0 + wm, n0 + wn);
+}
+
 // Layers of up to 64 k and 64 outputs, where a tile has nothing to keep the matrix pipe busy with: no LDS.  A lane's
 // eight k of a row are the instruction's own layout, so a wavefront splits what it loads and multiplies; it keeps the
 // parts of its 32 rows of W over `reps` blocks of 32 rows of X, the next block's loads in flight.  WN wavefronts side
@@ -391,16 +512,20 @@ __global__ __launch_bounds__(kThreads) void mlp_short(const float *__restrict__ 
     if (col >= N) return;
     int64_t row = (int64_t)(tile / n_tiles) * reps * kRows + 32 * (wave / WN);
     Chunk x[STEPS];
+    auto chunk = [&](const float *at, int s) {                // K > 16 (STEPS - 1)
+        const int k = 16 * s + 8 * half;
+        return s + 1 < STEPS || K == 16 * STEPS ? load_chunk<true>(at, k, K) : load_chunk<false>(at, k, K);
+    };
     auto load = [&]() {
         const float *at = X + std::min<int64_t>(row + l32, M - 1) * K;
 #pragma unroll
-        for (int s = 0; s < STEPS; ++s) x[s] = load_chunk<false>(at, 16 * s + 8 * half, K);
+        for (int s = 0; s < STEPS; ++s) x[s] = chunk(at, s);
     };
     load();
     u32x4 b[STEPS][3];
     const float *w = W + (int64_t)std::min(col + l32, N - 1) * K;
 #pragma unroll
-    for (int s = 0; s < STEPS; ++s) split(load_chunk<false>(w, 16 * s + 8 * half, K), b[s]);
+    for (int s = 0; s < STEPS; ++s) split(chunk(w, s), b[s]);
     for (int n = 0; n < reps && row < M; ++n) {
         u32x4 a[STEPS][3];
 #pragma unroll
@@ -703,16 +828,16 @@ __global__ __launch_bounds__(kThreads, SRC == FROM_PARTIALS ? 6 : 1) void intera
 
 // The largest tile that still gives every compute unit two workgroups: a large tile splits and reads a
 // value of X or W for more multiplies, but one workgroup alone does not fill a compute unit.  us with
-// tiles of 128 x 128 / 128 x 64 / 64 x 64, M K N: 16384 1024 512 (512 large tiles) 105 / 124 / 131,
-// 16384 512 256 (256) 37 / 35 / 37, 4096 1024 1024 (256) 58 / 58 / 64, 2048 1024 1024 (128) 50 / 36 / 36,
-// 2048 512 256 (32) 29 / 19 / 13, 512 1024 1024 (32) 47 / 31 / 22.
+// tiles of 128 x 128 / 128 x 64 / 64 x 64 (mlp_split), M K N: 16384 1024 512 (512 large tiles) 97 / 124 / -,
+// 16384 512 256 (256) 37 / 33 / 34, 4096 1024 1024 (256) 58 / 57 / 62, 2048 1024 1024 (128) 50 / 36 / 33,
+// 2048 512 256 (32) 29 / 19 / 11, 512 1024 1024 (32) 47 / 31 / 18.
 template <int TI, int TJ, int CH, int ACT>
 bool launch_tiles(const bls_ctx *ctx, const float *x, int64_t M, int K, const float *W, const float *bias, int N, float *y,
-                  bool any, hipStream_t st)
+                  hipStream_t st)
 {
     constexpr int BM = 64 * TI, BN = 64 * TJ;
     const uint64_t n_tiles = (uint64_t)((N + BN - 1) / BN), tiles = (uint64_t)((M + BM - 1) / BM) * n_tiles;
-    if (!any && tiles < 2 * (uint64_t)(ctx->compute_units > 0 ? ctx->compute_units : 256)) return false;
+    if (tiles < 2 * (uint64_t)(ctx->compute_units > 0 ? ctx->compute_units : 256)) return false;
     const dim3 grid((unsigned)((tiles + 7u) / 8u * 8u));
     mlp_gemm<TI, TJ, CH, ACT><<<grid, kThreads, 0, st>>>(x, W, bias, y, M, N, K, (uint32_t)n_tiles, (uint32_t)tiles);
     return true;
@@ -741,7 +866,7 @@ template <int ACT>
 void launch_layer(const bls_ctx *ctx, const float *x, int64_t M, int K, const float *W, const float *bias, int N, float *y,
                   hipStream_t st)
 {
-    // 10^6 samples, us, fp32 instruction / tiles of 128 and 64 / this: K N 1 4 75 / 88 / 42, 13 16 83 / 97 / 50,
+    // 10^6 samples, us, fp32 instruction / tiles of 128 and 64 / this: K N 1 4 75 / 88 / 42, 13 16 83 / 97 / 39,
     // 64 4 166 / 162 / 98, 1 64 124 / 133 / 99, 64 64 204 / 195 / 185; from 65 outputs on the tiles are faster
     // (65536 samples, 13 512: 51 / 57) and so they are from 65 k on, where the parts of W do not fit the registers
     if (K <= 64 && N <= 64) {
@@ -753,9 +878,13 @@ void launch_layer(const bls_ctx *ctx, const float *x, int64_t M, int K, const fl
     // M = 10^6 K = 96 246 / 196, K = 128 239 / 218, K = 256 373 / 375; N = 4, M = 65536 K = 256 46 / 26, K = 1024
     // 215 / 88.  By K and N alone: the sums' order, so that a sample's result does not depend on M.
     if (N == 1 && K >= kNarrowK) mlp_narrow<ACT><<<dim3((unsigned)((M + 3) / 4)), kThreads, 0, st>>>(x, W, bias, y, M, K);
-    else if (launch_tiles<2, 2, 2, ACT>(ctx, x, M, K, W, bias, N, y, false, st)) return;
-    else if (launch_tiles<2, 1, 4, ACT>(ctx, x, M, K, W, bias, N, y, false, st)) return;
-    else (void)launch_tiles<1, 1, 4, ACT>(ctx, x, M, K, W, bias, N, y, true, st);
+    else if (launch_tiles<2, 2, 2, ACT>(ctx, x, M, K, W, bias, N, y, st)) return;
+    else if (launch_tiles<2, 1, 4, ACT>(ctx, x, M, K, W, bias, N, y, st)) return;
+    else {
+        const uint64_t n_tiles = (uint64_t)((N + 63) / 64), tiles = (uint64_t)((M + 63) / 64) * n_tiles;
+        const dim3 grid((unsigned)((tiles + 7u) / 8u * 8u));
+        mlp_split<ACT><<<grid, kSplitThreads, 0, st>>>(x, W, bias, y, M, N, K, (uint32_t)n_tiles, (uint32_t)tiles);
+    }
 }
 
 }  // namespace
