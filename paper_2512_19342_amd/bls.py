@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes as C
 import os
 import struct
+from operator import index
 from typing import Optional, Sequence
 
 import torch
@@ -286,7 +287,7 @@ class Context:
         before them; ``rows = (b0, bn)``: those rows of x and of every y only (which may then have more).  Shapes are taken
         from the tensors."""
         M, K = x.shape
-        lo, m = (0, M) if rows is None else rows
+        lo, m = (0, M) if rows is None else (index(rows[0]), index(rows[1]))
         end, f32 = lo + m, torch.float32
         assert 0 <= lo <= end <= M and x.is_contiguous() and x.dtype is f32
         flat, k = [], K

@@ -3,6 +3,7 @@ points need (torch is used for memory and streams only) and issues the calls of 
 iteration in path order.  No arithmetic happens here."""
 from __future__ import annotations
 
+from operator import index
 from typing import List, Optional
 
 import torch
@@ -174,9 +175,19 @@ class DenseModel:
         (default: the model's own buffer, overwritten by the next call).  ``rows = (b0, bn)``
         restricts the work to those samples (one rank's mini-batch); every tensor is the full one."""
         ys = self.bot_act if x_out is None else self.bot_act[:-1] + [x_out]
-        self.ctx.bls_mlp(dense, [(W, b, bls.BLS_ACT_RELU, y) for (W, b), y in zip(self.bottom, ys)],
-                         (0, self.B) if rows is None else rows, stream)
+        self._mlp(dense, self.bottom, [bls.BLS_ACT_RELU] * len(ys), ys, (0, self.B) if rows is None else rows, stream)
         return ys[-1]
+
+    def _mlp(self, x, layers, acts, ys, rows, stream):
+        """Rows ``b0 .. b0 + bn - 1`` of x through the layers, to the same rows of every y.  Rows that are no plain range of
+        whole tensors (they end past the last sample, or are one row of a tensor whose rows are apart) are what slices make
+        of them; the others are addressed, which spares a launch two slices."""
+        lo, hi = index(rows[0]), index(rows[0]) + index(rows[1])
+        if 0 <= lo <= hi <= x.shape[0] and x.is_contiguous() and ys[-1].is_contiguous():
+            rows = (lo, hi - lo)
+        else:
+            x, ys, rows = x[lo:hi], [y[lo:hi] for y in ys], None
+        self.ctx.bls_mlp(x, [(W, b, act, y) for (W, b), act, y in zip(layers, acts, ys)], rows, stream)
 
     def compute_ctr(self, x: torch.Tensor, emb, p_out: Optional[torch.Tensor] = None, stream=None,
                     rows: Optional[tuple] = None) -> torch.Tensor:
@@ -189,10 +200,10 @@ class DenseModel:
             rows = (0, self.B)
         else:
             rows = (0, self.B) if rows is None else rows
-            self.ctx.bls_interact(x, emb, self.z, *rows, stream)
+            self.ctx.bls_interact(x, emb, self.z, rows[0], rows[1], stream)
         ys = self.top_act if p_out is None else self.top_act[:-1] + [p_out]
         acts = [bls.BLS_ACT_RELU] * (len(ys) - 1) + [bls.BLS_ACT_SIGMOID]
-        self.ctx.bls_mlp(self.z, [(W, b, act, y) for (W, b), act, y in zip(self.top, acts, ys)], rows, stream)
+        self._mlp(self.z, self.top, acts, ys, rows, stream)
         return ys[-1]
 
 
