@@ -618,22 +618,25 @@ extern "C" int bls_embbag_pool_exchange(bls_ctx *ctx, const int64_t *d_ridx, con
         if (rc == BLS_OK) rc = bls_ring_advance(ctx, iter_out, slot_out, hip_stream);
         return rc == BLS_OK ? bls_alltoallv_local(ctx, d_send, *slot_out, hip_stream) : rc;
     }
-    if (nnz < 0 || !d_segoff || !d_pooled || !d_send || d_pooled == d_send || (nnz > 0 && !d_ridx))
+    if (nnz < 0 || !d_segoff || !d_pooled || !d_send || d_pooled == d_send || (nnz > 0 && !d_ridx) || !iter_out || !slot_out)
         return bls_fail(ctx, BLS_EINVAL, "bls_embbag_pool_exchange: NULL or aliased argument");
     if ((((uintptr_t)d_pooled | (uintptr_t)d_send) & 15u) != 0)
         return bls_fail(ctx, BLS_EINVAL, "bls_embbag_pool_exchange: buffers must be 16-byte aligned");
     int rc = bls_ready(ctx);
-    if (rc == BLS_OK) rc = bls_ring_advance(ctx, iter_out, slot_out, hip_stream);
-    RingSlot *r = nullptr;
-    if (rc == BLS_OK) rc = slot_to_fill(ctx, *slot_out, "bls_embbag_pool_exchange", &r);
+    if (rc) return rc;
+    const int slot = (int)(ctx->head % ctx->K);
+    RingSlot &r = ctx->ring[slot];
+    rc = ensure_events(ctx, r);
     if (rc) return rc;
     hipStream_t st = (hipStream_t)hip_stream;
-    rc = bls_launch_pool_all(ctx, d_ridx, d_segoff, nnz, d_pooled, d_send,
-                             (float *)(ctx->slots + (size_t)*slot_out * ctx->slot_bytes), st);
+    if (r.has_released && r.released_on != st) BLS_HIP(ctx, hipStreamWaitEvent(st, r.released, 0));
+    // the slot is taken once it is being filled: a launch that fails leaves the ring as it was
+    rc = bls_launch_pool_all(ctx, d_ridx, d_segoff, nnz, d_pooled, d_send, (float *)(ctx->slots + (size_t)slot * ctx->slot_bytes), st);
+    if (rc == BLS_OK) rc = bls_ring_advance(ctx, iter_out, slot_out, hip_stream);
     if (rc) return rc;
-    BLS_HIP(ctx, hipEventRecord(r->filled, st));
-    r->filled_on = st;
-    r->state = 2;
+    BLS_HIP(ctx, hipEventRecord(r.filled, st));
+    r.filled_on = st;
+    r.state = 2;
     return BLS_OK;
 }
 

@@ -1,0 +1,114 @@
+"""Host side of bls_embbag_pool_exchange without a GPU: a few HIP runtime calls are replaced by a library that notes them and
+fails one launch on request.  No kernel runs; the calls' order and what they leave of the ring are what is looked at."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+RUNTIME = r"""
+#include <stddef.h>
+char noted[4096];                       /* L launch, W wait, R record; the stream's digit behind each */
+int launches_left = -1, waits_left = -1;   /* that many succeed, the next one fails; -1: all succeed */
+static int last;
+static int len;
+static void note(char c, size_t s) { noted[len++] = c; noted[len++] = (char)('0' + s % 10); noted[len] = 0; }
+void forget(void) { len = 0; noted[0] = 0; }
+typedef struct { unsigned x, y, z; } dim3;
+int hipGetDevice(int *d) { *d = 0; return 0; }
+int hipSetDevice(int d) { return 0; }
+int hipDeviceGetAttribute(int *v, int a, int d) { *v = 256; return 0; }
+int hipMemcpyAsync(void *d, const void *s, size_t n, int k, void *st) { return 0; }
+int hipStreamSynchronize(void *st) { return 0; }
+int hipDeviceSynchronize(void) { return 0; }
+int hipEventCreateWithFlags(void **e, unsigned f) { *e = (void *)16; return 0; }
+int hipEventDestroy(void *e) { return 0; }
+int hipEventRecord(void *e, void *st) { note('R', (size_t)st); return 0; }
+int hipStreamWaitEvent(void *st, void *e, unsigned f) { if (waits_left == 0) return 1; if (waits_left > 0) --waits_left; note('W', (size_t)st); return 0; }
+static dim3 grid, block;                /* what <<< >>> hands to the launch that follows */
+static size_t lds;
+static void *queue;
+int __hipPushCallConfiguration(dim3 g, dim3 b, size_t sh, void *st) { grid = g; block = b; lds = sh; queue = st; return 0; }
+int __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *sh, void **st) { *g = grid; *b = block; *sh = lds; *st = queue; return 0; }
+int hipLaunchKernel(const void *f, dim3 g, dim3 b, void **a, size_t sh, void *st)
+{
+    if (launches_left == 0) return last = 1;
+    if (launches_left > 0) --launches_left;
+    note('L', (size_t)st);
+    return 0;
+}
+int hipGetLastError(void) { int e = last; last = 0; return e; }
+"""
+
+DRIVER = r"""
+import ctypes as C, sys
+stub = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+L = C.CDLL(sys.argv[2])
+noted = C.c_char.in_dll(stub, "noted")
+left, waits = C.c_int.in_dll(stub, "launches_left"), C.c_int.in_dll(stub, "waits_left")
+class Config(C.Structure):
+    _fields_ = [("P", C.c_int32), ("T", C.c_int32), ("D", C.c_int32), ("k", C.c_int32), ("B", C.c_int64), ("table_dtype", C.c_int32),
+                ("part_kind", C.c_int32), ("rows", C.POINTER(C.c_int64)), ("table_owner", C.POINTER(C.c_int32))]
+vp = C.c_void_p
+at = lambda n: vp(0x10000 * n)                                # 16-byte aligned, never followed
+def ctx(k, D=64, dtype=0, B=64):
+    h = vp()
+    rows, own = (C.c_int64 * 2)(9, 9), (C.c_int32 * 2)(0, 1)
+    assert L.bls_create(C.byref(Config(2, 2, D, k, B, dtype, 0, rows, own)), C.byref(h)) == 0
+    for t in range(2):
+        assert L.bls_set_shard(h, t, t, at(1), C.c_int64(9)) == 0
+    n = C.c_size_t()
+    assert L.bls_desc_bytes(h, C.byref(n)) == 0
+    assert L.bls_commit(h, at(2), n, None) == 0
+    assert L.bls_set_ring(h, at(3), C.c_size_t(1 << 40)) == 0
+    return h
+def ring(h):
+    a, b, k = C.c_int64(), C.c_int64(), C.c_int32()
+    assert L.bls_ring_state(h, C.byref(a), C.byref(b), C.byref(k)) == 0
+    return a.value, b.value
+L.bls_last_error.restype = C.c_char_p
+def issue(h, st):
+    stub.forget()
+    it, slot = C.c_int64(-1), C.c_int32(-1)
+    rc = L.bls_embbag_pool_exchange(h, at(4), at(5), C.c_int64(100), at(6), at(7), C.byref(it), C.byref(slot), vp(st))
+    return rc, it.value, slot.value, C.string_at(C.addressof(noted)).decode()
+def unpack(h, it, st):
+    stub.forget()
+    rc = L.bls_unpack(h, C.c_int64(it), at(8), vp(st))
+    return rc, C.string_at(C.addressof(noted)).decode()
+"""
+
+
+def run(tmp_path, body):
+    import paper_2512_19342_amd as pkg
+    if not os.path.exists(pkg.lib_path()):
+        from paper_2512_19342_amd import build
+        build.build()
+    cc = shutil.which("gcc") or shutil.which("cc")
+    if cc is None:
+        pytest.skip("no C compiler")
+    src, so, py = tmp_path / "runtime.c", tmp_path / "runtime.so", tmp_path / "driver.py"
+    src.write_text(RUNTIME)
+    py.write_text(DRIVER + body)
+    subprocess.check_call([cc, "-shared", "-fPIC", "-O1", str(src), "-o", str(so)])
+    r = subprocess.run([sys.executable, str(py), str(so), pkg.lib_path()], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return r.stdout
+
+
+def test_a_failed_launch_leaves_the_ring_alone(tmp_path):
+    run(tmp_path, r"""
+for k in (1, 3):
+    h = ctx(k)
+    assert issue(h, 0) == (0, 0, 0, "L0R0")                   # one launch, the slot's event
+    assert unpack(h, 0, 0) == (0, "L0R0")
+    left.value = 0
+    rc, it, slot, calls = issue(h, 0)
+    assert rc != 0 and calls == "" and (it, slot) == (-1, -1) and ring(h) == (1, 1), (rc, it, slot, calls, ring(h))
+    left.value = -1
+    assert issue(h, 0) == (0, 1, 1 % k, "L0R0") and ring(h) == (2, 1)
+    assert unpack(h, 1, 0)[0] == 0 and ring(h) == (2, 2)
+""")
