@@ -226,7 +226,8 @@ int bls_alltoallv_local(bls_ctx *ctx, const float *d_send, int32_t slot, void *h
 /* bls_embbag_pool, bls_pack, bls_ring_advance and bls_alltoallv_local in that order, in one launch
  * where that is possible: a pooled vector is stored to Y, S and R out of the pooling kernel's
  * registers, so that pack and exchange need not read it again.  Every output, the ring and the errors
- * are as the four calls leave them; the stream waits for the slot's earlier copy-out before it pools.
+ * are as the four calls leave them.  Where another stream copied the slot out, Y and S are pooled before
+ * that copy-out is waited for and the exchange follows in a launch of its own.
  * The calls are made one by one for rows that are not four or more lanes' whole pieces and with
  * hot-row lists. */
 int bls_embbag_pool_exchange(bls_ctx *ctx, const int64_t *d_ridx, const int64_t *d_segoff, int64_t nnz, float *d_pooled,

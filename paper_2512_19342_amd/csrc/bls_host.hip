@@ -605,10 +605,7 @@ extern "C" int bls_embbag_pool_exchange(bls_ctx *ctx, const int64_t *d_ridx, con
                                         float *d_send, int64_t *iter_out, int32_t *slot_out, void *hip_stream)
 {
     if (!ctx) return BLS_EINVAL;
-    // One launch waits for the slot before it pools, the calls only before they exchange.  It is the shorter one
-    // also where another stream copies the slot out: us an iteration, the calls / one launch, rings of 1 and 2 slots,
-    // 16384 samples of 64 vectors of 128 1503 / 1392 and 1498 / 1381, row-wise 8192 of 26 1085 / 935 and 1088 / 906,
-    // 2048 of 26 of 64 50 / 43 and 39 / 34.  Where no slot can be taken the calls run, and end as they always did.
+    // Where no slot can be taken the calls run, and end as they always did.
     bool apart = !bls_pool_all_fits(ctx) || !ctx->slots || ctx->head - ctx->tail >= ctx->K;
     for (size_t r = 0; r < ctx->rr.put_next.size(); ++r)
         apart = apart || ctx->rr.put_next[r] != ctx->rr.done_next[r] || ctx->rr.put_next[r] != ctx->rr.put_next[0];
@@ -629,11 +626,20 @@ extern "C" int bls_embbag_pool_exchange(bls_ctx *ctx, const int64_t *d_ridx, con
     rc = ensure_events(ctx, r);
     if (rc) return rc;
     hipStream_t st = (hipStream_t)hip_stream;
-    if (r.has_released && r.released_on != st) BLS_HIP(ctx, hipStreamWaitEvent(st, r.released, 0));
-    // the slot is taken once it is being filled: a launch that fails leaves the ring as it was
-    rc = bls_launch_pool_all(ctx, d_ridx, d_segoff, nnz, d_pooled, d_send, (float *)(ctx->slots + (size_t)slot * ctx->slot_bytes), st);
+    // One launch may write the slot where stream order alone says that it has been copied out.  Where another stream
+    // copies it out, Y and S are pooled before that is waited for and the exchange follows it, as with the calls.
+    // us an iteration, the calls / one launch behind the wait / this, ring of one slot; the other stream waits for the
+    // iteration, is busy for 0, 300 and 1000 us, then copies out: 16384 samples of 64 vectors of 128 1569 / 1441 / 1467,
+    // 1585 / 1587 / 1510, 1582 / 2204 / 1494; row-wise 8192 of 26 1057 / 887 / 959, 1064 / 1097 / 951, 1363 / 1631 / 1337.
+    // Two slots, 1000 us: 1560 / 1873 / 1489, 1285 / 1362 / 1222.  A copy-out that is never late loses by it: 2048
+    // samples of 26 vectors of 64 over two slots 42 / 32 / 38.
+    const bool apart_from_slot = r.has_released && r.released_on != st;
+    rc = bls_launch_pool_all(ctx, d_ridx, d_segoff, nnz, d_pooled, d_send,
+                             apart_from_slot ? nullptr : (float *)(ctx->slots + (size_t)slot * ctx->slot_bytes), st);
+    // the slot is taken once the launch has gone through: one that fails leaves the ring as it was
     if (rc == BLS_OK) rc = bls_ring_advance(ctx, iter_out, slot_out, hip_stream);
     if (rc) return rc;
+    if (apart_from_slot) return bls_alltoallv_local(ctx, d_send, slot, hip_stream);
     BLS_HIP(ctx, hipEventRecord(r.filled, st));
     r.filled_on = st;
     r.state = 2;

@@ -39,7 +39,7 @@ constexpr int kRowsInFlightQuantised = BLS_POOL_UQ;
 __device__ __forceinline__ void flag_error(const DevDesc &dd) { atomicOr(dd.err, 1); }
 
 // Where a pooling launch leaves its vectors: Y alone (slot: Y is a ring slot, vectors in receive order), or
-// pooled order, send order and receive order at once.
+// pooled order, send order and, unless R is NULL, receive order at once.
 struct PoolDst {
     float *Y, *S, *R;
     int slot;
@@ -222,7 +222,7 @@ __device__ __forceinline__ void stream_group(const DevDesc &dd, int q, uint32_t 
                         // nobody on the path reads Y and S again, R is read by the completion
                         acc.template store<true>(Y + (int64_t)(y_at + cur) * dd.D + li * A::NV);
                         acc.template store<true>(S + (int64_t)(s_at + cur) * dd.D + li * A::NV);
-                        acc.store(R + (int64_t)(r_at + cur) * dd.D + li * A::NV);
+                        if (R) acc.store(R + (int64_t)(r_at + cur) * dd.D + li * A::NV);
                     } else {
                         acc.store(Y + (out0 + cur) * dd.D + li * A::NV);
                     }

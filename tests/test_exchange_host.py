@@ -112,3 +112,35 @@ for k in (1, 3):
     assert issue(h, 0) == (0, 1, 1 % k, "L0R0") and ring(h) == (2, 1)
     assert unpack(h, 1, 0)[0] == 0 and ring(h) == (2, 2)
 """)
+
+
+def test_the_slot_is_waited_for_only_before_it_is_written(tmp_path):
+    """Another stream's copy-out may be late: what does not touch the slot runs before the wait.  Stream order alone needs
+    neither a wait nor a second launch."""
+    run(tmp_path, r"""
+for k in (1, 2):
+    h = ctx(k)
+    for it in range(6):                                       # issued on stream 1, copied out by stream 2
+        rc, j, slot, calls = issue(h, 1)
+        assert (rc, j, slot) == (0, it, it % k)
+        assert calls == ("L1R1" if it < k else "L1W1L1R1"), (k, it, calls)
+        assert unpack(h, it, 2) == (0, "W2L2R2")
+    h = ctx(k)
+    for it in range(4):
+        assert issue(h, 3)[3] == "L3R3" and unpack(h, it, 3) == (0, "L3R3")
+    # the wait fails: the ring is as it was
+    h = ctx(1)
+    assert issue(h, 1)[0] == 0 and unpack(h, 0, 2)[0] == 0
+    waits.value = 0
+    rc, j, slot, calls = issue(h, 1)
+    waits.value = -1
+    assert rc != 0 and (j, slot) == (-1, -1) and ring(h) == (1, 1) and issue(h, 1)[3] == "L1W1L1R1"
+    # the second launch fails: the iteration has been started, as the separate calls leave it
+    h = ctx(1)
+    assert issue(h, 1)[0] == 0 and unpack(h, 0, 2)[0] == 0
+    left.value = 1
+    rc, j, slot, calls = issue(h, 1)
+    left.value = -1
+    assert rc != 0 and (j, slot) == (1, 0) and calls == "L1W1" and ring(h) == (2, 1)
+    assert L.bls_alltoallv_local(h, at(7), C.c_int32(0), vp(1)) == 0 and unpack(h, 1, 1)[0] == 0
+""")
