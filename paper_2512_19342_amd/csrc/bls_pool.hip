@@ -316,20 +316,31 @@ __device__ __forceinline__ void stream_group(const DevDesc &dd, int q, uint32_t 
     }
 }
 
+// ALL with 32-bit positions: held to the 80 registers of six wavefronts per SIMD.  Four floats a lane fit them.  Eight
+// (half-precision rows, 84) spill three, reloaded behind a wait for every block of G rows: a staged iteration, us, with the
+// bound / without, table-wise 26 vectors of 64, 27 MB, bags of 40 to 100 224 / 194, 32 of 128, 268 MB, bags of 1 to 64
+// 809 / 773, 26 of 128, 55 MB, bags of 20 to 60 255 / 246.  Blocks of 32 rows reload a quarter as often as those of 8, and
+// the sixth wavefront is worth more: 16 of 256 row-wise, 200 MB, bags of 1 193 / 204, of 20 to 60 312 / 336.
+// Eight 8-bit codes a lane spill seven, sixteen fit either way.
+constexpr bool six_wavefronts(int G, int dt, int vb)
+{
+    return lane_floats(dt, vb) == 4 || (lane_floats(dt, vb) == 8 && dt == BLS_FP16 && G == 32);
+}
+
 // grid: x over groups (s-major, then chunks of nb_max samples), y = q.
 // WIDE: row positions as 64-bit byte offsets; otherwise 32-bit, in units of VB bytes (shards
 // below 2^32 * VB bytes), which halves the lane exchanges and the registers they occupy.
 // WGT: per-sample weights rw[] (in ridx order) multiply every row before it is added.
 // ALL: every vector goes to Y (pooled order), S (send order) and R (a ring slot) from the registers it was summed in,
 // in place of pack and exchange, which read it again: five passes over the vectors up to the slot become three.  Vector
-// numbers of 32 bits and the launch bound keep the six wavefronts per SIMD of the plain kernel (81 registers without).
+// numbers of 32 bits and, where six_wavefronts, the launch bound keep the six wavefronts per SIMD of the plain kernel.
 // Y and S carry the streaming hint, the slot does not (the completion reads it).  A staged iteration, us, the separate
 // kernels / plain stores / this / the slot hinted as well: 16384 samples of 64 vectors of 128, Zipf 1568 / 1549 / 1495 /
 // 1488, bags of 1 to 4 743 / 656 / 640 / 522; row-wise 8192 of 26 over eight owners 1079 / 955 / 944 / 950, bags of one
 // 924 / 720 / 676 / 695; table-wise 168 MB of short bags 203 / - / 153 / 183; 2048 of 26 of 64 46.5 / 35.7 / 34.8 / 35.5.
 // Hinting the slot gains only for table-wise ones of 500 MB and loses up to a fifth elsewhere.
 template <int G, int DT, int VB, int U, bool WIDE, bool WGT, bool ALL>
-__global__ __launch_bounds__(kThreads, ALL && !WIDE ? 6 : 1) void pool_stream(DevDesc dd, const int64_t *__restrict__ ridx,
+__global__ __launch_bounds__(kThreads, ALL && !WIDE && six_wavefronts(G, DT, VB) ? 6 : 1) void pool_stream(DevDesc dd, const int64_t *__restrict__ ridx,
                                                         const float *__restrict__ rw,
                                                         const int64_t *__restrict__ segoff, int64_t nnz,
                                                         float *__restrict__ Y, float *__restrict__ S, float *__restrict__ R,

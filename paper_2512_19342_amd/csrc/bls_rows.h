@@ -28,13 +28,16 @@ __host__ __device__ __forceinline__ int64_t stride_bytes(int dtype, int D)
     return is_rowq(dtype) ? ((int64_t)D + 8 + 15) / 16 * 16 : payload_bytes(dtype, D);
 }
 
+// fp32 values in vb bytes of a row
+constexpr int lane_floats(int dt, int vb) { return is_rowq(dt) ? vb : dt == BLS_FP16 ? vb / 2 : vb / 4; }
+
 // Per-lane accumulator: VB bytes of table storage per lane and row, NV values in them.
 // Row-quantised rows also bring their scale and bias (8 bytes behind the codes, the same
 // address for every lane of the group), and a value is code * scale + bias with the product
 // and the sum each rounded to fp32.
 template <int DT, int VB> struct Acc {
     static constexpr int NW = VB / 4;                              // 32-bit words loaded per row
-    static constexpr int NV = is_rowq(DT) ? VB : DT == BLS_FP16 ? VB / 2 : VB / 4;   // fp32 values accumulated
+    static constexpr int NV = lane_floats(DT, VB);            // fp32 values accumulated
     static constexpr int NX = is_rowq(DT) ? 2 : 0;                  // scale, bias
     struct Raw { uint32_t w[NW + NX]; };
     float a[NV];
