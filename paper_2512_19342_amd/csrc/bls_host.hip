@@ -606,7 +606,7 @@ extern "C" int bls_embbag_pool_exchange(bls_ctx *ctx, const int64_t *d_ridx, con
 {
     if (!ctx) return BLS_EINVAL;
     // Where no slot can be taken the calls run, and end as they always did.
-    bool apart = !bls_pool_all_fits(ctx) || !ctx->slots || ctx->head - ctx->tail >= ctx->K;
+    bool apart = !bls_pool_all_fits(ctx, nnz) || !ctx->slots || ctx->head - ctx->tail >= ctx->K;
     for (size_t r = 0; r < ctx->rr.put_next.size(); ++r)
         apart = apart || ctx->rr.put_next[r] != ctx->rr.done_next[r] || ctx->rr.put_next[r] != ctx->rr.put_next[0];
     if (apart) {

@@ -117,7 +117,7 @@ size_t bls_plan_ws_bytes(const bls_ctx *ctx);
 int bls_launch_pool(bls_ctx *ctx, const int64_t *ridx, const float *rw, const int64_t *segoff, int64_t nnz, float *Y,
                     int to_slot, int q0, int qn, hipStream_t st);
 // Y, S and, unless it is NULL, the slot R by one launch, unweighted; only where bls_pool_all_fits
-bool bls_pool_all_fits(const bls_ctx *ctx);
+bool bls_pool_all_fits(const bls_ctx *ctx, int64_t nnz);
 int bls_launch_pool_all(bls_ctx *ctx, const int64_t *ridx, const int64_t *segoff, int64_t nnz, float *Y, float *S, float *R,
                         hipStream_t st);
 int bls_launch_step_tablewise(bls_ctx *ctx, const int64_t *idx, const int64_t *off, int64_t nnz, int64_t *sendcounts,

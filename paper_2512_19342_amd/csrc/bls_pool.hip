@@ -42,8 +42,10 @@ __device__ __forceinline__ void flag_error(const DevDesc &dd) { atomicOr(dd.err,
 // pooled order, send order and, unless R is NULL, receive order at once.
 struct PoolDst {
     float *Y, *S, *R;
-    int slot;
+    int slot, stores;
 };
+// PoolDst::stores: Y alone; three without the streaming hint; three, Y and S with it
+enum { kOneStore = 0, kThreePlain = 1, kThreeHinted = 3 };
 
 // 64-bit value of lane (gbase + k), k uniform.  A whole-wavefront group reads it into scalar
 // registers; narrower groups use the lane permute network (two ds_bpermute, no vector ALU
@@ -155,7 +157,7 @@ __device__ __forceinline__ uint32_t hot_hash(uint32_t row) { return (row * 26544
 // One lane group's work: G >= 4 lanes stream up to nb_max (< G) consecutive segments of (q, s)
 // block number gx / chunks_per_s, chunk gx % chunks_per_s.  HOT: rows found in `hot` are read from
 // LDS instead of global memory.
-template <int G, int DT, int VB, int U, bool WIDE, bool WGT, bool HOT, bool ALL>
+template <int G, int DT, int VB, int U, bool WIDE, bool WGT, bool HOT, int STORES>
 __device__ __forceinline__ void stream_group(const DevDesc &dd, int q, uint32_t gx, const int64_t *__restrict__ ridx,
                                              const float *__restrict__ rw, const int64_t *__restrict__ segoff, int64_t nnz,
                                              float *__restrict__ Y, float *__restrict__ S, float *__restrict__ R, int to_slot,
@@ -177,7 +179,7 @@ __device__ __forceinline__ void stream_group(const DevDesc &dd, int q, uint32_t 
     // this group's segments: samples [b0, b0 + nb) of mini-batch s
     int nb = 0;
     int64_t sg0 = 0, out0 = 0;                                // first segment, its vector in the output
-    uint32_t y_at = 0, s_at = 0, r_at = 0;                    // ALL: the first vector in Y, S and R
+    uint32_t y_at = 0, s_at = 0, r_at = 0;                    // three stores: the first vector in Y, S and R
     if (s < (uint32_t)dd.P) {
         const int64_t f = dd.first[s], n = dd.first[s + 1] - f;
         const int64_t bl0 = (int64_t)chunk * nb_max;
@@ -218,10 +220,11 @@ __device__ __forceinline__ void stream_group(const DevDesc &dd, int q, uint32_t 
             const int nxt = __shfl(rel, gbase + (cur + 2 < G ? cur + 2 : G - 1), 64);
             if (cur_end == pos) {
                 if (col_ok) {
-                    if constexpr (ALL) {
+                    if constexpr (STORES != kOneStore) {
                         // nobody on the path reads Y and S again, R is read by the completion
-                        acc.template store<true>(Y + (int64_t)(y_at + cur) * dd.D + li * A::NV);
-                        acc.template store<true>(S + (int64_t)(s_at + cur) * dd.D + li * A::NV);
+                        constexpr bool HINT = STORES == kThreeHinted;
+                        acc.template store<HINT>(Y + (int64_t)(y_at + cur) * dd.D + li * A::NV);
+                        acc.template store<HINT>(S + (int64_t)(s_at + cur) * dd.D + li * A::NV);
                         if (R) acc.store(R + (int64_t)(r_at + cur) * dd.D + li * A::NV);
                     } else {
                         acc.store(Y + (out0 + cur) * dd.D + li * A::NV);
@@ -316,7 +319,7 @@ __device__ __forceinline__ void stream_group(const DevDesc &dd, int q, uint32_t 
     }
 }
 
-// ALL with 32-bit positions: held to the 80 registers of six wavefronts per SIMD.  Four floats a lane fit them.  Eight
+// Three stores with 32-bit positions: held to the 80 registers of six wavefronts per SIMD.  Four floats a lane fit them.  Eight
 // (half-precision rows, 84) spill three, reloaded behind a wait for every block of G rows: a staged iteration, us, with the
 // bound / without, table-wise 26 vectors of 64, 27 MB, bags of 40 to 100 224 / 194, 32 of 128, 268 MB, bags of 1 to 64
 // 809 / 773, 26 of 128, 55 MB, bags of 20 to 60 255 / 246.  Blocks of 32 rows reload a quarter as often as those of 8, and
@@ -331,7 +334,7 @@ constexpr bool six_wavefronts(int G, int dt, int vb)
 // WIDE: row positions as 64-bit byte offsets; otherwise 32-bit, in units of VB bytes (shards
 // below 2^32 * VB bytes), which halves the lane exchanges and the registers they occupy.
 // WGT: per-sample weights rw[] (in ridx order) multiply every row before it is added.
-// ALL: every vector goes to Y (pooled order), S (send order) and R (a ring slot) from the registers it was summed in,
+// STORES not kOneStore: every vector goes to Y (pooled order), S (send order) and R (a ring slot) from the registers it was summed in,
 // in place of pack and exchange, which read it again: five passes over the vectors up to the slot become three.  Vector
 // numbers of 32 bits and, where six_wavefronts, the launch bound keep the six wavefronts per SIMD of the plain kernel.
 // Y and S carry the streaming hint, the slot does not (the completion reads it).  A staged iteration, us, the separate
@@ -339,8 +342,8 @@ constexpr bool six_wavefronts(int G, int dt, int vb)
 // 1488, bags of 1 to 4 743 / 656 / 640 / 522; row-wise 8192 of 26 over eight owners 1079 / 955 / 944 / 950, bags of one
 // 924 / 720 / 676 / 695; table-wise 168 MB of short bags 203 / - / 153 / 183; 2048 of 26 of 64 46.5 / 35.7 / 34.8 / 35.5.
 // Hinting the slot gains only for table-wise ones of 500 MB and loses up to a fifth elsewhere.
-template <int G, int DT, int VB, int U, bool WIDE, bool WGT, bool ALL>
-__global__ __launch_bounds__(kThreads, ALL && !WIDE && six_wavefronts(G, DT, VB) ? 6 : 1) void pool_stream(DevDesc dd, const int64_t *__restrict__ ridx,
+template <int G, int DT, int VB, int U, bool WIDE, bool WGT, int STORES>
+__global__ __launch_bounds__(kThreads, STORES != kOneStore && !WIDE && six_wavefronts(G, DT, VB) ? 6 : 1) void pool_stream(DevDesc dd, const int64_t *__restrict__ ridx,
                                                         const float *__restrict__ rw,
                                                         const int64_t *__restrict__ segoff, int64_t nnz,
                                                         float *__restrict__ Y, float *__restrict__ S, float *__restrict__ R,
@@ -360,7 +363,7 @@ __global__ __launch_bounds__(kThreads, ALL && !WIDE && six_wavefronts(G, DT, VB)
         q = qn == dd.Q ? dd.q_deal[pos] : q0 + pos;           // all shards: in the balanced order
     }
     const HotRows none{nullptr, nullptr, nullptr, 0};
-    stream_group<G, DT, VB, U, WIDE, WGT, false, ALL>(dd, q, bx * (kThreads / G) + threadIdx.x / G, ridx, rw, segoff, nnz, Y, S, R,
+    stream_group<G, DT, VB, U, WIDE, WGT, false, STORES>(dd, q, bx * (kThreads / G) + threadIdx.x / G, ridx, rw, segoff, nnz, Y, S, R,
                                                       to_slot, nb_max, chunks_per_s, none);
 }
 
@@ -413,7 +416,7 @@ __global__ __launch_bounds__(kHotThreads) void pool_stream_hot(DevDesc dd, const
         __syncthreads();
         const HotRows hot{data, keys, vals, n_hot};
         for (uint32_t blk = j; blk < blocks; blk += per_xcd)
-            stream_group<G, DT, VB, U, false, WGT, true, false>(dd, q, blk * per_wg + threadIdx.x / G, ridx, rw, segoff, nnz, Y,
+            stream_group<G, DT, VB, U, false, WGT, true, kOneStore>(dd, q, blk * per_wg + threadIdx.x / G, ridx, rw, segoff, nnz, Y,
                                                                 nullptr, nullptr, to_slot, nb_max, chunks_per_s, hot);
     }
 }
@@ -518,15 +521,20 @@ void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const
         auto launch = [&](auto kernel) {
             kernel<<<grid, kThreads, 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, to.Y, to.S, to.R, to.slot, nb, chunks, deal, q0, qn);
         };
+        auto three = [&](auto stores) {
+            if (wide) launch(pool_stream<G, DT, VB, UU, true, false, stores()>);
+            else launch(pool_stream<G, DT, VB, UU, false, false, stores()>);
+        };
         if (rw) {
-            if (wide) launch(pool_stream<G, DT, VB, UU, true, true, false>);
-            else launch(pool_stream<G, DT, VB, UU, false, true, false>);
-        } else if (to.S) {
-            if (wide) launch(pool_stream<G, DT, VB, UU, true, false, true>);
-            else launch(pool_stream<G, DT, VB, UU, false, false, true>);
+            if (wide) launch(pool_stream<G, DT, VB, UU, true, true, kOneStore>);
+            else launch(pool_stream<G, DT, VB, UU, false, true, kOneStore>);
+        } else if (to.stores == kOneStore) {
+            if (wide) launch(pool_stream<G, DT, VB, UU, true, false, kOneStore>);
+            else launch(pool_stream<G, DT, VB, UU, false, false, kOneStore>);
+        } else if (Acc<DT, VB>::NV == 16 && to.stores == kThreePlain) {
+            if constexpr (Acc<DT, VB>::NV == 16) three(std::integral_constant<int, kThreePlain>());
         } else {
-            if (wide) launch(pool_stream<G, DT, VB, UU, true, false, false>);
-            else launch(pool_stream<G, DT, VB, UU, false, false, false>);
+            three(std::integral_constant<int, kThreeHinted>());
         }
     } else {
         dim3 grid((unsigned)((ctx->B + per_block - 1) / per_block), qn);
@@ -603,20 +611,44 @@ static int launch_pool(bls_ctx *ctx, const int64_t *ridx, const float *rw, const
 
 int bls_launch_pool(bls_ctx *ctx, const int64_t *ridx, const float *rw, const int64_t *segoff, int64_t nnz, float *Y, int to_slot, int q0, int qn, hipStream_t st)
 {
-    return launch_pool(ctx, ridx, rw, segoff, nnz, PoolDst{Y, nullptr, nullptr, to_slot}, q0, qn, st);
+    return launch_pool(ctx, ridx, rw, segoff, nnz, PoolDst{Y, nullptr, nullptr, to_slot, kOneStore}, q0, qn, st);
 }
 
-bool bls_pool_all_fits(const bls_ctx *ctx)
+// What three stores from the pool's registers are made of where they take no longer than the pool, pack and exchange;
+// kOneStore where they do.  A lane stores its NV floats in pieces of 16 bytes, so one store of a group covers all of the
+// vector for NV = 4, every other piece for 8, every fourth for 16: the more pieces, the more the stores cost beside the
+// permutes, which always store whole lines.  us a staged iteration, the calls / one launch hinted / plain:
+// NV = 16 (8-bit rows), up to 5/4 rows a segment: 32 vectors of 128 10 MB 45 / 40 / 40, 60 MB 111 / 170 / 110, 200 MB 304 /
+// 498 / 310; 48 of 48, 24 MB 65 / 84 / 59; row-wise 12 of 64, 32 MB 66 / 84 / 63: plain, up to 24 MB.  Two to twelve rows:
+// 48 of 64, 32 MB 77 / 70 / 73, 32 of 128, 60 MB 130 / 127 / 134, 200 MB 342 / 336 / 349; row-wise 12 of 128, 45 MB 113 /
+// 104 / 110: hinted, up to 64 MB.  More: 48 of 128, 16 MB 82 / 77 / 79, 32 MB 140 / 144 / 144; 48 of 48, 24 MB 146 / 155 /
+// 155; 32 of 128, 60 MB, 40 rows 238 / 251 / 256: hinted, up to 16 MB.
+// NV = 8 (half-precision rows), hinted; a shorter pool, so that with many rows a segment its fifth wavefront per SIMD
+// counts for more than pack and exchange: 26 vectors of 64, 27 MB, 70 rows 201 / 214, 32 of 128, 200 MB, 40 rows 550 / 560,
+// 20 rows 460 / 463, 5 rows 321 / 305; small ones gain with any number (10 MB, 70 rows 104 / 96).
+// NV = 4: faster everywhere (100 rows, 17 MB, 149 / 140; 70 rows, 60 MB 435 / 415).
+static int stores_that_pay(const bls_ctx *ctx, int nv, int64_t nnz)
+{
+    const size_t MB = size_t(1) << 20;
+    if (nv == 16 && 4 * nnz <= 5 * ctx->nseg) return ctx->slot_bytes <= 24 * MB ? kThreePlain : kOneStore;
+    if (nv == 16) return ctx->slot_bytes <= (nnz <= 12 * ctx->nseg ? 64 : 16) * MB ? kThreeHinted : kOneStore;
+    if (nv == 8 && nnz > 32 * ctx->nseg && ctx->slot_bytes > 24 * MB) return kOneStore;
+    return kThreeHinted;
+}
+
+static int pool_all_stores(const bls_ctx *ctx, int64_t nnz)
 {
     int vb = 0, lanes = 0;
-    if (!pool_shape(ctx, &vb, &lanes) || ctx->nvec >= (int64_t)1 << 31) return false;   // 32-bit vector numbers
-    if (lanes < (vb == 16 ? 4 : 128 / vb)) return false;      // pool_rows, or no kernel of dispatch_lanes
+    if (!pool_shape(ctx, &vb, &lanes) || ctx->nvec >= (int64_t)1 << 31) return kOneStore;   // 32-bit vector numbers
+    if (lanes < (vb == 16 ? 4 : 128 / vb)) return kOneStore;  // pool_rows, or no kernel of dispatch_lanes
     for (const auto &h : ctx->q_hot)
-        if (!h.empty()) return false;
-    return true;
+        if (!h.empty()) return kOneStore;
+    return stores_that_pay(ctx, lane_floats(ctx->dtype, vb), nnz);
 }
+
+bool bls_pool_all_fits(const bls_ctx *ctx, int64_t nnz) { return pool_all_stores(ctx, nnz) != kOneStore; }
 
 int bls_launch_pool_all(bls_ctx *ctx, const int64_t *ridx, const int64_t *segoff, int64_t nnz, float *Y, float *S, float *R, hipStream_t st)
 {
-    return launch_pool(ctx, ridx, nullptr, segoff, nnz, PoolDst{Y, S, R, 0}, 0, ctx->Q, st);
+    return launch_pool(ctx, ridx, nullptr, segoff, nnz, PoolDst{Y, S, R, 0, pool_all_stores(ctx, nnz)}, 0, ctx->Q, st);
 }

@@ -70,10 +70,10 @@ def ring(h):
     assert L.bls_ring_state(h, C.byref(a), C.byref(b), C.byref(k)) == 0
     return a.value, b.value
 L.bls_last_error.restype = C.c_char_p
-def issue(h, st):
+def issue(h, st, nnz=100):
     stub.forget()
     it, slot = C.c_int64(-1), C.c_int32(-1)
-    rc = L.bls_embbag_pool_exchange(h, at(4), at(5), C.c_int64(100), at(6), at(7), C.byref(it), C.byref(slot), vp(st))
+    rc = L.bls_embbag_pool_exchange(h, at(4), at(5), C.c_int64(nnz), at(6), at(7), C.byref(it), C.byref(slot), vp(st))
     return rc, it.value, slot.value, C.string_at(C.addressof(noted)).decode()
 def unpack(h, it, st):
     stub.forget()
@@ -143,4 +143,21 @@ for k in (1, 2):
     left.value = -1
     assert rc != 0 and (j, slot) == (1, 0) and calls == "L1W1" and ring(h) == (2, 1)
     assert L.bls_alltoallv_local(h, at(7), C.c_int32(0), vp(1)) == 0 and unpack(h, 1, 1)[0] == 0
+""")
+
+
+def test_one_launch_only_where_its_stores_are_worth_it(tmp_path):
+    """Two tables of 64 floats, by storage, megabytes of vectors and rows a segment: either side of every line; the other
+    sizes take the separate calls (pool, pack, exchange)."""
+    run(tmp_path, r"""
+fp32, fp16, u8, f8 = 0, 1, 2, 3
+one, apart = "L0R0", "L0L0L0R0"
+for dtype, mb, rows, calls in ((u8, 24, 1.25, one), (f8, 25, 1.25, apart), (f8, 64, 1.5, one), (u8, 65, 1.5, apart), (u8, 64, 12, one),
+                               (f8, 64, 13, apart), (u8, 16, 99, one), (u8, 17, 99, apart), (fp16, 24, 99, one), (fp16, 25, 32, one),
+                               (fp16, 25, 33, apart), (fp32, 25, 99, one), (fp32, 999, 0, one), (u8, 24, 0, one), (u8, 25, 0, apart)):
+    B = (mb << 20) // (2 * 64 * 4)
+    h = ctx(1, dtype=dtype, B=B)
+    got = issue(h, 0, int(2 * B * rows))
+    assert got == (0, 0, 0, calls), (dtype, mb, rows, got)
+    assert unpack(h, 0, 0)[0] == 0 and ring(h) == (1, 1)
 """)
