@@ -44,8 +44,8 @@ struct PoolDst {
     float *Y, *S, *R;
     int slot, stores;
 };
-// PoolDst::stores: Y alone; three without the streaming hint; three, Y and S with it
-enum { kOneStore = 0, kThreePlain = 1, kThreeHinted = 3 };
+// PoolDst::stores: Y alone; three without the streaming hint; three, Y with it; three, Y and S with it
+enum { kOneStore = 0, kThreePlain = 1, kThreeHintedY = 2, kThreeHinted = 3 };
 
 // 64-bit value of lane (gbase + k), k uniform.  A whole-wavefront group reads it into scalar
 // registers; narrower groups use the lane permute network (two ds_bpermute, no vector ALU
@@ -222,9 +222,8 @@ __device__ __forceinline__ void stream_group(const DevDesc &dd, int q, uint32_t 
                 if (col_ok) {
                     if constexpr (STORES != kOneStore) {
                         // nobody on the path reads Y and S again, R is read by the completion
-                        constexpr bool HINT = STORES == kThreeHinted;
-                        acc.template store<HINT>(Y + (int64_t)(y_at + cur) * dd.D + li * A::NV);
-                        acc.template store<HINT>(S + (int64_t)(s_at + cur) * dd.D + li * A::NV);
+                        acc.template store<STORES >= kThreeHintedY>(Y + (int64_t)(y_at + cur) * dd.D + li * A::NV);
+                        acc.template store<STORES == kThreeHinted>(S + (int64_t)(s_at + cur) * dd.D + li * A::NV);
                         if (R) acc.store(R + (int64_t)(r_at + cur) * dd.D + li * A::NV);
                     } else {
                         acc.store(Y + (out0 + cur) * dd.D + li * A::NV);
@@ -531,8 +530,10 @@ void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const
         } else if (to.stores == kOneStore) {
             if (wide) launch(pool_stream<G, DT, VB, UU, true, false, kOneStore>);
             else launch(pool_stream<G, DT, VB, UU, false, false, kOneStore>);
-        } else if (Acc<DT, VB>::NV == 16 && to.stores == kThreePlain) {
+        } else if (to.stores == kThreePlain) {
             if constexpr (Acc<DT, VB>::NV == 16) three(std::integral_constant<int, kThreePlain>());
+        } else if (to.stores == kThreeHintedY) {
+            if constexpr (Acc<DT, VB>::NV == 8 || (Acc<DT, VB>::NV == 4 && G <= 16)) three(std::integral_constant<int, kThreeHintedY>());
         } else {
             three(std::integral_constant<int, kThreeHinted>());
         }
@@ -626,14 +627,28 @@ int bls_launch_pool(bls_ctx *ctx, const int64_t *ridx, const float *rw, const in
 // NV = 8 (half-precision rows), hinted; a shorter pool, so that with many rows a segment its fifth wavefront per SIMD
 // counts for more than pack and exchange: 26 vectors of 64, 27 MB, 70 rows 201 / 214, 32 of 128, 200 MB, 40 rows 550 / 560,
 // 20 rows 460 / 463, 5 rows 321 / 305; small ones gain with any number (10 MB, 70 rows 104 / 96).
-// NV = 4: faster everywhere (100 rows, 17 MB, 149 / 140; 70 rows, 60 MB 435 / 415).
+// NV = 4: faster everywhere (100 rows, 17 MB, 149 / 140; 70 rows, 60 MB 435 / 415) for vectors of whole 64-byte pieces.
+// Two of the others share one, which hinted stores write twice; the shorter the vector, the more of its pieces are shared
+// and the more lanes of a store have nothing to do.  Bags of 1 to 4, the calls / Y and S hinted / Y alone / neither:
+// table-wise 48 vectors of 20, 25 MB 86 / 86 / 79 / 85, 50 MB 141 / 164 / 142 / 140, 400 MB 1034 / 1231 / 1088 / 1034; of 28, 130
+// MB 288 / 369 / 343 / 313; of 52, 50 MB 116 / 114 / 108 / 114, 130 MB 259 / 282 / 273 / 264; row-wise 12 of 20, 60 MB 119 / 134 /
+// 99 / 117, 200 MB 352 / 429 / 363 / 335; of 28, 200 MB 301 / 386 / 342 / 314; of 36, 130 MB 228 / 224 / 169 / 209; of 52, 260 MB
+// 358 / 369 / 351 / 362; half-precision, row-wise of 24, 50 MB 96 / 128 / 77 / 101, of 104, 130 MB 173 / 192 / 150 / 186.  Many rows
+// a segment, the calls / Y alone: 48 of 28, 20 MB, 10 rows 111 / 112, 45 MB 202 / 213; row-wise 12 of 28, 120 MB, 7 rows 327 /
+// 358, half-precision of 24 346 / 385.  From 64
+// floats on (four a lane) both hinted: 48 of 68, 400 MB 858 / 794 / 753 / 753, row-wise 12 of 104 507 / 355 / 437 / 449.
+// NV < 4: no hint (stores of 4 and 8 bytes), half again as fast as the calls (48 of 33, 130 MB 657 / 400).
 static int stores_that_pay(const bls_ctx *ctx, int nv, int64_t nnz)
 {
     const size_t MB = size_t(1) << 20;
+    const int D = ctx->D;
     if (nv == 16 && 4 * nnz <= 5 * ctx->nseg) return ctx->slot_bytes <= 24 * MB ? kThreePlain : kOneStore;
     if (nv == 16) return ctx->slot_bytes <= (nnz <= 12 * ctx->nseg ? 64 : 16) * MB ? kThreeHinted : kOneStore;
     if (nv == 8 && nnz > 32 * ctx->nseg && ctx->slot_bytes > 24 * MB) return kOneStore;
-    return kThreeHinted;
+    if (nv < 4 || D % 16 == 0 || (nv == 4 && D >= 64)) return kThreeHinted;
+    const bool tables = ctx->part_kind == BLS_TABLE_WISE;
+    if (D < 32 && (nnz > 4 * ctx->nseg || ctx->slot_bytes > (tables ? 48 : 96) * MB)) return kOneStore;
+    return tables && D < 64 && ctx->slot_bytes > 48 * MB ? kOneStore : kThreeHintedY;
 }
 
 static int pool_all_stores(const bls_ctx *ctx, int64_t nnz)

@@ -54,12 +54,13 @@ class Config(C.Structure):
                 ("part_kind", C.c_int32), ("rows", C.POINTER(C.c_int64)), ("table_owner", C.POINTER(C.c_int32))]
 vp = C.c_void_p
 at = lambda n: vp(0x10000 * n)                                # 16-byte aligned, never followed
-def ctx(k, D=64, dtype=0, B=64):
+def ctx(k, D=64, dtype=0, B=64, part=0):
     h = vp()
     rows, own = (C.c_int64 * 2)(9, 9), (C.c_int32 * 2)(0, 1)
-    assert L.bls_create(C.byref(Config(2, 2, D, k, B, dtype, 0, rows, own)), C.byref(h)) == 0
+    assert L.bls_create(C.byref(Config(2, 2, D, k, B, dtype, part, rows, own)), C.byref(h)) == 0
     for t in range(2):
-        assert L.bls_set_shard(h, t, t, at(1), C.c_int64(9)) == 0
+        for rank, n in ((t, 9),) if part == 0 else ((0, 5), (1, 4)):
+            assert L.bls_set_shard(h, t, rank, at(1), C.c_int64(n)) == 0
     n = C.c_size_t()
     assert L.bls_desc_bytes(h, C.byref(n)) == 0
     assert L.bls_commit(h, at(2), n, None) == 0
@@ -147,8 +148,8 @@ for k in (1, 2):
 
 
 def test_one_launch_only_where_its_stores_are_worth_it(tmp_path):
-    """Two tables of 64 floats, by storage, megabytes of vectors and rows a segment: either side of every line; the other
-    sizes take the separate calls (pool, pack, exchange)."""
+    """Two tables, by storage, partition, length, megabytes of vectors and rows a segment: either side of every line; the
+    other sizes take the separate calls (pool, pack, exchange)."""
     run(tmp_path, r"""
 fp32, fp16, u8, f8 = 0, 1, 2, 3
 one, apart = "L0R0", "L0L0L0R0"
@@ -160,4 +161,14 @@ for dtype, mb, rows, calls in ((u8, 24, 1.25, one), (f8, 25, 1.25, apart), (f8, 
     got = issue(h, 0, int(2 * B * rows))
     assert got == (0, 0, 0, calls), (dtype, mb, rows, got)
     assert unpack(h, 0, 0)[0] == 0 and ring(h) == (1, 1)
+for dtype, part, D, mb, calls in ((fp32, 0, 20, 48, one), (fp32, 0, 20, 49, apart), (fp32, 0, 60, 49, apart), (fp32, 0, 64, 49, one), (fp32, 0, 68, 999, one),
+                                  (fp32, 0, 48, 999, one), (fp32, 1, 28, 96, one), (fp32, 1, 28, 97, apart), (fp32, 1, 36, 999, one),
+                                  (fp16, 0, 40, 49, apart), (fp16, 0, 72, 999, one), (fp16, 1, 24, 97, apart), (fp32, 0, 33, 999, one)):
+    B = (mb << 20) // ((1 + part) * 2 * D * 4)
+    h = ctx(1, D=D, dtype=dtype, B=B, part=part)
+    got = issue(h, 0, 2 * B)
+    assert got == (0, 0, 0, calls), (dtype, part, D, mb, got)
+for rows, calls in ((4, one), (5, apart)):
+    h = ctx(1, D=28)
+    assert issue(h, 0, 2 * 64 * rows) == (0, 0, 0, calls)
 """)
