@@ -2,7 +2,8 @@
 """Benchmark of the embedding-lookup hot path on one MI355X.
 
 One step = one pass of the whole path (plan, EmbeddingBag pool, pack, ring slot, local
-alltoallv, unpack) over one synthetic batch that is already resident in HBM.  Prints one
+alltoallv, unpack, each by a call of its own) over one synthetic batch that is already
+resident in HBM; Pipeline.issue's one call for the middle four is timed beside it.  Prints one
 JSON line: lookups/s for the whole path, the HBM roofline of the dominant kernel (the
 pool) from HIP events recorded inside the timed region, and the CPU oracle timed on a
 bounded sample of the same workload on this machine's host cores.
@@ -195,8 +196,8 @@ def dense_section(args, w, pipe, batches, nnzs, note) -> dict:
             "mfma_roofline": {"bound": "mfma", "kernel": f"mlp_gemm ({names[big]})", "achieved": kernels[names[big]]["tflops"],
                               # six bf16 products per fp32 one, at 2.5 PFLOP/s
                               "peak": 2500 / 6, "unit": "TFLOP/s", "frac": kernels[names[big]]["tflops"] / (2500 / 6)},
-            "loop": {"entry_points": "bls_plan + bls_embbag_pool_put + bls_mlp_layer x3 | bls_unpack + bls_interact "
-                                     "(or bls_unpack_interact) + bls_mlp_layer x5", "bound": w.k, **loops}}
+            "loop": {"entry_points": "bls_plan + bls_embbag_pool_put + bls_mlp | bls_unpack + bls_interact "
+                                     "(or bls_unpack_interact) + bls_mlp", "bound": w.k, **loops}}
 
 
 def alltoallv_demo(args) -> int:
@@ -514,7 +515,7 @@ def main() -> int:
         c.bls_unpack(it, out)
         return nnz
 
-    copy_gbps = dtf = dtr = fused_lookups = None
+    copy_gbps = dtf = dti = dtr = fused_lookups = issued_lookups = None
     if not args.timed_only:
         # achievable ceiling for the permute stages: a plain device copy of one pooled buffer
         cp = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
@@ -549,6 +550,21 @@ def main() -> int:
         dtf = time.perf_counter() - tf
         c.bls_check()
         note(f"{args.steps} fused steps: {dtf / args.steps * 1e3:.3f} ms per step")
+
+        # Pipeline.issue's form of the staged step: pool, pack, ring slot and alltoallv by one call, in one launch where that pays
+        for i in range(args.warmup):
+            pipe.step(*batches[i % len(batches)], nnzs[i % len(batches)], out)
+        torch.cuda.synchronize()
+        ti = time.perf_counter()
+        issued_lookups = 0
+        for i in range(args.steps):
+            k = (args.warmup + i) % len(batches)
+            pipe.step(*batches[k], nnzs[k], out)
+            issued_lookups += nnzs[k]
+        torch.cuda.synchronize()
+        dti = time.perf_counter() - ti
+        c.bls_check()
+        note(f"{args.steps} staged steps through Pipeline.issue: {dti / args.steps * 1e3:.3f} ms per step")
 
         # the ring at work: K-1 iterations stay in flight, completion runs on a second stream
         side = torch.cuda.Stream()
@@ -718,13 +734,16 @@ def main() -> int:
         "stage_ms": stage_ms,
         "stage_ms_stats": run["stage_ms_stats"],
         "stage_gbps": {n: sb[n] / (stage_ms[n] * 1e-3) / 1e9 for n in names},
+        "staged_by_one_call": None if dti is None else {
+            "entry_point": "bls_plan + bls_embbag_pool_exchange + bls_unpack", "ms_per_step": dti / args.steps * 1e3,
+            "lookups_per_s": issued_lookups / dti},
         "fused_owner_side": None if dtf is None else {
             "entry_point": "bls_plan + bls_embbag_pool_put + bls_unpack", "ms_per_step": dtf / args.steps * 1e3,
             "lookups_per_s": fused_lookups / dtf},
         "one_launch_step": one,
         "ring_in_flight": None if dtr is None else {
             "K": c.K, "ms_per_step": dtr / args.steps * 1e3,
-            "note": "staged path, completion deferred K-1 iterations on a second stream"},
+            "note": "staged path by separate calls, completion deferred K-1 iterations on a second stream"},
         "dlrm_model": dlrm,
         "bucket_pool_pack": {"ms": stage_ms["plan"] + stage_ms["pool"] + stage_ms["pack"],
                              "lookups_per_s": mean_nnz / ((stage_ms["plan"] + stage_ms["pool"] + stage_ms["pack"]) * 1e-3)},

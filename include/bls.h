@@ -223,13 +223,18 @@ int bls_ring_advance(bls_ctx *ctx, int64_t *iter_out, int32_t *slot_out, void *h
  * `slot` must be the slot of the youngest iteration started and not yet exchanged. */
 int bls_alltoallv_local(bls_ctx *ctx, const float *d_send, int32_t slot, void *hip_stream);
 
-/* bls_embbag_pool, bls_pack, bls_ring_advance and bls_alltoallv_local in that order, in one launch
- * where that is possible: a pooled vector is stored to Y, S and R out of the pooling kernel's
- * registers, so that pack and exchange need not read it again.  Every output, the ring and the errors
- * are as the four calls leave them.  Where another stream copied the slot out, Y and S are pooled before
- * that copy-out is waited for and the exchange follows in a launch of its own.
- * The calls are made one by one for rows that are not four or more lanes' whole pieces and with
- * hot-row lists. */
+/* bls_embbag_pool, bls_pack, bls_ring_advance and bls_alltoallv_local in that order.  Where that is the
+ * faster, a pooled vector is stored to Y, S and R out of the pooling kernel's registers in one launch, so
+ * that pack and exchange need not read it again; if another stream copied the slot out, Y and S are
+ * pooled before that copy-out is waited for and the exchange follows in a launch of its own.  Otherwise
+ * the four calls are made one by one: for rows of fewer lanes than 4 of 16 bytes, 16 of 8 or 32 of 4
+ * (or longer than 64 lanes of 16), for 2^31 or more vectors, with hot-row lists, where no slot can be
+ * taken (a full ring, no ring, per-rank iterations in flight), and for the storage types, lengths and
+ * sizes whose stores cost more than the calls (stores_that_pay in bls_pool.hip).
+ * A call that succeeds, and after which bls_check reports nothing, leaves every output and the ring as
+ * the four calls do.  Otherwise, with one launch: arguments that one of the calls refuses are refused
+ * before anything is launched (Y is not pooled yet); a pooling launch that fails leaves the ring as it
+ * was; where bls_check reports BLS_ERANGE, Y, S and R are unspecified (the four calls at least move Y on). */
 int bls_embbag_pool_exchange(bls_ctx *ctx, const int64_t *d_ridx, const int64_t *d_segoff, int64_t nnz, float *d_pooled,
                              float *d_send, int64_t *iter_out, int32_t *slot_out, void *hip_stream);
 

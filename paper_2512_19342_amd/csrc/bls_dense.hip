@@ -388,9 +388,10 @@ __global__ __launch_bounds__(kThreads, 2) void mlp_gemm(const float *__restrict_
 // Tiles of 64 x 64 for the layers that do not fill the card with larger ones: few wavefronts per SIMD, so that
 // splitting, LDS and multiplies of one wavefront follow each other more than they overlap (512 x 1024 -> 1024: 1300
 // cycles a step of 32 k, of them 384 of multiplies).  Here they have wavefronts of their own: four multiply (32 x 32
-// each), eight load, split and write, one chunk a step and thread, three per SIMD in all.  Per step one SIMD issues
-// 106 vector operations for 12 multiplies, 5 to 8 cycles each: that bounds it now (without the splitting 12.7 us of
-// 18.2, without the loads nothing less).
+// each), eight load, split and write, one chunk a step and thread, three per SIMD in all.  What bounds it: with one
+// workgroup per compute unit or less the chain of a step, no part of which counts for more than an eighth (512 1024
+// 1024, 18.3 us: without the splitting 16.5, without the loads 16.2, with a sixth of the multiplies 16.1); with two the
+// multiplies (2048 1024 1024, 34.0: 29.5, 26.4, 23.0).
 // us, four wavefronts for everything / this, M K N: 512 1024 1024 20.8 / 18.2, 512 415 1024 13.9 / 11.0, 512 512 256
 // 12.2 / 10.5, 2048 1024 1024 34.1 / 32.7, 2048 1024 512 22.1 / 19.5, 2048 512 256 13.1 / 11.4, 16384 256 128
 // 15.1 / 13.7.  Four wavefronts that split: 20.9 at the first; steps of 64 k: 18.2 there and 37.3 for 2048 1024 1024;
@@ -581,9 +582,9 @@ __global__ __launch_bounds__(kThreads) void mlp_narrow(const float *__restrict__
 // +0, exactly as the copy-out kernel does.
 // Memory bounds the kernel (16384 samples of 64 vectors of 128: 0.68 GB, 130 us at the rate of a copy).  A
 // thread's eight loads of a round are all issued before the first is used: added up one by one as they
-// come, a slot's took 290 us at that size, now 206.  Partial vectors of eight owners, us, one load after another /
-// eight pieces of one partial at a time (four wavefronts per SIMD) / as it is (six): 16384 samples of 2 vectors
-// 108 / 156 / 105, of 4 141 / 193 / 118, 8192 of 26 222 / 234 / 225.
+// come, a slot's took interact_gram 290 us at that size, this way 206 (interact_tiles 188).  Partial vectors of eight
+// owners, interact_gram, us, one load after another / eight pieces of one partial at a time (four wavefronts per SIMD) /
+// as it is (six): 16384 samples of 2 vectors 108 / 156 / 105, of 4 141 / 193 / 118, 8192 of 26 222 / 234 / 225.
 enum Source { FROM_OUT, FROM_SLOT, FROM_PARTIALS };
 
 // The sample's vectors in pieces of V (one float, or four), thread by thread, to rows of LD floats at Es.
@@ -658,9 +659,10 @@ __device__ __forceinline__ void fill_vectors(float *Es, uint32_t T, uint32_t D, 
     }
 }
 
-// The T vectors of a completed lookup in pieces of four floats: one stream, one address.  us in the model's order,
-// 16384 samples of 64 vectors of 128: 181 after layers on the fp32 instruction (186 through fill_vectors), 196 after
-// those on the bf16 one (199).
+// The T vectors of a completed lookup in pieces of four floats: one stream, one address.  us, 16384 samples, interact_tiles
+// with this / with fill_vectors alone: 1 vector of 128 46.9 / 51.7, 4 51.2 / 51.2, 12 55.9 / 53.2, 64 191 / 189 (behind
+// layers 200 / 197); 2 of 64 34.8 / 37.6, 26 52.4 / 49.3; 12 of 20 39.2 / 43.2; 2048 samples of 26 of 64 12.5 / 11.0.  Both
+// in one kernel, chosen by the sample's size, are as this one at every size.
 template <int kFill>
 __device__ __forceinline__ void copy_vectors(float *Es, uint32_t T, uint32_t D, uint32_t LD, const float *vec0)
 {

@@ -12,9 +12,10 @@
 // Bags are short (tens of rows), so a group does not stop at one: it streams the rows of
 // several consecutive segments - they are contiguous in ridx - and stores and clears its
 // accumulator whenever the stream crosses a segment boundary.  That amortises the
-// dependent loads at the start (segment offsets, then row numbers, then rows), lets the
-// next block of row numbers be fetched while the current one is consumed, and evens out
-// the lengths of the streams that share a wavefront.
+// dependent loads at the start (segment offsets, then row numbers, then rows) and evens out
+// the lengths of the streams that share a wavefront.  A block's row numbers are asked for a
+// block ahead but tested against the shard's rows at once, so that they are waited for there:
+// one exposed round trip per G rows.
 #include <algorithm>
 #include <type_traits>
 
@@ -275,7 +276,7 @@ __device__ __forceinline__ void stream_group(const DevDesc &dd, int q, uint32_t 
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = A::none();
     for (int c0 = 0; __any(c0 < total); c0 += G) {
-        const pos_t ahead = fetch(c0 + G);                   // next block of row numbers, in flight
+        const pos_t ahead = fetch(c0 + G);                   // next block of row numbers: waited for inside, by the test
         const float wahead = fetch_weight(c0 + G);
         const int left = total - c0;
         const int rem = left < 0 ? 0 : (left > G ? G : left);
@@ -301,7 +302,8 @@ __device__ __forceinline__ void stream_group(const DevDesc &dd, int q, uint32_t 
                 }
             }
             // every load of the batch has landed before the first add: said once, here, so that
-            // no wait is placed between the conditional loads of the next batch
+            // no wait is placed between the conditional loads of the next batch (the counter holds
+            // stores as well: those of segments that ended in the batch before are waited for too)
             __builtin_amdgcn_s_waitcnt(0x0f70);              // vmcnt(0)
             const int at = c0 + j;                           // stream position of the batch (uniform)
 #pragma unroll

@@ -167,7 +167,7 @@ __global__ __launch_bounds__(kThreads) void step_tablewise(DevDesc dd, const int
 
     A acc;
     acc.zero();
-    int64_t ahead = li < len ? idx[beg + li] : -1;            // a block's row numbers are asked for one block early
+    int64_t ahead = li < len ? idx[beg + li] : -1;            // asked for one block early, and waited for with the block at hand
     for (int64_t c0 = 0; __any(c0 < len); c0 += G) {
         const int64_t left = len - c0;
         const int rem = left < 0 ? 0 : (left > G ? G : (int)left);
