@@ -234,7 +234,7 @@ int bls_alltoallv_local(bls_ctx *ctx, const float *d_send, int32_t slot, void *h
  * A call that succeeds, and after which bls_check reports nothing, leaves every output and the ring as
  * the four calls do.  Otherwise, with one launch: arguments that one of the calls refuses are refused
  * before anything is launched (Y is not pooled yet); a pooling launch that fails leaves the ring as it
- * was; where bls_check reports BLS_ERANGE, Y, S and R are unspecified (the four calls at least move Y on). */
+ * was; where bls_check reports BLS_ERANGE, the outputs are unspecified, and S and R need not hold Y's vectors. */
 int bls_embbag_pool_exchange(bls_ctx *ctx, const int64_t *d_ridx, const int64_t *d_segoff, int64_t nnz, float *d_pooled,
                              float *d_send, int64_t *iter_out, int32_t *slot_out, void *hip_stream);
 

@@ -13,8 +13,8 @@ pytestmark = pytest.mark.gpu
 # (storage, D, bags): 16 floats a lane stored plain (few rows a segment) and hinted; four and eight of vectors that share
 # 64-byte pieces, short and long; fewer than four
 SHAPES = [(dt, D, bag) for dt in ("u8rq", "f8rq") for D in (64, 112, 256) for bag in ((1, 1), (0, 9))]
-SHAPES += [("fp32", D, (0, 9)) for D in (20, 28, 36, 60, 68, 132, 34, 33)] + [("fp16", D, (0, 9)) for D in (24, 40, 56, 72, 136, 100, 66, 64)]
-SHAPES += [("u8rq", D, (0, 9)) for D in (72, 136, 100)]
+SHAPES += [("fp32", D, (0, 7)) for D in (20, 28, 36, 60, 68, 132, 34, 33)] + [("fp16", D, (0, 7)) for D in (24, 40, 56, 72, 136, 100, 66, 64)]
+SHAPES += [("u8rq", D, (0, 7)) for D in (72, 136, 100)]
 
 
 @pytest.mark.parametrize("part", [0, 1], ids=["tables", "rows"])
