@@ -489,7 +489,14 @@ void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const
         const uint32_t chunks = (uint32_t)((n_max + nb - 1) / nb);
         const int64_t groups = (int64_t)chunks * ctx->P;
         const uint32_t wgx = (uint32_t)((groups + per_block - 1) / per_block);
-        const bool xcd = ctx->tune_xcd != 0;
+        // A shard's workgroups on one XCD leave the others idle where the shards are few, and three stores are then as many
+        // on a part of the XCDs' path to memory, where pack and exchange use all: such launches are not dealt.  us a staged
+        // iteration, vectors of 64, bags of 1 to 4, the calls / one launch dealt / not: fp32 1 table, 30 MB 99 / 112 / 46, 100
+        // MB 292 / 331 / 140, 3 201 / 197 / 146, 5 184 / 166 / 148, 9 186 / 172 / 151; 8-bit, 8 MB 1 54 / 82 / 34, 3 42 / 46 / 34;
+        // half-precision, 100 MB 2 210 / 247 / 137, 9 180 / 180 / 149.  With most XCDs at work the deal's caches count for more
+        // with many rows a segment (7 tables, 8 MB, bags of 1 to 30 44 / 37 / 40), the even spread with few (30 MB 65 / 50 / 49).
+        const bool idle = to.stores != kOneStore && 10 * qn < 7 * 8 * ((qn + 7) / 8);
+        const bool xcd = ctx->tune_xcd == 1 || (ctx->tune_xcd != 0 && !idle);
         const dim3 grid = xcd ? dim3((unsigned)((uint64_t)((qn + 7) / 8) * 8u * wgx)) : dim3(wgx, qn);
         const uint32_t deal = xcd ? wgx : 0u;
         // 32-bit row positions unless some shard is too large for them

@@ -13,6 +13,7 @@ RUNTIME = r"""
 #include <stddef.h>
 char noted[4096];                       /* L launch, W wait, R record; the stream's digit behind each */
 int launches_left = -1, waits_left = -1;   /* that many succeed, the next one fails; -1: all succeed */
+unsigned grid_y;                        /* of the latest launch */
 static int last;
 static int len;
 static void note(char c, size_t s) { noted[len++] = c; noted[len++] = (char)('0' + s % 10); noted[len] = 0; }
@@ -37,6 +38,7 @@ int hipLaunchKernel(const void *f, dim3 g, dim3 b, void **a, size_t sh, void *st
 {
     if (launches_left == 0) return last = 1;
     if (launches_left > 0) --launches_left;
+    grid_y = g.y;
     note('L', (size_t)st);
     return 0;
 }
@@ -54,12 +56,12 @@ class Config(C.Structure):
                 ("part_kind", C.c_int32), ("rows", C.POINTER(C.c_int64)), ("table_owner", C.POINTER(C.c_int32))]
 vp = C.c_void_p
 at = lambda n: vp(0x10000 * n)                                # 16-byte aligned, never followed
-def ctx(k, D=64, dtype=0, B=64, part=0):
+def ctx(k, D=64, dtype=0, B=64, part=0, T=2):
     h = vp()
-    rows, own = (C.c_int64 * 2)(9, 9), (C.c_int32 * 2)(0, 1)
-    assert L.bls_create(C.byref(Config(2, 2, D, k, B, dtype, part, rows, own)), C.byref(h)) == 0
-    for t in range(2):
-        for rank, n in ((t, 9),) if part == 0 else ((0, 5), (1, 4)):
+    rows, own = (C.c_int64 * T)(*[9] * T), (C.c_int32 * T)(*[t % 2 for t in range(T)])
+    assert L.bls_create(C.byref(Config(2, T, D, k, B, dtype, part, rows, own)), C.byref(h)) == 0
+    for t in range(T):
+        for rank, n in ((t % 2, 9),) if part == 0 else ((0, 5), (1, 4)):
             assert L.bls_set_shard(h, t, rank, at(1), C.c_int64(n)) == 0
     n = C.c_size_t()
     assert L.bls_desc_bytes(h, C.byref(n)) == 0
@@ -171,4 +173,17 @@ for dtype, part, D, mb, calls in ((fp32, 0, 20, 48, one), (fp32, 0, 20, 49, apar
 for rows, calls in ((4, one), (5, apart)):
     h = ctx(1, D=28)
     assert issue(h, 0, 2 * 64 * rows) == (0, 0, 0, calls)
+""")
+
+
+def test_few_shards_are_spread_over_the_whole_chip(tmp_path):
+    """Three stores of shards that would keep under seven tenths of the eight XCDs busy: a grid with a row per shard in place of
+    the flat one that deals shards to XCDs, unless bls_set_pool_tuning asks for the deal."""
+    run(tmp_path, r"""
+grid_y = C.c_uint.in_dll(stub, "grid_y")
+for T, y in ((1, 1), (2, 2), (5, 5), (6, 1), (8, 1), (9, 9), (11, 11), (12, 1), (16, 1), (17, 1)):
+    h = ctx(1, T=T)
+    assert issue(h, 0)[0] == 0 and grid_y.value == y, (T, grid_y.value)
+    assert L.bls_set_pool_tuning(h, 0, 0, 1, -1) == 0 and unpack(h, 0, 0)[0] == 0
+    assert issue(h, 0)[0] == 0 and grid_y.value == 1, T
 """)
