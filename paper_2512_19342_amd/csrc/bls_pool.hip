@@ -540,10 +540,10 @@ void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const
             if (wide) launch(pool_stream<G, DT, VB, UU, true, false, kOneStore>);
             else launch(pool_stream<G, DT, VB, UU, false, false, kOneStore>);
         } else if (to.stores == kThreePlain) {
-            if constexpr (Acc<DT, VB>::NV == 16) three(std::integral_constant<int, kThreePlain>());
+            if constexpr (Acc<DT, VB>::NV == 16 || (Acc<DT, VB>::NV == 8 && G >= 16)) three(std::integral_constant<int, kThreePlain>());
         } else if (to.stores == kThreeHintedY) {
             if constexpr (Acc<DT, VB>::NV == 8 || (Acc<DT, VB>::NV == 4 && G <= 16)) three(std::integral_constant<int, kThreeHintedY>());
-        } else {
+        } else if constexpr (Acc<DT, VB>::NV <= 8) {
             three(std::integral_constant<int, kThreeHinted>());
         }
     } else {
@@ -628,14 +628,17 @@ int bls_launch_pool(bls_ctx *ctx, const int64_t *ridx, const float *rw, const in
 // kOneStore where they do.  A lane stores its NV floats in pieces of 16 bytes, so one store of a group covers all of the
 // vector for NV = 4, every other piece for 8, every fourth for 16: the more pieces, the more the stores cost beside the
 // permutes, which always store whole lines.  us a staged iteration, the calls / one launch hinted / plain:
-// NV = 16 (8-bit rows), up to 5/4 rows a segment: 32 vectors of 128 10 MB 45 / 40 / 40, 60 MB 111 / 170 / 110, 200 MB 304 /
-// 498 / 310; 48 of 48, 24 MB 65 / 84 / 59; row-wise 12 of 64, 32 MB 66 / 84 / 63: plain, up to 24 MB.  Two to twelve rows:
-// 48 of 64, 32 MB 77 / 70 / 73, 32 of 128, 60 MB 130 / 127 / 134, 200 MB 342 / 336 / 349; row-wise 12 of 128, 45 MB 113 /
-// 104 / 110: hinted, up to 64 MB.  More: 48 of 128, 16 MB 82 / 77 / 79, 32 MB 140 / 144 / 144; 48 of 48, 24 MB 146 / 155 /
-// 155; 32 of 128, 60 MB, 40 rows 238 / 251 / 256: hinted, up to 16 MB.
-// NV = 8 (half-precision rows), hinted; a shorter pool, so that with many rows a segment its fifth wavefront per SIMD
-// counts for more than pack and exchange: 26 vectors of 64, 27 MB, 70 rows 201 / 214, 32 of 128, 200 MB, 40 rows 550 / 560,
-// 20 rows 460 / 463, 5 rows 321 / 305; small ones gain with any number (10 MB, 70 rows 104 / 96).
+// NV = 16 (8-bit rows): every piece that is hinted goes past the caches by itself, which shows as soon as the rows come out
+// of a cache (24 vectors of 64, 30 MB, 3 rows a segment 68 / 92 / 63, 50 MB 98 / 146 / 93; 32 of 128, 200 MB, 1 row 304 /
+// 498 / 310) and gains little where they do not (48 of 64, 32 MB, 2 rows 77 / 70 / 73).  Plain, up to 24 MB (48 of 48 65 / 84 /
+// 59; 14 of 64, 30 MB, 4 rows 88 / 91 / 93; 32 of 128, 60 MB, 5 rows 130 / 127 / 134) or, with many rows a segment, 16 MB (48 of
+// 128, 40 rows 82 / 77 / 79, 32 MB 140 / 144 / 144; 48 of 48, 24 MB 146 / 155 / 155).
+// NV = 8 (half-precision rows): a shorter pool, so that with many rows a segment its fifth wavefront per SIMD counts for
+// more than pack and exchange: 26 vectors of 64, 27 MB, 70 rows 201 / 214, 32 of 128, 200 MB, 40 rows 550 / 560, 20 rows 460 /
+// 463, 5 rows 321 / 305; small ones gain with any number (10 MB, 70 rows 104 / 96).  Hinted, but for long vectors
+// of hardly any rows: row-wise 21 of 512, 150 MB, 1/7 of a row 182 / 204 / 149, of 256 171 / 184 / 151, of 128 175 / 180 / 158,
+// but of 64 174 / 163 / 174; table-wise 24 of 256, 1 row 214 / 201 / 195, 2 rows 199 / 176 / 216, of 128, 1 row 191 / 187 / 191;
+// and of 192, where a quarter of the lanes idles, 178 / 152 / 181 (row-wise, 1/3 of a row).
 // NV = 4: faster everywhere (100 rows, 17 MB, 149 / 140; 70 rows, 60 MB 435 / 415) for vectors of whole 64-byte pieces.
 // Two of the others share one, which hinted stores write twice; the shorter the vector, the more of its pieces are shared
 // and the more lanes of a store have nothing to do.  Bags of 1 to 4, the calls / Y and S hinted / Y alone / neither:
@@ -651,9 +654,10 @@ static int stores_that_pay(const bls_ctx *ctx, int nv, int64_t nnz)
 {
     const size_t MB = size_t(1) << 20;
     const int D = ctx->D;
-    if (nv == 16 && 4 * nnz <= 5 * ctx->nseg) return ctx->slot_bytes <= 24 * MB ? kThreePlain : kOneStore;
-    if (nv == 16) return ctx->slot_bytes <= (nnz <= 12 * ctx->nseg ? 64 : 16) * MB ? kThreeHinted : kOneStore;
+    if (nv == 16) return ctx->slot_bytes <= (nnz <= 12 * ctx->nseg ? 24 : 16) * MB ? kThreePlain : kOneStore;
     if (nv == 8 && nnz > 32 * ctx->nseg && ctx->slot_bytes > 24 * MB) return kOneStore;
+    const bool whole = (D & (D - 1)) == 0;                    // every lane of a group stores
+    if (nv == 8 && (D >= 256 ? nnz <= ctx->nseg : D >= 128 && whole && 2 * nnz <= ctx->nseg)) return kThreePlain;
     if (nv < 4 || D % 16 == 0 || (nv == 4 && D >= 64)) return kThreeHinted;
     const bool tables = ctx->part_kind == BLS_TABLE_WISE;
     if (D < 32 && (nnz > 4 * ctx->nseg || ctx->slot_bytes > (tables ? 48 : 96) * MB)) return kOneStore;

@@ -10,9 +10,10 @@ from tests.test_gpu_pool_exchange import make
 
 pytestmark = pytest.mark.gpu
 
-# (storage, D, bags): 16 floats a lane stored plain (few rows a segment) and hinted; four and eight of vectors that share
-# 64-byte pieces, short and long; fewer than four
+# (storage, D, bags): 16 floats a lane; eight of long vectors, few rows a segment (plain) and more; four and eight of vectors
+# that share 64-byte pieces, short and long; fewer than four
 SHAPES = [(dt, D, bag) for dt in ("u8rq", "f8rq") for D in (64, 112, 256) for bag in ((1, 1), (0, 9))]
+SHAPES += [("fp16", D, bag) for D in (128, 256, 272, 264, 512) for bag in ((0, 1), (0, 2), (2, 6))] + [("u8rq", 264, (0, 2))]
 SHAPES += [("fp32", D, (0, 7)) for D in (20, 28, 36, 60, 68, 132, 34, 33)] + [("fp16", D, (0, 7)) for D in (24, 40, 56, 72, 136, 100, 66, 64)]
 SHAPES += [("u8rq", D, (0, 7)) for D in (72, 136, 100)]
 
