@@ -589,8 +589,10 @@ enum Source { FROM_OUT, FROM_SLOT, FROM_PARTIALS };
 
 // The sample's vectors in pieces of V (one float, or four), thread by thread, to rows of LD floats at Es.
 // The d-th partial of vector t starts at vec0 + t_q[t] * vec_step + d * part_step (FROM_OUT: t for t_q[t]).
-// A thread loads kFill pieces of a round together, of kParts partials each.
-template <Source SRC, typename V, int kFill, int kParts>
+// A thread loads kFill pieces of a round together, of kParts partials each.  PIECES: every row of Es starts on a 16-byte
+// boundary.  (Known when the kernel is built: asked while it runs, interact_gram took 3 to 5 % longer, 16384 samples of 8
+// vectors of 24 35.1 / 36.8 us, and interact_tiles 2 %; both spilled a register for row-wise slots.)
+template <Source SRC, typename V, int kFill, int kParts, bool PIECES>
 __device__ __forceinline__ void fill_vectors(float *Es, uint32_t T, uint32_t D, uint32_t LD, int F, const float *vec0,
                                              const int32_t *__restrict__ t_q, int64_t vec_step, int64_t part_step)
 {
@@ -650,7 +652,7 @@ __device__ __forceinline__ void fill_vectors(float *Es, uint32_t T, uint32_t D, 
         for (int u = 0; u < kFill; ++u)
             if (live[u]) {
                 if constexpr (W == 1) Es[at[u]] = v[u];
-                else if (LD % 4 == 0) *reinterpret_cast<V *>(Es + at[u]) = v[u];
+                else if constexpr (PIECES) *reinterpret_cast<V *>(Es + at[u]) = v[u];
                 else {
 #pragma unroll
                     for (uint32_t j = 0; j < W; ++j) Es[at[u] + j] = v[u][j];
@@ -663,7 +665,7 @@ __device__ __forceinline__ void fill_vectors(float *Es, uint32_t T, uint32_t D, 
 // with this / with fill_vectors alone: 1 vector of 128 46.9 / 51.7, 4 51.2 / 51.2, 12 55.9 / 53.2, 64 191 / 189 (behind
 // layers 200 / 197); 2 of 64 34.8 / 37.6, 26 52.4 / 49.3; 12 of 20 39.2 / 43.2; 2048 samples of 26 of 64 12.5 / 11.0.  Both
 // in one kernel, chosen by the sample's size, are as this one at every size.
-template <int kFill>
+template <int kFill, bool PIECES>
 __device__ __forceinline__ void copy_vectors(float *Es, uint32_t T, uint32_t D, uint32_t LD, const float *vec0)
 {
     const f32x4 *e = reinterpret_cast<const f32x4 *>(vec0);
@@ -679,7 +681,7 @@ __device__ __forceinline__ void copy_vectors(float *Es, uint32_t T, uint32_t D, 
         for (int u = 0; u < kFill; ++u) {
             const uint32_t i = base + u * kThreads, r = i / per, c = (i - r * per) * 4;
             if (i < n) {
-                if (LD % 4 == 0) *reinterpret_cast<f32x4 *>(Es + r * LD + c) = v[u];
+                if constexpr (PIECES) *reinterpret_cast<f32x4 *>(Es + r * LD + c) = v[u];
                 else {
 #pragma unroll
                     for (int j = 0; j < 4; ++j) Es[r * LD + c + j] = v[u][j];
@@ -690,7 +692,7 @@ __device__ __forceinline__ void copy_vectors(float *Es, uint32_t T, uint32_t D, 
 }
 
 // Sample b's vectors to rows of LD floats at Es, from the completed lookup or out of a slot.
-template <Source SRC, int kFill, int kParts>
+template <Source SRC, int kFill, int kParts, bool PIECES>
 __device__ __forceinline__ void fetch_sample(const DevDesc &dd, float *Es, const float *emb, int64_t b, int T, int D, int LD, int vec4)
 {
     int64_t slot_base = 0, slot_step = 0;                        // vector (q, b) of the slot: slot_base + q * slot_step
@@ -702,9 +704,9 @@ __device__ __forceinline__ void fetch_sample(const DevDesc &dd, float *Es, const
     }
     const float *vec0 = emb + (SRC == FROM_OUT ? b * T : slot_base) * D;
     const int64_t vec_step = SRC == FROM_OUT ? D : slot_step * D, part_step = dd.T * slot_step * D;
-    if (SRC == FROM_OUT && vec4) copy_vectors<kFill>(Es, T, D, LD, vec0);
-    else if (vec4) fill_vectors<SRC, f32x4, kFill, kParts>(Es, T, D, LD, dd.F, vec0, dd.t_q, vec_step, part_step);
-    else fill_vectors<SRC, float, kFill, kParts>(Es, T, D, LD, dd.F, vec0, dd.t_q, vec_step, part_step);
+    if (SRC == FROM_OUT && vec4) copy_vectors<kFill, PIECES>(Es, T, D, LD, vec0);
+    else if (vec4) fill_vectors<SRC, f32x4, kFill, kParts, PIECES>(Es, T, D, LD, dd.F, vec0, dd.t_q, vec_step, part_step);
+    else fill_vectors<SRC, float, kFill, kParts, PIECES>(Es, T, D, LD, dd.F, vec0, dd.t_q, vec_step, part_step);
 }
 
 // D a multiple of 16: tiles of 16 x 16 on v_mfma_f32_16x16x4_f32 (lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16];
@@ -716,7 +718,9 @@ __device__ __forceinline__ void fetch_sample(const DevDesc &dd, float *Es, const
 // four.  Padding rows stay as they are: a product of theirs is stored nowhere.
 // us, tiles of 32 x 32 / this: 16384 samples of 64 vectors of 128 185-199 / 178-190 (147 without the products: they
 // still cost what the next samples' loads do not hide), 8192 of 26 of 128 50.2 / 38.8, of 64 of 112 94 / 89, 16384 of 2
-// 78 / 42, 4096 of 30 of 256 51 / 39, 8192 of 100 of 64 139 / 117, 2048 of 26 of 64 10.2 / 9.0.  Half or a quarter of the
+// 78 / 42, 4096 of 30 of 256 51 / 39, 8192 of 100 of 64 139 / 117, 2048 of 26 of 64 10.2 / 9.0; a few samples of whole
+// tiles of 32 x 32 lose: 64 vectors of 32, 128 samples 4.2 / 4.6, 2048 13.6 / 13.8, 16384 76 / 67; 200 of 16 13.1 / 14.6, 54 /
+// 52, 559 / 526 (and a sample's result may not depend on how many others are in the call).  Half or a quarter of the
 // columns at a time, for more workgroups per compute unit: 187, 227 at the first.
 template <Source SRC, int kFill, int kParts>
 __global__ __launch_bounds__(kThreads, SRC == FROM_PARTIALS ? 6 : 1) void interact_tiles(DevDesc dd, const float *__restrict__ x,
@@ -731,7 +735,7 @@ __global__ __launch_bounds__(kThreads, SRC == FROM_PARTIALS ? 6 : 1) void intera
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = ((tid >> 6) + (blockIdx.x >> 3) + (blockIdx.x >> 8)) & 3;
     float *__restrict__ zb = z + b * ((int64_t)D + (int64_t)T * (T + 1) / 2);
-    fetch_sample<SRC, kFill, kParts>(dd, Es, emb, b, T, D, LD, vec4);
+    fetch_sample<SRC, kFill, kParts, true>(dd, Es, emb, b, T, D, LD, vec4);
     for (int c = tid; c < D; c += kThreads) {
         const float v = x[b * D + c];
         xsh[c] = v;
@@ -791,7 +795,7 @@ __global__ __launch_bounds__(kThreads, SRC == FROM_PARTIALS ? 6 : 1) void intera
     const int padc = LD - D;
     for (int i = tid; i < T * padc; i += kThreads) Es[(i / padc) * LD + D + i % padc] = 0.f;
     for (int i = T * LD + tid; i < TP * LD; i += kThreads) Es[i] = 0.f;
-    fetch_sample<SRC, kFill, kParts>(dd, Es, emb, b, T, D, LD, vec4);
+    fetch_sample<SRC, kFill, kParts, false>(dd, Es, emb, b, T, D, LD, vec4);
     for (int c = tid; c < D; c += kThreads) {
         const float v = x[b * D + c];
         xsh[c] = v;

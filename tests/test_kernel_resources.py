@@ -22,7 +22,10 @@ def kernels():
         at += 8
     assert found
     names = subprocess.run(["c++filt"], input="\n".join(k[".name"] for k in found), text=True, capture_output=True).stdout.splitlines()
-    return {re.sub(r"\(anonymous namespace\)::", "", n).removeprefix("void ").split("(")[0]: k for n, k in zip(names, found)}
+    # "pool_stream<32, 0, ...>" out of "void (anonymous namespace)::pool_stream<32, 0, ...>((anonymous namespace)::DevDesc, ...)"
+    short = [re.match(r"(?:void )?([^<(]*(?:<.*?>(?=\())?)", n.replace("(anonymous namespace)::", ""))[1] for n in names]
+    assert len(set(short)) == len(short)
+    return dict(zip(short, found))
 
 
 def test_pooling_kernels_spill_only_where_it_was_measured(kernels):
@@ -38,3 +41,8 @@ def test_three_stores_keep_the_plain_kernels_wavefronts(kernels):
     """fp32 rows of 16 bytes a lane: at most 80 registers, six wavefronts per SIMD."""
     three = [k for n, k in kernels.items() if re.match(r"pool_stream<(8|16|32|64), 0, 16, 8, false, false, ", n)]
     assert len(three) >= 8 and all(k[".vgpr_count"] <= 80 for k in three)
+
+
+def test_interaction_kernels_do_not_spill(kernels):
+    inter = {n: k for n, k in kernels.items() if n.startswith("interact_")}
+    assert inter and not [n for n, k in inter.items() if k[".private_segment_fixed_size"] or k.get(".vgpr_spill_count")]
