@@ -662,9 +662,8 @@ __device__ __forceinline__ void fill_vectors(float *Es, uint32_t T, uint32_t D, 
 }
 
 // The T vectors of a completed lookup in pieces of four floats: one stream, one address.  us, 16384 samples, interact_tiles
-// with this / with fill_vectors alone: 1 vector of 128 46.9 / 51.7, 4 51.2 / 51.2, 12 55.9 / 53.2, 64 191 / 189 (behind
-// layers 200 / 197); 2 of 64 34.8 / 37.6, 26 52.4 / 49.3; 12 of 20 39.2 / 43.2; 2048 samples of 26 of 64 12.5 / 11.0.  Both
-// in one kernel, chosen by the sample's size, are as this one at every size.
+// with this / with fill_vectors: 1 vector of 128 42.3 / 47.2, 4 44.0 / 46.9, 12 50.2 / 48.3, 64 171 / 171; 2 of 64 30.5 /
+// 33.6, 26 45.0 / 43.3; interact_gram, 12 of 20 34.3 / 38.9, 64 64.4 / 65.3; 2048 samples of 26 of 64 9.7 / 8.6.
 template <int kFill, bool PIECES>
 __device__ __forceinline__ void copy_vectors(float *Es, uint32_t T, uint32_t D, uint32_t LD, const float *vec0)
 {
