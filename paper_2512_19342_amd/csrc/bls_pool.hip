@@ -601,6 +601,7 @@ static bool pool_shape(const bls_ctx *ctx, int *lane_bytes, int *row_lanes)
 
 static int launch_pool(bls_ctx *ctx, const int64_t *ridx, const float *rw, const int64_t *segoff, int64_t nnz, const PoolDst &to, int q0, int qn, hipStream_t st)
 {
+    if (qn == 0) return BLS_OK;                               // a rank that owns no table
     int vb = 0, lanes = 0;
     bool done = false;
     if (pool_shape(ctx, &vb, &lanes))

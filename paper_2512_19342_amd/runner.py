@@ -179,14 +179,14 @@ class DenseModel:
         return ys[-1]
 
     def _mlp(self, x, layers, acts, ys, rows, stream):
-        """Rows ``b0 .. b0 + bn - 1`` of x through the layers, to the same rows of every y.  Rows that are no plain range of
-        whole tensors (they end past the last sample, or are one row of a tensor whose rows are apart) are what slices make
-        of them; the others are addressed, which spares a launch two slices."""
-        lo, hi = index(rows[0]), index(rows[0]) + index(rows[1])
-        if 0 <= lo <= hi <= x.shape[0] and x.is_contiguous() and ys[-1].is_contiguous():
-            rows = (lo, hi - lo)
+        """Rows ``b0 .. b0 + bn - 1`` of x through the layers, to the same rows of every y.  Ranges that leave the batch, and
+        single rows (which may lie in tensors whose rows are apart), are what slices make of them; the others are
+        addressed, which spares a launch two slices."""
+        lo, n = index(rows[0]), index(rows[1])
+        if n > 1 and 0 <= lo and lo + n <= self.B:
+            rows = (lo, n)
         else:
-            x, ys, rows = x[lo:hi], [y[lo:hi] for y in ys], None
+            x, ys, rows = x[lo:lo + n], [y[lo:lo + n] for y in ys], None
         self.ctx.bls_mlp(x, [(W, b, act, y) for (W, b), act, y in zip(layers, acts, ys)], rows, stream)
 
     def compute_ctr(self, x: torch.Tensor, emb, p_out: Optional[torch.Tensor] = None, stream=None,

@@ -37,6 +37,7 @@ int __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *sh, void **st) { *g = gr
 int hipLaunchKernel(const void *f, dim3 g, dim3 b, void **a, size_t sh, void *st)
 {
     if (launches_left == 0) return last = 1;
+    if (g.x == 0 || g.y == 0 || g.z == 0) return last = 9;   /* as the runtime: invalid configuration */
     if (launches_left > 0) --launches_left;
     grid_y = g.y;
     note('L', (size_t)st);
@@ -186,4 +187,19 @@ for T, y in ((1, 1), (2, 2), (5, 5), (6, 1), (8, 1), (9, 9), (11, 11), (12, 1), 
     assert issue(h, 0)[0] == 0 and grid_y.value == y, (T, grid_y.value)
     assert L.bls_set_pool_tuning(h, 0, 0, 1, -1) == 0 and unpack(h, 0, 0)[0] == 0
     assert issue(h, 0)[0] == 0 and grid_y.value == 1, T
+""")
+
+
+def test_a_rank_without_tables_takes_part(tmp_path):
+    """One table, owned by rank 0: rank 1 has nothing to pool, and its put is its arrival alone."""
+    run(tmp_path, r"""
+h = ctx(1, T=1)
+for it in range(3):
+    for rank in range(2):
+        stub.forget()
+        assert L.bls_rank_put(h, rank, at(4), None, at(5), C.c_int64(100), C.c_int64(it), vp(rank + 1)) == 0, (it, rank)
+        waits_first = "" if it == 0 else f"W{rank + 1}"       # for the other requester's copy-out
+        assert C.string_at(C.addressof(noted)).decode() == waits_first + (f"L{rank + 1}" if rank == 0 else "") + f"R{rank + 1}"
+    for rank in range(2):
+        assert L.bls_rank_complete(h, rank, C.c_int64(it), None, at(8), vp(rank + 1)) == 0
 """)
