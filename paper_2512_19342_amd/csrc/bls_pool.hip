@@ -222,7 +222,7 @@ __device__ __forceinline__ void stream_group(const DevDesc &dd, int q, uint32_t 
             if (cur_end == pos) {
                 if (col_ok) {
                     if constexpr (STORES != kOneStore) {
-                        // nobody on the path reads Y and S again, R is read by the completion
+                        // R is read by the completion, S only where there is no R (by the exchange), Y by nobody on the path
                         acc.template store<STORES >= kThreeHintedY>(Y + (int64_t)(y_at + cur) * dd.D + li * A::NV);
                         acc.template store<STORES == kThreeHinted>(S + (int64_t)(s_at + cur) * dd.D + li * A::NV);
                         if (R) acc.store(R + (int64_t)(r_at + cur) * dd.D + li * A::NV);
@@ -338,7 +338,7 @@ constexpr bool six_wavefronts(int G, int dt, int vb)
 // STORES not kOneStore: every vector goes to Y (pooled order), S (send order) and R (a ring slot) from the registers it was summed in,
 // in place of pack and exchange, which read it again: five passes over the vectors up to the slot become three.  Vector
 // numbers of 32 bits and, where six_wavefronts, the launch bound keep the six wavefronts per SIMD of the plain kernel.
-// Y and S carry the streaming hint, the slot does not (the completion reads it).  A staged iteration, us, the separate
+// Y and S carry the streaming hint unless stores_that_pay says otherwise, the slot does not (the completion reads it).  A staged iteration, us, the separate
 // kernels / plain stores / this / the slot hinted as well: 16384 samples of 64 vectors of 128, Zipf 1568 / 1549 / 1495 /
 // 1488, bags of 1 to 4 743 / 656 / 640 / 522; row-wise 8192 of 26 over eight owners 1079 / 955 / 944 / 950, bags of one
 // 924 / 720 / 676 / 695; table-wise 168 MB of short bags 203 / - / 153 / 183; 2048 of 26 of 64 46.5 / 35.7 / 34.8 / 35.5.
