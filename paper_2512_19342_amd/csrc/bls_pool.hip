@@ -13,9 +13,7 @@
 // several consecutive segments - they are contiguous in ridx - and stores and clears its
 // accumulator whenever the stream crosses a segment boundary.  That amortises the
 // dependent loads at the start (segment offsets, then row numbers, then rows) and evens out
-// the lengths of the streams that share a wavefront.  A block's row numbers are asked for a
-// block ahead but tested against the shard's rows at once, so that they are waited for there:
-// one exposed round trip per G rows.
+// the lengths of the streams that share a wavefront.
 #include <algorithm>
 #include <type_traits>
 
@@ -157,8 +155,8 @@ __device__ __forceinline__ uint32_t hot_hash(uint32_t row) { return (row * 26544
 
 // One lane group's work: G >= 4 lanes stream up to nb_max (< G) consecutive segments of (q, s)
 // block number gx / chunks_per_s, chunk gx % chunks_per_s.  HOT: rows found in `hot` are read from
-// LDS instead of global memory.
-template <int G, int DT, int VB, int U, bool WIDE, bool WGT, bool HOT, int STORES>
+// LDS instead of global memory.  RING: see below.
+template <int G, int DT, int VB, int U, bool WIDE, bool WGT, bool HOT, bool RING, int STORES>
 __device__ __forceinline__ void stream_group(const DevDesc &dd, int q, uint32_t gx, const int64_t *__restrict__ ridx,
                                              const float *__restrict__ rw, const int64_t *__restrict__ segoff, int64_t nnz,
                                              float *__restrict__ Y, float *__restrict__ S, float *__restrict__ R, int to_slot,
@@ -237,6 +235,65 @@ __device__ __forceinline__ void stream_group(const DevDesc &dd, int q, uint32_t 
         } while (__any(cur_end == pos));
     };
     flush(0);
+
+    // RING: U rows in flight all the time.  A row is added as soon as it has come, whatever is still on its way behind it,
+    // and the next row of the stream is asked for into its registers; row numbers are asked for two blocks ahead and
+    // tested when their block is next.  Rows are read through the shard's descriptor, so that a lookup without a row
+    // (the stream's end, a bad index) needs no branch: it reads zeros, and adding +0 changes no sum, which is never -0.
+    // Without branches between the loads the compiler knows how many are younger than the one it waits for.  What the
+    // loop below costs beside this one: all U rows are waited for, with nothing in flight while they are added, a
+    // block's row numbers are waited for before its rows, and every row has its execution mask.
+    if constexpr (RING) {
+        static_assert(!WIDE && !HOT);
+        const __amdgpu_buffer_rsrc_t shard = shard_buffer(dd.q_base[q], (uint32_t)shard_rows * row_stride);
+        const uint32_t col = col_ok ? (uint32_t)li * VB : 0u;
+        auto ask = [&](int c0) -> int64_t { return c0 + li < total ? ridx[beg + c0 + li] : -1; };
+        auto ask_weight = [&](int c0) -> float {
+            if constexpr (WGT) return c0 + li < total ? rw[beg + c0 + li] : 0.f;
+            else return 0.f;
+        };
+        // this lane's row of block c0 as an offset into the shard; the weight of a lookup without a row is 0 (it may be no number)
+        auto place = [&](int c0, int64_t r, float &w) -> uint32_t {
+            const bool ok = (uint64_t)r < (uint64_t)shard_rows;
+            if (!ok && c0 + li < total) flag_error(dd);
+            if (!ok) w = 0.f;
+            return ok ? (uint32_t)r * row_stride : kPastEnd;
+        };
+        int64_t raw = ask(0);
+        float wraw = ask_weight(0);
+        uint32_t mine = place(0, raw, wraw);
+        float wmine = wraw;
+        raw = ask(G);
+        wraw = ask_weight(G);
+        typename A::Raw v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = A::load_buffer(shard, group_broadcast32<G>(mine, gbase * 4, u) + col, tail);
+        for (int at = 0; __any(at < total); at += U) {
+            float wt[WGT ? U : 1];
+            if constexpr (WGT) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) wt[u] = __uint_as_float(group_broadcast32<G>(__float_as_uint(wmine), gbase * 4, (at & (G - 1)) + u));
+            }
+            const int next = at + U;
+            if ((next & (G - 1)) == 0) {
+                mine = place(next, raw, wraw);
+                wmine = wraw;
+                raw = ask(next + G);
+                wraw = ask_weight(next + G);
+            }
+            uint32_t off[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) off[u] = group_broadcast32<G>(mine, gbase * 4, (next & (G - 1)) + u);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if constexpr (WGT) acc.add_weighted(v[u], wt[u]);
+                else acc.add(v[u]);
+                v[u] = A::load_buffer(shard, off[u] + col, tail);
+                flush(at + u + 1);                           // positions past the stream's end match nothing
+            }
+        }
+        return;
+    }
 
     // this lane's row of block c0 as a position in the shard (all ones: none or out of range)
     using pos_t = typename std::conditional<WIDE, uint64_t, uint32_t>::type;
@@ -332,6 +389,7 @@ constexpr bool six_wavefronts(int G, int dt, int vb)
 }
 
 // grid: x over groups (s-major, then chunks of nb_max samples), y = q.
+// RING: rows one by one through the shard's descriptor, for shards below 4 GB (ring_pays says where).
 // WIDE: row positions as 64-bit byte offsets; otherwise 32-bit, in units of VB bytes (shards
 // below 2^32 * VB bytes), which halves the lane exchanges and the registers they occupy.
 // WGT: per-sample weights rw[] (in ridx order) multiply every row before it is added.
@@ -343,8 +401,8 @@ constexpr bool six_wavefronts(int G, int dt, int vb)
 // 1488, bags of 1 to 4 743 / 656 / 640 / 522; row-wise 8192 of 26 over eight owners 1079 / 955 / 944 / 950, bags of one
 // 924 / 720 / 676 / 695; table-wise 168 MB of short bags 203 / - / 153 / 183; 2048 of 26 of 64 46.5 / 35.7 / 34.8 / 35.5.
 // Hinting the slot gains only for table-wise ones of 500 MB and loses up to a fifth elsewhere.
-template <int G, int DT, int VB, int U, bool WIDE, bool WGT, int STORES>
-__global__ __launch_bounds__(kThreads, STORES != kOneStore && !WIDE && six_wavefronts(G, DT, VB) ? 6 : 1) void pool_stream(DevDesc dd, const int64_t *__restrict__ ridx,
+template <int G, int DT, int VB, int U, bool WIDE, bool WGT, bool RING, int STORES>
+__global__ __launch_bounds__(kThreads, STORES != kOneStore && !WIDE && !RING && six_wavefronts(G, DT, VB) ? 6 : 1) void pool_stream(DevDesc dd, const int64_t *__restrict__ ridx,
                                                         const float *__restrict__ rw,
                                                         const int64_t *__restrict__ segoff, int64_t nnz,
                                                         float *__restrict__ Y, float *__restrict__ S, float *__restrict__ R,
@@ -364,7 +422,7 @@ __global__ __launch_bounds__(kThreads, STORES != kOneStore && !WIDE && six_wavef
         q = qn == dd.Q ? dd.q_deal[pos] : q0 + pos;           // all shards: in the balanced order
     }
     const HotRows none{nullptr, nullptr, nullptr, 0};
-    stream_group<G, DT, VB, U, WIDE, WGT, false, STORES>(dd, q, bx * (kThreads / G) + threadIdx.x / G, ridx, rw, segoff, nnz, Y, S, R,
+    stream_group<G, DT, VB, U, WIDE, WGT, false, RING, STORES>(dd, q, bx * (kThreads / G) + threadIdx.x / G, ridx, rw, segoff, nnz, Y, S, R,
                                                       to_slot, nb_max, chunks_per_s, none);
 }
 
@@ -417,7 +475,7 @@ __global__ __launch_bounds__(kHotThreads) void pool_stream_hot(DevDesc dd, const
         __syncthreads();
         const HotRows hot{data, keys, vals, n_hot};
         for (uint32_t blk = j; blk < blocks; blk += per_xcd)
-            stream_group<G, DT, VB, U, false, WGT, true, kOneStore>(dd, q, blk * per_wg + threadIdx.x / G, ridx, rw, segoff, nnz, Y,
+            stream_group<G, DT, VB, U, false, WGT, true, false, kOneStore>(dd, q, blk * per_wg + threadIdx.x / G, ridx, rw, segoff, nnz, Y,
                                                                 nullptr, nullptr, to_slot, nb_max, chunks_per_s, hot);
     }
 }
@@ -467,6 +525,26 @@ __global__ __launch_bounds__(kThreads) void pool_rows_generic(DevDesc dd, const 
     }
 }
 
+// Where rows are read in a ring (RING above): where the loop that waits for whole batches leaves time between them, which is
+// wherever rows, not stored vectors, are most of the traffic.  A store counts among the accesses a later row waits behind,
+// so that with a store every few rows a ring is no deeper than a batch and waits for its stores sooner.  us a pass with
+// vectors of 128, batch / ring, by rows a segment and MB of vectors.  fp32: 32 rows, 134 MB 483 / 458, 32 of 64 floats 296 / 266, of
+// 32 195 / 169, 8 rows, 250 MB 352 / 346, 2 of 64 floats 231 / 238, 1 row, 800 MB 399 / 408.  Half precision: 32 rows, 134 MB
+// 355 / 321, 8, 800 MB 944 / 937, 4, 800 MB 541 / 545, staged 1024 / 1040.  8-bit: 32 rows, 134 MB 377 / 341, 250 MB
+// 585 / 574, 8, 250 MB 310 / 312, 1 row, 800 MB 648 / 672.  What fits the memory-side cache gains from one row on: 60 MB, fp32,
+// 1 to 4 rows 74 / 73, 8 rows 114 / 110, 8-bit 2.5 rows 74 / 73.  Weights cost the batch a wavefront per SIMD (87
+// registers; 80 here): fp32 1 row, 250 MB 202 / 196, 4 rows 220 / 209, 800 MB 611 / 587; half precision 4 rows 198 / 195.
+static bool ring_pays(const bls_ctx *ctx, bool weighted, int64_t nnz, int qn)
+{
+    const int64_t rows = is_rowq(ctx->dtype) ? 12 : !weighted ? 8 : ctx->dtype == BLS_FP16 ? 4 : 2;
+    if (nnz >= rows * ctx->nseg) return true;
+    return nnz >= ctx->nseg && (int64_t)qn * ctx->B * ctx->D * 4 <= (int64_t)96 << 20;
+}
+// Four workgroups per compute unit keep the memory busy in a ring, and more of them only share the caches: the kernels, which would
+// run with five to seven, ask for LDS that they do not use.  us, as many as fit / four / three: fp32 rows of 128, 134 MB of vectors 463 / 458 / 456,
+// of 64 275 / 265 / 267, of 32 173 / 169 / 173, with three stores 508 / 504 / 504, half precision 322 / 321 / 325, 8-bit 343 / 341 / 346.
+static constexpr size_t kRingLds = 36 * 1024;
+
 template <int G, int DT, int VB, int U>
 void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const int64_t *segoff, int64_t nnz, const PoolDst &to, int q0, int qn, hipStream_t st)
 {
@@ -502,7 +580,12 @@ void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const
         // 32-bit row positions unless some shard is too large for them
         const int64_t row_stride = stride_bytes(DT, ctx->D);
         bool wide = ctx->tune_wide == 1;
-        for (int q = q0; q < q0 + qn; ++q) wide = wide || ctx->q_rows[q] * (row_stride / VB) >= 0xffffffffLL;
+        bool ring = ring_pays(ctx, rw != nullptr, nnz, qn);
+        for (int q = q0; q < q0 + qn; ++q) {
+            wide = wide || ctx->q_rows[q] * (row_stride / VB) >= 0xffffffffLL;
+            ring = ring && ctx->q_rows[q] < (int64_t)kPastEnd / row_stride;
+        }
+        ring = ring && !wide;
         // popular rows named for some shard of this launch: the staying workgroups that keep them in LDS,
         // if every row position leaves the top bit free for the "in LDS" mark
         bool hot = VB == 16 && !wide && ctx->tune_hot != 0 && ctx->compute_units >= 8;
@@ -527,24 +610,25 @@ void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const
             }
         }
         auto launch = [&](auto kernel) {
-            kernel<<<grid, kThreads, 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, to.Y, to.S, to.R, to.slot, nb, chunks, deal, q0, qn);
+            kernel<<<grid, kThreads, ring ? kRingLds : 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, to.Y, to.S, to.R, to.slot, nb, chunks, deal, q0, qn);
         };
-        auto three = [&](auto stores) {
-            if (wide) launch(pool_stream<G, DT, VB, UU, true, false, stores()>);
-            else launch(pool_stream<G, DT, VB, UU, false, false, stores()>);
+        auto pick = [&](auto weighted, auto stores) {
+            if constexpr (VB == 16) {
+                if (ring) return launch(pool_stream<G, DT, VB, UU, false, weighted(), true, stores()>);
+            }
+            if (wide) launch(pool_stream<G, DT, VB, UU, true, weighted(), false, stores()>);
+            else launch(pool_stream<G, DT, VB, UU, false, weighted(), false, stores()>);
         };
         if (rw) {
-            if (wide) launch(pool_stream<G, DT, VB, UU, true, true, kOneStore>);
-            else launch(pool_stream<G, DT, VB, UU, false, true, kOneStore>);
+            pick(std::true_type(), std::integral_constant<int, kOneStore>());
         } else if (to.stores == kOneStore) {
-            if (wide) launch(pool_stream<G, DT, VB, UU, true, false, kOneStore>);
-            else launch(pool_stream<G, DT, VB, UU, false, false, kOneStore>);
+            pick(std::false_type(), std::integral_constant<int, kOneStore>());
         } else if (to.stores == kThreePlain) {
-            if constexpr (Acc<DT, VB>::NV == 16 || (Acc<DT, VB>::NV == 8 && G >= 16)) three(std::integral_constant<int, kThreePlain>());
+            if constexpr (Acc<DT, VB>::NV == 16 || (Acc<DT, VB>::NV == 8 && G >= 16)) pick(std::false_type(), std::integral_constant<int, kThreePlain>());
         } else if (to.stores == kThreeHintedY) {
-            if constexpr (Acc<DT, VB>::NV == 8 || (Acc<DT, VB>::NV == 4 && G <= 16)) three(std::integral_constant<int, kThreeHintedY>());
+            if constexpr (Acc<DT, VB>::NV == 8 || (Acc<DT, VB>::NV == 4 && G <= 16)) pick(std::false_type(), std::integral_constant<int, kThreeHintedY>());
         } else if constexpr (Acc<DT, VB>::NV <= 8) {
-            three(std::integral_constant<int, kThreeHinted>());
+            pick(std::false_type(), std::integral_constant<int, kThreeHinted>());
         }
     } else {
         dim3 grid((unsigned)((ctx->B + per_block - 1) / per_block), qn);

@@ -31,6 +31,20 @@ __host__ __device__ __forceinline__ int64_t stride_bytes(int dtype, int D)
 // fp32 values in vb bytes of a row
 constexpr int lane_floats(int dt, int vb) { return is_rowq(dt) ? vb : dt == BLS_FP16 ? vb / 2 : vb / 4; }
 
+// A shard as a buffer descriptor: offsets of 32 bits, reads past its end give zeros without an access.  kPastEnd is
+// what a lookup without a row carries as its offset; a lane's place in a row of at most 1 KB and its scale
+// and bias stay below 2^32 behind it, so a shard has to end before it.
+constexpr uint32_t kPastEnd = 0xfffff000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t shard_buffer(const void *start, uint32_t bytes)
+{
+    // uniform over the workgroup, which the compiler has to be told, or it loops over the lanes' descriptors
+    const uint64_t at = (uint64_t)start;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc((void *)((uint64_t)hi << 32 | lo), 0, __builtin_amdgcn_readfirstlane((int)bytes),
+                                             0x00027000);   // 32-bit data, no stride, no swizzle
+}
+
 // Per-lane accumulator: VB bytes of table storage per lane and row, NV values in them.
 // Row-quantised rows also bring their scale and bias (8 bytes behind the codes, the same
 // address for every lane of the group), and a value is code * scale + bias with the product
@@ -72,6 +86,20 @@ template <int DT, int VB> struct Acc {
         } else {
             r.w[0] = *(const __attribute__((address_space(1))) uint32_t *)p;
         }
+        return r;
+    }
+    // the same through a buffer descriptor of the shard: at = this lane's bytes as an offset from the shard's start.
+    // Past the shard's end nothing is fetched and the row reads as zeros.
+    static __device__ __forceinline__ Raw load_buffer(__amdgpu_buffer_rsrc_t shard, uint32_t at, uint32_t tail)
+    {
+        Raw r;
+        if constexpr (NX == 2) {
+            const u32x2 sb = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(shard, at + tail, 0, 0));
+            r.w[NW] = sb.x; r.w[NW + 1] = sb.y;
+        }
+        static_assert(NW == 4);
+        const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(shard, at, 0, 0));
+        r.w[0] = v.x; r.w[1] = v.y; r.w[2] = v.z; r.w[3] = v.w;
         return r;
     }
     // the same from LDS (a row copied there whole, scale and bias included)

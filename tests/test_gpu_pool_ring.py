@@ -1,0 +1,94 @@
+"""The pooling kernels that keep a ring of rows in flight: the oracle's bits, and those of the kernels that take rows in
+batches (64-bit positions), where a stream ends inside a ring or a block, in the shard's first and last rows, and for lookups
+that have no row."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from tests.test_gpu_parity import bits, case_of
+
+pytestmark = pytest.mark.gpu
+
+# lanes of a row: 4, 8, 16, 32, 64 (64: whole-wavefront groups), and rows whose last lanes idle
+SHAPES = [("fp32", D) for D in (16, 32, 64, 100, 128, 256)] + [("fp16", D) for D in (32, 64, 128, 200, 512)] + [
+    (dt, D) for dt in ("u8rq", "f8rq") for D in (64, 112, 128, 512)]
+BAGS = [(1, 1), (0, 3), (3, 9), (7, 17), (30, 70)]
+
+
+def make(dt, D, part, bag):
+    from paper_2512_19342_amd.runner import Pipeline
+    w = synth.custom("ring", P=3, T=5, D=D, B=37, k=1, rows=[1, 2, 700, 33, 5], table_owner=[0, 1, 2, 0, 1] if part == 0 else None,
+                     part_kind=part, bag=("uniform", *bag), table_dtype=dt, values="gauss", seed=D + bag[1], index_dist=("zipf", 1.1))
+    tabs = [synth.make_table(w, t) for t in range(w.T)]       # row-wise, tables of one and two rows leave owners with none
+    pipes = [Pipeline(w, [t.cuda() for t in tabs], 1 << 16) for _ in range(2)]
+    pipes[1].ctx.bls_set_pool_tuning(wide_positions=1)
+    return w, [t.numpy() for t in tabs], pipes
+
+
+@pytest.mark.parametrize("bag", BAGS, ids=str)
+@pytest.mark.parametrize("part", [0, 1], ids=["tables", "rows"])
+@pytest.mark.parametrize("dt,D", SHAPES, ids=str)
+def test_ring_adds_the_same_rows_in_the_same_order(dt, D, part, bag):
+    w, tabs, pipes = make(dt, D, part, bag)
+    ix, off = synth.make_batch(w, 0)
+    nnz = int(off[-1])
+    wts = torch.from_numpy(np.random.default_rng(nnz).uniform(-2.0, 2.0, size=nnz).astype(np.float32))
+    for weights in (None, wts):
+        ref = oracle.pipeline(case_of(w), tabs, ix.numpy(), off.numpy(), weights=None if weights is None else weights.numpy())
+        for pipe in pipes:
+            pipe.slots.fill_(float("nan"))
+            if weights is None:
+                j, slot = pipe.issue_fused(ix.cuda(), off.cuda(), nnz)
+            else:
+                j, slot = pipe.issue_weighted(ix.cuda(), off.cuda(), weights.cuda(), nnz, fused=True)
+            assert (bits(pipe.slot_view(slot).cpu().numpy()) == bits(ref["R"].reshape(-1))).all()
+            pipe.complete(j, pipe.new_out())
+            pipe.ctx.bls_check()
+
+
+@pytest.mark.parametrize("part", [0, 1], ids=["tables", "rows"])
+@pytest.mark.parametrize("dt,D", [("fp32", 64), ("fp16", 128), ("u8rq", 64), ("f8rq", 128)], ids=str)
+def test_lookups_without_a_row_add_nothing(dt, D, part):
+    """Bad indices among good ones, their weights no numbers; infinities and NaN in the rows; sums that are exactly zero."""
+    import paper_2512_19342_amd as B
+    w, tabs, pipes = make(dt, D, part, (7, 17))
+    if dt in ("fp32", "fp16"):
+        for t in tabs:
+            t[::3, ::5] = np.inf
+            t[1::4, 1::7] = np.nan
+            t[:, 2::5] = -0.0
+        pipes = []
+        for wide in (-1, 1):
+            from paper_2512_19342_amd.runner import Pipeline
+            pipes.append(Pipeline(w, [torch.from_numpy(t).cuda() for t in tabs], 1 << 16))
+            pipes[-1].ctx.bls_set_pool_tuning(wide_positions=wide)
+    ix, off = synth.make_batch(w, 1)
+    nnz = int(off[-1])
+    wts = torch.linspace(-1.0, 2.0, nnz)
+    table = torch.repeat_interleave(torch.arange(w.T).repeat_interleave(w.B), off[1:] - off[:-1])
+    bad = torch.arange(nnz) % 5 == 2
+    rows = torch.tensor(w.rows)[table]
+    ix = torch.where(bad, torch.where(torch.arange(nnz) % 2 == 0, rows, torch.full_like(rows, -1)), ix)
+    wts[bad] = torch.tensor([float("nan"), float("inf")])[torch.arange(int(bad.sum())) % 2]
+    got = []
+    for pipe in pipes:
+        out = pipe.new_out()
+        j, slot = pipe.issue_weighted(ix.cuda(), off.cuda(), wts.cuda(), nnz, fused=True)
+        pipe.complete(j, out)
+        with pytest.raises(B.BlsError):
+            pipe.ctx.bls_check()
+        plain = pipe.new_out()
+        j, _ = pipe.issue_fused(ix.cuda(), off.cuda(), nnz)
+        pipe.complete(j, plain)
+        with pytest.raises(B.BlsError):
+            pipe.ctx.bls_check()
+        got.append((out.cpu().numpy(), plain.cpu().numpy()))
+    good = ~bad
+    goff = torch.cat([torch.zeros(1, dtype=torch.int64), torch.cumsum(good, 0)])[off]
+    want = [oracle.pipeline(case_of(w), tabs, ix[good].numpy(), goff.numpy(), weights=x)["Out"] for x in (wts[good].numpy(), None)]
+    for g in got:
+        for a, b in zip(g, want):
+            assert (np.isnan(a) == np.isnan(b)).all()
+            assert (bits(a)[~np.isnan(b)] == bits(b)[~np.isnan(b)]).all()
