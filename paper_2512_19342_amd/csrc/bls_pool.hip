@@ -567,13 +567,14 @@ void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const
         const uint32_t chunks = (uint32_t)((n_max + nb - 1) / nb);
         const int64_t groups = (int64_t)chunks * ctx->P;
         const uint32_t wgx = (uint32_t)((groups + per_block - 1) / per_block);
-        // A shard's workgroups on one XCD leave the others idle where the shards are few, and three stores are then as many
-        // on a part of the XCDs' path to memory, where pack and exchange use all: such launches are not dealt.  us a staged
-        // iteration, vectors of 64, bags of 1 to 4, the calls / one launch dealt / not: fp32 1 table, 30 MB 99 / 112 / 46, 100
-        // MB 292 / 331 / 140, 3 201 / 197 / 146, 5 184 / 166 / 148, 9 186 / 172 / 151; 8-bit, 8 MB 1 54 / 82 / 34, 3 42 / 46 / 34;
-        // half-precision, 100 MB 2 210 / 247 / 137, 9 180 / 180 / 149.  With most XCDs at work the deal's caches count for more
-        // with many rows a segment (7 tables, 8 MB, bags of 1 to 30 44 / 37 / 40), the even spread with few (30 MB 65 / 50 / 49).
-        const bool idle = to.stores != kOneStore && 10 * qn < 7 * 8 * ((qn + 7) / 8);
+        // A shard's workgroups on one XCD leave the others idle where the shards are few: such launches are not dealt.  us, dealt /
+        // not, vectors of 128, one store, fp32, 60 MB of bags of one: 1 shard 131 / 58, 2 88 / 60, 3 72 / 59, 5 65 / 60, 9 68 / 60, 10 67 / 61;
+        // of 20 to 60 rows 1 shard 1028 / 228, 3 435 / 238, 5 312 / 248, 9 341 / 260, 10 322 / 259; 8 MB of them 1 130 / 43, 5 54 / 47,
+        // 10 53 / 50; 8-bit, 60 MB 1 693 / 182, 9 262 / 199; row-wise, 4 owners 343 / 252.  Three stores and the calls they stand for (four launches, their pool
+        // dealt), vectors of 64, bags of 1 to 4, calls / dealt / not: 1 table, 30 MB 99 / 112 / 46, 5, 100 MB 184 / 166 / 148, 8-bit, 8 MB 1
+        // 54 / 82 / 34.  With most XCDs at work the deal's caches count for more with many rows a segment (three stores,
+        // 7 tables, 8 MB, bags of 1 to 30 37 / 40), the even spread with few (30 MB 50 / 49).
+        const bool idle = 10 * qn < 7 * 8 * ((qn + 7) / 8);
         const bool xcd = ctx->tune_xcd == 1 || (ctx->tune_xcd != 0 && !idle);
         const dim3 grid = xcd ? dim3((unsigned)((uint64_t)((qn + 7) / 8) * 8u * wgx)) : dim3(wgx, qn);
         const uint32_t deal = xcd ? wgx : 0u;
