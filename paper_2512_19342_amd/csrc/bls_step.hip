@@ -11,6 +11,7 @@
 // closed-form address.  Bit for bit what bls_plan, bls_embbag_pool, bls_pack, bls_alltoallv_local
 // and bls_unpack leave behind.
 #include <algorithm>
+#include <type_traits>
 
 #include "bls_internal.h"
 #include "bls_rows.h"
@@ -20,8 +21,12 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kMaxRuns = 2048;                 // runs (q, s) whose starts one workgroup scans in LDS
-constexpr int kPerThread = kMaxRuns / kThreads;
-constexpr int kU = 8;                          // independent row loads per lane before the first add
+// Rows of a group in flight, and wavefronts per SIMD the kernel is held to (1: as it comes): what is best with long bags among those that
+// cost short ones nothing.  us, 26 tables, as it was / eight rows / this: half precision of 64, 2048 bags of one 23.4 / 24.0 / 23.1, 512 of 1
+// to 100 32.2 / 24.6 / 27.6; fp32 of 128, 4096 bags of up to 4, without the bound 92 / 96 / 91; 8-bit of 128 86 / 88 / 85;
+// 8-bit, 4 tables of 64, 4096 bags of 1 to 100, with a bound of five 51 / 34 / 32.
+template <int G, int DT> constexpr int kRows = is_rowq(DT) || (DT == BLS_FP16 && G == 8) ? 4 : 8;
+template <int G, int DT> constexpr int kWavesHeld = DT == BLS_FP32 ? 6 : DT == BLS_FP16 ? (G < 16 ? 5 : 6) : G == 8 ? 5 : 1;
 
 __device__ __forceinline__ void flag_error(const DevDesc &dd) { atomicOr(dd.err, 1); }
 
@@ -43,8 +48,13 @@ __device__ __forceinline__ int run_entry(const DevDesc &dd, int q, int s)
 }
 
 // grid: x over (requester s, chunk of its mini-batch), y = q.  G lanes per bag, 16 bytes of a row per lane.
-template <int G, int DT>
-__global__ __launch_bounds__(kThreads) void step_tablewise(DevDesc dd, const int64_t *__restrict__ idx,
+// WIDE: some shard is too large for 32-bit offsets; rows are then taken in batches through 64-bit addresses.
+// What bounds it is the chain from offsets to lookups to rows, and how many rows a group has in flight along a bag: the chain's
+// start runs beside the count of the runs, and rows are read in a ring.  us a step, counted first and rows in
+// batches of eight / this: 26 tables of 64, 512 bags of 1 to 100 41 / 37 (fp32), 32 / 28 (half precision), 52 / 38 (8-bit);
+// 64 tables of 128, 2048 bags of 1 to 40 280 / 276, 211 / 204, 214 / 211; eight tables of 16, 128 bags of one 9.3 / 9.1.
+template <int G, int DT, bool WIDE>
+__global__ __launch_bounds__(kThreads, (WIDE ? 1 : kWavesHeld<G, DT>)) void step_tablewise(DevDesc dd, const int64_t *__restrict__ idx,
                                                            const int64_t *__restrict__ off, int64_t nnz,
                                                            int64_t *__restrict__ sendcounts, int64_t *__restrict__ sdispls,
                                                            int64_t *__restrict__ recvcounts, int64_t *__restrict__ rdispls,
@@ -54,15 +64,61 @@ __global__ __launch_bounds__(kThreads) void step_tablewise(DevDesc dd, const int
                                                            float *__restrict__ out, uint32_t chunks)
 {
     using A = Acc<DT, 16>;
-    __shared__ int64_t rb[kMaxRuns + 1];       // run lengths in owner order, then their exclusive scan
+    __shared__ int64_t rb[kMaxRuns];           // run lengths in owner order, then their exclusive scan
     __shared__ int64_t part[kWaves];
     __shared__ int64_t red[kWaves];
     const int P = dd.P, nruns = dd.Q * P;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 
-    // 1. run lengths from the offsets at the run edges, scanned in owner order
-    for (int i = threadIdx.x; i < kMaxRuns + 1; i += kThreads) rb[i] = 0;
-    __syncthreads();
+    // 1. this workgroup's bags: samples of requester s, table q.  Their rows need none of what the workgroups agree
+    // on below, so the first of them are asked for here and come while the runs are counted.
+    const int q = blockIdx.y;
+    const int s = (int)(blockIdx.x / chunks);
+    const uint32_t chunk = blockIdx.x - (uint32_t)s * chunks;
+    const int t = dd.q_t[q], d = dd.q_d[q];
+    const int64_t f = dd.first[s], n = dd.first[s + 1] - f;
+    const int64_t g0 = (int64_t)t * dd.B + f;
+    const int li = threadIdx.x & (G - 1);
+    const int gbase = lane & ~(G - 1);
+    const int64_t b_loc = (int64_t)chunk * (kThreads / G) + threadIdx.x / G;
+    const bool live = b_loc < n;
+    const uint32_t row_bytes = (uint32_t)payload_bytes(DT, dd.D), row_stride = (uint32_t)stride_bytes(DT, dd.D);
+    const bool col_ok = (uint32_t)li * 16 < row_bytes;        // lanes past the row's end idle
+    const int tail = (int)row_bytes - (col_ok ? li * 16 : 0);
+    const int64_t rows = dd.q_rows[q];
+    int64_t lo_run = off[g0], hi_run = off[g0 + n];
+    int64_t beg = 0, len = 0, at_run = 0;
+    if (live) {
+        beg = off[g0 + b_loc];
+        len = off[g0 + b_loc + 1] - beg;
+    }
+    if (lo_run < 0 || hi_run > nnz || hi_run < lo_run) lo_run = hi_run = 0;   // flagged below; the run counts as empty
+    if (live) {
+        const int64_t run_len = hi_run - lo_run;
+        at_run = beg - lo_run;
+        if (at_run < 0 || at_run > run_len || len < 0 || at_run + len > run_len) {   // a bag outside its run: treated as empty
+            if (li == 0) flag_error(dd);
+            at_run = at_run < 0 ? 0 : (at_run > run_len ? run_len : at_run);
+            len = 0;
+        }
+    }
+    constexpr int kU = kRows<G, DT>, U = kU < G ? kU : G;     // rows in flight
+    const __amdgpu_buffer_rsrc_t shard = shard_buffer(dd.q_base[q], WIDE ? 0u : (uint32_t)rows * row_stride);
+    const char *__restrict__ base = (const char *)dd.q_base[q] + (col_ok ? (uint32_t)li * 16 : 0u);
+    const uint32_t col = col_ok ? (uint32_t)li * 16 : 0u;
+    auto ask = [&](int64_t c0) -> int64_t { return c0 + li < len ? idx[beg + c0 + li] : -1; };
+    auto offset = [&](int64_t r) -> uint32_t { return (uint64_t)r < (uint64_t)rows ? (uint32_t)r * row_stride : kPastEnd; };
+    int64_t here = ask(0), ahead = ask(G);                    // this lane's lookup of a block, and of the next
+    typename A::Raw v[U];
+    if constexpr (!WIDE) {
+        const uint32_t mine = offset(here);
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = A::load_buffer(shard, (uint32_t)__shfl((int)mine, gbase + u, 64) + col, tail);
+    }
+
+    // 2. run lengths from the offsets at the run edges, scanned in owner order
+    const int per = (nruns + kThreads - 1) / kThreads;        // runs of a thread in the scan
+    for (int i = nruns + threadIdx.x; i < per * kThreads; i += kThreads) rb[i] = 0;
     bool bad_edges = false;
     for (int i = threadIdx.x; i < nruns; i += kThreads) {
         const int q = i / P, s = i - q * P;
@@ -74,29 +130,35 @@ __global__ __launch_bounds__(kThreads) void step_tablewise(DevDesc dd, const int
     }
     if (bad_edges) flag_error(dd);
     __syncthreads();
+    int64_t placed;                                           // the total
     {
-        int64_t x[kPerThread], run = 0;
-#pragma unroll
-        for (int k = 0; k < kPerThread; ++k) { x[k] = run; run += rb[threadIdx.x * kPerThread + k]; }
+        int64_t run = 0;
+        for (int k = 0; k < per; ++k) run += rb[threadIdx.x * per + k];
         const int64_t inc = wave_inclusive_scan(run, lane);
         if (lane == 63) part[wv] = inc;
         __syncthreads();
         int64_t before = inc - run;
-        for (int w = 0; w < wv; ++w) before += part[w];
-#pragma unroll
-        for (int k = 0; k < kPerThread; ++k) rb[threadIdx.x * kPerThread + k] = x[k] + before;
-        if (threadIdx.x == kThreads - 1) rb[kMaxRuns] = before + run;
+        placed = 0;
+        for (int w = 0; w < kWaves; ++w) {
+            if (w < wv) before += part[w];
+            placed += part[w];
+        }
+        for (int k = 0; k < per; ++k) {
+            const int64_t x = rb[threadIdx.x * per + k];
+            rb[threadIdx.x * per + k] = before;
+            before += x;
+        }
     }
     __syncthreads();
-    const int64_t placed = rb[kMaxRuns];                      // runs past nruns are empty: this is the total
     auto edge = [&](int d, int s) -> int64_t {                // start of the owner-side block (d, s); (P, 0) is the end
-        return d >= P ? placed : rb[dd.nsum[d] * P + s * dd.n_loc[d]];
+        const int i = d >= P ? nruns : dd.nsum[d] * P + s * dd.n_loc[d];
+        return i >= nruns ? placed : rb[i];                   // ranks without a table behind the last run: the end too
     };
     auto count = [&](int s, int d) -> int64_t {               // lookups rank s asks of rank d
         return (s + 1 < P ? edge(d, s + 1) : edge(d + 1, 0)) - edge(d, s);
     };
 
-    // 2. the alltoallv counts and displacements, by the first workgroup
+    // 3. the alltoallv counts and displacements, by the first workgroup
     if (blockIdx.x == 0 && blockIdx.y == 0) {
         for (int e = threadIdx.x; e < P * P; e += kThreads) {
             const int d = e / P, s = e - d * P;
@@ -110,19 +172,10 @@ __global__ __launch_bounds__(kThreads) void step_tablewise(DevDesc dd, const int
         if (threadIdx.x == 0) segoff[dd.nseg] = placed;
     }
 
-    // 3. this workgroup's bags: samples of requester s, table q
-    const int q = blockIdx.y;
-    const int s = (int)(blockIdx.x / chunks);
-    const uint32_t chunk = blockIdx.x - (uint32_t)s * chunks;
-    const int t = dd.q_t[q], d = dd.q_d[q];
-    const int64_t f = dd.first[s], n = dd.first[s + 1] - f;
-    const int64_t g0 = (int64_t)t * dd.B + f;
-    int64_t lo_run = off[g0], hi_run = off[g0 + n];
-    if (lo_run < 0 || hi_run > nnz || hi_run < lo_run) lo_run = hi_run = 0;   // flagged above; the run counts as empty
-    const int64_t dst = rb[run_entry(dd, q, s)];
-    // owner-side place -> requester-side place of the run's lookups: start of bucket (s, d) in requester
+    // 4. owner-side place -> requester-side place of the run's lookups: start of bucket (s, d) in requester
     // order minus its start in owner order.  The requester-side start adds up every count of an
     // earlier requester and this requester's counts for earlier owners.
+    const int64_t dst = rb[run_entry(dd, q, s)];
     int64_t to_send = 0;
     if (perm) {
         int64_t a = 0;
@@ -137,61 +190,63 @@ __global__ __launch_bounds__(kThreads) void step_tablewise(DevDesc dd, const int
         for (int w = 0; w < kWaves; ++w) to_send += red[w];
         to_send -= edge(d, s);
     }
-
-    const int li = threadIdx.x & (G - 1);
-    const int gbase = lane & ~(G - 1);
-    const int64_t b_loc = (int64_t)chunk * (kThreads / G) + threadIdx.x / G;
-    const bool live = b_loc < n;
-    const uint32_t row_bytes = (uint32_t)payload_bytes(DT, dd.D), row_stride = (uint32_t)stride_bytes(DT, dd.D);
-    const bool col_ok = (uint32_t)li * 16 < row_bytes;        // lanes past the row's end idle
-    const char *__restrict__ base = (const char *)dd.q_base[q] + (col_ok ? (uint32_t)li * 16 : 0u);
-    const int tail = (int)row_bytes - (col_ok ? li * 16 : 0);
-    const int64_t rows = dd.q_rows[q], run_len = hi_run - lo_run;
-
-    int64_t beg = 0, len = 0, place = 0;
+    int64_t place = 0;
     if (live) {
-        beg = off[g0 + b_loc];
-        const int64_t end = off[g0 + b_loc + 1];
-        len = end - beg;
-        int64_t at = beg - lo_run;
-        if (at < 0 || at > run_len || len < 0 || at + len > run_len) {   // a bag outside its run: treated as empty
-            if (li == 0) flag_error(dd);
-            at = at < 0 ? 0 : (at > run_len ? run_len : at);
-            len = 0;
-        }
-        place = dst + at;
+        place = dst + at_run;
         const int64_t sg = (int64_t)dd.nsum[d] * dd.B + (int64_t)dd.n_loc[d] * f + (int64_t)(q - dd.nsum[d]) * n + b_loc;
         if (li == 0) segoff[sg] = place;
         if (place < 0 || place + len > nnz) { if (li == 0) flag_error(dd); len = 0; }
     }
 
+    // 5. a block's lookups to their places on the owner's side, its rows added in order.  A ring of U rows in flight as in
+    // the pooling kernels: lookups without a row read zeros, which change no sum.
+    auto put = [&](int64_t c0, int64_t r) {
+        if (c0 + li >= len) return;
+        const bool ok = (uint64_t)r < (uint64_t)rows;
+        if (!ok) flag_error(dd);                              // adds nothing to the bag
+        ridx[place + c0 + li] = ok ? r : -1;
+        if (perm) perm[beg + c0 + li] = place + c0 + li + to_send;
+    };
     A acc;
     acc.zero();
-    int64_t ahead = li < len ? idx[beg + li] : -1;            // asked for one block early, and waited for with the block at hand
-    for (int64_t c0 = 0; __any(c0 < len); c0 += G) {
-        const int64_t left = len - c0;
-        const int rem = left < 0 ? 0 : (left > G ? G : (int)left);
-        int64_t mine = -1;
-        const int64_t got = ahead;
-        ahead = c0 + G + li < len ? idx[beg + c0 + G + li] : -1;
-        if (li < rem) {
-            mine = got;
-            if (mine < 0 || mine >= rows) { flag_error(dd); mine = -1; }       // adds nothing to the bag
-            ridx[place + c0 + li] = mine;
-            if (perm) perm[beg + c0 + li] = place + c0 + li + to_send;
-        }
-        for (int j = 0; __any(j < rem); j += kU) {
-            int64_t r[kU];
-            typename A::Raw v[kU];
-#pragma unroll
-            for (int u = 0; u < kU; ++u) r[u] = __shfl(mine, gbase + ((j + u) & (G - 1)), 64);
-#pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                v[u] = A::none();
-                if (j + u < rem && r[u] >= 0) v[u] = A::load(base + (uint64_t)r[u] * row_stride, tail);
+    if constexpr (!WIDE) {
+        put(0, here);
+        uint32_t mine = offset(here);
+        for (int64_t at = 0; __any(at < len); at += U) {
+            const int64_t next = at + U;
+            if ((next & (G - 1)) == 0) {
+                here = ahead;
+                ahead = ask(next + G);
+                put(next, here);
+                mine = offset(here);
             }
+            uint32_t o[U];
 #pragma unroll
-            for (int u = 0; u < kU; ++u) acc.add(v[u]);       // adding +0 for the rows not there changes nothing
+            for (int u = 0; u < U; ++u) o[u] = (uint32_t)__shfl((int)mine, gbase + ((int)next & (G - 1)) + u, 64);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                acc.add(v[u]);
+                v[u] = A::load_buffer(shard, o[u] + col, tail);
+            }
+        }
+    } else {
+        for (int64_t c0 = 0; __any(c0 < len); c0 += G) {
+            put(c0, here);
+            const int64_t mine = c0 + li < len && (uint64_t)here < (uint64_t)rows ? here : -1;
+            here = ahead;
+            ahead = ask(c0 + 2 * G);
+            for (int j = 0; __any(c0 + j < len) && j < G; j += U) {
+                int64_t r[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) r[u] = __shfl(mine, gbase + j + u, 64);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    v[u] = A::none();
+                    if (r[u] >= 0) v[u] = A::load(base + (uint64_t)r[u] * row_stride, tail);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) acc.add(v[u]);
+            }
         }
     }
     if (live && col_ok) {
@@ -205,19 +260,19 @@ __global__ __launch_bounds__(kThreads) void step_tablewise(DevDesc dd, const int
     }
 }
 
-template <int DT>
+template <int DT, bool WIDE>
 bool dispatch(const bls_ctx *ctx, int lanes, dim3 grid, hipStream_t st, const int64_t *idx, const int64_t *off, int64_t nnz,
               int64_t *sc, int64_t *sd, int64_t *rc, int64_t *rd, int64_t *ridx, int64_t *segoff, int64_t *perm, float *Y,
               float *S, float *R, float *out, uint32_t chunks)
 {
     switch (lanes) {
-    case 1: step_tablewise<1, DT><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
-    case 2: step_tablewise<2, DT><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
-    case 4: step_tablewise<4, DT><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
-    case 8: step_tablewise<8, DT><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
-    case 16: step_tablewise<16, DT><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
-    case 32: step_tablewise<32, DT><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
-    case 64: step_tablewise<64, DT><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
+    case 1: step_tablewise<1, DT, WIDE><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
+    case 2: step_tablewise<2, DT, WIDE><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
+    case 4: step_tablewise<4, DT, WIDE><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
+    case 8: step_tablewise<8, DT, WIDE><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
+    case 16: step_tablewise<16, DT, WIDE><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
+    case 32: step_tablewise<32, DT, WIDE><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
+    case 64: step_tablewise<64, DT, WIDE><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
     }
     return false;
 }
@@ -242,13 +297,17 @@ int bls_launch_step_tablewise(bls_ctx *ctx, const int64_t *idx, const int64_t *o
     const uint64_t gx = (uint64_t)chunks * ctx->P;
     if (gx > 0x7fffffffull) return bls_fail(ctx, BLS_EINVAL, "bls_step_tablewise: batch too large for one launch");
     const dim3 grid((unsigned)gx, (unsigned)ctx->Q);
-    bool ok;
-    switch (ctx->dtype) {
-    case BLS_FP16: ok = dispatch<BLS_FP16>(ctx, lanes, grid, st, idx, off, nnz, sendcounts, sdispls, recvcounts, rdispls, ridx, segoff, perm, Y, S, R, out, chunks); break;
-    case BLS_U8_ROWQ: ok = dispatch<BLS_U8_ROWQ>(ctx, lanes, grid, st, idx, off, nnz, sendcounts, sdispls, recvcounts, rdispls, ridx, segoff, perm, Y, S, R, out, chunks); break;
-    case BLS_F8_ROWQ: ok = dispatch<BLS_F8_ROWQ>(ctx, lanes, grid, st, idx, off, nnz, sendcounts, sdispls, recvcounts, rdispls, ridx, segoff, perm, Y, S, R, out, chunks); break;
-    default: ok = dispatch<BLS_FP32>(ctx, lanes, grid, st, idx, off, nnz, sendcounts, sdispls, recvcounts, rdispls, ridx, segoff, perm, Y, S, R, out, chunks); break;
-    }
+    // a shard's bytes as 32-bit offsets, unless one is too large for them
+    bool wide = ctx->tune_wide == 1;
+    for (int q = 0; q < ctx->Q; ++q) wide = wide || ctx->q_rows[q] >= (int64_t)kPastEnd / stride_bytes(ctx->dtype, ctx->D);
+    auto go = [&](auto dt) -> bool {
+        return wide ? dispatch<dt(), true>(ctx, lanes, grid, st, idx, off, nnz, sendcounts, sdispls, recvcounts, rdispls, ridx, segoff, perm, Y, S, R, out, chunks)
+                    : dispatch<dt(), false>(ctx, lanes, grid, st, idx, off, nnz, sendcounts, sdispls, recvcounts, rdispls, ridx, segoff, perm, Y, S, R, out, chunks);
+    };
+    const bool ok = ctx->dtype == BLS_FP16    ? go(std::integral_constant<int, BLS_FP16>())
+                  : ctx->dtype == BLS_U8_ROWQ ? go(std::integral_constant<int, BLS_U8_ROWQ>())
+                  : ctx->dtype == BLS_F8_ROWQ ? go(std::integral_constant<int, BLS_F8_ROWQ>())
+                                              : go(std::integral_constant<int, BLS_FP32>());
     if (!ok) return bls_fail(ctx, BLS_EINVAL, "bls_step_tablewise: unsupported row length");
     BLS_HIP(ctx, hipGetLastError());
     return BLS_OK;

@@ -92,3 +92,35 @@ def test_lookups_without_a_row_add_nothing(dt, D, part):
         for a, b in zip(g, want):
             assert (np.isnan(a) == np.isnan(b)).all()
             assert (bits(a)[~np.isnan(b)] == bits(b)[~np.isnan(b)]).all()
+
+
+@pytest.mark.parametrize("bag", BAGS, ids=str)
+@pytest.mark.parametrize("dt,D", [s for s in SHAPES if s[1] * {"fp32": 4, "fp16": 2}.get(s[0], 1) % 16 == 0], ids=str)
+def test_one_launch_step_ring(dt, D, bag):
+    """The one-launch step reads rows in a ring as well: every buffer, in either form of its positions, an index without a row
+    among them."""
+    import paper_2512_19342_amd as B
+    w, tabs, pipes = make(dt, D, 0, bag)
+    ix, off = synth.make_batch(w, 2)
+    nnz = int(off[-1])
+    ref = oracle.pipeline(case_of(w), tabs, ix.numpy(), off.numpy())
+    for pipe in pipes:
+        out = pipe.new_out().fill_(float("nan"))
+        j = pipe.step_one_launch(ix.cuda(), off.cuda(), nnz, out)
+        for k in ("ridx", "segoff", "sendcounts", "sdispls", "recvcounts", "rdispls"):
+            assert (getattr(pipe, k).cpu().numpy()[:len(ref[k])] == ref[k]).all(), k
+        for k, buf in (("Y", pipe.pooled), ("S", pipe.send), ("R", pipe.slot_view(j % pipe.ctx.K)), ("Out", out)):
+            assert (bits(buf.cpu().numpy().reshape(-1)) == bits(ref[k].reshape(-1))).all(), k
+        pipe.ctx.bls_check()
+    at = nnz // 2
+    bad = ix.clone()
+    bad[at] = -1
+    goff = off.clone()
+    goff[goff > at] -= 1
+    want = oracle.pipeline(case_of(w), tabs, np.delete(ix.numpy(), at), goff.numpy())["Out"]
+    for pipe in pipes:
+        out = pipe.new_out()
+        pipe.step_one_launch(bad.cuda(), off.cuda(), nnz, out)
+        with pytest.raises(B.BlsError):
+            pipe.ctx.bls_check()
+        assert (bits(out.cpu().numpy()) == bits(want)).all()
