@@ -493,10 +493,12 @@ __global__ __launch_bounds__(kThreads) void plan_place_runs(DevDesc dd, const in
 // Table-wise with up to kMaxRuns runs: count, scan and place in one launch.  A run's place on the
 // owner's side follows from the run lengths alone, and those are differences of the offsets at
 // the run edges: every workgroup reads the edges for itself (a few hundred values out of L2),
-// scans the lengths in owner order in LDS, and then copies its runs as plan_place_runs does; the
-// first workgroup also writes the counts and displacements.
+// scans the lengths in owner order in LDS, and then copies its run as plan_place_runs does; the
+// first workgroup also writes the counts and displacements.  grid: x over a run's lookups, y = run.
+// A chain of dependent reads bounds it: the run's own offsets and first lookups are asked for ahead of the count, and the scan
+// covers the runs there are.  us a staged iteration with vectors of 16, the run read after the scan of 2048 / this: 26 tables, 8 ranks, 512
+// bags of 1 to 100 40.7 / 37.6, 64 tables, 4096 bags of up to 20 75.4 / 71.8, 26 tables, 4 ranks, 2048 bags of one 24.1 / 22.9.
 constexpr int kMaxRuns = 2048;
-constexpr int kRunsPerThread = kMaxRuns / kThreads;
 __global__ __launch_bounds__(kThreads) void plan_runs_one_launch(DevDesc dd, const int64_t *__restrict__ idx,
                                                                  const int64_t *__restrict__ off, int64_t nnz,
                                                                  int64_t *__restrict__ sendcounts, int64_t *__restrict__ sdispls,
@@ -516,8 +518,29 @@ __global__ __launch_bounds__(kThreads) void plan_runs_one_launch(DevDesc dd, con
         return dd.nsum[d] * P + s * dd.n_loc[d] + (q - dd.nsum[d]);
     };
 
-    for (int i = threadIdx.x; i < kMaxRuns + 1; i += kThreads) rb[i] = 0;
-    __syncthreads();
+    // this workgroup's run: its bags' offsets and its first lookups come while the runs are counted
+    const int run = blockIdx.y, q = run / P, s = run - q * P;
+    const int t = dd.q_t[q], d = dd.q_d[q];
+    const int64_t f = dd.first[s], n = dd.first[s + 1] - f;
+    const int64_t g0 = (int64_t)t * dd.B + f;
+    int64_t lo = off[g0], hi = off[g0 + n];
+    const int64_t b0 = (int64_t)blockIdx.x * kThreads + threadIdx.x, i0 = (int64_t)blockIdx.x * kThreads * kPer + threadIdx.x;
+    int64_t bag = 0, bag_end = 0;
+    if (b0 < n) {
+        bag = off[g0 + b0];
+        bag_end = off[g0 + b0 + 1];
+    }
+    if (lo < 0 || hi > nnz || hi < lo) lo = hi = 0;           // flagged below; the run counts as empty
+    const int64_t len = hi - lo;
+    auto ask = [&](int64_t i, int64_t (&v)[kPer]) {
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) v[k] = i + k * kThreads < len ? idx[lo + i + k * kThreads] : 0;
+    };
+    int64_t v[kPer];
+    ask(i0, v);
+
+    const int per = (nruns + kThreads - 1) / kThreads;        // runs of a thread in the scan
+    for (int i = nruns + threadIdx.x; i < per * kThreads; i += kThreads) rb[i] = 0;
     bool bad_edges = false;
     for (int i = threadIdx.x; i < nruns; i += kThreads) {
         const int q = i / P, s = i - q * P;
@@ -530,37 +553,41 @@ __global__ __launch_bounds__(kThreads) void plan_runs_one_launch(DevDesc dd, con
     if (bad_edges && blockIdx.x == 0 && blockIdx.y == 0) flag_error(dd);
     __syncthreads();
     {
-        int64_t x[kRunsPerThread], run = 0;
-#pragma unroll
-        for (int k = 0; k < kRunsPerThread; ++k) { x[k] = run; run += rb[threadIdx.x * kRunsPerThread + k]; }
-        const int64_t inc = wave_inclusive_scan(run, lane);
+        int64_t sum = 0;
+        for (int k = 0; k < per; ++k) sum += rb[threadIdx.x * per + k];
+        const int64_t inc = wave_inclusive_scan(sum, lane);
         if (lane == 63) part[wv] = inc;
         __syncthreads();
-        int64_t before = inc - run;
+        int64_t before = inc - sum;
         for (int w = 0; w < wv; ++w) before += part[w];
-#pragma unroll
-        for (int k = 0; k < kRunsPerThread; ++k) rb[threadIdx.x * kRunsPerThread + k] = x[k] + before;
-        if (threadIdx.x == kThreads - 1) rb[kMaxRuns] = before + run;
+        for (int k = 0; k < per; ++k) {
+            const int64_t x = rb[threadIdx.x * per + k];
+            rb[threadIdx.x * per + k] = before;
+            before += x;
+        }
+        if (threadIdx.x == kThreads - 1) rb[per * kThreads] = before;
     }
     __syncthreads();
-    const int64_t placed = rb[kMaxRuns];                      // runs past nruns are empty: this is the total
+    const int64_t placed = rb[nruns];                         // the total
     auto edge = [&](int d, int s) -> int64_t {                // start of the owner-side block (d, s); (P, 0) is the end
-        return d >= P ? placed : rb[dd.nsum[d] * P + s * dd.n_loc[d]];
+        return rb[d >= P ? nruns : dd.nsum[d] * P + s * dd.n_loc[d]];
     };
     auto count = [&](int s, int d) -> int64_t {               // lookups rank s asks of rank d
         return (s + 1 < P ? edge(d, s + 1) : edge(d + 1, 0)) - edge(d, s);
     };
-    if (threadIdx.x < P) {                                    // lookups per requester, then those of earlier requesters
-        int64_t run = 0;
-        for (int d = 0; d < P; ++d) run += count(threadIdx.x, d);
-        req_before[threadIdx.x + 1] = run;
+    if (perm) {                                               // lookups per requester, then those of earlier requesters
+        if (threadIdx.x < P) {
+            int64_t sum = 0;
+            for (int d = 0; d < P; ++d) sum += count(threadIdx.x, d);
+            req_before[threadIdx.x + 1] = sum;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            req_before[0] = 0;
+            for (int s = 0; s < P; ++s) req_before[s + 1] += req_before[s];
+        }
+        __syncthreads();
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        req_before[0] = 0;
-        for (int s = 0; s < P; ++s) req_before[s + 1] += req_before[s];
-    }
-    __syncthreads();
 
     if (blockIdx.x == 0 && blockIdx.y == 0) {
         for (int e = threadIdx.x; e < P * P; e += kThreads) {
@@ -568,58 +595,50 @@ __global__ __launch_bounds__(kThreads) void plan_runs_one_launch(DevDesc dd, con
             recvcounts[d * P + s] = count(s, d);
             sendcounts[s * P + d] = count(s, d);
             rdispls[d * P + s] = edge(d, s) - edge(d, 0);
-            int64_t run = 0;
-            for (int o = 0; o < d; ++o) run += count(s, o);
-            sdispls[s * P + d] = run;
+            int64_t sum = 0;
+            for (int o = 0; o < d; ++o) sum += count(s, o);
+            sdispls[s * P + d] = sum;
         }
         if (threadIdx.x == 0) segoff[dd.nseg] = placed;
     }
 
-    for (int run = blockIdx.y; run < nruns; run += gridDim.y) {
-        const int q = run / P, s = run - q * P;
-        const int t = dd.q_t[q], d = dd.q_d[q];
-        const int64_t f = dd.first[s], n = dd.first[s + 1] - f;
-        const int64_t g0 = (int64_t)t * dd.B + f;
-        int64_t lo = off[g0], hi = off[g0 + n];
-        if (lo < 0 || hi > nnz || hi < lo) lo = hi = 0;       // flagged above; the run counts as empty
-        const int64_t len = hi - lo;
-        const int64_t dst = rb[entry(q, s)];
-        const int64_t sg0 = (int64_t)dd.nsum[d] * dd.B + (int64_t)dd.n_loc[d] * f + (int64_t)(q - dd.nsum[d]) * n;
-        for (int64_t b = (int64_t)blockIdx.x * kThreads + threadIdx.x; b < n; b += (int64_t)gridDim.x * kThreads) {
-            int64_t at = off[g0 + b] - lo;
-            const int64_t nxt = off[g0 + b + 1] - lo;
-            if (at < 0 || at > len || nxt < at) { flag_error(dd); at = at < 0 ? 0 : (at > len ? len : at); }
-            segoff[sg0 + b] = dst + at;
+    const int64_t dst = rb[entry(q, s)];
+    const int64_t sg0 = (int64_t)dd.nsum[d] * dd.B + (int64_t)dd.n_loc[d] * f + (int64_t)(q - dd.nsum[d]) * n;
+    for (int64_t b = b0; b < n;) {
+        int64_t at = bag - lo;
+        const int64_t nxt = bag_end - lo;
+        if (at < 0 || at > len || nxt < at) { flag_error(dd); at = at < 0 ? 0 : (at > len ? len : at); }
+        segoff[sg0 + b] = dst + at;
+        b += (int64_t)gridDim.x * kThreads;
+        if (b < n) {
+            bag = off[g0 + b];
+            bag_end = off[g0 + b + 1];
         }
-        if (len <= 0) continue;
-        if (dst < 0 || dst + len > nnz) { if (threadIdx.x == 0 && blockIdx.x == 0) flag_error(dd); continue; }
-        const int64_t rows = dd.rows[t];
-        // owner-side place -> requester-side place: start of bucket (s, d) in requester order (the lookups of
-        // earlier requesters, and this requester's for earlier owners) minus its start in owner order
-        int64_t to_send = 0;
-        if (perm) {
-            to_send = req_before[s] - edge(d, s);
-            for (int o = 0; o < d; ++o) to_send += count(s, o);
-        }
-        const int64_t stride = (int64_t)gridDim.x * kThreads * kPer;
-        for (int64_t i0 = (int64_t)blockIdx.x * kThreads * kPer + threadIdx.x; i0 < len; i0 += stride) {
-            int64_t v[kPer];
+    }
+    if (len <= 0) return;
+    if (dst < 0 || dst + len > nnz) { if (threadIdx.x == 0 && blockIdx.x == 0) flag_error(dd); return; }
+    const int64_t rows = dd.rows[t];
+    // owner-side place -> requester-side place: start of bucket (s, d) in requester order (the lookups of
+    // earlier requesters, and this requester's for earlier owners) minus its start in owner order
+    int64_t to_send = 0;
+    if (perm) {
+        to_send = req_before[s] - edge(d, s);
+        for (int o = 0; o < d; ++o) to_send += count(s, o);
+    }
+    const int64_t stride = (int64_t)gridDim.x * kThreads * kPer;
+    for (int64_t at = i0; at < len;) {
 #pragma unroll
-            for (int k = 0; k < kPer; ++k) {
-                const int64_t i = i0 + k * kThreads;
-                v[k] = i < len ? idx[lo + i] : 0;
-            }
-#pragma unroll
-            for (int k = 0; k < kPer; ++k) {
-                const int64_t i = i0 + k * kThreads;
-                if (i < len) {
-                    if (v[k] < 0 || v[k] >= rows) { flag_error(dd); v[k] = -1; }   // the pool skips negative rows
-                    ridx[dst + i] = v[k];
-                    if (w_in) w_out[dst + i] = w_in[lo + i];
-                    if (perm) perm[lo + i] = dst + i + to_send;
-                }
+        for (int k = 0; k < kPer; ++k) {
+            const int64_t i = at + k * kThreads;
+            if (i < len) {
+                if (v[k] < 0 || v[k] >= rows) { flag_error(dd); v[k] = -1; }   // the pool skips negative rows
+                ridx[dst + i] = v[k];
+                if (w_in) w_out[dst + i] = w_in[lo + i];
+                if (perm) perm[lo + i] = dst + i + to_send;
             }
         }
+        at += stride;
+        ask(at, v);
     }
 }
 

@@ -64,7 +64,7 @@ __global__ __launch_bounds__(kThreads, (WIDE ? 1 : kWavesHeld<G, DT>)) void step
                                                            float *__restrict__ out, uint32_t chunks)
 {
     using A = Acc<DT, 16>;
-    __shared__ int64_t rb[kMaxRuns];           // run lengths in owner order, then their exclusive scan
+    __shared__ int64_t rb[kMaxRuns + 1];       // run lengths in owner order, then their exclusive scan
     __shared__ int64_t part[kWaves];
     __shared__ int64_t red[kWaves];
     const int P = dd.P, nruns = dd.Q * P;
@@ -130,7 +130,6 @@ __global__ __launch_bounds__(kThreads, (WIDE ? 1 : kWavesHeld<G, DT>)) void step
     }
     if (bad_edges) flag_error(dd);
     __syncthreads();
-    int64_t placed;                                           // the total
     {
         int64_t run = 0;
         for (int k = 0; k < per; ++k) run += rb[threadIdx.x * per + k];
@@ -138,21 +137,18 @@ __global__ __launch_bounds__(kThreads, (WIDE ? 1 : kWavesHeld<G, DT>)) void step
         if (lane == 63) part[wv] = inc;
         __syncthreads();
         int64_t before = inc - run;
-        placed = 0;
-        for (int w = 0; w < kWaves; ++w) {
-            if (w < wv) before += part[w];
-            placed += part[w];
-        }
+        for (int w = 0; w < wv; ++w) before += part[w];
         for (int k = 0; k < per; ++k) {
             const int64_t x = rb[threadIdx.x * per + k];
             rb[threadIdx.x * per + k] = before;
             before += x;
         }
+        if (threadIdx.x == kThreads - 1) rb[per * kThreads] = before;
     }
     __syncthreads();
+    const int64_t placed = rb[nruns];                         // the total
     auto edge = [&](int d, int s) -> int64_t {                // start of the owner-side block (d, s); (P, 0) is the end
-        const int i = d >= P ? nruns : dd.nsum[d] * P + s * dd.n_loc[d];
-        return i >= nruns ? placed : rb[i];                   // ranks without a table behind the last run: the end too
+        return rb[d >= P ? nruns : dd.nsum[d] * P + s * dd.n_loc[d]];
     };
     auto count = [&](int s, int d) -> int64_t {               // lookups rank s asks of rank d
         return (s + 1 < P ? edge(d, s + 1) : edge(d + 1, 0)) - edge(d, s);
