@@ -1027,14 +1027,16 @@ int bls_launch_plan(bls_ctx *ctx, const int64_t *idx, const int64_t *off, int64_
     int64_t *segoff_end = segoff + ctx->nseg;
     const dim3 tgrid(tg.tiles, (unsigned)(ctx->T * ctx->P));
 
-    // small table-wise batches (large ones are a copy of hundreds of megabytes, which three launches do faster:
-    // workload 4, 34 M lookups, 0.121 ms against 0.145)
-    if (!rowwise && (int64_t)ctx->Q * ctx->P <= kMaxRuns && nnz <= ((int64_t)1 << 22) && ctx->tune_plan_scan != 0) {
-        const int64_t runs = (int64_t)ctx->Q * ctx->P;
-        // every workgroup pays for the scan of the run edges: about four thousand workgroups in all, none
+    // Table-wise batches that are not too large in one launch: up to 2^22 lookups, and up to 2^24 where a thread scans one run.  us a
+    // fused iteration with vectors of 16, three launches / one: 5.5 M lookups in 91 runs 101 / 94, 8.1 M in 4 119 / 111, 8.5 M in 256
+    // 113.5 / 109, in 128 111 / 105, 14.9 M in 160 192 / 191, 16.1 M in 104 263 / 260, 28 M in 40 427 / 427; in 1600 200 / 230, in
+    // 512 8.4 M 147 / 148, 34 M 487 / 499.
+    const int64_t runs = (int64_t)ctx->Q * ctx->P;
+    if (!rowwise && runs <= kMaxRuns && nnz <= ((int64_t)1 << (runs <= kThreads ? 24 : 22)) && ctx->tune_plan_scan != 0) {
+        // every workgroup pays for the scan of the run edges: about two thousand workgroups in all, none
         // with less than 2048 lookups or bags to work on
         const int64_t per_run = std::max<int64_t>(nnz / runs, n_max) + 1;
-        const int64_t want = (4096 + runs - 1) / runs;
+        const int64_t want = (2048 + runs - 1) / runs;
         const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, (per_run + 2047) / 2048));
         plan_runs_one_launch<<<dim3(gx, (unsigned)runs), kThreads, 0, st>>>(dd, idx, off, nnz, sendcounts, sdispls, recvcounts, rdispls,
                                                                              segoff, ridx, perm, w_in, w_out);
@@ -1068,7 +1070,6 @@ int bls_launch_plan(bls_ctx *ctx, const int64_t *idx, const int64_t *off, int64_
         else if (w_in) plan_place_tiles<false, true><<<tgrid, kThreads, 0, st>>>(dd, tg, idx, off, nnz, X, segoff, ridx, perm, sabs, rabs, w_in, w_out);
         else plan_place_tiles<false, false><<<tgrid, kThreads, 0, st>>>(dd, tg, idx, off, nnz, X, segoff, ridx, perm, sabs, rabs, w_in, w_out);
     } else {
-        const int64_t runs = (int64_t)ctx->Q * ctx->P;
         const int64_t per_run = std::max<int64_t>(nnz / runs, n_max) + 1;
         const unsigned gx = (unsigned)std::min<int64_t>(256, std::max<int64_t>(1, (per_run + 2047) / 2048));
         dim3 grid(gx, (unsigned)std::min<int64_t>(runs, 65535));

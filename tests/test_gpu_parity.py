@@ -231,6 +231,20 @@ def test_tablewise_plan_in_three_launches(spec):
     check_against_oracle(w, tabs, batches, got)
 
 
+@pytest.mark.parametrize("P,T,B,hi", [(2, 2, 5000, 900), (2, 1, 9000, 4000), (1, 300, 64, 500)])
+def test_tablewise_plan_of_millions_of_lookups(P, T, B, hi):
+    """Past 2^22 lookups one launch plans for up to 256 runs, several workgroups a run, up to 2^24; beyond either, three."""
+    w = synth.custom("many", k=1, values="grid", seed=9, P=P, T=T, D=4, B=B, part_kind=0, rows=[50] * T, bag=("uniform", 0, hi))
+    tabs = [synth.make_table(w, t) for t in range(w.T)]
+    batches = [synth.make_batch(w, 0)]
+    assert int(batches[0][1][-1]) > 1 << 22
+    got, _ = run_gpu(w, tabs, batches)
+    ref = oracle.pipeline(case_of(w), [t.numpy() for t in tabs], batches[0][0].numpy(), batches[0][1].numpy())
+    for k in ("sendcounts", "sdispls", "recvcounts", "rdispls", "ridx", "segoff", "perm"):
+        assert np.array_equal(got[0][k], ref[k]), k
+    assert np.array_equal(bits(got[0]["Out"]), bits(ref["Out"]))
+
+
 def test_tablewise_plan_with_more_runs_than_one_launch_takes():
     """P * Q = 2112 runs: beyond what the one-launch form scans in LDS, so the three launches serve."""
     w = synth.custom("manyruns", P=64, T=33, D=4, B=128, k=1, part_kind=0, rows=[50 + 3 * t for t in range(33)],
