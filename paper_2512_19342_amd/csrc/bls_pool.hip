@@ -70,7 +70,7 @@ __device__ __forceinline__ uint64_t group_broadcast64(uint64_t v, int gbase4, in
     }
 }
 
-// One segment per group of G lanes (used for G < 4, rows of 16 or 32 bytes).
+// One segment per group of G lanes (G = 1 and 2: rows of 16 and 32 bytes with few rows a segment, pool_shape).
 // grid: x over groups of samples, y = q (owner, local table).
 template <int G, int DT, int VB, int U>
 __global__ __launch_bounds__(kThreads) void pool_rows(DevDesc dd, const int64_t *__restrict__ ridx,
@@ -480,8 +480,9 @@ __global__ __launch_bounds__(kHotThreads) void pool_stream_hot(DevDesc dd, const
     }
 }
 
-// Any D (odd lengths, rows longer than 1 KB): one wavefront per segment, lanes stride the
-// columns, scalar loads.
+// Rows that no lanes of 4, 8 or 16 bytes cover (odd lengths of half-precision and 8-bit rows, rows longer than 1 KB): one wavefront per
+// segment, lanes stride the columns, scalar loads.  us, this / the streaming kernels, 8192 bags of one row of 26 tables and of 1 to 64: half
+// precision of 20 85 / 35, 779 / 148, 8-bit of 20 88 / 38, 811 / 173; of one row fp32 of 10 88 / 36, of 5 83 / 31, 8-bit of 60 100 / 51.
 template <int DT>
 __global__ __launch_bounds__(kThreads) void pool_rows_generic(DevDesc dd, const int64_t *__restrict__ ridx,
                                                               const float *__restrict__ rw,
@@ -614,21 +615,22 @@ void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const
             kernel<<<grid, kThreads, ring ? kRingLds : 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, to.Y, to.S, to.R, to.slot, nb, chunks, deal, q0, qn);
         };
         auto pick = [&](auto weighted, auto stores) {
-            if constexpr (VB == 16) {
+            if constexpr (VB == 16 || G <= 16) {
                 if (ring) return launch(pool_stream<G, DT, VB, UU, false, weighted(), true, stores()>);
             }
             if (wide) launch(pool_stream<G, DT, VB, UU, true, weighted(), false, stores()>);
             else launch(pool_stream<G, DT, VB, UU, false, weighted(), false, stores()>);
         };
+        constexpr bool kThree = VB == 16 || G * VB >= 128;    // three stores: bls_pool_all_fits
         if (rw) {
             pick(std::true_type(), std::integral_constant<int, kOneStore>());
         } else if (to.stores == kOneStore) {
             pick(std::false_type(), std::integral_constant<int, kOneStore>());
         } else if (to.stores == kThreePlain) {
-            if constexpr (Acc<DT, VB>::NV == 16 || (Acc<DT, VB>::NV == 8 && G >= 16)) pick(std::false_type(), std::integral_constant<int, kThreePlain>());
+            if constexpr (kThree && (Acc<DT, VB>::NV == 16 || (Acc<DT, VB>::NV == 8 && G >= 16))) pick(std::false_type(), std::integral_constant<int, kThreePlain>());
         } else if (to.stores == kThreeHintedY) {
-            if constexpr (Acc<DT, VB>::NV == 8 || (Acc<DT, VB>::NV == 4 && G <= 16)) pick(std::false_type(), std::integral_constant<int, kThreeHintedY>());
-        } else if constexpr (Acc<DT, VB>::NV <= 8) {
+            if constexpr (kThree && (Acc<DT, VB>::NV == 8 || (Acc<DT, VB>::NV == 4 && G <= 16))) pick(std::false_type(), std::integral_constant<int, kThreeHintedY>());
+        } else if constexpr (kThree && Acc<DT, VB>::NV <= 8) {
             pick(std::false_type(), std::integral_constant<int, kThreeHinted>());
         }
     } else {
@@ -644,9 +646,9 @@ bool dispatch_lanes(const bls_ctx *ctx, int lanes, const int64_t *ridx, const fl
     switch (lanes) {
     case 1: if constexpr (VB == 16) { launch_rows<1, DT, VB, U>(ctx, ridx, rw, segoff, nnz, to, q0, qn, st); return true; } break;
     case 2: if constexpr (VB == 16) { launch_rows<2, DT, VB, U>(ctx, ridx, rw, segoff, nnz, to, q0, qn, st); return true; } break;
-    case 4: if constexpr (VB == 16) { launch_rows<4, DT, VB, U>(ctx, ridx, rw, segoff, nnz, to, q0, qn, st); return true; } break;
-    case 8: if constexpr (VB == 16) { launch_rows<8, DT, VB, U>(ctx, ridx, rw, segoff, nnz, to, q0, qn, st); return true; } break;
-    case 16: if constexpr (VB >= 8) { launch_rows<16, DT, VB, U>(ctx, ridx, rw, segoff, nnz, to, q0, qn, st); return true; } break;
+    case 4: launch_rows<4, DT, VB, U>(ctx, ridx, rw, segoff, nnz, to, q0, qn, st); return true;
+    case 8: launch_rows<8, DT, VB, U>(ctx, ridx, rw, segoff, nnz, to, q0, qn, st); return true;
+    case 16: launch_rows<16, DT, VB, U>(ctx, ridx, rw, segoff, nnz, to, q0, qn, st); return true;
     case 32: launch_rows<32, DT, VB, U>(ctx, ridx, rw, segoff, nnz, to, q0, qn, st); return true;
     case 64: launch_rows<64, DT, VB, U>(ctx, ridx, rw, segoff, nnz, to, q0, qn, st); return true;
     }
@@ -669,7 +671,7 @@ bool dispatch_rows(const bls_ctx *ctx, int vb, int lanes, const int64_t *ridx, c
 }  // namespace
 
 // Bytes per lane and lanes per row of the kernels that read whole pieces of rows; false: pool_rows_generic.
-static bool pool_shape(const bls_ctx *ctx, int *lane_bytes, int *row_lanes)
+static bool pool_shape(const bls_ctx *ctx, int64_t nnz, int *lane_bytes, int *row_lanes)
 {
     const int64_t row_bytes = payload_bytes(ctx->dtype, ctx->D);
     // bytes per lane and row: 16 when the row length allows, unless bls_set_pool_tuning says otherwise
@@ -679,6 +681,14 @@ static bool pool_shape(const bls_ctx *ctx, int *lane_bytes, int *row_lanes)
     if (row_bytes % vb != 0 || row_bytes > 64 * (int64_t)vb) return false;
     int lanes = 1;
     while ((int64_t)lanes * vb < row_bytes) lanes <<= 1;
+    // Rows that one or two lanes cover whole: four lanes with a part each, which stream several segments, or with few rows a segment
+    // pool_rows, whose groups are done after one.  us, pool_rows / four lanes: 8192 bags of 26 tables of 1 to 64 rows, half precision of 16 163 /
+    // 125, of 8 166 / 96, fp32 of 8 155 / 111, 8-bit of 16 185 / 130, of 32 187 / 167; over four owners (8 rows) 108 / 99, 122 / 89, 98 / 91, 130 / 101,
+    // 138 / 126; up to 6 rows (3) 34.6 / 37.8, 32 / 35, 31 / 36, 38.1 / 38.8, 48 / 47; one row 29 / 31, 25 / 28, 25 / 28, 32 / 32, 42 / 39.
+    if (lanes < 4 && (vb < 16 || nnz >= 6 * ctx->nseg || (is_rowq(ctx->dtype) && lanes == 2))) {
+        while (lanes < 4 && vb > 4) { vb >>= 1; lanes <<= 1; }
+        lanes = 4;
+    }
     *lane_bytes = vb;
     *row_lanes = lanes;
     return true;
@@ -689,7 +699,7 @@ static int launch_pool(bls_ctx *ctx, const int64_t *ridx, const float *rw, const
     if (qn == 0) return BLS_OK;                               // a rank that owns no table
     int vb = 0, lanes = 0;
     bool done = false;
-    if (pool_shape(ctx, &vb, &lanes))
+    if (pool_shape(ctx, nnz, &vb, &lanes))
         done = ctx->dtype == BLS_U8_ROWQ ? dispatch_rows<BLS_U8_ROWQ>(ctx, vb, lanes, ridx, rw, segoff, nnz, to, q0, qn, st)
              : ctx->dtype == BLS_F8_ROWQ ? dispatch_rows<BLS_F8_ROWQ>(ctx, vb, lanes, ridx, rw, segoff, nnz, to, q0, qn, st)
              : ctx->dtype == BLS_FP16  ? dispatch_rows<BLS_FP16>(ctx, vb, lanes, ridx, rw, segoff, nnz, to, q0, qn, st)
@@ -753,7 +763,7 @@ static int stores_that_pay(const bls_ctx *ctx, int nv, int64_t nnz)
 static int pool_all_stores(const bls_ctx *ctx, int64_t nnz)
 {
     int vb = 0, lanes = 0;
-    if (!pool_shape(ctx, &vb, &lanes) || ctx->nvec >= (int64_t)1 << 31) return kOneStore;   // 32-bit vector numbers
+    if (!pool_shape(ctx, nnz, &vb, &lanes) || ctx->nvec >= (int64_t)1 << 31) return kOneStore;   // 32-bit vector numbers
     if (lanes < (vb == 16 ? 4 : 128 / vb)) return kOneStore;  // pool_rows, or no kernel of dispatch_lanes
     for (const auto &h : ctx->q_hot)
         if (!h.empty()) return kOneStore;

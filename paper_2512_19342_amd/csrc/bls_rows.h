@@ -97,9 +97,15 @@ template <int DT, int VB> struct Acc {
             const u32x2 sb = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(shard, at + tail, 0, 0));
             r.w[NW] = sb.x; r.w[NW + 1] = sb.y;
         }
-        static_assert(NW == 4);
-        const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(shard, at, 0, 0));
-        r.w[0] = v.x; r.w[1] = v.y; r.w[2] = v.z; r.w[3] = v.w;
+        if constexpr (NW == 4) {
+            const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(shard, at, 0, 0));
+            r.w[0] = v.x; r.w[1] = v.y; r.w[2] = v.z; r.w[3] = v.w;
+        } else if constexpr (NW == 2) {
+            const u32x2 v = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(shard, at, 0, 0));
+            r.w[0] = v.x; r.w[1] = v.y;
+        } else {
+            r.w[0] = __builtin_amdgcn_raw_buffer_load_b32(shard, at, 0, 0);
+        }
         return r;
     }
     // the same from LDS (a row copied there whole, scale and bias included)
