@@ -558,10 +558,12 @@ void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const
         const int64_t mean = nnz / std::max<int64_t>(1, ctx->nseg) + 1;
         int nb = 1;
         while (nb * 2 < G && nb * 2 <= 16 && nb * mean < 192) nb *= 2;
-        // ... but a small batch takes shorter streams (down to some sixty rows) rather than fewer than two
-        // workgroups per compute unit
+        // ... but a small batch takes shorter streams (down to eight rows) rather than fewer than two
+        // workgroups per compute unit.  us a pass, down to sixty / this: 1024 bags of up to 4, 26 tables, half precision of 128 30.7 / 28.8; 1000 of
+        // up to 6, 40 tables of 32 26.9 / 25.7; 3000 of up to 20, 12 tables of 64 8-bit 38.9 / 36.7, half precision 35.2 / 34.0; 300 of up to 2,
+        // 64 tables of 256 39.9 / 39.0; 2048 bags of one, 26 tables of 64 30.5 / 30.8 and 34.3 / 34.1; four workgroups each 34.5
         const int64_t room = 2 * (int64_t)std::max(ctx->compute_units, 1);
-        while (nb > 1 && nb * mean >= 64 && (int64_t)qn * ((ctx->B + nb - 1) / nb) < room * per_block) nb /= 2;
+        while (nb > 1 && nb * mean >= 8 && (int64_t)qn * ((ctx->B + nb - 1) / nb) < room * per_block) nb /= 2;
         if (ctx->tune_segs > 0) nb = ctx->tune_segs;
         nb = std::max(1, std::min(nb, G - 1));
         const int64_t n_max = ctx->B / ctx->P + (ctx->B % ctx->P ? 1 : 0);
