@@ -131,14 +131,15 @@ int bls_set_hot_rows(bls_ctx *ctx, int32_t t, int32_t rank, const int64_t *rows,
  * library's choice); segments_per_group: consecutive segments one lane group streams (1..63, capped
  * at lanes - 1; 0 = chosen from the mean bag length); xcd_map: 1 deals workgroups so that one XCD
  * works on the same tables, 0 plain grid (-1 = library's choice); wide_positions: 1 forces 64-bit
- * row positions (-1 / 0 = only when a shard needs them). */
+ * row positions (-1 / 0 = only when a shard needs them), here and in bls_step_tablewise, and with them the loops that
+ * take rows in batches in place of the ring. */
 int bls_set_pool_tuning(bls_ctx *ctx, int32_t lane_bytes, int32_t segments_per_group, int32_t xcd_map,
                         int32_t wide_positions);
 
 /* Form of bls_plan, for tests and experiments; results are the same bit for bit.
  * scan_while_placing = 0: always three launches (count, scan, place).  -1 or 1: fewer where the
  * problem allows it.  Table-wise with at most 2048 runs (pairs of an (owner, table) and a
- * requester) and at most 2^22 lookups: one launch, every workgroup works the run starts out for
+ * requester) and at most 2^22 lookups (2^24 with at most 256 runs): one launch, every workgroup works the run starts out for
  * itself from the offsets at the run edges.  Row-wise with at most eight ranks and batches below 2^32 lookups: two launches,
  * every placing workgroup adds the tile counts up for itself instead of reading a scanned array. */
 int bls_set_plan_tuning(bls_ctx *ctx, int32_t scan_while_placing);

@@ -5,8 +5,8 @@
 // is fetched with one load per lane and consecutive lanes read consecutive addresses.
 // G*VB covers the row: a 512-byte row is read by a whole wavefront with 8 bytes per lane
 // or by half a wavefront with 16.  The group first loads up to G of its row numbers with
-// one coalesced load, then walks them U at a time: U independent row loads are issued
-// before the first add so that many rows are in flight per lane, and the adds follow in
+// one coalesced load, then walks them with U independent row loads in flight per lane: as a ring
+// (RING), or U at a time, all of them waited for before the first add.  The adds follow in
 // segment order, which keeps the fp32 result identical to a sequential sum.
 //
 // Bags are short (tens of rows), so a group does not stop at one: it streams the rows of
