@@ -532,14 +532,15 @@ __global__ __launch_bounds__(kThreads) void pool_rows_generic(DevDesc dd, const 
 // vectors of 128, batch / ring, by rows a segment and MB of vectors.  fp32: 32 rows, 134 MB 483 / 458, 32 of 64 floats 296 / 266, of
 // 32 195 / 169, 8 rows, 250 MB 352 / 346, 2 of 64 floats 231 / 238, 1 row, 800 MB 399 / 408.  Half precision: 32 rows, 134 MB
 // 355 / 321, 8, 800 MB 944 / 937, 4, 800 MB 541 / 545, staged 1024 / 1040.  8-bit: 32 rows, 134 MB 377 / 341, 250 MB
-// 585 / 574, 8, 250 MB 310 / 312, 1 row, 800 MB 648 / 672.  What fits the memory-side cache gains from one row on: 60 MB, fp32,
-// 1 to 4 rows 74 / 73, 8 rows 114 / 110, 8-bit 2.5 rows 74 / 73.  Weights cost the batch a wavefront per SIMD (87
+// 585 / 574, 8, 250 MB 310 / 312, 1 row, 800 MB 648 / 672.  What fits the memory-side cache gains from one row on, 8-bit rows from two: 60 MB, fp32,
+// 1 to 4 rows 74 / 73, 8 rows 114 / 110, 8-bit 2.5 rows 74 / 73, staged 85 MB of one row 137 / 141.  Lanes of 8 and 4 bytes, 32 rows: half precision of
+// 100 367 / 315, weighted 289 / 243, of 180 593 / 502, fp32 of 33 456 / 294, staged 246 / 167, of 62 366 / 320, 8-bit of 100 431 / 402.  Weights cost the batch a wavefront per SIMD (87
 // registers; 80 here): fp32 1 row, 250 MB 202 / 196, 4 rows 220 / 209, 800 MB 611 / 587; half precision 4 rows 198 / 195.
 static bool ring_pays(const bls_ctx *ctx, bool weighted, int64_t nnz, int qn)
 {
     const int64_t rows = is_rowq(ctx->dtype) ? 12 : !weighted ? 8 : ctx->dtype == BLS_FP16 ? 4 : 2;
     if (nnz >= rows * ctx->nseg) return true;
-    return nnz >= ctx->nseg && (int64_t)qn * ctx->B * ctx->D * 4 <= (int64_t)96 << 20;
+    return nnz >= (is_rowq(ctx->dtype) ? 2 : 1) * ctx->nseg && (int64_t)qn * ctx->B * ctx->D * 4 <= (int64_t)96 << 20;
 }
 // Four workgroups per compute unit keep the memory busy in a ring, and more of them only share the caches: the kernels, which would
 // run with five to seven, ask for LDS that they do not use.  us, as many as fit / four / three: fp32 rows of 128, 134 MB of vectors 463 / 458 / 456,
@@ -617,9 +618,7 @@ void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const
             kernel<<<grid, kThreads, ring ? kRingLds : 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, to.Y, to.S, to.R, to.slot, nb, chunks, deal, q0, qn);
         };
         auto pick = [&](auto weighted, auto stores) {
-            if constexpr (VB == 16 || G <= 16) {
-                if (ring) return launch(pool_stream<G, DT, VB, UU, false, weighted(), true, stores()>);
-            }
+            if (ring) return launch(pool_stream<G, DT, VB, UU, false, weighted(), true, stores()>);
             if (wide) launch(pool_stream<G, DT, VB, UU, true, weighted(), false, stores()>);
             else launch(pool_stream<G, DT, VB, UU, false, weighted(), false, stores()>);
         };

@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
 # lanes of a row: 4, 8, 16, 32, 64 (64: whole-wavefront groups), and rows whose last lanes idle
 SHAPES = [("fp32", D) for D in (16, 32, 64, 100, 128, 256)] + [("fp16", D) for D in (32, 64, 128, 200, 512)] + [
     (dt, D) for dt in ("u8rq", "f8rq") for D in (64, 112, 128, 512)]
+SHAPES += [("fp32", D) for D in (33, 62)] + [("fp16", D) for D in (36, 100, 180)] + [("u8rq", D) for D in (72, 100, 200)]   # wide groups of 4 and 8 bytes a lane
 # rows of less than 64 bytes: four, eight and sixteen lanes of 4 or 8 bytes each, or one and two of 16 with few rows a segment
 SHAPES += [("fp32", D) for D in (1, 2, 4, 5, 8, 10, 15)] + [("fp16", D) for D in (2, 8, 10, 16, 18, 20, 28)] + [
     (dt, D) for dt in ("u8rq", "f8rq") for D in (4, 16, 20, 32, 40, 60)]
