@@ -128,3 +128,38 @@ def test_one_launch_step_ring(dt, D, bag):
         with pytest.raises(B.BlsError):
             pipe.ctx.bls_check()
         assert (bits(out.cpu().numpy()) == bits(want)).all()
+
+
+@pytest.mark.parametrize("rows", [8388599, 8388600], ids=["the largest shard of a ring", "one row more"])
+def test_shards_that_end_where_32_bit_offsets_do(rows):
+    """Rows of 512 bytes on both sides of 2 GB and at the shard's end, one and twelve a bag, and an index just past it."""
+    import paper_2512_19342_amd as B
+    from types import SimpleNamespace
+    from paper_2512_19342_amd.runner import Pipeline
+    P, n = 2, 64
+    tab = torch.zeros(rows, 128, device="cuda")
+    at = torch.tensor([0, 1, 4194303, 4194304, rows // 2, rows - 2, rows - 1])
+    vals = torch.from_numpy(np.random.default_rng(rows).standard_normal((len(at), 128)).astype(np.float32))
+    tab[at.cuda()] = vals.cuda()
+    w = SimpleNamespace(P=P, T=1, D=128, k=1, B=n, rows=[rows], table_owner=[1], table_dtype="fp32", part_kind=B.BLS_TABLE_WISE)
+    pipe = Pipeline(w, [tab], 12 * n)
+    for per in (1, 12):
+        pick = torch.from_numpy(np.random.default_rng(per).integers(0, len(at), n * per))
+        off = torch.arange(n + 1) * per
+        want = np.zeros((n, 128), np.float32)
+        for j in range(per):
+            want += vals[pick.view(n, per)[:, j]].numpy()
+        out = pipe.new_out()
+        j, _ = pipe.issue_fused(at[pick].cuda(), off.cuda(), n * per)
+        pipe.complete(j, out)
+        pipe.ctx.bls_check()
+        assert (bits(out.cpu().numpy().reshape(n, 128)) == bits(want)).all(), per
+        pipe.step_one_launch(at[pick].cuda(), off.cuda(), n * per, out)
+        pipe.ctx.bls_check()
+        assert (bits(out.cpu().numpy().reshape(n, 128)) == bits(want)).all(), per
+    past = torch.full((n,), rows)
+    j, _ = pipe.issue_fused(past.cuda(), torch.arange(n + 1).cuda(), n)
+    pipe.complete(j, out)
+    with pytest.raises(B.BlsError):
+        pipe.ctx.bls_check()
+    assert not out.any()
