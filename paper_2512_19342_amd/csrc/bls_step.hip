@@ -191,7 +191,15 @@ __global__ __launch_bounds__(kThreads, (WIDE ? 1 : kWavesHeld<G, DT>)) void step
         place = dst + at_run;
         const int64_t sg = (int64_t)dd.nsum[d] * dd.B + (int64_t)dd.n_loc[d] * f + (int64_t)(q - dd.nsum[d]) * n + b_loc;
         if (li == 0) segoff[sg] = place;
-        if (place < 0 || place + len > nnz) { if (li == 0) flag_error(dd); len = 0; }
+        if (place < 0 || place + len > nnz) {                 // run edges that decrease: the bag is empty, and its rows are dropped
+            if (li == 0) flag_error(dd);
+            len = 0;
+            here = ahead = -1;
+            if constexpr (!WIDE) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[u] = A::none();
+            }
+        }
     }
 
     // 5. a block's lookups to their places on the owner's side, its rows added in order.  A ring of U rows in flight as in

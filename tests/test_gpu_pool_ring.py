@@ -130,6 +130,35 @@ def test_one_launch_step_ring(dt, D, bag):
         assert (bits(out.cpu().numpy()) == bits(want)).all()
 
 
+@pytest.mark.parametrize("dt,D", [("fp32", 16), ("fp32", 64), ("fp16", 64), ("fp16", 256), ("u8rq", 16), ("u8rq", 128), ("f8rq", 64)], ids=str)
+def test_bags_past_the_lookups_are_empty(dt, D):
+    """A run edge that lies past the next one makes the runs longer than the lookups there are: the bags that no longer fit are
+    empty, whatever their neighbours of the same wavefront still have, and the error is raised."""
+    import paper_2512_19342_amd as B
+    w, tabs, pipes = make(dt, D, 0, (3, 9))
+    ix, off = synth.make_batch(w, 3)
+    nnz, n = int(off[-1]), w.B
+    past = 11                                                 # table 2 starts behind table 3
+    boff = off.clone()
+    boff[2 * n] = int(off[3 * n]) + past
+    outs = []
+    for pipe in pipes:
+        out = pipe.new_out().fill_(float("nan"))
+        j = pipe.step_one_launch(ix.cuda(), boff.cuda(), nnz, out)
+        with pytest.raises(B.BlsError) as e:
+            pipe.ctx.bls_check()
+        assert e.value.code == B.BLS_ERANGE
+        outs.append([t.cpu().numpy().reshape(-1).copy() for t in (pipe.pooled, pipe.send, pipe.slot_view(j % pipe.ctx.K), out)])
+        starts = pipe.segoff.cpu().numpy()[:w.T * n + 1]      # in the send order
+    assert starts[-1] > nnz                                   # what the runs add up to
+    for a, b in zip(*outs):
+        assert (bits(a) == bits(b)).all()
+    over = (starts[1:] > nnz) & (starts[1:] > starts[:-1])
+    assert over.any() and not over.all()
+    for S in (o[1] for o in outs):
+        assert not S.reshape(-1, D)[over].any() and S.reshape(-1, D)[~over].any()
+
+
 @pytest.mark.parametrize("rows", [8388599, 8388600], ids=["the largest shard of a ring", "one row more"])
 def test_shards_that_end_where_32_bit_offsets_do(rows):
     """Rows of 512 bytes on both sides of 2 GB and at the shard's end, one and twelve a bag, and an index just past it."""
