@@ -139,7 +139,7 @@ int bls_set_pool_tuning(bls_ctx *ctx, int32_t lane_bytes, int32_t segments_per_g
 /* Form of bls_plan, for tests and experiments; results are the same bit for bit.
  * scan_while_placing = 0: always three launches (count, scan, place).  -1 or 1: fewer where the
  * problem allows it.  Table-wise with at most 2048 runs (pairs of an (owner, table) and a
- * requester) and at most 2^22 lookups (2^24 with at most 256 runs): one launch, every workgroup works the run starts out for
+ * requester) and at most 2^22 lookups (10 * 2^20 with at most 256 runs): one launch, every workgroup works the run starts out for
  * itself from the offsets at the run edges.  Row-wise with at most eight ranks and batches below 2^32 lookups: two launches,
  * every placing workgroup adds the tile counts up for itself instead of reading a scanned array. */
 int bls_set_plan_tuning(bls_ctx *ctx, int32_t scan_while_placing);

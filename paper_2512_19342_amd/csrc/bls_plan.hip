@@ -1027,16 +1027,18 @@ int bls_launch_plan(bls_ctx *ctx, const int64_t *idx, const int64_t *off, int64_
     int64_t *segoff_end = segoff + ctx->nseg;
     const dim3 tgrid(tg.tiles, (unsigned)(ctx->T * ctx->P));
 
-    // Table-wise batches that are not too large in one launch: up to 2^22 lookups, and up to 2^24 where a thread scans one run.  us a
-    // fused iteration with vectors of 16, three launches / one: 5.5 M lookups in 91 runs 101 / 94, 8.1 M in 4 119 / 111, 8.5 M in 256
-    // 113.5 / 109, in 128 111 / 105, 14.9 M in 160 192 / 191, 16.1 M in 104 263 / 260, 28 M in 40 427 / 427; in 1600 200 / 230, in
-    // 512 8.4 M 147 / 148, 34 M 487 / 499.
+    // Table-wise batches that are not too large in one launch: up to 2^22 lookups, and up to 10 * 2^20 where a thread scans one run.  us a
+    // fused iteration with vectors of 16, three launches / one: 5.5 M lookups in 91 runs 101 / 94, 8.1 M in 4 119 / 113, 8.5 M in 256
+    // 113 / 110, in 128 111 / 105, 13.5 M in 256, tables with bags of 100 and of one, 224 / 225 (staged, with the exchange's order 295 / 310), 14.9 M in
+    // 160 192 / 194, 16.1 M in 104 263 / 260, 28 M in 40 427 / 427; in 1600 200 / 230, in 512 8.4 M 147 / 148, 34 M 487 / 499.
     const int64_t runs = (int64_t)ctx->Q * ctx->P;
-    if (!rowwise && runs <= kMaxRuns && nnz <= ((int64_t)1 << (runs <= kThreads ? 24 : 22)) && ctx->tune_plan_scan != 0) {
-        // every workgroup pays for the scan of the run edges: about two thousand workgroups in all, none
-        // with less than 2048 lookups or bags to work on
+    if (!rowwise && runs <= kMaxRuns && nnz <= (int64_t)(runs <= kThreads ? 10 : 4) << 20 && ctx->tune_plan_scan != 0) {
+        // every workgroup pays for the scan of the run edges: about four thousand workgroups in all, none with less than 2048 lookups or
+        // bags to work on.  Beyond 2^22 lookups a run gets as many as the three launches give it, for a run's workgroups
+        // copy all of it and tables differ: 16384 samples, one table with bags of 512, 31 with bags of one, eight owners, three launches / 2048
+        // workgroups in all / this 462 / 487 / 440; of 400, 63 of one, two owners 460 / 514 / 438.
         const int64_t per_run = std::max<int64_t>(nnz / runs, n_max) + 1;
-        const int64_t want = (2048 + runs - 1) / runs;
+        const int64_t want = std::max<int64_t>((4096 + runs - 1) / runs, nnz > (int64_t)1 << 22 ? 256 : 1);
         const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, (per_run + 2047) / 2048));
         plan_runs_one_launch<<<dim3(gx, (unsigned)runs), kThreads, 0, st>>>(dd, idx, off, nnz, sendcounts, sdispls, recvcounts, rdispls,
                                                                              segoff, ridx, perm, w_in, w_out);

@@ -233,7 +233,7 @@ def test_tablewise_plan_in_three_launches(spec):
 
 @pytest.mark.parametrize("P,T,B,hi", [(2, 2, 5000, 900), (2, 1, 9000, 4000), (1, 300, 64, 500)])
 def test_tablewise_plan_of_millions_of_lookups(P, T, B, hi):
-    """Past 2^22 lookups one launch plans for up to 256 runs, several workgroups a run, up to 2^24; beyond either, three."""
+    """Past 2^22 lookups one launch plans for up to 256 runs, several workgroups a run, up to 10 * 2^20; beyond either, three."""
     w = synth.custom("many", k=1, values="grid", seed=9, P=P, T=T, D=4, B=B, part_kind=0, rows=[50] * T, bag=("uniform", 0, hi))
     tabs = [synth.make_table(w, t) for t in range(w.T)]
     batches = [synth.make_batch(w, 0)]

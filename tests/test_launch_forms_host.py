@@ -1,0 +1,75 @@
+"""Which kernel a call launches, and on how many workgroups, without a GPU: the few HIP runtime calls are replaced by a library
+that notes the launches, and the kernels' names as the library registers them."""
+from tests import test_exchange_host as host
+
+NAMES = r"""
+static const void *known[2048];
+static const char *called[2048];
+static int n_known;
+void __hipRegisterFunction(void **m, const void *f, char *d, const char *name, unsigned l, void *a, void *b, void *c, void *e, int *w)
+{
+    if (n_known < 2048) { known[n_known] = f; called[n_known++] = name; }
+}
+char kernel[1024];                      /* of the latest launch, as the compiler spells it */
+unsigned grid_x, lds_bytes;
+static void look(const void *f, unsigned x, size_t sh)
+{
+    const char *s = "?";
+    for (int i = 0; i < n_known; ++i) if (known[i] == f) s = called[i];
+    int k = 0;
+    while (s[k] && k < 1023) { kernel[k] = s[k]; ++k; }
+    kernel[k] = 0;
+    grid_x = x;
+    lds_bytes = (unsigned)sh;
+}
+int hipLaunchKernel("""
+
+LOOK = r"""
+import re, subprocess
+x, y, lds = (C.c_uint.in_dll(stub, n) for n in ("grid_x", "grid_y", "lds_bytes"))
+def kernel():                                                 # "pool_stream<16, 0, ...>"
+    name = C.string_at(C.addressof(C.c_char.in_dll(stub, "kernel")))
+    name = subprocess.run(["c++filt"], input=name, capture_output=True).stdout.decode().replace("(anonymous namespace)::", "")
+    return re.match(r"(?:void )?([^<(]*(?:<.*?>(?=\())?)", name)[1]
+def config(P, T, D, B, dtype=0, part=0, rows=9, k=1):
+    h = vp()
+    assert L.bls_create(C.byref(Config(P, T, D, k, B, dtype, part, (C.c_int64 * T)(*[rows] * T), (C.c_int32 * T)(*[t % P for t in range(T)]))), C.byref(h)) == 0
+    for t in range(T):
+        for d in [t % P] if part == 0 else range(P):
+            a, n = C.c_int64(), C.c_int64()
+            assert L.bls_shard_range(h, t, d, C.byref(a), C.byref(n)) == 0
+            if n.value: assert L.bls_set_shard(h, t, d, at(1), n) == 0
+    n = C.c_size_t()
+    assert L.bls_desc_bytes(h, C.byref(n)) == 0 and L.bls_commit(h, at(2), n, None) == 0
+    assert L.bls_set_ring(h, at(3), C.c_size_t(1 << 44)) == 0
+    return h
+def plan(h, nnz):
+    stub.forget()
+    assert L.bls_plan(h, at(4), at(5), C.c_int64(nnz), at(6), at(7), at(8), at(9), at(10), at(11), None, at(12), C.c_size_t(1 << 40), None) == 0
+    return C.string_at(C.addressof(noted)).decode().count("L")
+"""
+
+
+def run(tmp_path, monkeypatch, body):
+    runtime = host.RUNTIME.replace("int hipLaunchKernel(", NAMES).replace("grid_y = g.y;", "grid_y = g.y; look(f, g.x, sh);")
+    assert runtime.count("look(") == 2
+    monkeypatch.setattr(host, "RUNTIME", runtime)
+    return host.run(tmp_path, LOOK + body)
+
+
+def test_a_runs_workgroups_in_a_plan_of_one_launch(tmp_path, monkeypatch):
+    """Tables differ in their bags, and a run's workgroups copy all of it: past 2^22 lookups a run gets no fewer of them than the
+    three launches give it, below about four thousand in all."""
+    run(tmp_path, monkeypatch, r"""
+for P, T, B, nnz in ((8, 32, 16384, 8_900_000), (2, 64, 16384, 7_600_000), (8, 26, 16384, 5_700_000), (8, 32, 16384, 10 << 20), (1, 4, 40000, 8_100_000),
+                     (1, 300, 64, 1 << 22), (8, 32, 4096, 1 << 22), (4, 26, 2048, 53248), (8, 200, 512, 1 << 20)):
+    h = config(P, T, 16, B)
+    runs = P * T
+    assert L.bls_set_plan_tuning(h, 0) == 0 and plan(h, nnz) == 3 and kernel() == "plan_place_runs"
+    three = x.value
+    assert L.bls_set_plan_tuning(h, -1) == 0 and plan(h, nnz) == 1 and kernel() == "plan_runs_one_launch" and y.value == runs
+    assert x.value >= (three if nnz > 1 << 22 else min(three, -(-4096 // runs))), (P, T, B, nnz, x.value, three)
+for P, T, nnz, launches in ((8, 32, (10 << 20) + 1, 3), (1, 300, (1 << 22) + 1, 3), (8, 300, 1 << 20, 3)):
+    h = config(P, T, 16, 4096)
+    assert plan(h, nnz) == launches, (P, T, nnz)
+""")
