@@ -22,11 +22,12 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kMaxRuns = 2048;                 // runs (q, s) whose starts one workgroup scans in LDS
 // Rows of a group in flight, and wavefronts per SIMD the kernel is held to (1: as it comes): what is best with long bags among those that
-// cost short ones nothing.  us, 26 tables, as it was / eight rows / this: half precision of 64, 2048 bags of one 23.4 / 24.0 / 23.1, 512 of 1
-// to 100 32.2 / 24.6 / 27.6; fp32 of 128, 4096 bags of up to 4, without the bound 92 / 96 / 91; 8-bit of 128 86 / 88 / 85;
-// 8-bit, 4 tables of 64, 4096 bags of 1 to 100, with a bound of five 51 / 34 / 32.
+// cost short ones nothing.  us, 26 tables.  Half precision of 64, batches of eight / a ring of eight / of four: 2048 bags of one 23.4 / 24.5 /
+// 23.4, 512 of 1 to 100 32.2 / 24.3 / 27.1.  Held / as it comes, 4096 bags of up to 4, then 512 of 1 to 100: fp32 of 128 91 / 96, 43.2 / 42.6, of 64
+// 43.0 / 45.6, 29.9 / 29.5; half precision of 128 67 / 72, 32.7 / 32.7; 8-bit of 128 86 / 88, 44.2 / 42.9, e4m3 86 / 88, 40.5 / 41.7.  Eight lanes of fp32 hold more
+// registers than six wavefronts leave (two spilled): of 32, six / five, 2048 bags of one 18.8 / 18.3, 512 of 1 to 100 22.3 / 21.9.
 template <int G, int DT> constexpr int kRows = is_rowq(DT) || (DT == BLS_FP16 && G == 8) ? 4 : 8;
-template <int G, int DT> constexpr int kWavesHeld = DT == BLS_FP32 ? 6 : DT == BLS_FP16 ? (G < 16 ? 5 : 6) : G == 8 ? 5 : 1;
+template <int G, int DT> constexpr int kWavesHeld = DT == BLS_FP32 ? (G == 8 ? 5 : 6) : DT == BLS_FP16 ? (G < 16 ? 5 : 6) : G == 8 ? 5 : 1;
 
 __device__ __forceinline__ void flag_error(const DevDesc &dd) { atomicOr(dd.err, 1); }
 

@@ -34,7 +34,12 @@ def test_pooling_kernels_spill_only_where_it_was_measured(kernels):
     pools = {n: k for n, k in kernels.items() if n.startswith("pool_")}
     assert len(pools) > 100
     spilling = {n for n, k in pools.items() if k[".private_segment_fixed_size"] or k.get(".vgpr_spill_count")}
-    assert all(re.match(r"pool_stream<32, 1, 16, 8, false, false, ", n) for n in spilling), spilling
+    assert all(re.match(r"pool_stream<32, 1, 16, 8, false, false, false, [123]>", n) for n in spilling), spilling   # not the ring
+
+
+def test_one_launch_steps_do_not_spill(kernels):
+    steps = {n: k for n, k in kernels.items() if n.startswith("step_tablewise<")}
+    assert len(steps) == 56 and not [n for n, k in steps.items() if k[".private_segment_fixed_size"] or k.get(".vgpr_spill_count")]
 
 
 def test_three_stores_keep_the_plain_kernels_wavefronts(kernels):
