@@ -49,13 +49,13 @@ __device__ __forceinline__ int run_entry(const DevDesc &dd, int q, int s)
 }
 
 // grid: x over (requester s, chunk of its mini-batch), y = q.  G lanes per bag, 16 bytes of a row per lane.
-// WIDE: some shard is too large for 32-bit offsets; rows are then taken in batches through 64-bit addresses.
+// BATCH: rows in batches through 64-bit addresses, where some shard is too large for 32-bit offsets and where bags are short (ring_rows).
 // What bounds it is the chain from offsets to lookups to rows, and how many rows a group has in flight along a bag: the chain's
 // start runs beside the count of the runs, and rows are read in a ring.  us a step, counted first and rows in
 // batches of eight / this: 26 tables of 64, 512 bags of 1 to 100 41 / 37 (fp32), 32 / 28 (half precision), 52 / 38 (8-bit);
 // 64 tables of 128, 2048 bags of 1 to 40 280 / 276, 211 / 204, 214 / 211; eight tables of 16, 128 bags of one 9.3 / 9.1.
-template <int G, int DT, bool WIDE>
-__global__ __launch_bounds__(kThreads, (WIDE ? 1 : kWavesHeld<G, DT>)) void step_tablewise(DevDesc dd, const int64_t *__restrict__ idx,
+template <int G, int DT, bool BATCH>
+__global__ __launch_bounds__(kThreads, (BATCH ? 1 : kWavesHeld<G, DT>)) void step_tablewise(DevDesc dd, const int64_t *__restrict__ idx,
                                                            const int64_t *__restrict__ off, int64_t nnz,
                                                            int64_t *__restrict__ sendcounts, int64_t *__restrict__ sdispls,
                                                            int64_t *__restrict__ recvcounts, int64_t *__restrict__ rdispls,
@@ -104,14 +104,14 @@ __global__ __launch_bounds__(kThreads, (WIDE ? 1 : kWavesHeld<G, DT>)) void step
         }
     }
     constexpr int kU = kRows<G, DT>, U = kU < G ? kU : G;     // rows in flight
-    const __amdgpu_buffer_rsrc_t shard = shard_buffer(dd.q_base[q], WIDE ? 0u : (uint32_t)rows * row_stride);
+    const __amdgpu_buffer_rsrc_t shard = shard_buffer(dd.q_base[q], BATCH ? 0u : (uint32_t)rows * row_stride);
     const char *__restrict__ base = (const char *)dd.q_base[q] + (col_ok ? (uint32_t)li * 16 : 0u);
     const uint32_t col = col_ok ? (uint32_t)li * 16 : 0u;
     auto ask = [&](int64_t c0) -> int64_t { return c0 + li < len ? idx[beg + c0 + li] : -1; };
     auto offset = [&](int64_t r) -> uint32_t { return (uint64_t)r < (uint64_t)rows ? (uint32_t)r * row_stride : kPastEnd; };
     int64_t here = ask(0), ahead = ask(G);                    // this lane's lookup of a block, and of the next
     typename A::Raw v[U];
-    if constexpr (!WIDE) {
+    if constexpr (!BATCH) {
         const uint32_t mine = offset(here);
 #pragma unroll
         for (int u = 0; u < U; ++u) v[u] = A::load_buffer(shard, (uint32_t)__shfl((int)mine, gbase + u, 64) + col, tail);
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(kThreads, (WIDE ? 1 : kWavesHeld<G, DT>)) void step
             if (li == 0) flag_error(dd);
             len = 0;
             here = ahead = -1;
-            if constexpr (!WIDE) {
+            if constexpr (!BATCH) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) v[u] = A::none();
             }
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(kThreads, (WIDE ? 1 : kWavesHeld<G, DT>)) void step
     };
     A acc;
     acc.zero();
-    if constexpr (!WIDE) {
+    if constexpr (!BATCH) {
         put(0, here);
         uint32_t mine = offset(here);
         for (int64_t at = 0; __any(at < len); at += U) {
@@ -265,21 +265,35 @@ __global__ __launch_bounds__(kThreads, (WIDE ? 1 : kWavesHeld<G, DT>)) void step
     }
 }
 
-template <int DT, bool WIDE>
+template <int DT, bool BATCH>
 bool dispatch(const bls_ctx *ctx, int lanes, dim3 grid, hipStream_t st, const int64_t *idx, const int64_t *off, int64_t nnz,
               int64_t *sc, int64_t *sd, int64_t *rc, int64_t *rd, int64_t *ridx, int64_t *segoff, int64_t *perm, float *Y,
               float *S, float *R, float *out, uint32_t chunks)
 {
     switch (lanes) {
-    case 1: step_tablewise<1, DT, WIDE><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
-    case 2: step_tablewise<2, DT, WIDE><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
-    case 4: step_tablewise<4, DT, WIDE><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
-    case 8: step_tablewise<8, DT, WIDE><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
-    case 16: step_tablewise<16, DT, WIDE><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
-    case 32: step_tablewise<32, DT, WIDE><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
-    case 64: step_tablewise<64, DT, WIDE><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
+    case 1: step_tablewise<1, DT, BATCH><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
+    case 2: step_tablewise<2, DT, BATCH><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
+    case 4: step_tablewise<4, DT, BATCH><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
+    case 8: step_tablewise<8, DT, BATCH><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
+    case 16: step_tablewise<16, DT, BATCH><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
+    case 32: step_tablewise<32, DT, BATCH><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
+    case 64: step_tablewise<64, DT, BATCH><<<grid, kThreads, 0, st>>>(ctx->desc, idx, off, nnz, sc, sd, rc, rd, ridx, segoff, perm, Y, S, R, out, chunks); return true;
     }
     return false;
+}
+
+// Rows a bag from which the ring is the faster form.  A ring asks for at least twice U rows whatever a bag has, and a step of short bags is
+// made of such requests: they are answered without an access, but take their turn.  With a workgroup or less for each compute
+// unit nobody waits for it, and the longest bag's chain decides.  us, before the ring came / ring / batches, 26 tables, 2048 bags: fp32 of 128, of
+// one row 40.9 / 42.0 / 34.2, 5 44.0 / 44.1 / 38.3, 12 64.8 / 67.2 / 59.0, 1024 of 16 37.8 / 37.0 / 36.2, of 24 44.5 / 43.8 / 44.5; of 32,
+// one row 18.3 / 18.2 / 14.8, 1024 of 24 21.6 / 19.2 / 20.0; of 16, one row 13.2 / 12.3 / 11.7, 3 15.3 / 13.3 / 13.5; half precision of 128, one
+// row 34.6 / 36.5 / 34.1, 8 39.2 / 41.7 / 40.8, 12 43.3 / 45.3 / 43.5, of 64, one row 23.4 / 23.1 / 20.5, 12 27.8 / 27.8 / 25.7, 1024 of 16 21.2 / 20.3 /
+// 20.9; 8-bit of 128, one row 49.0 / 47.6 / 46.3, 8 53.5 / 51.5 / 52.6.  Few workgroups: four tables of 64, 512 bags of up to 15 9.3 / 8.9 / 9.3.
+int64_t ring_rows(int dtype, int lanes)
+{
+    if (lanes < 4) return 0;
+    if (lanes == 4) return 3;
+    return dtype == BLS_FP32 ? 16 : dtype == BLS_FP16 ? 13 : 4;
 }
 
 }  // namespace
@@ -302,11 +316,11 @@ int bls_launch_step_tablewise(bls_ctx *ctx, const int64_t *idx, const int64_t *o
     const uint64_t gx = (uint64_t)chunks * ctx->P;
     if (gx > 0x7fffffffull) return bls_fail(ctx, BLS_EINVAL, "bls_step_tablewise: batch too large for one launch");
     const dim3 grid((unsigned)gx, (unsigned)ctx->Q);
-    // a shard's bytes as 32-bit offsets, unless one is too large for them
-    bool wide = ctx->tune_wide == 1;
-    for (int q = 0; q < ctx->Q; ++q) wide = wide || ctx->q_rows[q] >= (int64_t)kPastEnd / stride_bytes(ctx->dtype, ctx->D);
+    // in a ring unless a shard is too large for 32-bit offsets, or bags are short and there are workgroups for every compute unit
+    bool batch = ctx->tune_wide == 1 || (ctx->tune_wide != 0 && nnz < ring_rows(ctx->dtype, lanes) * ctx->nseg && (int64_t)gx * ctx->Q > ctx->compute_units);
+    for (int q = 0; q < ctx->Q; ++q) batch = batch || ctx->q_rows[q] >= (int64_t)kPastEnd / stride_bytes(ctx->dtype, ctx->D);
     auto go = [&](auto dt) -> bool {
-        return wide ? dispatch<dt(), true>(ctx, lanes, grid, st, idx, off, nnz, sendcounts, sdispls, recvcounts, rdispls, ridx, segoff, perm, Y, S, R, out, chunks)
+        return batch ? dispatch<dt(), true>(ctx, lanes, grid, st, idx, off, nnz, sendcounts, sdispls, recvcounts, rdispls, ridx, segoff, perm, Y, S, R, out, chunks)
                     : dispatch<dt(), false>(ctx, lanes, grid, st, idx, off, nnz, sendcounts, sdispls, recvcounts, rdispls, ridx, segoff, perm, Y, S, R, out, chunks);
     };
     const bool ok = ctx->dtype == BLS_FP16    ? go(std::integral_constant<int, BLS_FP16>())

@@ -47,6 +47,9 @@ def plan(h, nnz):
     stub.forget()
     assert L.bls_plan(h, at(4), at(5), C.c_int64(nnz), at(6), at(7), at(8), at(9), at(10), at(11), None, at(12), C.c_size_t(1 << 40), None) == 0
     return C.string_at(C.addressof(noted)).decode().count("L")
+def step(h, nnz):
+    assert L.bls_step_tablewise(h, at(4), at(5), C.c_int64(nnz), at(6), at(7), at(8), at(9), at(10), at(11), None, at(13), at(14), at(15), None, None) == 0
+    return kernel()
 """
 
 
@@ -72,4 +75,26 @@ for P, T, B, nnz in ((8, 32, 16384, 8_900_000), (2, 64, 16384, 7_600_000), (8, 2
 for P, T, nnz, launches in ((8, 32, (10 << 20) + 1, 3), (1, 300, (1 << 22) + 1, 3), (8, 300, 1 << 20, 3)):
     h = config(P, T, 16, 4096)
     assert plan(h, nnz) == launches, (P, T, nnz)
+""")
+
+
+def test_the_one_launch_step_takes_short_bags_in_batches(tmp_path, monkeypatch):
+    """Either side of every line: rows a bag by storage and lanes, workgroups, and shards at the end of 32-bit offsets."""
+    run(tmp_path, monkeypatch, r"""
+fp32, fp16, u8, f8 = 0, 1, 2, 3
+for dtype, D, lanes, rows in ((fp32, 128, 32, 16), (fp32, 20, 8, 16), (fp32, 16, 4, 3), (fp32, 8, 2, 0), (fp32, 4, 1, 0), (fp16, 64, 8, 13), (fp16, 200, 32, 13),
+                              (fp16, 32, 4, 3), (fp16, 16, 2, 0), (u8, 128, 8, 4), (f8, 112, 8, 4), (u8, 64, 4, 3), (f8, 32, 2, 0)):
+    for P, T, B in ((4, 26, 2048), (1, 1, 256 * 256 // lanes + 1)):   # many workgroups, and one more than there are compute units
+        h = config(P, T, D, B, dtype)
+        for nnz, batch in ((rows * T * B, "false"), (rows * T * B - 1, "true"), (T * B if rows > 1 else 0, "true" if rows else "false")):
+            if nnz < 0: continue
+            assert step(h, nnz) == f"step_tablewise<{lanes}, {dtype}, {batch}>", (dtype, D, P, nnz, kernel())
+            for tuned, batch in ((0, "false"), (1, "true")):
+                assert L.bls_set_pool_tuning(h, 0, 0, -1, tuned) == 0 and step(h, nnz) == f"step_tablewise<{lanes}, {dtype}, {batch}>"
+            assert L.bls_set_pool_tuning(h, 0, 0, -1, -1) == 0
+    h = config(1, 1, D, 256 * 256 // lanes, dtype)
+    assert step(h, 1) == f"step_tablewise<{lanes}, {dtype}, false>"
+for rows, batch in ((0xfffff000 // 512 - 1, "false"), (0xfffff000 // 512, "true")):
+    h = config(2, 2, 128, 64, fp32, rows=rows)
+    assert step(h, 6400) == f"step_tablewise<32, 0, {batch}>", rows
 """)
