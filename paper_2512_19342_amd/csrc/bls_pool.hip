@@ -532,15 +532,17 @@ __global__ __launch_bounds__(kThreads) void pool_rows_generic(DevDesc dd, const 
 // vectors of 128, batch / ring, by rows a segment and MB of vectors.  fp32: 32 rows, 134 MB 483 / 458, 32 of 64 floats 296 / 266, of
 // 32 195 / 169, 8 rows, 250 MB 352 / 346, 2 of 64 floats 231 / 238, 1 row, 800 MB 399 / 408.  Half precision: 32 rows, 134 MB
 // 355 / 321, 8, 800 MB 944 / 937, 4, 800 MB 541 / 545, staged 1024 / 1040.  8-bit: 32 rows, 134 MB 377 / 341, 250 MB
-// 585 / 574, 8, 250 MB 310 / 312, 1 row, 800 MB 648 / 672.  What fits the memory-side cache gains from one row on, 8-bit rows from two: 60 MB, fp32,
-// 1 to 4 rows 74 / 73, 8 rows 114 / 110, 8-bit 2.5 rows 74 / 73, staged 85 MB of one row 137 / 141.  Lanes of 8 and 4 bytes, 32 rows: half precision of
+// 585 / 574, 8, 250 MB 310 / 312, 1 row, 800 MB 648 / 672.  What fits the memory-side cache gains from one row on, fp32 without weights and 8-bit rows
+// from two: fp32, 14 MB of 64 floats, 1 row 27.4 / 28.1, 60 MB, 5 rows 90 / 88, 8 rows 114 / 110, staged 67 MB, 1 row 83 / 89, 90 MB, 1 row 123 / 128, 1.5 131 / 134, 2
+// 134.8 / 134.3, 5 159.5 / 158.9; half precision, 30 MB, 1 row 38.7 / 38.3, staged 67 MB, 1 row 102 / 100; 8-bit 2.5 rows 74 / 73.  Lanes of 8 and 4 bytes, 32 rows: half precision of
 // 100 367 / 315, weighted 289 / 243, of 180 593 / 502, fp32 of 33 456 / 294, staged 246 / 167, of 62 366 / 320, 8-bit of 100 431 / 402.  Weights cost the batch a wavefront per SIMD (87
 // registers; 80 here): fp32 1 row, 250 MB 202 / 196, 4 rows 220 / 209, 800 MB 611 / 587; half precision 4 rows 198 / 195.
 static bool ring_pays(const bls_ctx *ctx, bool weighted, int64_t nnz, int qn)
 {
     const int64_t rows = is_rowq(ctx->dtype) ? 12 : !weighted ? 8 : ctx->dtype == BLS_FP16 ? 4 : 2;
     if (nnz >= rows * ctx->nseg) return true;
-    return nnz >= (is_rowq(ctx->dtype) ? 2 : 1) * ctx->nseg && (int64_t)qn * ctx->B * ctx->D * 4 <= (int64_t)96 << 20;
+    const int64_t cached = is_rowq(ctx->dtype) || (ctx->dtype == BLS_FP32 && !weighted) ? 2 : 1;
+    return nnz >= cached * ctx->nseg && (int64_t)qn * ctx->B * ctx->D * 4 <= (int64_t)96 << 20;
 }
 // Four workgroups per compute unit keep the memory busy in a ring, and more of them only share the caches: the kernels, which would
 // run with five to seven, ask for LDS that they do not use.  us, as many as fit / four / three: fp32 rows of 128, 134 MB of vectors 463 / 458 / 456,
@@ -562,7 +564,7 @@ void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const
         // ... but a small batch takes shorter streams (down to eight rows) rather than fewer than two
         // workgroups per compute unit.  us a pass, down to sixty / this: 1024 bags of up to 4, 26 tables, half precision of 128 30.7 / 28.8; 1000 of
         // up to 6, 40 tables of 32 26.9 / 25.7; 3000 of up to 20, 12 tables of 64 8-bit 38.9 / 36.7, half precision 35.2 / 34.0; 300 of up to 2,
-        // 64 tables of 256 39.9 / 39.0; 2048 bags of one, 26 tables of 64 30.5 / 30.8 and 34.3 / 34.1; four workgroups each 34.5
+        // 64 tables of 256 39.9 / 39.0; 2048 bags of one, 26 tables of 64 27.8 / 27.4, of 128 36.6 / 35.7; in a ring of 64 34.3 / 34.1, down to four workgroups each 34.5
         const int64_t room = 2 * (int64_t)std::max(ctx->compute_units, 1);
         while (nb > 1 && nb * mean >= 8 && (int64_t)qn * ((ctx->B + nb - 1) / nb) < room * per_block) nb /= 2;
         if (ctx->tune_segs > 0) nb = ctx->tune_segs;

@@ -43,6 +43,10 @@ def config(P, T, D, B, dtype=0, part=0, rows=9, k=1):
     assert L.bls_desc_bytes(h, C.byref(n)) == 0 and L.bls_commit(h, at(2), n, None) == 0
     assert L.bls_set_ring(h, at(3), C.c_size_t(1 << 44)) == 0
     return h
+def pool(h, nnz, weighted=False):
+    rc = L.bls_embbag_pool_weighted(h, at(4), at(5), at(6), C.c_int64(nnz), at(7), None) if weighted else L.bls_embbag_pool(h, at(4), at(5), C.c_int64(nnz), at(7), None)
+    assert rc == 0
+    return kernel()
 def plan(h, nnz):
     stub.forget()
     assert L.bls_plan(h, at(4), at(5), C.c_int64(nnz), at(6), at(7), at(8), at(9), at(10), at(11), None, at(12), C.c_size_t(1 << 40), None) == 0
@@ -97,4 +101,19 @@ for dtype, D, lanes, rows in ((fp32, 128, 32, 16), (fp32, 20, 8, 16), (fp32, 16,
 for rows, batch in ((0xfffff000 // 512 - 1, "false"), (0xfffff000 // 512, "true")):
     h = config(2, 2, 128, 64, fp32, rows=rows)
     assert step(h, 6400) == f"step_tablewise<32, 0, {batch}>", rows
+""")
+
+
+def test_the_pools_ring_by_rows_a_segment(tmp_path, monkeypatch):
+    """Either side of every line: storage, weights, rows a segment, megabytes of vectors."""
+    run(tmp_path, monkeypatch, r"""
+fp32, fp16, u8, f8 = 0, 1, 2, 3
+for dtype, weighted, small, large in ((fp32, False, 2, 8), (fp32, True, 1, 2), (fp16, False, 1, 8), (fp16, True, 1, 4), (u8, False, 2, 12), (f8, True, 2, 12)):
+    for mb, rows in ((1, small), (96, small), (97, large), (999, large)):
+        B = (mb << 20) // (8 * 128 * 4)
+        h = config(2, 8, 128, B, dtype)
+        for nnz, ring_ in ((rows * 8 * B, "true"), (rows * 8 * B - 1, "false")):
+            name = pool(h, nnz, weighted)
+            assert name.startswith(f"pool_stream<{ {fp32: 32, fp16: 16}.get(dtype, 8)}, {dtype}, 16, "), name
+            assert name.endswith(f" false, {str(weighted).lower()}, {ring_}, 0>"), (dtype, weighted, mb, rows, name)
 """)
