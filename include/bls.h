@@ -130,9 +130,9 @@ int bls_set_hot_rows(bls_ctx *ctx, int32_t t, int32_t rank, const int64_t *rows,
  * bit under every setting.  lane_bytes: table bytes one lane holds of a row (4, 8, 16; 0 = the
  * library's choice); segments_per_group: consecutive segments one lane group streams (1..63, capped
  * at lanes - 1; 0 = chosen from the mean bag length); xcd_map: 1 deals workgroups so that one XCD
- * works on the same tables, 0 plain grid (-1 = library's choice); wide_positions: 1 forces 64-bit
- * row positions (-1 / 0 = only when a shard needs them), here and in bls_step_tablewise, and with them the loops that
- * take rows in batches in place of the ring (the step takes short bags in batches at -1 as well, at 0 it does not). */
+ * works on the same tables, 0 plain grid (-1 = library's choice); wide_positions: 64-bit row positions where a shard needs
+ * them, and in place of 32-bit ones at 1, here and in bls_step_tablewise.  64-bit ones take rows in batches; with 32-bit ones
+ * the pool takes them in batches at 0 and the step in a ring, and -1 leaves it to the library. */
 int bls_set_pool_tuning(bls_ctx *ctx, int32_t lane_bytes, int32_t segments_per_group, int32_t xcd_map,
                         int32_t wide_positions);
 

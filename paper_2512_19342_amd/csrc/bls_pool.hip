@@ -587,7 +587,7 @@ void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const
         // 32-bit row positions unless some shard is too large for them
         const int64_t row_stride = stride_bytes(DT, ctx->D);
         bool wide = ctx->tune_wide == 1;
-        bool ring = ring_pays(ctx, rw != nullptr, nnz, qn);
+        bool ring = ctx->tune_wide != 0 && ring_pays(ctx, rw != nullptr, nnz, qn);
         for (int q = q0; q < q0 + qn; ++q) {
             wide = wide || ctx->q_rows[q] * (row_stride / VB) >= 0xffffffffLL;
             ring = ring && ctx->q_rows[q] < (int64_t)kPastEnd / row_stride;

@@ -1,5 +1,5 @@
 """The pooling kernels that keep a ring of rows in flight: the oracle's bits, and those of the kernels that take rows in
-batches (64-bit positions), where a stream ends inside a ring or a block, in the shard's first and last rows, and for lookups
+batches (64-bit and 32-bit positions), where a stream ends inside a ring or a block, in the shard's first and last rows, and for lookups
 that have no row."""
 import numpy as np
 import pytest
@@ -26,8 +26,9 @@ def make(dt, D, part, bag):
     w = synth.custom("ring", P=3, T=5, D=D, B=37, k=1, rows=[1, 2, 700, 33, 5], table_owner=[0, 1, 2, 0, 1] if part == 0 else None,
                      part_kind=part, bag=("uniform", *bag), table_dtype=dt, values="gauss", seed=D + bag[1], index_dist=("zipf", 1.1))
     tabs = [synth.make_table(w, t) for t in range(w.T)]       # row-wise, tables of one and two rows leave owners with none
-    pipes = [Pipeline(w, [t.cuda() for t in tabs], 1 << 16) for _ in range(2)]
+    pipes = [Pipeline(w, [t.cuda() for t in tabs], 1 << 16) for _ in range(3)]
     pipes[1].ctx.bls_set_pool_tuning(wide_positions=1)
+    pipes[2].ctx.bls_set_pool_tuning(wide_positions=0)        # the pool in batches with 32-bit positions
     return w, [t.numpy() for t in tabs], pipes
 
 
@@ -52,6 +53,35 @@ def test_ring_adds_the_same_rows_in_the_same_order(dt, D, part, bag):
             pipe.ctx.bls_check()
 
 
+@pytest.mark.parametrize("bag", BAGS[1:], ids=str)
+@pytest.mark.parametrize("part", [0, 1], ids=["tables", "rows"])
+@pytest.mark.parametrize("dt,D", [("fp32", D) for D in (16, 64, 100)] + [("fp16", D) for D in (32, 64, 128, 200, 512)] + [("u8rq", 64), ("u8rq", 128), ("f8rq", 128)], ids=str)
+def test_streams_of_nine_segments(dt, D, part, bag):
+    """Streams that a batch this small does not get by itself: blocks handed on and several ends of segments in a batch, with one store, with
+    weights and, staged, with three."""
+    w, tabs, pipes = make(dt, D, part, bag)
+    ix, off = synth.make_batch(w, 4)
+    nnz = int(off[-1])
+    wts = torch.linspace(-1.0, 2.0, nnz)
+    plain, weighted = (oracle.pipeline(case_of(w), tabs, ix.numpy(), off.numpy(), weights=x) for x in (None, wts.numpy()))
+    for pipe, wide in zip(pipes, (-1, 1, 0)):
+        pipe.ctx.bls_set_pool_tuning(segments_per_group=9, wide_positions=wide)
+        for how, ref in (("fused", plain), ("weighted", weighted), ("staged", plain)):
+            for buf in (pipe.pooled, pipe.send, pipe.slots):
+                buf.fill_(float("nan"))
+            if how == "fused":
+                j, slot = pipe.issue_fused(ix.cuda(), off.cuda(), nnz)
+            elif how == "weighted":
+                j, slot = pipe.issue_weighted(ix.cuda(), off.cuda(), wts.cuda(), nnz, fused=True)
+            else:
+                j, slot = pipe.issue(ix.cuda(), off.cuda(), nnz)
+                for k, buf in (("Y", pipe.pooled), ("S", pipe.send)):
+                    assert (bits(buf.cpu().numpy()) == bits(ref[k].reshape(-1))).all(), (wide, k)
+            assert (bits(pipe.slot_view(slot).cpu().numpy()) == bits(ref["R"].reshape(-1))).all(), (wide, how)
+            pipe.complete(j, pipe.new_out())
+        pipe.ctx.bls_check()
+
+
 @pytest.mark.parametrize("part", [0, 1], ids=["tables", "rows"])
 @pytest.mark.parametrize("dt,D", [("fp32", 64), ("fp16", 128), ("u8rq", 64), ("f8rq", 128)], ids=str)
 def test_lookups_without_a_row_add_nothing(dt, D, part):
@@ -64,7 +94,7 @@ def test_lookups_without_a_row_add_nothing(dt, D, part):
             t[1::4, 1::7] = np.nan
             t[:, 2::5] = -0.0
         pipes = []
-        for wide in (-1, 1):
+        for wide in (-1, 1, 0):
             from paper_2512_19342_amd.runner import Pipeline
             pipes.append(Pipeline(w, [torch.from_numpy(t).cuda() for t in tabs], 1 << 16))
             pipes[-1].ctx.bls_set_pool_tuning(wide_positions=wide)
@@ -151,8 +181,8 @@ def test_bags_past_the_lookups_are_empty(dt, D):
         outs.append([t.cpu().numpy().reshape(-1).copy() for t in (pipe.pooled, pipe.send, pipe.slot_view(j % pipe.ctx.K), out)])
         starts = pipe.segoff.cpu().numpy()[:w.T * n + 1]      # in the send order
     assert starts[-1] > nnz                                   # what the runs add up to
-    for a, b in zip(*outs):
-        assert (bits(a) == bits(b)).all()
+    for a, *others in zip(*outs):
+        assert all((bits(a) == bits(b)).all() for b in others)
     over = (starts[1:] > nnz) & (starts[1:] > starts[:-1])
     assert over.any() and not over.all()
     for S in (o[1] for o in outs):

@@ -117,3 +117,19 @@ for dtype, weighted, small, large in ((fp32, False, 2, 8), (fp32, True, 1, 2), (
             assert name.startswith(f"pool_stream<{ {fp32: 32, fp16: 16}.get(dtype, 8)}, {dtype}, 16, "), name
             assert name.endswith(f" false, {str(weighted).lower()}, {ring_}, 0>"), (dtype, weighted, mb, rows, name)
 """)
+
+
+def test_positions_and_the_ring_can_be_chosen_apart(tmp_path, monkeypatch):
+    """wide_positions 0: the loop in batches with 32-bit positions, which the library takes for shards from 4 GB on (up to 64 GB with
+    lanes of 16 bytes) and where the ring does not pay."""
+    run(tmp_path, monkeypatch, r"""
+for rows, own, zero in ((9, "false, false, true", "false, false, false"), (0xfffff000 // 512, "false, false, false", "false, false, false"),
+                        (0xffffffff // 32 + 1, "true, false, false", "true, false, false")):
+    h = config(2, 8, 128, 64, rows=rows)
+    for tuned, form in ((-1, own), (0, zero), (1, "true, false, false")):
+        assert L.bls_set_pool_tuning(h, 0, 0, -1, tuned) == 0
+        assert pool(h, 8 * 64 * 32) == f"pool_stream<32, 0, 16, 8, {form}, 0>", (rows, tuned, kernel())
+        rc, it, slot, calls = issue(h, 0, 8 * 64 * 32)
+        assert rc == 0 and calls == "L0R0" and kernel() == f"pool_stream<32, 0, 16, 8, {form}, 3>", kernel()
+        assert unpack(h, it, 0)[0] == 0
+""")
