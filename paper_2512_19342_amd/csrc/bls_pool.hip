@@ -70,7 +70,7 @@ __device__ __forceinline__ uint64_t group_broadcast64(uint64_t v, int gbase4, in
     }
 }
 
-// One segment per group of G lanes (G = 1 and 2: rows of 16 and 32 bytes with few rows a segment, pool_shape).
+// One segment per group of G lanes (G = 1 and 2: rows of 16 and 32 bytes with few rows a segment, and where lanes of 16 bytes are asked for, pool_shape).
 // grid: x over groups of samples, y = q (owner, local table).
 template <int G, int DT, int VB, int U>
 __global__ __launch_bounds__(kThreads) void pool_rows(DevDesc dd, const int64_t *__restrict__ ridx,
@@ -480,7 +480,7 @@ __global__ __launch_bounds__(kHotThreads) void pool_stream_hot(DevDesc dd, const
     }
 }
 
-// Rows that no lanes of 4, 8 or 16 bytes cover (odd lengths of half-precision and 8-bit rows, rows longer than 1 KB): one wavefront per
+// Rows that no lanes of 4, 8 or 16 bytes cover (half-precision rows of odd length, 8-bit ones of lengths that 4 does not divide, rows longer than 1 KB): one wavefront per
 // segment, lanes stride the columns, scalar loads.  us, this / the streaming kernels, 8192 bags of one row of 26 tables and of 1 to 64: half
 // precision of 20 85 / 35, 779 / 148, 8-bit of 20 88 / 38, 811 / 173; of one row fp32 of 10 88 / 36, of 5 83 / 31, 8-bit of 60 100 / 51.
 template <int DT>
@@ -688,8 +688,10 @@ static bool pool_shape(const bls_ctx *ctx, int64_t nnz, int *lane_bytes, int *ro
     // pool_rows, whose groups are done after one.  us, pool_rows / four lanes: 8192 bags of 26 tables of 1 to 64 rows, half precision of 16 163 /
     // 125, of 8 166 / 96, fp32 of 8 155 / 111, 8-bit of 16 185 / 130, of 32 187 / 167; over four owners (8 rows) 108 / 99, 122 / 89, 98 / 91, 130 / 101,
     // 138 / 126; up to 6 rows (3) 34.6 / 37.8, 32 / 35, 31 / 36, 38.1 / 38.8, 48 / 47; one row 29 / 31, 25 / 28, 25 / 28, 32 / 32, 42 / 39.
-    if (lanes < 4 && (vb < 16 || nnz >= 6 * ctx->nseg || (is_rowq(ctx->dtype) && lanes == 2))) {
-        while (lanes < 4 && vb > 4) { vb >>= 1; lanes <<= 1; }
+    // A width that the caller chose is kept; of four lanes some idle then.
+    const bool chosen = ctx->tune_lane_bytes != 0;
+    if (lanes < 4 && (vb < 16 || (!chosen && (nnz >= 6 * ctx->nseg || (is_rowq(ctx->dtype) && lanes == 2))))) {
+        while (!chosen && lanes < 4 && vb > 4) { vb >>= 1; lanes <<= 1; }
         lanes = 4;
     }
     *lane_bytes = vb;
@@ -767,7 +769,7 @@ static int pool_all_stores(const bls_ctx *ctx, int64_t nnz)
 {
     int vb = 0, lanes = 0;
     if (!pool_shape(ctx, nnz, &vb, &lanes) || ctx->nvec >= (int64_t)1 << 31) return kOneStore;   // 32-bit vector numbers
-    if (lanes < (vb == 16 ? 4 : 128 / vb)) return kOneStore;  // pool_rows, or no kernel of dispatch_lanes
+    if (lanes < (vb == 16 ? 4 : 128 / vb)) return kOneStore;  // pool_rows, or lanes of 4 and 8 bytes without kernels of three stores
     for (const auto &h : ctx->q_hot)
         if (!h.empty()) return kOneStore;
     return stores_that_pay(ctx, lane_floats(ctx->dtype, vb), nnz);

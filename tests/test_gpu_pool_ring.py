@@ -82,6 +82,25 @@ def test_streams_of_nine_segments(dt, D, part, bag):
         pipe.ctx.bls_check()
 
 
+@pytest.mark.parametrize("width", [4, 8, 16])
+@pytest.mark.parametrize("dt,D", [("fp32", 1), ("fp32", 2), ("fp32", 4), ("fp32", 8), ("fp16", 2), ("fp16", 8), ("fp16", 16), ("u8rq", 8), ("u8rq", 16),
+                                  ("u8rq", 32), ("f8rq", 32)], ids=str)
+def test_short_rows_by_chosen_lanes(dt, D, width):
+    """Rows of at most 32 bytes with lanes of a width that the caller chose, some of them idle, with few and with many rows a segment."""
+    for bag in ((0, 3), (7, 17)):
+        w, tabs, pipes = make(dt, D, 1, bag)
+        ix, off = synth.make_batch(w, 5)
+        nnz = int(off[-1])
+        ref = oracle.pipeline(case_of(w), tabs, ix.numpy(), off.numpy())
+        for pipe, wide in zip(pipes, (-1, 1, 0)):
+            pipe.ctx.bls_set_pool_tuning(lane_bytes=width, segments_per_group=3, wide_positions=wide)
+            pipe.slots.fill_(float("nan"))
+            j, slot = pipe.issue_fused(ix.cuda(), off.cuda(), nnz)
+            assert (bits(pipe.slot_view(slot).cpu().numpy()) == bits(ref["R"].reshape(-1))).all(), (bag, wide)
+            pipe.complete(j, pipe.new_out())
+            pipe.ctx.bls_check()
+
+
 @pytest.mark.parametrize("part", [0, 1], ids=["tables", "rows"])
 @pytest.mark.parametrize("dt,D", [("fp32", 64), ("fp16", 128), ("u8rq", 64), ("f8rq", 128)], ids=str)
 def test_lookups_without_a_row_add_nothing(dt, D, part):

@@ -133,3 +133,21 @@ for rows, own, zero in ((9, "false, false, true", "false, false, false"), (0xfff
         assert rc == 0 and calls == "L0R0" and kernel() == f"pool_stream<32, 0, 16, 8, {form}, 3>", kernel()
         assert unpack(h, it, 0)[0] == 0
 """)
+
+
+def test_lane_bytes_are_what_was_asked_for(tmp_path, monkeypatch):
+    """Rows that one or two lanes of 16 bytes cover are split over four narrower ones by the library, not where the caller chose a
+    width.  Widths that do not divide a row are halved until they do."""
+    run(tmp_path, monkeypatch, r"""
+fp32, fp16, u8, f8 = 0, 1, 2, 3
+for dtype, D, few, many, widths in ((fp16, 8, (1, 16), (4, 4), {16: (1, 16), 8: (4, 8), 4: (4, 4)}), (fp32, 8, (2, 16), (4, 8), {16: (2, 16), 8: (4, 8), 4: (8, 4)}),
+                                    (u8, 16, (1, 16), (4, 4), {16: (1, 16), 8: (4, 8), 4: (4, 4)}), (f8, 32, (4, 8), (4, 8), {16: (2, 16), 8: (4, 8), 4: (8, 4)}),
+                                    (fp32, 2, (4, 4), (4, 4), {16: (4, 8), 8: (4, 8), 4: (4, 4)}), (fp32, 64, (16, 16), (16, 16), {16: (16, 16), 8: (32, 8), 4: (64, 4)}),
+                                    (fp16, 10, (8, 4), (8, 4), {16: (8, 4), 8: (8, 4), 4: (8, 4)})):
+    h = config(2, 4, D, 64, dtype)
+    for rows, free in ((5, few), (6, many)):
+        for chosen, (lanes, vb) in ((0, free), *widths.items()):
+            assert L.bls_set_pool_tuning(h, chosen, 0, -1, -1) == 0
+            name = pool(h, rows * 4 * 64)
+            assert name.startswith(f"pool_{'stream' if lanes >= 4 else 'rows'}<{lanes}, {dtype}, {vb}, "), (dtype, D, rows, chosen, name)
+""")
