@@ -283,17 +283,19 @@ bool dispatch(const bls_ctx *ctx, int lanes, dim3 grid, hipStream_t st, const in
 }
 
 // Rows a bag from which the ring is the faster form.  A ring asks for at least twice U rows whatever a bag has, and a step of short bags is
-// made of such requests: they are answered without an access, but take their turn.  With a workgroup or less for each compute
-// unit nobody waits for it, and the longest bag's chain decides.  us, before the ring came / ring / batches, 26 tables, 2048 bags: fp32 of 128, of
+// made of such requests: they are answered without an access, but take their turn.  Where the chip holds all workgroups at once nobody
+// waits for that turn, and the longest bag's chain decides.  us, before the ring came / ring / batches, 26 tables, 2048 bags: fp32 of 128, of
 // one row 40.9 / 42.0 / 34.2, 5 44.0 / 44.1 / 38.3, 12 64.8 / 67.2 / 59.0, 1024 of 16 37.8 / 37.0 / 36.2, of 24 44.5 / 43.8 / 44.5; of 32,
 // one row 18.3 / 18.2 / 14.8, 1024 of 24 21.6 / 19.2 / 20.0; of 16, one row 13.2 / 12.3 / 11.7, 3 15.3 / 13.3 / 13.5; half precision of 128, one
 // row 34.6 / 36.5 / 34.1, 8 39.2 / 41.7 / 40.8, 12 43.3 / 45.3 / 43.5, of 64, one row 23.4 / 23.1 / 20.5, 12 27.8 / 27.8 / 25.7, 1024 of 16 21.2 / 20.3 /
-// 20.9; 8-bit of 128, one row 49.0 / 47.6 / 46.3, 8 53.5 / 51.5 / 52.6.  Few workgroups: four tables of 64, 512 bags of up to 15 9.3 / 8.9 / 9.3.
-int64_t ring_rows(int dtype, int lanes)
+// 20.9; 8-bit of 128, one row 49.0 / 47.6 / 46.3, 8 53.5 / 51.5 / 52.6.  By workgroups a compute unit: 6.6, fp32 of 128, 13 rows 29.7 / 27.2 / 28.0; 3.3, half
+// precision of 64, 8 rows 21.0 / 19.2 / 20.2, fp32 of 128, 4 rows 13.5 / 12.8 / 12.4; 2.6, half precision of 128, 12 rows 18.3 / 16.4 / 17.2; 0.5,
+// fp32 of 64, 8 rows 9.3 / 8.9 / 9.3.
+int64_t ring_rows(const bls_ctx *ctx, int lanes, int64_t workgroups)
 {
-    if (lanes < 4) return 0;
-    if (lanes == 4) return 3;
-    return dtype == BLS_FP32 ? 16 : dtype == BLS_FP16 ? 13 : 4;
+    if (lanes < 4 || workgroups <= ctx->compute_units) return 0;
+    const int64_t rows = lanes == 4 ? 3 : ctx->dtype == BLS_FP32 ? 16 : ctx->dtype == BLS_FP16 ? 13 : 4;
+    return workgroups > 7 * (int64_t)ctx->compute_units ? rows : std::min<int64_t>(rows, 6);
 }
 
 }  // namespace
@@ -316,8 +318,8 @@ int bls_launch_step_tablewise(bls_ctx *ctx, const int64_t *idx, const int64_t *o
     const uint64_t gx = (uint64_t)chunks * ctx->P;
     if (gx > 0x7fffffffull) return bls_fail(ctx, BLS_EINVAL, "bls_step_tablewise: batch too large for one launch");
     const dim3 grid((unsigned)gx, (unsigned)ctx->Q);
-    // in a ring unless a shard is too large for 32-bit offsets, or bags are short and there are workgroups for every compute unit
-    bool batch = ctx->tune_wide == 1 || (ctx->tune_wide != 0 && nnz < ring_rows(ctx->dtype, lanes) * ctx->nseg && (int64_t)gx * ctx->Q > ctx->compute_units);
+    // in a ring unless a shard is too large for 32-bit offsets, or bags are short
+    bool batch = ctx->tune_wide == 1 || (ctx->tune_wide != 0 && nnz < ring_rows(ctx, lanes, (int64_t)gx * ctx->Q) * ctx->nseg);
     for (int q = 0; q < ctx->Q; ++q) batch = batch || ctx->q_rows[q] >= (int64_t)kPastEnd / stride_bytes(ctx->dtype, ctx->D);
     auto go = [&](auto dt) -> bool {
         return batch ? dispatch<dt(), true>(ctx, lanes, grid, st, idx, off, nnz, sendcounts, sdispls, recvcounts, rdispls, ridx, segoff, perm, Y, S, R, out, chunks)

@@ -88,7 +88,8 @@ def test_the_one_launch_step_takes_short_bags_in_batches(tmp_path, monkeypatch):
 fp32, fp16, u8, f8 = 0, 1, 2, 3
 for dtype, D, lanes, rows in ((fp32, 128, 32, 16), (fp32, 20, 8, 16), (fp32, 16, 4, 3), (fp32, 8, 2, 0), (fp32, 4, 1, 0), (fp16, 64, 8, 13), (fp16, 200, 32, 13),
                               (fp16, 32, 4, 3), (fp16, 16, 2, 0), (u8, 128, 8, 4), (f8, 112, 8, 4), (u8, 64, 4, 3), (f8, 32, 2, 0)):
-    for P, T, B in ((4, 26, 2048), (1, 1, 256 * 256 // lanes + 1)):   # many workgroups, and one more than there are compute units
+    # one workgroup more than the chip holds at once, as many as that, one more than there are compute units
+    for P, T, B, rows in ((1, 1, 7 * 256 * (256 // lanes) + 1, rows), (1, 1, 7 * 256 * (256 // lanes), min(rows, 6)), (1, 1, 256 * (256 // lanes) + 1, min(rows, 6))):
         h = config(P, T, D, B, dtype)
         for nnz, batch in ((rows * T * B, "false"), (rows * T * B - 1, "true"), (T * B if rows > 1 else 0, "true" if rows else "false")):
             if nnz < 0: continue
@@ -96,7 +97,7 @@ for dtype, D, lanes, rows in ((fp32, 128, 32, 16), (fp32, 20, 8, 16), (fp32, 16,
             for tuned, batch in ((0, "false"), (1, "true")):
                 assert L.bls_set_pool_tuning(h, 0, 0, -1, tuned) == 0 and step(h, nnz) == f"step_tablewise<{lanes}, {dtype}, {batch}>"
             assert L.bls_set_pool_tuning(h, 0, 0, -1, -1) == 0
-    h = config(1, 1, D, 256 * 256 // lanes, dtype)
+    h = config(1, 1, D, 256 * (256 // lanes), dtype)
     assert step(h, 1) == f"step_tablewise<{lanes}, {dtype}, false>"
 for rows, batch in ((0xfffff000 // 512 - 1, "false"), (0xfffff000 // 512, "true")):
     h = config(2, 2, 128, 64, fp32, rows=rows)
