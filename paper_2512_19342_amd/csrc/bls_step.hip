@@ -21,12 +21,15 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kMaxRuns = 2048;                 // runs (q, s) whose starts one workgroup scans in LDS
-// Rows of a group in flight, and wavefronts per SIMD the kernel is held to (1: as it comes): what is best with long bags among those that
-// cost short ones nothing.  us, 26 tables.  Half precision of 64, batches of eight / a ring of eight / of four: 2048 bags of one 23.4 / 24.5 /
-// 23.4, 512 of 1 to 100 32.2 / 24.3 / 27.1.  Held / as it comes, 4096 bags of up to 4, then 512 of 1 to 100: fp32 of 128 91 / 96, 43.2 / 42.6, of 64
+// Rows of a group in flight, in batches or in a ring: what is best with long bags among those that cost short ones little.  us, 26 tables, before
+// the ring came / four / eight.  Batches, one table of 4.9 GB, 2048 bags of one, 512 of 1 to 100, 2048 of 1 to 40: 8-bit of 128 49.6 / 47.4 / 48.8, 63.8 / 64.3 /
+// 60.9, 111 / 109 / 104, half precision of 64 24.3 / 22.4 / 24.0, 46.9 / 46.7 / 41.7, 58.9 / 56.8 / 54.4 (batches are its form for short bags, so
+// four); 8192 bags of 1 to 15, 8-bit of 512 838 / 850 / 820.  Rings, half precision of 64, 2048 bags of one 23.4 / 23.4 / 24.5, 512 of 1 to 100 32.2 /
+// 27.1 / 24.3; 8-bit of 128, 2048 bags of 1 to 23 81.0 / 74.7 / 100.
+// Wavefronts per SIMD that a ring is held to (1: as it comes).  Held / as it comes, 4096 bags of up to 4, then 512 of 1 to 100: fp32 of 128 91 / 96, 43.2 / 42.6, of 64
 // 43.0 / 45.6, 29.9 / 29.5; half precision of 128 67 / 72, 32.7 / 32.7; 8-bit of 128 86 / 88, 44.2 / 42.9, e4m3 86 / 88, 40.5 / 41.7.  Eight lanes of fp32 hold more
 // registers than six wavefronts leave (two spilled): of 32, six / five, 2048 bags of one 18.8 / 18.3, 512 of 1 to 100 22.3 / 21.9.
-template <int G, int DT> constexpr int kRows = is_rowq(DT) || (DT == BLS_FP16 && G == 8) ? 4 : 8;
+template <int G, int DT, bool BATCH> constexpr int kRows = DT == BLS_FP16 && G == 8 ? 4 : is_rowq(DT) && !BATCH ? 4 : 8;
 template <int G, int DT> constexpr int kWavesHeld = DT == BLS_FP32 ? (G == 8 ? 5 : 6) : DT == BLS_FP16 ? (G < 16 ? 5 : 6) : G == 8 ? 5 : 1;
 
 __device__ __forceinline__ void flag_error(const DevDesc &dd) { atomicOr(dd.err, 1); }
@@ -103,7 +106,7 @@ __global__ __launch_bounds__(kThreads, (BATCH ? 1 : kWavesHeld<G, DT>)) void ste
             len = 0;
         }
     }
-    constexpr int kU = kRows<G, DT>, U = kU < G ? kU : G;     // rows in flight
+    constexpr int kU = kRows<G, DT, BATCH>, U = kU < G ? kU : G;     // rows in flight
     const __amdgpu_buffer_rsrc_t shard = shard_buffer(dd.q_base[q], BATCH ? 0u : (uint32_t)rows * row_stride);
     const char *__restrict__ base = (const char *)dd.q_base[q] + (col_ok ? (uint32_t)li * 16 : 0u);
     const uint32_t col = col_ok ? (uint32_t)li * 16 : 0u;
@@ -288,13 +291,14 @@ bool dispatch(const bls_ctx *ctx, int lanes, dim3 grid, hipStream_t st, const in
 // one row 40.9 / 42.0 / 34.2, 5 44.0 / 44.1 / 38.3, 12 64.8 / 67.2 / 59.0, 1024 of 16 37.8 / 37.0 / 36.2, of 24 44.5 / 43.8 / 44.5; of 32,
 // one row 18.3 / 18.2 / 14.8, 1024 of 24 21.6 / 19.2 / 20.0; of 16, one row 13.2 / 12.3 / 11.7, 3 15.3 / 13.3 / 13.5; half precision of 128, one
 // row 34.6 / 36.5 / 34.1, 8 39.2 / 41.7 / 40.8, 12 43.3 / 45.3 / 43.5, of 64, one row 23.4 / 23.1 / 20.5, 12 27.8 / 27.8 / 25.7, 1024 of 16 21.2 / 20.3 /
-// 20.9; 8-bit of 128, one row 49.0 / 47.6 / 46.3, 8 53.5 / 51.5 / 52.6.  By workgroups a compute unit: 6.6, fp32 of 128, 13 rows 29.7 / 27.2 / 28.0; 3.3, half
+// 20.9; 8-bit of 128, 8192 bags, 4 rows 199 / 209 / 193, 12 270 / 263 / 264, 24 349 / 339 / 332, of 512, 8
+// rows 218 / 227 / 215, 16 260 / 266 / 258, 50 411 / 401 / 404 (never the ring).  By workgroups a compute unit: 6.6, fp32 of 128, 13 rows 29.7 / 27.2 / 28.0; 3.3, half
 // precision of 64, 8 rows 21.0 / 19.2 / 20.2, fp32 of 128, 4 rows 13.5 / 12.8 / 12.4; 2.6, half precision of 128, 12 rows 18.3 / 16.4 / 17.2; 0.5,
-// fp32 of 64, 8 rows 9.3 / 8.9 / 9.3.
+// fp32 of 64, 8 rows 9.3 / 8.9 / 9.3; 6.5, 8-bit of 128, 4 rows 57.3 / 56.2 / 55.6, 6 62.8 / 60.8 / 62.4, 24 112 / 103 / 105.
 int64_t ring_rows(const bls_ctx *ctx, int lanes, int64_t workgroups)
 {
     if (lanes < 4 || workgroups <= ctx->compute_units) return 0;
-    const int64_t rows = lanes == 4 ? 3 : ctx->dtype == BLS_FP32 ? 16 : ctx->dtype == BLS_FP16 ? 13 : 4;
+    const int64_t rows = lanes == 4 ? 3 : ctx->dtype == BLS_FP32 ? 16 : ctx->dtype == BLS_FP16 ? 13 : 1 << 20;
     return workgroups > 7 * (int64_t)ctx->compute_units ? rows : std::min<int64_t>(rows, 6);
 }
 

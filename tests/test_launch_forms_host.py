@@ -87,7 +87,7 @@ def test_the_one_launch_step_takes_short_bags_in_batches(tmp_path, monkeypatch):
     run(tmp_path, monkeypatch, r"""
 fp32, fp16, u8, f8 = 0, 1, 2, 3
 for dtype, D, lanes, rows in ((fp32, 128, 32, 16), (fp32, 20, 8, 16), (fp32, 16, 4, 3), (fp32, 8, 2, 0), (fp32, 4, 1, 0), (fp16, 64, 8, 13), (fp16, 200, 32, 13),
-                              (fp16, 32, 4, 3), (fp16, 16, 2, 0), (u8, 128, 8, 4), (f8, 112, 8, 4), (u8, 64, 4, 3), (f8, 32, 2, 0)):
+                              (fp16, 32, 4, 3), (fp16, 16, 2, 0), (u8, 128, 8, 1 << 20), (f8, 112, 8, 1 << 20), (u8, 512, 32, 1 << 20), (u8, 64, 4, 3), (f8, 32, 2, 0)):
     # one workgroup more than the chip holds at once, as many as that, one more than there are compute units
     for P, T, B, rows in ((1, 1, 7 * 256 * (256 // lanes) + 1, rows), (1, 1, 7 * 256 * (256 // lanes), min(rows, 6)), (1, 1, 256 * (256 // lanes) + 1, min(rows, 6))):
         h = config(P, T, D, B, dtype)
