@@ -29,7 +29,7 @@ constexpr int kMaxRuns = 2048;                 // runs (q, s) whose starts one w
 // Wavefronts per SIMD that a ring is held to (1: as it comes).  Held / as it comes, 4096 bags of up to 4, then 512 of 1 to 100: fp32 of 128 91 / 96, 43.2 / 42.6, of 64
 // 43.0 / 45.6, 29.9 / 29.5; half precision of 128 67 / 72, 32.7 / 32.7; 8-bit of 128 86 / 88, 44.2 / 42.9, e4m3 86 / 88, 40.5 / 41.7.  Eight lanes of fp32 hold more
 // registers than six wavefronts leave (two spilled): of 32, six / five, 2048 bags of one 18.8 / 18.3, 512 of 1 to 100 22.3 / 21.9.
-template <int G, int DT, bool BATCH> constexpr int kRows = DT == BLS_FP16 && G == 8 ? 4 : is_rowq(DT) && !BATCH ? 4 : 8;
+template <int G, int DT, bool BATCH> constexpr int kRows = (BATCH ? DT == BLS_FP16 && G == 8 : is_rowq(DT)) ? 4 : 8;
 template <int G, int DT> constexpr int kWavesHeld = DT == BLS_FP32 ? (G == 8 ? 5 : 6) : DT == BLS_FP16 ? (G < 16 ? 5 : 6) : G == 8 ? 5 : 1;
 
 __device__ __forceinline__ void flag_error(const DevDesc &dd) { atomicOr(dd.err, 1); }
@@ -290,11 +290,11 @@ bool dispatch(const bls_ctx *ctx, int lanes, dim3 grid, hipStream_t st, const in
 // waits for that turn, and the longest bag's chain decides.  us, before the ring came / ring / batches, 26 tables, 2048 bags: fp32 of 128, of
 // one row 40.9 / 42.0 / 34.2, 5 44.0 / 44.1 / 38.3, 12 64.8 / 67.2 / 59.0, 1024 of 16 37.8 / 37.0 / 36.2, of 24 44.5 / 43.8 / 44.5; of 32,
 // one row 18.3 / 18.2 / 14.8, 1024 of 24 21.6 / 19.2 / 20.0; of 16, one row 13.2 / 12.3 / 11.7, 3 15.3 / 13.3 / 13.5; half precision of 128, one
-// row 34.6 / 36.5 / 34.1, 8 39.2 / 41.7 / 40.8, 12 43.3 / 45.3 / 43.5, of 64, one row 23.4 / 23.1 / 20.5, 12 27.8 / 27.8 / 25.7, 1024 of 16 21.2 / 20.3 /
-// 20.9; 8-bit of 128, 8192 bags, 4 rows 199 / 209 / 193, 12 270 / 263 / 264, 24 349 / 339 / 332, of 512, 8
-// rows 218 / 227 / 215, 16 260 / 266 / 258, 50 411 / 401 / 404 (never the ring).  By workgroups a compute unit: 6.6, fp32 of 128, 13 rows 29.7 / 27.2 / 28.0; 3.3, half
-// precision of 64, 8 rows 21.0 / 19.2 / 20.2, fp32 of 128, 4 rows 13.5 / 12.8 / 12.4; 2.6, half precision of 128, 12 rows 18.3 / 16.4 / 17.2; 0.5,
-// fp32 of 64, 8 rows 9.3 / 8.9 / 9.3; 6.5, 8-bit of 128, 4 rows 57.3 / 56.2 / 55.6, 6 62.8 / 60.8 / 62.4, 24 112 / 103 / 105.
+// row 34.6 / 36.5 / 34.1, 8 39.2 / 41.7 / 40.8, 12 43.3 / 45.3 / 43.5, of 64, one row 24.6 / 25.1 / 22.2, 8 36.6 / 34.8 / 35.0, 12 42.9 / 38.9 / 41.9,
+// 8192 of 8 124 / 122 / 119, of 12 146 / 138 / 140; 8-bit of 128, 8192 bags, 4 rows 199 / 209 / 193, 12 270 / 263 / 264, 24 349 / 339 / 332, of 512, 8
+// rows 218 / 227 / 215, 16 260 / 266 / 258, 50 411 / 401 / 404 (never the ring).  By workgroups a compute unit: 6.6, fp32 of 128, 13 rows 29.7 / 27.2 / 28.0; 3.3,
+// fp32 of 128, 4 rows 13.5 / 12.8 / 12.4; 2.6, half precision of 128, 12 rows 18.3 / 16.4 / 17.2; 1.6,
+// half precision of 64, 6 rows 17.5 / 16.1 / 17.0; 0.5, fp32 of 64, 8 rows 9.3 / 8.9 / 9.3; 6.5, 8-bit of 128, 4 rows 57.3 / 56.2 / 55.6, 6 62.8 / 60.8 / 62.4, 24 112 / 103 / 105.
 int64_t ring_rows(const bls_ctx *ctx, int lanes, int64_t workgroups)
 {
     if (lanes < 4 || workgroups <= ctx->compute_units) return 0;
