@@ -152,3 +152,21 @@ for dtype, D, few, many, widths in ((fp16, 8, (1, 16), (4, 4), {16: (1, 16), 8: 
             name = pool(h, rows * 4 * 64)
             assert name.startswith(f"pool_{'stream' if lanes >= 4 else 'rows'}<{lanes}, {dtype}, {vb}, "), (dtype, D, rows, chosen, name)
 """)
+
+
+def test_a_ring_is_held_to_four_workgroups_with_long_segments(tmp_path, monkeypatch):
+    """LDS that nothing uses, from twelve rows a segment on; fewer rows, 32 and 64 lanes of 4 bytes, and batches ask for none."""
+    run(tmp_path, monkeypatch, r"""
+fp32, fp16, u8, f8 = 0, 1, 2, 3
+for dtype, D, held in ((fp32, 128, True), (fp32, 16, True), (fp32, 6, True), (fp32, 8, True), (fp32, 17, False), (fp32, 33, False), (fp16, 64, True), (fp16, 20, True), (fp16, 50, False),
+                       (fp16, 100, True), (u8, 128, True), (u8, 32, True), (u8, 60, True), (u8, 100, False), (f8, 24, True)):
+    h = config(2, 8, D, 512, dtype)
+    for nnz in (3 * 8 * 512, 12 * 8 * 512 - 1, 12 * 8 * 512, 99 * 8 * 512):
+        for weighted in (False, True):
+            name = pool(h, nnz, weighted)
+            in_ring = name.startswith("pool_stream<") and name.endswith("true, 0>")
+            assert in_ring or nnz < 12 * 8 * 512, (dtype, D, name)
+            assert lds.value == (36 * 1024 if in_ring and held and nnz >= 12 * 8 * 512 else 0), (dtype, D, nnz, name, lds.value)
+            assert L.bls_set_pool_tuning(h, 0, 0, -1, 0) == 0 and not pool(h, nnz, weighted).endswith("true, 0>") and lds.value == 0
+            assert L.bls_set_pool_tuning(h, 0, 0, -1, -1) == 0
+""")
