@@ -532,16 +532,18 @@ __global__ __launch_bounds__(kThreads) void pool_rows_generic(DevDesc dd, const 
 // vectors of 128, batch / ring, by rows a segment and MB of vectors.  fp32: 32 rows, 134 MB 483 / 458, 32 of 64 floats 296 / 266, of
 // 32 195 / 169, 8 rows, 250 MB 352 / 346, 2 of 64 floats 231 / 238, 1 row, 800 MB 399 / 408.  Half precision: 32 rows, 134 MB
 // 355 / 321, 8, 800 MB 944 / 937, 4, 800 MB 541 / 545, staged 1024 / 1040.  8-bit: 32 rows, 134 MB 377 / 341, 250 MB
-// 585 / 574, 8, 250 MB 310 / 312, 1 row, 800 MB 648 / 672.  What fits the memory-side cache gains from one row on, fp32 without weights and 8-bit rows
-// from two: fp32, 14 MB of 64 floats, 1 row 27.4 / 28.1, 60 MB, 5 rows 90 / 88, 8 rows 114 / 110, staged 67 MB, 1 row 83 / 89, 90 MB, 1 row 123 / 128, 1.5 131 / 134, 2
-// 134.8 / 134.3, 5 159.5 / 158.9; half precision, 30 MB, 1 row 38.7 / 38.3, staged 67 MB, 1 row 102 / 100; 8-bit 2.5 rows 74 / 73.  Lanes of 8 and 4 bytes, 32 rows: half precision of
+// 585 / 574, 8, 250 MB 310 / 312, 1 row, 800 MB 648 / 672.  What fits the memory-side cache gains earlier: fp32, 14 MB of 64 floats, 1 row 27.4 / 28.1,
+// 60 MB, 5 rows 90 / 88, 8 rows 114 / 110, staged 67 MB, 1 row 83 / 89, 90 MB, 1.5 rows 131 / 134, 2 134.8 / 134.3, 5 159.5 / 158.9; ring over batches,
+// geometric means of 20 to 90 MB, vectors of 16 to 512, 1, 2, 3, 4 and 6 rows: fp32 fused 0.998 0.994 0.985 0.976 0.968, staged 0.999 0.997 1.000 0.989 0.982,
+// weighted 0.993 0.974 0.976 0.963 0.955; half precision 1.010 0.997 0.998 0.987 0.974, 1.009 1.006 1.010 0.995 0.983, 1.011 0.993 0.999 0.982 0.970; 8-bit
+// 0.998 1.006 1.014 1.008 0.997, 1.002 1.011 1.015 1.005 0.998, 0.999 1.005 1.006 1.003 0.990.  Lanes of 8 and 4 bytes, 32 rows: half precision of
 // 100 367 / 315, weighted 289 / 243, of 180 593 / 502, fp32 of 33 456 / 294, staged 246 / 167, of 62 366 / 320, 8-bit of 100 431 / 402.  Weights cost the batch a wavefront per SIMD (87
 // registers; 80 here): fp32 1 row, 250 MB 202 / 196, 4 rows 220 / 209, 800 MB 611 / 587; half precision 4 rows 198 / 195.
 static bool ring_pays(const bls_ctx *ctx, bool weighted, int64_t nnz, int qn)
 {
     const int64_t rows = is_rowq(ctx->dtype) ? 12 : !weighted ? 8 : ctx->dtype == BLS_FP16 ? 4 : 2;
     if (nnz >= rows * ctx->nseg) return true;
-    const int64_t cached = is_rowq(ctx->dtype) || (ctx->dtype == BLS_FP32 && !weighted) ? 2 : 1;
+    const int64_t cached = is_rowq(ctx->dtype) ? 6 : ctx->dtype == BLS_FP16 ? (weighted ? 2 : 4) : weighted ? 1 : 2;
     return nnz >= cached * ctx->nseg && (int64_t)qn * ctx->B * ctx->D * 4 <= (int64_t)96 << 20;
 }
 // Four workgroups per compute unit keep the memory busy in a ring, and with long segments more of them only share the caches: the kernels, which would

@@ -109,7 +109,7 @@ def test_the_pools_ring_by_rows_a_segment(tmp_path, monkeypatch):
     """Either side of every line: storage, weights, rows a segment, megabytes of vectors."""
     run(tmp_path, monkeypatch, r"""
 fp32, fp16, u8, f8 = 0, 1, 2, 3
-for dtype, weighted, small, large in ((fp32, False, 2, 8), (fp32, True, 1, 2), (fp16, False, 1, 8), (fp16, True, 1, 4), (u8, False, 2, 12), (f8, True, 2, 12)):
+for dtype, weighted, small, large in ((fp32, False, 2, 8), (fp32, True, 1, 2), (fp16, False, 4, 8), (fp16, True, 2, 4), (u8, False, 6, 12), (f8, True, 6, 12)):
     for mb, rows in ((1, small), (96, small), (97, large), (999, large)):
         B = (mb << 20) // (8 * 128 * 4)
         h = config(2, 8, 128, B, dtype)
