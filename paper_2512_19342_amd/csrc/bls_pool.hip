@@ -546,16 +546,18 @@ static bool ring_pays(const bls_ctx *ctx, bool weighted, int64_t nnz, int qn)
     const int64_t cached = is_rowq(ctx->dtype) ? 6 : ctx->dtype == BLS_FP16 ? (weighted ? 2 : 4) : weighted ? 1 : 2;
     return nnz >= cached * ctx->nseg && (int64_t)qn * ctx->B * ctx->D * 4 <= (int64_t)96 << 20;
 }
-// Four workgroups per compute unit keep the memory busy in a ring, and with long segments more of them only share the caches: the kernels, which would
-// run with five to seven, ask for LDS that they do not use.  us, as many as fit / four / three: fp32 rows of 128, 134 MB of vectors 463 / 458 / 456, of 64
-// 275 / 265 / 267, of 32 173 / 169 / 173, with three stores 508 / 504 / 504, half precision 322 / 321 / 325, 8-bit 343 / 341 / 346, of 60, 46 rows 360 / 327.
-// Segments of less than twelve rows are starts and stores as well and want all that fit, and so do a wavefront's lanes of 4 bytes: as many as fit / four /
-// in batches, half precision of 32, weighted, 3.5 rows 86 / 94 / 90, fp32 of 16, weighted, 8 rows 52 / 54 / 53; fp32 of 33, 7 rows 959 / 1095 / 1029, 41 108 / 121 / 130,
-// 8-bit of 100, weighted, 87 214 / 247 / 302.  319 shapes: this 0.995 of the time with four everywhere, from 0.89 to 1.03; 0.99 of it below twelve rows.
+// Four workgroups per compute unit keep the memory busy in a ring, and with long segments of large shards more of them only share the caches: the
+// kernels, which would run with five to seven, ask for LDS that they do not use.  us, as many as fit / four / three: fp32 rows of 128, 134 MB of vectors 463 /
+// 458 / 456, of 64 275 / 265 / 267, of 32 173 / 169 / 173, with three stores 508 / 504 / 504, half precision 322 / 321 / 325, 8-bit 343 / 341 / 346, of 60, shards of 25 MB
+// 360 / 327.  Segments of less than twelve rows are starts and stores as well and want all that fit, and so do a wavefront's lanes of 4 bytes and shards that an
+// XCD's L2 of 4 MB holds: as many as fit / four / in batches, half precision of 32, weighted, 3.5 rows 86 / 94 / 90, fp32 of 16, weighted, 8 rows 52 / 54 / 53;
+// fp32 of 33, 7 rows 959 / 1095 / 1029, 41 108 / 121 / 130, 8-bit of 100, weighted, 87 214 / 247 / 302; fp32 of 128, 38 rows, shards of 2 MB 78 / 83 / 77.
+// 592 shapes, geometric means of the former over the latter: below twelve rows 0.99, shards of up to 2 MB 0.998, 4 to 16 1.002, 16 to 64 1.005 (up to 1.10).
+// Beside other streams' kernels: the model's window of 64 tables of 128 with a lookup stream 7003 / 6765, of 26 1173 / 1190; per-rank streams level.
 static constexpr size_t kRingLds = 36 * 1024;
-static size_t ring_lds(const bls_ctx *ctx, int lanes, int lane_bytes, int64_t nnz)
+static size_t ring_lds(const bls_ctx *ctx, int lanes, int lane_bytes, int64_t nnz, int64_t mean_shard)
 {
-    return nnz >= 12 * ctx->nseg && !(lane_bytes == 4 && lanes >= 32) ? kRingLds : 0;
+    return nnz >= 12 * ctx->nseg && !(lane_bytes == 4 && lanes >= 32) && mean_shard > (int64_t)4 << 20 ? kRingLds : 0;
 }
 
 template <int G, int DT, int VB, int U>
@@ -597,7 +599,9 @@ void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const
         const int64_t row_stride = stride_bytes(DT, ctx->D);
         bool wide = ctx->tune_wide == 1;
         bool ring = ctx->tune_wide != 0 && ring_pays(ctx, rw != nullptr, nnz, qn);
+        int64_t bytes = 0;                                    // of the launch's shards
         for (int q = q0; q < q0 + qn; ++q) {
+            bytes += ctx->q_rows[q] * row_stride;
             wide = wide || ctx->q_rows[q] * (row_stride / VB) >= 0xffffffffLL;
             ring = ring && ctx->q_rows[q] < (int64_t)kPastEnd / row_stride;
         }
@@ -626,7 +630,7 @@ void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const
             }
         }
         auto launch = [&](auto kernel) {
-            kernel<<<grid, kThreads, ring ? ring_lds(ctx, G, VB, nnz) : 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, to.Y, to.S, to.R, to.slot, nb, chunks, deal, q0, qn);
+            kernel<<<grid, kThreads, ring ? ring_lds(ctx, G, VB, nnz, bytes / qn) : 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, to.Y, to.S, to.R, to.slot, nb, chunks, deal, q0, qn);
         };
         auto pick = [&](auto weighted, auto stores) {
             if (ring) return launch(pool_stream<G, DT, VB, UU, false, weighted(), true, stores()>);

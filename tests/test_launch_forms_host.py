@@ -155,12 +155,16 @@ for dtype, D, few, many, widths in ((fp16, 8, (1, 16), (4, 4), {16: (1, 16), 8: 
 
 
 def test_a_ring_is_held_to_four_workgroups_with_long_segments(tmp_path, monkeypatch):
-    """LDS that nothing uses, from twelve rows a segment on; fewer rows, 32 and 64 lanes of 4 bytes, and batches ask for none."""
+    """LDS that nothing uses, from twelve rows a segment on; fewer rows, 32 and 64 lanes of 4 bytes, shards that an XCD's L2 holds, and
+    batches ask for none."""
     run(tmp_path, monkeypatch, r"""
 fp32, fp16, u8, f8 = 0, 1, 2, 3
 for dtype, D, held in ((fp32, 128, True), (fp32, 16, True), (fp32, 6, True), (fp32, 8, True), (fp32, 17, False), (fp32, 33, False), (fp16, 64, True), (fp16, 20, True), (fp16, 50, False),
                        (fp16, 100, True), (u8, 128, True), (u8, 32, True), (u8, 60, True), (u8, 100, False), (f8, 24, True)):
-    h = config(2, 8, D, 512, dtype)
+    row = D * 4 if dtype == fp32 else D * 2 if dtype == fp16 else (D + 8 + 15) // 16 * 16
+    h = config(2, 8, D, 512, dtype, rows=(4 << 20) // row)
+    assert "true" in pool(h, 99 * 8 * 512) and lds.value == 0
+    h = config(2, 8, D, 512, dtype, rows=(4 << 20) // row + 1)
     for nnz in (3 * 8 * 512, 12 * 8 * 512 - 1, 12 * 8 * 512, 99 * 8 * 512):
         for weighted in (False, True):
             name = pool(h, nnz, weighted)
