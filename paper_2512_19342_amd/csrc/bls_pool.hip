@@ -590,18 +590,22 @@ void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const
         // 10 53 / 50; 8-bit, 60 MB 1 693 / 182, 9 262 / 199; row-wise, 4 owners 343 / 252.  Three stores and the calls they stand for (four launches, their pool
         // dealt), vectors of 64, bags of 1 to 4, calls / dealt / not: 1 table, 30 MB 99 / 112 / 46, 5, 100 MB 184 / 166 / 148, 8-bit, 8 MB 1
         // 54 / 82 / 34.  With most XCDs at work the deal's caches count for more with many rows a segment (three stores,
-        // 7 tables, 8 MB, bags of 1 to 30 37 / 40), the even spread with few (30 MB 50 / 49).
-        const bool idle = 10 * qn < 7 * 8 * ((qn + 7) / 8);
+        // 7 tables, 8 MB, bags of 1 to 30 37 / 40), the even spread with few (30 MB 50 / 49).  Long rows of shards about as large as an XCD's L2 miss it eight times
+        // when they are spread: fp32 of 128, one store, spread over dealt, 10 rows a segment with 20 MB and 150 MB of vectors, shards of 2.5 MB, 5 1.11 0.96, 9 1.10 1.08, 10 1.13
+        // 1.18, 11 1.18 1.27, 4 rows 1.01 to 1.24, one 0.92 to 1.02, of 6 MB 1.00 to 1.22, of 1 MB 0.82 to 1.10; fp32 of 32 and 8-bit of 128 0.83.
+        int64_t mean_shard = 0;
+        const int64_t row_stride = stride_bytes(DT, ctx->D);
+        for (int q = q0; q < q0 + qn; ++q) mean_shard += ctx->q_rows[q] * row_stride;
+        mean_shard /= qn;
+        const bool fits = to.stores == kOneStore && row_stride >= 512 && nnz >= 4 * ctx->nseg && mean_shard > (int64_t)3 << 19 && mean_shard <= (int64_t)8 << 20;
+        const bool idle = 100 * qn < (fits ? 55 : 70) * 8 * ((qn + 7) / 8);
         const bool xcd = ctx->tune_xcd == 1 || (ctx->tune_xcd != 0 && !idle);
         const dim3 grid = xcd ? dim3((unsigned)((uint64_t)((qn + 7) / 8) * 8u * wgx)) : dim3(wgx, qn);
         const uint32_t deal = xcd ? wgx : 0u;
         // 32-bit row positions unless some shard is too large for them
-        const int64_t row_stride = stride_bytes(DT, ctx->D);
         bool wide = ctx->tune_wide == 1;
         bool ring = ctx->tune_wide != 0 && ring_pays(ctx, rw != nullptr, nnz, qn);
-        int64_t bytes = 0;                                    // of the launch's shards
         for (int q = q0; q < q0 + qn; ++q) {
-            bytes += ctx->q_rows[q] * row_stride;
             wide = wide || ctx->q_rows[q] * (row_stride / VB) >= 0xffffffffLL;
             ring = ring && ctx->q_rows[q] < (int64_t)kPastEnd / row_stride;
         }
@@ -630,7 +634,7 @@ void launch_rows(const bls_ctx *ctx, const int64_t *ridx, const float *rw, const
             }
         }
         auto launch = [&](auto kernel) {
-            kernel<<<grid, kThreads, ring ? ring_lds(ctx, G, VB, nnz, bytes / qn) : 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, to.Y, to.S, to.R, to.slot, nb, chunks, deal, q0, qn);
+            kernel<<<grid, kThreads, ring ? ring_lds(ctx, G, VB, nnz, mean_shard) : 0, st>>>(ctx->desc, ridx, rw, segoff, nnz, to.Y, to.S, to.R, to.slot, nb, chunks, deal, q0, qn);
         };
         auto pick = [&](auto weighted, auto stores) {
             if (ring) return launch(pool_stream<G, DT, VB, UU, false, weighted(), true, stores()>);

@@ -174,3 +174,17 @@ for dtype, D, held in ((fp32, 128, True), (fp32, 16, True), (fp32, 6, True), (fp
             assert L.bls_set_pool_tuning(h, 0, 0, -1, 0) == 0 and not pool(h, nnz, weighted).endswith("true, 0>") and lds.value == 0
             assert L.bls_set_pool_tuning(h, 0, 0, -1, -1) == 0
 """)
+
+
+def test_few_shards_are_dealt_where_one_xcds_l2_holds_them(tmp_path, monkeypatch):
+    """One store: rows of 512 bytes and more, of shards of 1.5 to 8 MB, with four rows a segment, are dealt to the XCDs from 55 % of them at work
+    on, all others from 70 %."""
+    run(tmp_path, monkeypatch, r"""
+for D, rows, size, line in ((128, 4, 2 << 20, 55), (128, 4, (3 << 19) + 512, 55), (128, 4, 3 << 19, 70), (128, 40, 8 << 20, 55), (128, 8, (8 << 20) + 512, 70), (128, 3, 2 << 20, 70),
+                            (64, 8, 2 << 20, 70), (256, 8, 2 << 20, 55), (128, 40, 50 << 20, 70)):
+    for T in (1, 4, 5, 6, 8, 9, 10, 11, 12, 16, 17, 40):
+        B = (20 << 20) // (T * 512)
+        h = config(1, T, D, B, rows=size // (4 * D))
+        assert pool(h, rows * T * B).startswith(f"pool_stream<{D // 4}, 0, 16, 8, ")
+        assert y.value == (1 if 100 * T >= line * 8 * ((T + 7) // 8) else T), (D, rows, size, T, y.value)
+""")
