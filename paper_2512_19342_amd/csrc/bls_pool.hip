@@ -690,6 +690,27 @@ bool dispatch_rows(const bls_ctx *ctx, int vb, int lanes, const int64_t *ridx, c
 
 }  // namespace
 
+// Whether rows that one or two lanes of 16 bytes cover take four narrower ones.  Figures with 26 tables at pool_shape.  A row of a small shard comes out of the
+// caches, and with many vectors the launch is full without streams: pool_rows is ahead then up to more rows a segment.  Four lanes over pool_rows, 12
+// tables, fused, 7, 10 and 20 rows a segment, by MB of vectors.  Shards of 0.25 MB: fp32 of 8, 10 MB 1.05 1.02 0.89, 60 MB 1.19 1.22 1.12; half precision of 16, 10 MB
+// 1.02 0.97 0.87, 60 MB 1.08 1.06 1.08, 150 MB 1.16 1.19 1.11; of 8, 10 MB 0.83 0.69 0.55, 60 MB 1.01 0.96 0.83, 150 MB 1.11 1.05; fp32 of 4, 60 MB 1.07 1.00; 8-bit of 16, 60 MB
+// 0.89 0.76 0.70, 150 MB 1.07 1.02 0.91.  Of 25 MB: fp32 of 8, 60 MB 0.99 0.92 0.81, 150 MB 1.06 0.97, half precision of 16 0.94 0.89 0.79, 1.01 0.92 0.82, one lane below 0.92.
+// 8-bit of 32, either shard, 1 row 0.84 to 0.97, 5 0.97 to 1.03, 7 to 10, 60 MB 0.97 to 1.03, 150 MB 1.01 to 1.04, 400 MB 1.04 to 1.11, 20, 60 MB 0.91 0.98, 150 MB 0.96 1.05.
+static bool four_lanes_pay(const bls_ctx *ctx, int64_t nnz, int lanes)
+{
+    const bool rowq = is_rowq(ctx->dtype);
+    const int64_t vectors = ctx->nseg * ctx->D * 4;
+    const bool little = vectors <= (int64_t)24 << 20, many = vectors > (int64_t)96 << 20;
+    int64_t shards = 0;
+    for (int q = 0; q < ctx->Q; ++q) shards += ctx->q_rows[q] * stride_bytes(ctx->dtype, ctx->D);
+    const bool small = shards <= ctx->Q * ((int64_t)4 << 20);
+    if (rowq && lanes == 2) return !many || nnz < 4 * ctx->nseg || (!small && nnz >= 16 * ctx->nseg);
+    if (!small) return nnz >= (lanes == 2 && many ? 8 : 6) * ctx->nseg;
+    if (rowq) return nnz >= (many ? 16 : 6) * ctx->nseg;
+    if (lanes == 2) return little && nnz >= 16 * ctx->nseg;
+    return nnz >= (little ? 6 : many ? 16 : 12) * ctx->nseg;
+}
+
 // Bytes per lane and lanes per row of the kernels that read whole pieces of rows; false: pool_rows_generic.
 static bool pool_shape(const bls_ctx *ctx, int64_t nnz, int *lane_bytes, int *row_lanes)
 {
@@ -707,7 +728,7 @@ static bool pool_shape(const bls_ctx *ctx, int64_t nnz, int *lane_bytes, int *ro
     // 138 / 126; up to 6 rows (3) 34.6 / 37.8, 32 / 35, 31 / 36, 38.1 / 38.8, 48 / 47; one row 29 / 31, 25 / 28, 25 / 28, 32 / 32, 42 / 39.
     // A width that the caller chose is kept; of four lanes some idle then.
     const bool chosen = ctx->tune_lane_bytes != 0;
-    if (lanes < 4 && (vb < 16 || (!chosen && (nnz >= 6 * ctx->nseg || (is_rowq(ctx->dtype) && lanes == 2))))) {
+    if (lanes < 4 && (vb < 16 || (!chosen && four_lanes_pay(ctx, nnz, lanes)))) {
         while (!chosen && lanes < 4 && vb > 4) { vb >>= 1; lanes <<= 1; }
         lanes = 4;
     }

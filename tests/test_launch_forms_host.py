@@ -145,7 +145,7 @@ for dtype, D, few, many, widths in ((fp16, 8, (1, 16), (4, 4), {16: (1, 16), 8: 
                                     (u8, 16, (1, 16), (4, 4), {16: (1, 16), 8: (4, 8), 4: (4, 4)}), (f8, 32, (4, 8), (4, 8), {16: (2, 16), 8: (4, 8), 4: (8, 4)}),
                                     (fp32, 2, (4, 4), (4, 4), {16: (4, 8), 8: (4, 8), 4: (4, 4)}), (fp32, 64, (16, 16), (16, 16), {16: (16, 16), 8: (32, 8), 4: (64, 4)}),
                                     (fp16, 10, (8, 4), (8, 4), {16: (8, 4), 8: (8, 4), 4: (8, 4)})):
-    h = config(2, 4, D, 64, dtype)
+    h = config(2, 4, D, 64, dtype, rows=1 << 21)
     for rows, free in ((5, few), (6, many)):
         for chosen, (lanes, vb) in ((0, free), *widths.items()):
             assert L.bls_set_pool_tuning(h, chosen, 0, -1, -1) == 0
@@ -187,4 +187,29 @@ for D, rows, size, line in ((128, 4, 2 << 20, 55), (128, 4, (3 << 19) + 512, 55)
         h = config(1, T, D, B, rows=size // (4 * D))
         assert pool(h, rows * T * B).startswith(f"pool_stream<{D // 4}, 0, 16, 8, ")
         assert y.value == (1 if 100 * T >= line * 8 * ((T + 7) // 8) else T), (D, rows, size, T, y.value)
+""")
+
+
+def test_short_rows_take_four_lanes_where_they_pay(tmp_path, monkeypatch):
+    """Either side of every line: one and two lanes of 16 bytes, shards that the caches hold, megabytes of vectors, rows a segment."""
+    run(tmp_path, monkeypatch, r"""
+fp32, fp16, u8, f8 = 0, 1, 2, 3
+never = 1 << 40
+for dtype, D, lanes, lines in ((fp32, 8, 2, ((16, never, never), (6, 6, 8))), (fp16, 16, 2, ((16, never, never), (6, 6, 8))), (fp32, 4, 1, ((6, 12, 16), (6, 6, 6))),
+                               (fp16, 8, 1, ((6, 12, 16), (6, 6, 6))), (u8, 16, 1, ((6, 6, 16), (6, 6, 6))), (f8, 16, 1, ((6, 6, 16), (6, 6, 6)))):
+    row = D * 4 if dtype == fp32 else D * 2 if dtype == fp16 else (D + 8 + 15) // 16 * 16
+    for size, by_mb in zip((4 << 20, (4 << 20) + row), lines):
+        for mb, line in zip((20, 60, 400), by_mb):
+            B = (mb << 20) // (4 * D * 4)
+            h = config(2, 4, D, B, dtype, rows=size // row)
+            for nnz in (4 * B, min(line, 99) * 4 * B - 1, min(line, 99) * 4 * B):
+                four = nnz >= line * 4 * B
+                assert pool(h, nnz).startswith(f"pool_stream<4, {dtype}, " if four else f"pool_rows<{lanes}, {dtype}, 16, "), (dtype, D, size, mb, nnz / (4 * B), kernel())
+for mb in (20, 400):
+  B = (mb << 20) // (4 * 32 * 4)
+  for size in (4 << 20, 5 << 20):
+    h = config(2, 4, 32, B, u8, rows=size // 48)
+    for rows in (1, 3, 4, 15, 16):
+        four = mb == 20 or rows < 4 or (rows >= 16 and size > 4 << 20)
+        assert pool(h, rows * 4 * B).startswith("pool_stream<4, 2, 8, " if four else "pool_rows<2, 2, 16, "), (mb, rows, kernel())
 """)
